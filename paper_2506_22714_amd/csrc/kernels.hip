@@ -13,9 +13,10 @@
 //                A segment of a decomposed long row is the same task with no blocks and one
 //                atomic output row.
 //   SDDMM window task  X window x gathered Y rows on v_mfma_f32_16x16x32_f16 (both operands are
-//                contiguous along K, so they load straight into MFMA layout), sampled through
-//                the bitmap, write offsets by popcount.
-//   SDDMM segment task per-nonzero dot products on the VALU with a cross-lane reduction.
+//                contiguous along K; the rows of Y pass through LDS), sampled through output
+//                records made at plan time.
+//   SDDMM segment task 16 residual nonzeros per tile on the same instruction; fp32 storage:
+//                per-nonzero dot products on the VALU with a cross-lane reduction.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -665,7 +666,9 @@ struct SddmmArgs {
     const int32_t *blk_valptr;
     const uint2 *dense_pv;      // per packed dense nonzero: CSR position, value bits
     int32_t n_dense;
-    const SdEnt *res_ent;
+    const void *res_ent;        // blocked words and values
+    const int32_t *res_base, *res_row;
+    const int32_t *res_perm;    // nullptr: residual entry i is nonzero i
     const void *X;
     const void *Y;
     float *out;
@@ -690,24 +693,72 @@ __device__ inline float group_sum(float s) {
     return s;
 }
 
-// Dense blocks of one window: D = Xwin * Y[cols]^T on the MFMA (both operands are contiguous along K: 16-byte global
-// loads straight into the operand registers).  The blocks of a task are taken in groups of SD_GROUP; a group's 16 x 16
-// products go to an LDS stage as they come out of the matrix cores (slot sd_stage_slot(block, row, column slot): lane l
-// writes its e-th accumulator of block x to x * 256 + e * 64 + l, no bank conflicts, no bitmap needed), and the group's
-// output records - {CSR position, value | stage slot << 16}, stored at plan time in ascending CSR position inside every
-// group - are then read by consecutive lanes: coalesced record loads, and stores that fall into the row-contiguous runs
-// of the output instead of one 4-byte store per matrix-core lane (the write-back of Section 4.4.2, with the popcount
-// offsets resolved when the plan is built).
+// 16 bytes per lane from global memory to LDS, past the registers: lane l's piece lands at lds + 16 l.
+__device__ inline void load_to_lds(const void *src, unsigned char *lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+__device__ inline void wait_for_loads() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    wave_sync();
+}
+
+// 16-bit rows of Y come through LDS: a row's consecutive pieces are fetched by consecutive lanes, so that the address unit
+// handles 64 bytes per access (operand-shaped loads touch four rows with every four lanes: 544 M instead of 184 M accesses
+// for the segments of the GAT graph at K = 64, 910 instead of 690 us; window tasks of the community matrix K = 64 / 128
+// 222 / 372 -> 201 / 328 us).  Piece c of row r is kept
+// at place c ^ swizzle(r), which spreads the pieces that 16 lanes read together over all banks.
+// The stage's readers are done: fetches into it may be issued.
+__device__ inline void wait_for_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_sync();
+}
+
+template <int K>
+struct RowStage {
+    static constexpr int ROW = 2 * K;                        // bytes of a row
+    static constexpr int PIECES = K / 8;                     // 16-byte pieces of a row = lanes that fetch it
+    static constexpr int RPL = WAVE / PIECES;                // rows per wave load
+    static constexpr int ROWS = K >= 128 ? 32 : 64;          // rows staged together
+    static constexpr int BYTES = ROWS * ROW;
+    __device__ static int swizzle(int row) { return (row * PIECES / 16) & (PIECES - 1); }
+    // rows ids[first], ids[first + 1], ... (one id per lane of the wave) of `base` to stage rows at, at + 1, ...
+    template <int COUNT>
+    __device__ static void fetch(const void *base, int ids, int first, unsigned char *stage, int at) {
+        const int lane = threadIdx.x % WAVE;
+        int id[COUNT / RPL];
+#pragma unroll
+        for (int i = 0; i < COUNT / RPL; ++i) id[i] = __builtin_amdgcn_ds_bpermute((first + i * RPL + lane / PIECES) * 4, ids);
+#pragma unroll
+        for (int i = 0; i < COUNT / RPL; ++i) asm volatile("" : "+v"(id[i]));        // all ids before the first fetch
+#pragma unroll
+        for (int i = 0; i < COUNT / RPL; ++i) {
+            const int piece = (lane % PIECES) ^ swizzle(at + i * RPL + lane / PIECES);
+            load_to_lds(reinterpret_cast<const char *>(base) + ((uint64_t)(uint32_t)id[i] * ROW + (uint32_t)piece * 16u), stage + (at + i * RPL) * ROW);
+        }
+    }
+    // operand of 16 staged rows from `at` on: piece g + 4 s of row j
+    __device__ static uint4 operand(const unsigned char *stage, int at, int g, int j, int s) {
+        return *reinterpret_cast<const uint4 *>(stage + (at + j) * ROW + ((g + 4 * s) ^ swizzle(at + j)) * 16);
+    }
+};
+
+// Dense blocks of one window: D = Xwin * Y[cols]^T on the MFMA.  The blocks of a task are taken in groups of SD_GROUP: the
+// group's 64 rows of Y go through the row stage, and its 16 x 16 products come out of the matrix cores into the same LDS
+// bytes (slot sd_stage_slot(block, row, column slot): lane l writes its e-th accumulator of block x to x * 256 + e * 64 + l,
+// no bank conflicts, no bitmap needed).  The group's output records - {CSR position, value | stage slot << 16}, stored at
+// plan time in ascending CSR position inside every group - are then read by consecutive lanes: coalesced record loads, and
+// stores that fall into the row-contiguous runs of the output instead of one 4-byte store per matrix-core lane (the
+// write-back of Section 4.4.2, with the popcount offsets resolved when the plan is built).
 template <class T, int K>
-__device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, float *stage) {
+__device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, unsigned char *stage) {
+    using S = RowStage<K>;
     constexpr int KS = K / 32;               // MFMA k-steps
-    constexpr int BB = K <= 64 ? 4 : 2;      // blocks whose Y rows are in registers together
     constexpr int RU = 4;                    // record loads in flight per lane
-    static_assert(SD_GROUP % BB == 0, "a group is whole register batches");
+    static_assert(SD_GROUP * KB == WAVE, "a lane holds the column of one slot of the group");
     const int lane = threadIdx.x % WAVE;
     const int g = lane >> 4, j = lane & 15;
     const uint16_t *X = reinterpret_cast<const uint16_t *>(a.X);
-    const uint16_t *Y = reinterpret_cast<const uint16_t *>(a.Y);
+    float *products = reinterpret_cast<float *>(stage);
     // A operand: row j of the window, k = 32*s + 8g .. +7 (rows past M repeat the last row; no record points at them)
     const int64_t xr = min((int64_t)t.id * W + j, a.M - 1);
     uint4 xa[KS];
@@ -715,34 +766,35 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, f
     for (int s = 0; s < KS; ++s) xa[s] = *reinterpret_cast<const uint4 *>(X + xr * K + 32 * s + 8 * g);
     for (int b0 = t.blk_begin; b0 < t.blk_end; b0 += SD_GROUP) {
         const int nb = min(SD_GROUP, t.blk_end - b0);
-        int col[SD_GROUP];
-#pragma unroll
-        for (int x = 0; x < SD_GROUP; ++x) col[x] = a.blk_cols[(int64_t)(b0 + min(x, nb - 1)) * KB + j];
+        // padding slots and blocks past the group fetch a row that no record points at
+        const int col = max(a.blk_cols[(int64_t)(b0 + min(g, nb - 1)) * KB + j], 0);
         const int v0 = a.blk_valptr[b0], v1 = a.blk_valptr[b0 + nb];
         // the first records of the group travel with the Y rows
         uint2 rec[RU];
 #pragma unroll
         for (int u = 0; u < RU; ++u) rec[u] = a.dense_pv[min(v0 + u * WAVE + lane, a.n_dense - 1)];
+        float4_t d[SD_GROUP];
 #pragma unroll
-        for (int h = 0; h < SD_GROUP; h += BB) {
+        for (int h = 0; h < SD_GROUP; h += S::ROWS / KB) {
             if (h < nb) {
-                uint4 yb[BB][KS];
+                if (S::ROWS > 2 * KB && nb <= 2) S::template fetch<2 * KB>(a.Y, col, h * KB, stage, 0);
+                else S::template fetch<S::ROWS>(a.Y, col, h * KB, stage, 0);
+                wait_for_loads();
 #pragma unroll
-                for (int x = 0; x < BB; ++x) {
-                    const int c = max(col[h + x], 0);            // padding slot (or a block past the group): no record points at it
+                for (int x = 0; x < S::ROWS / KB; ++x) {
+                    d[h + x] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int s = 0; s < KS; ++s) yb[x][s] = *reinterpret_cast<const uint4 *>(Y + (int64_t)c * K + 32 * s + 8 * g);
+                    for (int s = 0; s < KS; ++s) d[h + x] = mfma_k32<T>(xa[s], S::operand(stage, x * KB, g, j, s), d[h + x]);
                 }
-#pragma unroll
-                for (int x = 0; x < BB; ++x) {
-                    float4_t d = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int s = 0; s < KS; ++s) d = mfma_k32<T>(xa[s], yb[x][s], d);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) stage[(h + x) * 256 + e * WAVE + lane] = d[e];
-                }
+                wait_for_lds();
             }
         }
+#pragma unroll
+        for (int x = 0; x < SD_GROUP; ++x)
+            if (x < nb) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) products[x * 256 + e * WAVE + lane] = d[x][e];
+            }
         wave_sync();
         for (int q = v0; q < v1; q += RU * WAVE) {
             if (q > v0) {
@@ -752,13 +804,12 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, f
 #pragma unroll
             for (int u = 0; u < RU; ++u)
                 if (q + u * WAVE + lane < v1)
-                    a.out[(int32_t)rec[u].x] = (a.pattern_only ? 1.f : Elem<T>::word_val(rec[u].y)) * stage[rec[u].y >> 16];
+                    a.out[(int32_t)rec[u].x] = (a.pattern_only ? 1.f : Elem<T>::word_val(rec[u].y)) * products[rec[u].y >> 16];
         }
-        wave_sync();                         // the next group overwrites the stage
+        wait_for_lds();                      // the next group overwrites the stage
     }
 }
 
-// Residual nonzeros: LPN lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.
 // The same for fp32 storage: v_mfma_f32_16x16x4_f32.  A lane (g, j) fetches X[row j][16t + 4g .. +3] and Y[col j][16t + 4g .. +3] as
 // 16-byte loads; k-step 4t + e of the product takes element e of both, i.e. lane group g contributes k = 16t + 4g + e to
 // that step - any assignment of the k's to steps and lane groups gives the same sum as long as both operands use it.
@@ -825,9 +876,118 @@ __device__ inline void sddmm_window_task_f32(const SddmmArgs &a, const DevTask &
     }
 }
 
+// A lane's residual entry: what is loaded, back to back, and what it says.
+template <class T>
+struct SegmentEntry {
+    uint32_t word;
+    typename Elem<T>::val_t v;
+    int i, base, pos;
+    __device__ void load(const SddmmArgs &a, int at) {
+        i = at;
+        load_blocked_entry(a.res_ent, (int64_t)i, word, v);
+        base = a.res_base[i / RES_BLOCK];
+        pos = i;
+        if (a.res_perm) pos = a.res_perm[i];
+    }
+    __device__ int col() const { return (int)(word & RES_COL_MASK); }
+    __device__ int row(const SddmmArgs &a) const {
+        const uint32_t delta = word >> RES_ROW_SHIFT;
+        int r = base + (int)delta;
+        if (__any(delta == RES_FAR)) {           // rows far apart (nearly empty rows): one more load, whole waves only
+            const int far = a.res_row[i];
+            if (delta == RES_FAR) r = far;
+        }
+        return r;
+    }
+    __device__ float value() const {
+        if constexpr (sizeof(v) == 2) return Elem<T>::word_val((uint32_t)v);
+        else return v;
+    }
+};
+
+// Residual nonzeros, 16-bit storage, on the matrix cores.  16 nonzeros are the 16 columns of a tile: lane (g, j) holds pieces
+// g, g + 4, ... (16 bytes each) of Y[col of nonzero j] as B operand.  If the rows of 64 nonzeros in CSR order lie within 16
+// consecutive rows (nearly always) the A operand is those rows of X, fetched once and not once per nonzero, and the products
+// are the elements (row slot of j, j) of the tile; otherwise slot i of A is the row of nonzero i and the products are the
+// diagonal.  Nothing is widened or summed across lanes.
+// Bound by the address and data-return units of the L1s (96 % busy when every nonzero fetched its two rows with K/8 lanes and
+// the vector ALUs formed the dot product): X once per batch and 6 instead of 16 bytes per entry take that to one row of Y.
+// f16, against that version: GAT graph K = 64 772 -> 680 us (648 us with segments of 128), power-law K = 32 35.4 -> 27.3,
+// community K = 32 177 -> 146, irregular 1,905 -> 1,770 us.  Fetching the next batch's entries early: no change.
 template <class T, int K>
-__device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t) {
-    using E = Elem<T>;
+__device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, unsigned char *stage) {
+    using S = RowStage<K>;
+    constexpr int KS = K / 32;                   // MFMA k-steps
+    const int lane = threadIdx.x % WAVE;
+    const int g = lane >> 4, j = lane & 15;
+    float *out_stage = reinterpret_cast<float *>(stage);
+    for (int q0 = t.res_begin; q0 < t.res_end; q0 += WAVE) {
+        SegmentEntry<T> ent;
+        ent.load(a, min(q0 + lane, t.res_end - 1));
+        const int col = ent.col(), row = ent.row(a);
+        const int r0 = __builtin_amdgcn_readfirstlane(row), r1 = __builtin_amdgcn_readlane(row, WAVE - 1);
+        float v[4];
+        bool mine[4];
+        auto product = [&](int x, const uint4 (&xa)[KS], const uint4 (&yb)[KS], int slot) {
+            float4_t d = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) d = mfma_k32<T>(xa[s], yb[s], d);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(d[e]));           // selects, not branches
+            const float lo = slot & 1 ? d[1] : d[0], hi = slot & 1 ? d[3] : d[2];
+            v[x] = slot & 2 ? hi : lo;
+            mine[x] = (slot >> 2) == g;          // the lane that holds row `slot` of column j
+        };
+        if (r1 - r0 < W) {
+            uint4 xa[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                xa[s] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(a.X) + ((uint64_t)(uint32_t)min(r0 + j, r1) * S::ROW + 64u * s + 16u * g));
+#pragma unroll
+            for (int h = 0; h < WAVE; h += S::ROWS) {
+                S::template fetch<S::ROWS>(a.Y, col, h, stage, 0);
+                wait_for_loads();
+#pragma unroll
+                for (int x = 0; x < S::ROWS / 16; ++x) {
+                    uint4 yb[KS];
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) yb[s] = S::operand(stage, x * 16, g, j, s);
+                    product(h / 16 + x, xa, yb, __builtin_amdgcn_ds_bpermute((h + x * 16 + j) * 4, row - r0));
+                }
+                wait_for_lds();
+            }
+        } else {
+            constexpr int HALF = S::ROWS / 2;    // rows of Y in one half of the stage, the same number of X in the other
+#pragma unroll
+            for (int h = 0; h < WAVE; h += HALF) {
+                S::template fetch<HALF>(a.Y, col, h, stage, 0);
+                S::template fetch<HALF>(a.X, row, h, stage, HALF);
+                wait_for_loads();
+#pragma unroll
+                for (int x = 0; x < HALF / 16; ++x) {
+                    uint4 xd[KS], yd[KS];
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) { yd[s] = S::operand(stage, x * 16, g, j, s); xd[s] = S::operand(stage, HALF + x * 16, g, j, s); }
+                    product(h / 16 + x, xd, yd, j);
+                }
+                wait_for_lds();
+            }
+        }
+        // to entry order through the same LDS bytes: one store of 64 consecutive entries
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            if (mine[x]) out_stage[x * 16 + j] = v[x];
+        wave_sync();
+        if (q0 + lane < t.res_end) a.out[ent.pos] = (a.pattern_only ? 1.f : ent.value()) * out_stage[lane];
+        wait_for_lds();                          // the next batch overwrites the stage
+    }
+}
+
+// The same for fp32 storage, where the vector ALUs are the faster unit (v_mfma_f32_16x16x4 forms 16 products per column of
+// the tile to use one): K/4 lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.
+template <int K>
+__device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, float *stage) {
+    using E = Elem<float>;
     constexpr int PL = E::PER_LANE;
     constexpr int LPN = K / PL;              // lanes per nonzero
     constexpr int NPW = WAVE / LPN;          // nonzeros per wave pass
@@ -835,34 +995,29 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t) 
     static_assert(LPN >= 4 && LPN % 4 == 0 && LPN <= WAVE, "unsupported K (whole quads per nonzero)");
     const int lane = threadIdx.x % WAVE;
     const int sub = lane % LPN, grp = lane / LPN;
-    for (int q0 = t.res_begin; q0 < t.res_end; q0 += NPW * U) {
-        // An entry is 4 words (row, col, position, value bits).  Each lane of a quad fetches one of them (a quad then
-        // costs the texture path 16 bytes instead of 64) and the quad shares them with DPP moves.
-        uint32_t word[U];
-        uint4 ent[U];
-        typename E::raw_t x[U], y[U];
+    for (int q0 = t.res_begin; q0 < t.res_end; q0 += WAVE) {
+        const int n = min(WAVE, t.res_end - q0);
+        SegmentEntry<float> ent;
+        ent.load(a, q0 + min(lane, n - 1));
+        const int col = ent.col(), row = ent.row(a);
+        for (int e0 = 0; e0 < n; e0 += NPW * U) {
+            E::raw_t x[U], y[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            word[u] = reinterpret_cast<const uint32_t *>(a.res_ent)[(int64_t)min(q0 + u * NPW + grp, t.res_end - 1) * 4 + (sub & 3)];
+            for (int u = 0; u < U; ++u) {
+                const int from = (e0 + u * NPW + grp) * 4;
+                const int r = __builtin_amdgcn_ds_bpermute(from, row), c = __builtin_amdgcn_ds_bpermute(from, col);
+                x[u] = E::load(a.X, (int64_t)r * K + sub * PL);
+                y[u] = E::load(a.Y, (int64_t)c * K + sub * PL);
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int w = (int)word[u];
-            ent[u].x = (uint32_t)__builtin_amdgcn_update_dpp(0, w, 0x00, 0xf, 0xf, true);      // quad_perm [0,0,0,0]
-            ent[u].y = (uint32_t)__builtin_amdgcn_update_dpp(0, w, 0x55, 0xf, 0xf, true);      // quad_perm [1,1,1,1]
-            ent[u].z = (uint32_t)__builtin_amdgcn_update_dpp(0, w, 0xAA, 0xf, 0xf, true);      // quad_perm [2,2,2,2]
-            ent[u].w = (uint32_t)__builtin_amdgcn_update_dpp(0, w, 0xFF, 0xf, 0xf, true);      // quad_perm [3,3,3,3]
+            for (int u = 0; u < U; ++u) {
+                const float s = group_sum<LPN>(E::dot(x[u], y[u], 0.f));
+                if (sub == 0) stage[e0 + u * NPW + grp] = s;
+            }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            x[u] = E::load(a.X, (int64_t)(int32_t)ent[u].x * K + sub * PL);
-            y[u] = E::load(a.Y, (int64_t)(int32_t)ent[u].y * K + sub * PL);
-        }
-        float s[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) s[u] = group_sum<LPN>(E::dot(x[u], y[u], 0.f));
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (sub == 0 && q0 + u * NPW + grp < t.res_end) a.out[(int32_t)ent[u].z] = (a.pattern_only ? 1.f : E::word_val(ent[u].w)) * s[u];
+        wave_sync();
+        if (lane < n) a.out[ent.pos] = (a.pattern_only ? 1.f : ent.value()) * stage[lane];
+        wave_sync();
     }
 }
 
@@ -873,19 +1028,26 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t) 
 // same rows of Y, and four of them on one compute unit find each other's rows in its L1 (community matrix, K = 64:
 // matrix-unit-only 249 -> 208 us, hybrid 265 -> 247 us, same box).  Elsewhere one wave per workgroup is better (power-law
 // graph 31.0 vs 32.3 us: a workgroup's slots are only free again when its slowest wave has finished).
-template <class T, int K, int WPB>
-__global__ __launch_bounds__(WAVE * WPB) void sddmm_task_kernel(SddmmArgs a) {
-    __shared__ float stage_all[std::is_same<T, float>::value ? 1 : WPB * SD_GROUP * 256];
+// DENSE = false: the table has no window task (a plan without dense blocks).  At K = 64 the LDS allows five waves per SIMD
+// and the registers are held to that (GAT 688 -> 674 us, power-law 41.9 -> 40.4); at K = 128 it would spill (327 -> 373).
+template <class T, int K, int WPB, bool DENSE>
+__global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K == 64 && !std::is_same<T, float>::value ? 5 : 1))) void sddmm_task_kernel(SddmmArgs a) {
+    constexpr bool F32 = std::is_same<T, float>::value;
+    constexpr int PRODUCTS = DENSE ? SD_GROUP * 256 * 4 : WAVE * 4, ROWS = RowStage<K>::BYTES;
+    constexpr int STAGE = F32 ? WAVE * 4 : PRODUCTS > ROWS ? PRODUCTS : ROWS;           // bytes per wave
+    __shared__ __attribute__((aligned(16))) unsigned char stage_all[WPB * STAGE];
     const unsigned wave = threadIdx.x / WAVE;
     const unsigned seq = (blockIdx.x >> 3) * WPB + wave;                // position in the die's part of the table
     if (seq >= (unsigned)a.tasks_per_die) return;
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + seq];
-    if (t.kind == LIBRA_TASK_WINDOW) {
-        if constexpr (std::is_same<T, float>::value) sddmm_window_task_f32<K>(a, t);
-        else sddmm_window_task<T, K>(a, t, stage_all + wave * (SD_GROUP * 256));
+    unsigned char *stage = stage_all + wave * STAGE;
+    if (DENSE && t.kind == LIBRA_TASK_WINDOW) {
+        if constexpr (F32) sddmm_window_task_f32<K>(a, t);
+        else sddmm_window_task<T, K>(a, t, stage);
         return;
     }
-    sddmm_segment_task<T, K>(a, t);
+    if constexpr (F32) sddmm_segment_task_f32<K>(a, t, reinterpret_cast<float *>(stage));
+    else sddmm_segment_task<T, K>(a, t, stage);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1154,6 +1316,17 @@ __global__ __launch_bounds__(256) void scatter_values16_x8_kernel(const uint16_t
     auto where = [&](int64_t i) {
         return BLOCKED ? dst + (i / RES_BLOCK) * (RES_BLOCK * 6) + RES_BLOCK * 4 + (i % RES_BLOCK) * 2 : dst + i * 2;
     };
+    if (!perm) {                            // destination i takes value i
+        const bool whole = ((uintptr_t)src & 15) == 0;
+        for (int64_t g = tid; g < groups; g += nthreads) {
+            uint4 v;
+            if (whole) v = reinterpret_cast<const uint4 *>(src)[g];
+            else __builtin_memcpy(&v, src + g * 8, 16);
+            *reinterpret_cast<uint4 *>(where(g * 8)) = v;
+        }
+        for (int64_t i = groups * 8 + tid; i < n; i += nthreads) *reinterpret_cast<uint16_t *>(where(i)) = src[i];
+        return;
+    }
     for (int64_t g = tid; g < groups; g += nthreads) {
         const int4 p0 = reinterpret_cast<const int4 *>(perm)[2 * g], p1 = reinterpret_cast<const int4 *>(perm)[2 * g + 1];
         const uint32_t v0 = src[p0.x], v1 = src[p0.y], v2 = src[p0.z], v3 = src[p0.w];
@@ -1165,7 +1338,7 @@ __global__ __launch_bounds__(256) void scatter_values16_x8_kernel(const uint16_t
 template <class T>
 __global__ __launch_bounds__(256) void scatter_blocked_values_kernel(const T *src, const int32_t *perm, int64_t n, unsigned char *dst) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        reinterpret_cast<T *>(dst + (i / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(T))) + RES_BLOCK * 4)[i % RES_BLOCK] = src[perm[i]];
+        reinterpret_cast<T *>(dst + (i / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(T))) + RES_BLOCK * 4)[i % RES_BLOCK] = src[perm ? perm[i] : i];
 }
 
 inline int hip_rc(hipError_t e) { return e == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP; }
@@ -1284,24 +1457,29 @@ std::vector<DevTask> pack_tasks(const libra_plan_t *P, const SubPlan &sp, bool s
 struct Staging {
     std::vector<DevTask> tasks_a, tasks_d;
     std::vector<unsigned char> res_blocks;  // SpMM residual entries: blocked words and values
-    std::vector<SdEnt> sdent;
+    std::vector<unsigned char> sd_res_blocks;
+    std::vector<int32_t> sd_res_base;
     std::vector<SdPv> sdpv;
 };
 
-// Record layouts written on the device when the arrays come from the device planner.
+// Record layouts written on the device when the arrays come from the device planner.  `base`: nullptr for the SpMM entries
+// (upper bits = row in the window); for the SDDMM ones, where the first rows of the blocks go (upper bits = row minus that).
 template <class V>
-__global__ __launch_bounds__(256) void pack_blocked_entries_kernel(const int32_t *col, const V *val, const int32_t *row, int64_t n, unsigned char *out) {
+__global__ __launch_bounds__(256) void pack_blocked_entries_kernel(const int32_t *col, const V *val, const int32_t *row, int64_t n, unsigned char *out, int32_t *base) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         unsigned char *blk = out + (i / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(V)));
         const int slot = (int)(i % RES_BLOCK);
-        reinterpret_cast<uint32_t *>(blk)[slot] = (uint32_t)col[i] | (uint32_t)(row[i] % W) << RES_ROW_SHIFT;
+        uint32_t upper;
+        if (base) {
+            const int32_t first = row[i - slot];
+            upper = min((uint32_t)(row[i] - first), RES_FAR);
+            if (slot == 0) base[i / RES_BLOCK] = first;
+        } else {
+            upper = (uint32_t)(row[i] % W);
+        }
+        reinterpret_cast<uint32_t *>(blk)[slot] = (uint32_t)col[i] | upper << RES_ROW_SHIFT;
         reinterpret_cast<V *>(blk + RES_BLOCK * 4)[slot] = val[i];
     }
-}
-template <class V>
-__global__ __launch_bounds__(256) void pack_sddmm_entries_kernel(const int32_t *row, const int32_t *col, const int32_t *perm, const V *val, int64_t n, SdEnt *out) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = SdEnt{row[i], col[i], perm[i], (uint32_t)val[i]};
 }
 template <class V>
 __global__ __launch_bounds__(256) void pack_sddmm_values_kernel(const int32_t *perm, const V *val, int64_t n, SdPv *out) {
@@ -1366,16 +1544,17 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     u.put(H(sa.dense_perm.data()), da ? da->dense_perm : nullptr, (size_t)sa.n.dense * 4, sa.dev.dense_perm);
     const size_t nres = (size_t)sa.n.res;
     const size_t res_bytes = res_blocked_bytes(nres + 1, vs);      // + 1: a task without entries still reads the slot at its (clamped) first index
-    if (from_host) {
-        const int Wp = P->o.W;
-        st->res_blocks.assign(res_bytes, 0);
-        for (size_t i = 0; i < nres; ++i) {
-            unsigned char *blk = st->res_blocks.data() + i / RES_BLOCK * res_block_bytes(vs);
-            const uint32_t word = (uint32_t)sa.res_col[i] | (uint32_t)(sa.res_row[i] % Wp) << RES_ROW_SHIFT;
+    // host-side packing of one sub-plan's entries into blocks; upper(i): what goes above the column
+    auto pack_entries = [&](const SubPlan &sp, std::vector<unsigned char> &blocks, size_t bytes, auto upper) {
+        blocks.assign(bytes, 0);
+        for (size_t i = 0; i < (size_t)sp.n.res; ++i) {
+            unsigned char *blk = blocks.data() + i / RES_BLOCK * res_block_bytes(vs);
+            const uint32_t word = (uint32_t)sp.res_col[i] | upper(i) << RES_ROW_SHIFT;
             std::memcpy(blk + i % RES_BLOCK * 4, &word, 4);
-            std::memcpy(blk + RES_BLOCK * 4 + i % RES_BLOCK * vs, sa.res_val.data() + i * vs, vs);
+            std::memcpy(blk + RES_BLOCK * 4 + i % RES_BLOCK * vs, sp.res_val.data() + i * vs, vs);
         }
-    }
+    };
+    if (from_host) pack_entries(sa, st->res_blocks, res_bytes, [&](size_t i) { return (uint32_t)(sa.res_row[i] % P->o.W); });
     u.put(from_host ? (const void *)st->res_blocks.data() : nullptr, nullptr, res_bytes, sa.dev.res_ent);
     u.put(H(sa.res_perm.data()), da ? da->res_perm : nullptr, nres * 4, sa.dev.res_perm);
     u.put(H(sa.zero_rows.data()), da ? da->zero_rows : nullptr, (size_t)sa.n.zero_rows * 4, sa.dev.zero_rows);
@@ -1419,17 +1598,19 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     }
     u.put(from_host ? (const void *)st->sdpv.data() : nullptr, nullptr, ndd * sizeof(SdPv), sd.dev.dense_pv);
     u.put(H(sd.dense_perm.data()), dd ? dd->dense_perm : nullptr, ndd * 4, sd.dev.dense_perm);
-    const size_t nrd = (size_t)sd.n.res;
+    const size_t nrd = (size_t)sd.n.res, nblocks = (nrd + RES_BLOCK - 1) / RES_BLOCK;
     if (from_host) {
-        st->sdent.resize(nrd);
-        for (size_t i = 0; i < nrd; ++i) {
-            uint32_t bits = 0;
-            std::memcpy(&bits, sd.res_val.data() + i * vs, vs);
-            st->sdent[i] = {sd.res_row[i], sd.res_col[i], sd.res_perm[i], bits};
-        }
+        auto first = [&](size_t i) { return sd.res_row[i / RES_BLOCK * RES_BLOCK]; };
+        pack_entries(sd, st->sd_res_blocks, res_blocked_bytes(nrd, vs), [&](size_t i) { return std::min((uint32_t)(sd.res_row[i] - first(i)), RES_FAR); });
+        st->sd_res_base.resize(nblocks);
+        for (size_t b = 0; b < nblocks; ++b) st->sd_res_base[b] = first(b * RES_BLOCK);
     }
-    u.put(from_host ? (const void *)st->sdent.data() : nullptr, nullptr, nrd * sizeof(SdEnt), sd.dev.res_ent);
-    u.put(H(sd.res_perm.data()), dd ? dd->res_perm : nullptr, nrd * 4, sd.dev.res_perm);
+    u.put(from_host ? (const void *)st->sd_res_blocks.data() : nullptr, nullptr, res_blocked_bytes(nrd, vs), sd.dev.res_ent);
+    u.put(from_host ? (const void *)st->sd_res_base.data() : nullptr, nullptr, nblocks * 4, sd.dev.res_base);
+    u.put(H(sd.res_row.data()), dd ? dd->res_row : nullptr, nrd * 4, sd.dev.res_row);
+    // the residual list is ascending in CSR position: if it is the whole matrix, entry i is nonzero i
+    if ((int64_t)nrd == P->nnz) sd.dev.res_perm = nullptr;
+    else u.put(H(sd.res_perm.data()), dd ? dd->res_perm : nullptr, nrd * 4, sd.dev.res_perm);
 }
 }  // namespace
 
@@ -1455,18 +1636,18 @@ int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const De
         if (sa.n.res) {
             if (P->vdt == LIBRA_F32)
                 hipLaunchKernelGGL((pack_blocked_entries_kernel<float>), grid(sa.n.res), dim3(256), 0, s, da.res_col,
-                                   (const float *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent);
+                                   (const float *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent, (int32_t *)nullptr);
             else
                 hipLaunchKernelGGL((pack_blocked_entries_kernel<uint16_t>), grid(sa.n.res), dim3(256), 0, s, da.res_col,
-                                   (const uint16_t *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent);
+                                   (const uint16_t *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent, (int32_t *)nullptr);
         }
         if (sd.n.res) {
             if (P->vdt == LIBRA_F32)
-                hipLaunchKernelGGL((pack_sddmm_entries_kernel<uint32_t>), grid(sd.n.res), dim3(256), 0, s, dd.res_row, dd.res_col, dd.res_perm,
-                                   (const uint32_t *)dd.res_val, sd.n.res, (SdEnt *)sd.dev.res_ent);
+                hipLaunchKernelGGL((pack_blocked_entries_kernel<float>), grid(sd.n.res), dim3(256), 0, s, dd.res_col,
+                                   (const float *)dd.res_val, dd.res_row, sd.n.res, (unsigned char *)sd.dev.res_ent, (int32_t *)sd.dev.res_base);
             else
-                hipLaunchKernelGGL((pack_sddmm_entries_kernel<uint16_t>), grid(sd.n.res), dim3(256), 0, s, dd.res_row, dd.res_col, dd.res_perm,
-                                   (const uint16_t *)dd.res_val, sd.n.res, (SdEnt *)sd.dev.res_ent);
+                hipLaunchKernelGGL((pack_blocked_entries_kernel<uint16_t>), grid(sd.n.res), dim3(256), 0, s, dd.res_col,
+                                   (const uint16_t *)dd.res_val, dd.res_row, sd.n.res, (unsigned char *)sd.dev.res_ent, (int32_t *)sd.dev.res_base);
         }
         if (sd.n.dense) {
             if (P->vdt == LIBRA_F32)
@@ -1570,34 +1751,31 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
     const SubPlan &sp = P->sddmm;
     SddmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr,
                 reinterpret_cast<const uint2 *>(sp.dev.dense_pv), (int32_t)sp.n.dense,
-                reinterpret_cast<const SdEnt *>(sp.dev.res_ent), X, Y, out, P->M, 0, pattern_only};
+                sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, out, P->M, 0, pattern_only};
     if (sp.tasks.empty()) return LIBRA_OK;
     a.tasks_per_die = (int32_t)(((int64_t)sp.tasks.size() + LIBRA_XCDS - 1) / LIBRA_XCDS);
-    auto launch = [&](auto wpb) {
+    auto launch = [&](auto wpb, auto with_blocks) {
         constexpr int WPB = decltype(wpb)::value;
+        constexpr bool DENSE = decltype(with_blocks)::value;
         const dim3 grid((unsigned)((a.tasks_per_die + WPB - 1) / WPB * LIBRA_XCDS)), block(WAVE * WPB);
-        if (P->vdt == LIBRA_F16) {
+        auto width = [&](auto tag) {
+            typedef decltype(tag) T;
             switch (K) {
-            case 32: hipLaunchKernelGGL((sddmm_task_kernel<half_t, 32, WPB>), grid, block, 0, s, a); break;
-            case 64: hipLaunchKernelGGL((sddmm_task_kernel<half_t, 64, WPB>), grid, block, 0, s, a); break;
-            case 128: hipLaunchKernelGGL((sddmm_task_kernel<half_t, 128, WPB>), grid, block, 0, s, a); break;
+            case 32: hipLaunchKernelGGL((sddmm_task_kernel<T, 32, WPB, DENSE>), grid, block, 0, s, a); break;
+            case 64: hipLaunchKernelGGL((sddmm_task_kernel<T, 64, WPB, DENSE>), grid, block, 0, s, a); break;
+            case 128: hipLaunchKernelGGL((sddmm_task_kernel<T, 128, WPB, DENSE>), grid, block, 0, s, a); break;
             }
-        } else if (P->vdt == LIBRA_BF16) {
-            switch (K) {
-            case 32: hipLaunchKernelGGL((sddmm_task_kernel<bf16_t, 32, WPB>), grid, block, 0, s, a); break;
-            case 64: hipLaunchKernelGGL((sddmm_task_kernel<bf16_t, 64, WPB>), grid, block, 0, s, a); break;
-            case 128: hipLaunchKernelGGL((sddmm_task_kernel<bf16_t, 128, WPB>), grid, block, 0, s, a); break;
-            }
-        } else {
-            switch (K) {
-            case 32: hipLaunchKernelGGL((sddmm_task_kernel<float, 32, WPB>), grid, block, 0, s, a); break;
-            case 64: hipLaunchKernelGGL((sddmm_task_kernel<float, 64, WPB>), grid, block, 0, s, a); break;
-            case 128: hipLaunchKernelGGL((sddmm_task_kernel<float, 128, WPB>), grid, block, 0, s, a); break;
-            }
-        }
+        };
+        if (P->vdt == LIBRA_F16) width(half_t{});
+        else if (P->vdt == LIBRA_BF16) width(bf16_t{});
+        else width(float{});
     };
-    if (P->o.xcd_order == 1) launch(std::integral_constant<int, 4>{});
-    else launch(std::integral_constant<int, 1>{});
+    auto shape = [&](auto with_blocks) {
+        if (P->o.xcd_order == 1) launch(std::integral_constant<int, 4>{}, with_blocks);
+        else launch(std::integral_constant<int, 1>{}, with_blocks);
+    };
+    if (sp.n_window_tasks > 0) shape(std::true_type{});
+    else shape(std::false_type{});
     if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
     return LIBRA_OK;
 }
@@ -1661,7 +1839,7 @@ extern "C" int libra_plan_set_values_for(libra_plan_t *P, const void *vals, int 
         {sa.dev.dense_perm, sa.dev.dense_val, sa.n.dense, vs, 0},
         {sa.dev.res_perm, sa.dev.res_ent, sa.n.res, 0, 0},                  // stride 0: the blocked entry layout
         {sd.dev.dense_perm, sd.dev.dense_pv, sd.n.dense, (int)sizeof(SdPv), 4},
-        {sd.dev.res_perm, sd.dev.res_ent, sd.n.res, (int)sizeof(SdEnt), 12}};
+        {sd.dev.res_perm, sd.dev.res_ent, sd.n.res, 0, 0}};
     for (int k = 0; k < 4; ++k) {
         const Seg &g = segs[k];
         if (g.n == 0 || !(ops & (k < 2 ? LIBRA_OP_SPMM : LIBRA_OP_SDDMM))) continue;

@@ -681,7 +681,8 @@ extern "C" int libra_plan_device_buffer_bound(int64_t M, int64_t nnz, int val_dt
         // a plan with the largest arrays this matrix size can produce (only the sizes matter)
         const Sizes z = make_sizes(M, std::max<int64_t>(nnz, 1), o);
         libra_plan_t fake;
-        fake.M = M; fake.nnz = nnz; fake.vdt = val_dtype; fake.vsize = val_dtype == LIBRA_F32 ? 4 : 2;
+        fake.M = M; fake.nnz = -1;      // no residual list is "the whole matrix": the SDDMM position array is counted
+        fake.vdt = val_dtype; fake.vsize = val_dtype == LIBRA_F32 ? 4 : 2;
         fake.o = o;
         for (SubPlan *sp : {&fake.spmm, &fake.sddmm}) {
             sp->n.blocks = z.nbmax; sp->n.col_slots = z.nbmax * KB; sp->n.bitmap_words = z.nbmax * 4;

@@ -43,11 +43,11 @@ constexpr int RES_ROW_SHIFT = 27;                               // windows of up
 constexpr uint32_t RES_COL_MASK = (1u << RES_ROW_SHIFT) - 1u;
 inline size_t res_block_bytes(size_t value_bytes) { return RES_BLOCK * (4 + value_bytes); }
 inline size_t res_blocked_bytes(size_t n, size_t value_bytes) { return (n + RES_BLOCK - 1) / RES_BLOCK * res_block_bytes(value_bytes); }
-// Residual entry of the SDDMM sub-plan: 16 bytes.
-struct SdEnt {
-    int32_t row, col, perm;
-    uint32_t val;               // fp16 bits in the low half, or fp32 bits
-};
+// The SDDMM sub-plan's residual entries use the same blocks.  Their upper bits hold the row's distance from the row of the
+// block's first entry (RES_FAR: further than fits, the row is read from the row array), and the first rows are a small array
+// of their own: 6 bytes per nonzero with 16-bit values, plus its CSR position only where the residual list is not the whole
+// matrix.
+constexpr uint32_t RES_FAR = 31;
 
 // Packed dense nonzero of the SDDMM sub-plan: where the result goes and the value that scales it.
 struct SdPv {
@@ -64,8 +64,10 @@ struct SubPlanDev {
     void *dense_val = nullptr;          // SpMM: packed values in bit order
     void *dense_pv = nullptr;           // SDDMM: SdPv per packed value
     const int32_t *dense_perm = nullptr;
-    void *res_ent = nullptr;            // SpMM: blocked words and values (see RES_BLOCK); SDDMM: SdEnt per entry
-    const int32_t *res_perm = nullptr;
+    void *res_ent = nullptr;            // blocked words and values (see RES_BLOCK)
+    const int32_t *res_perm = nullptr;  // CSR position per entry; SDDMM: nullptr where entry i is nonzero i
+    const int32_t *res_row = nullptr;   // SDDMM: row per entry ...
+    const int32_t *res_base = nullptr;  // ... and per block of RES_BLOCK entries, of its first entry
     const int32_t *zero_rows = nullptr;
 };
 
