@@ -242,9 +242,9 @@ int libra_plan_upload(libra_plan_t *plan, void *dev_buf, size_t bytes, void *str
  * Dense blocks run on MFMA (operands of the plan's value type, fp32 accumulate), residual nonzeros on the VALU (fp32 FMA);
  * rows with one writer are stored once, rows with several writers are cleared and accumulated with
  * fp32 atomics (their summation order is not deterministic).
- * B must hold finite numbers: a dense block multiplies the empty slots of its tile (zeros) by the gathered rows of B, so
- * an Inf or NaN in row j of B reaches every row of a window that has a dense block with column j, not only the rows
- * with a nonzero in column j (0 * Inf = NaN), where the definition would leave them untouched.  The same holds for
+ * B must hold finite numbers: a tile multiplies its empty places (zeros) by the gathered rows of B, so an Inf or NaN in
+ * row j of B can reach every row of a window that has a nonzero in column j, not only the rows with that nonzero
+ * (0 * Inf = NaN), where the definition would leave them untouched.  The same holds for
  * X and Y in libra_sddmm only for outputs that exist (an output is always a sampled product).
  * ldb * (bytes per element) must be below 2^32.
  * Errors: NULL, SHAPE, UNSUPPORTED, NOT_UPLOADED, NOT_BUILT, HIP.

@@ -2,16 +2,15 @@
 //
 // One wavefront (64 lanes) owns one task of the plan's task table.
 //
-//   SpMM task    dense blocks -> v_mfma_f32_16x16x16_f16: the A tile is decoded from the block
-//                bitmap in registers (Section 4.4 of the paper), the gathered B rows are staged
-//                in LDS and read back in MFMA operand layout with ds_read_b64_tr_b16.  The
-//                accumulators are parked in an fp32 LDS tile of the window.  The residual
-//                nonzeros of the task are then cut into equal contiguous runs, one per lane
-//                group; a group keeps a row's partial sum in registers and adds it into the LDS
-//                tile when the row changes.  Finally the tile is written once: plain coalesced
-//                stores for rows this task owns, fp32 atomics for rows with other writers.
-//                A segment of a decomposed long row is the same task with no blocks and one
-//                atomic output row.
+//   SpMM task    rows of B gathered into LDS 32 at a time (one per vector of a dense block, one
+//                per residual nonzero) x the 16 x 32 piece of A that belongs to them, decoded
+//                from block bitmaps in registers (Section 4.4 of the paper) or built from the
+//                residual nonzeros, on v_mfma_f32_16x16x32; B comes back in operand layout with
+//                ds_read_b64_tr_b16.  The sums stay in the accumulators until the window's rows
+//                are written: plain coalesced stores for rows this task owns, fp32 atomics for
+//                rows with other writers.  A segment of a decomposed long row is the same task
+//                with no blocks and one atomic output row.  fp32 storage: dense blocks on
+//                v_mfma_f32_16x16x4, residual nonzeros on the VALU.
 //   SDDMM window task  X window x gathered Y rows on v_mfma_f32_16x16x32_f16 (both operands are
 //                contiguous along K; the rows of Y pass through LDS), sampled through output
 //                records made at plan time.
@@ -29,11 +28,9 @@
 using namespace libra;
 
 typedef _Float16 half_t;
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef short short8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 struct bf16_t { uint16_t bits; };     // bfloat16 storage: the upper half of a binary32
 
@@ -66,48 +63,10 @@ struct SpmmArgs {
     int32_t phase;          // 0: a task does all its work; 1: dense blocks only; 2: residual nonzeros only, added to what phase 1 wrote
 };
 
-// Per storage type: how a lane reads its piece of a dense-operand row and a residual entry.
+// Per storage type: a residual entry's value as it is stored and as a number.
 template <class T> struct Elem;
 template <> struct Elem<half_t> {
-    static constexpr int PER_LANE = 8;                   // 16 bytes
-    typedef uint4 raw_t;
-    typedef uint16_t val_t;                              // a residual entry's value as stored
-    static constexpr int VALS_PER_WORD = 2;
-    __device__ static raw_t load(const void *base, int64_t elem_off) {
-        return *reinterpret_cast<const uint4 *>(reinterpret_cast<const half_t *>(base) + elem_off);
-    }
-    __device__ static void fma(float v, const raw_t &r, float (&acc)[8]) {
-        half8_t h;
-        __builtin_memcpy(&h, &r, 16);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = fmaf(v, (float)h[e], acc[e]);
-    }
-    __device__ static float dot(const raw_t &x, const raw_t &y, float s) {
-        half8_t a, b;
-        __builtin_memcpy(&a, &x, 16);
-        __builtin_memcpy(&b, &y, 16);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s = fmaf((float)a[e], (float)b[e], s);
-        return s;
-    }
-    __device__ static float pair_lo(uint32_t w) {
-        const uint16_t lo = (uint16_t)(w & 0xffffu);
-        half_t h;
-        __builtin_memcpy(&h, &lo, 2);
-        return (float)h;
-    }
-    __device__ static float pair_hi(uint32_t w) {
-        const uint16_t hi = (uint16_t)(w >> 16);
-        half_t h;
-        __builtin_memcpy(&h, &hi, 2);
-        return (float)h;
-    }
-    __device__ static void mask(raw_t &r, uint32_t keep) { r.x &= keep; r.y &= keep; r.z &= keep; r.w &= keep; }
-    // the lane's 16 bytes of row `col`: one 32x32->64 multiply-add for the address
-    __device__ static raw_t load_row(const void *base, int32_t col, uint32_t ld_bytes, int sub) {
-        const char *p = reinterpret_cast<const char *>(base) + ((uint64_t)(uint32_t)col * ld_bytes + (uint32_t)sub * 16u);
-        return *reinterpret_cast<const uint4 *>(p);
-    }
+    typedef uint16_t val_t;
     __device__ static float word_val(uint32_t bits) {
         const uint16_t lo = (uint16_t)bits;
         half_t h;
@@ -115,74 +74,34 @@ template <> struct Elem<half_t> {
         return (float)h;
     }
 };
-template <> struct Elem<bf16_t> : Elem<half_t> {
-    // same 16-byte pieces and 2-byte entry values as binary16; only the widening differs (a shift)
-    __device__ static float widen(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
-    __device__ static void fma(float v, const raw_t &r, float (&acc)[8]) {
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc[2 * e] = fmaf(v, __uint_as_float(w[e] << 16), acc[2 * e]);
-            acc[2 * e + 1] = fmaf(v, __uint_as_float(w[e] & 0xffff0000u), acc[2 * e + 1]);
-        }
-    }
-    __device__ static float dot(const raw_t &x, const raw_t &y, float s) {
-        const uint32_t a[4] = {x.x, x.y, x.z, x.w}, b[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            s = fmaf(__uint_as_float(a[e] << 16), __uint_as_float(b[e] << 16), s);
-            s = fmaf(__uint_as_float(a[e] & 0xffff0000u), __uint_as_float(b[e] & 0xffff0000u), s);
-        }
-        return s;
-    }
-    __device__ static float pair_lo(uint32_t w) { return __uint_as_float(w << 16); }
-    __device__ static float pair_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-    __device__ static float word_val(uint32_t bits) { return widen(bits & 0xffffu); }
+template <> struct Elem<bf16_t> {
+    typedef uint16_t val_t;
+    __device__ static float word_val(uint32_t bits) { return __uint_as_float(bits << 16); }
 };
 template <> struct Elem<float> {
-    static constexpr int PER_LANE = 4;                   // 16 bytes
-    typedef float4_t raw_t;
     typedef float val_t;
-    static constexpr int VALS_PER_WORD = 1;
-    __device__ static raw_t load(const void *base, int64_t elem_off) {
-        return *reinterpret_cast<const float4_t *>(reinterpret_cast<const float *>(base) + elem_off);
-    }
-    __device__ static void fma(float v, const raw_t &r, float (&acc)[8]) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = fmaf(v, r[e], acc[e]);
-    }
-    __device__ static float dot(const raw_t &x, const raw_t &y, float s) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = fmaf(x[e], y[e], s);
-        return s;
-    }
-    __device__ static float pair_lo(uint32_t w) { return __uint_as_float(w); }
-    __device__ static float pair_hi(uint32_t w) { return __uint_as_float(w); }
-    __device__ static void mask(raw_t &r, uint32_t keep) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(__float_as_uint(r[e]) & keep);
-    }
-    __device__ static raw_t load_row(const void *base, int32_t col, uint32_t ld_bytes, int sub) {
-        const char *p = reinterpret_cast<const char *>(base) + ((uint64_t)(uint32_t)col * ld_bytes + (uint32_t)sub * 16u);
-        return *reinterpret_cast<const float4_t *>(p);
-    }
     __device__ static float word_val(uint32_t bits) { return __uint_as_float(bits); }
 };
+// fp32 storage, vector ALU paths: a lane's 16 bytes of row `row` of an operand, and what is done with them
+__device__ inline float4_t load_row4(const void *base, int32_t row, uint32_t ld_bytes, int sub) {
+    return *reinterpret_cast<const float4_t *>(reinterpret_cast<const char *>(base) + ((uint64_t)(uint32_t)row * ld_bytes + (uint32_t)sub * 16u));
+}
+__device__ inline float dot4(const float4_t &x, const float4_t &y) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = fmaf(x[e], y[e], s);
+    return s;
+}
 
-// NW 32-bit words from an LDS address aligned to their size (16 bytes from four words up): 16-byte reads issued back to
-// back; every word then goes through an opaque move, so that it is read once and whole however its fields are used.
+// NW 32-bit words from a 16-byte aligned LDS address: 16-byte reads issued back to back; every word then goes through an
+// opaque move, so that it is read once and whole however its fields are used.
 template <int NW>
 __device__ inline void lds_words(const void *lds, uint32_t (&w)[NW]) {
-    static_assert(NW == 2 || NW % 4 == 0, "8 bytes, or whole 16-byte reads");
-    if constexpr (NW == 2) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(lds);
-        w[0] = v.x; w[1] = v.y;
-    } else {
+    static_assert(NW % 4 == 0, "whole 16-byte reads");
 #pragma unroll
-        for (int k = 0; k < NW / 4; ++k) {
-            const uint4 v = reinterpret_cast<const uint4 *>(lds)[k];
-            w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
-        }
+    for (int k = 0; k < NW / 4; ++k) {
+        const uint4 v = reinterpret_cast<const uint4 *>(lds)[k];
+        w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
     }
 #pragma unroll
     for (int k = 0; k < NW; ++k) asm volatile("" : "+v"(w[k]));
@@ -190,8 +109,9 @@ __device__ inline void lds_words(const void *lds, uint32_t (&w)[NW]) {
 // entry i of the blocked layout: its word and its value
 template <class V>
 __device__ inline void load_blocked_entry(const void *base, int64_t i, uint32_t &word, V &val) {
-    const char *blk = reinterpret_cast<const char *>(base) + (i / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(V)));
-    const int slot = (int)(i % RES_BLOCK);
+    const uint32_t u = (uint32_t)i;                        // entries are counted in 31 bits
+    const char *blk = reinterpret_cast<const char *>(base) + (uint64_t)(u / RES_BLOCK) * (RES_BLOCK * (4u + (uint32_t)sizeof(V)));
+    const uint32_t slot = u % RES_BLOCK;
     word = reinterpret_cast<const uint32_t *>(blk)[slot];
     val = reinterpret_cast<const V *>(blk + RES_BLOCK * 4)[slot];
 }
@@ -200,18 +120,7 @@ __device__ inline void global_add(float *p, float v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One 16x16 tile step on the matrix cores for either 16-bit storage type; operands are passed as raw bits.
-template <class T>
-__device__ inline float4_t mfma_k16(short4_t a, short4_t b, float4_t c) {
-    if constexpr (std::is_same<T, half_t>::value) {
-        half4_t ha, hb;
-        __builtin_memcpy(&ha, &a, 8);
-        __builtin_memcpy(&hb, &b, 8);
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(ha, hb, c, 0, 0, 0);
-    } else {
-        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-    }
-}
+// One 16x16x32 tile step on the matrix cores for either 16-bit storage type; operands are passed as raw bits.
 template <class T>
 __device__ inline float4_t mfma_k32(const uint4 &a, const uint4 &b, float4_t c) {
     if constexpr (std::is_same<T, half_t>::value) {
@@ -257,49 +166,120 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-#ifndef SPMM_U
-#define SPMM_U 8
-#endif
-// Register budget: a 128-column task is held to four waves per SIMD by its 10 KB of LDS anyway; narrower ones gain
-// from six (community N=64: 176 -> 139 us, power-law N=64: 49 -> 45 us), which four fetches in flight per group allow.
+// LDS addresses that are handed around keep their address space (a generic pointer costs a test and a select at every use).
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef __attribute__((address_space(3))) float lds_float;
+typedef uint32_t word4_t __attribute__((ext_vector_type(4)));
+__device__ inline uint4 lds_read16(const lds_byte *p) {
+    const word4_t v = *reinterpret_cast<const __attribute__((address_space(3))) word4_t *>(p);
+    return uint4{v[0], v[1], v[2], v[3]};
+}
+// 16 bytes per lane from global memory to LDS, past the registers: lane l's piece lands at lds + 16 l.
+__device__ inline void load_to_lds(const void *src, lds_byte *lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+__device__ inline void wait_for_loads() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    wave_sync();
+}
+
+// The stage's readers are done: fetches into it may be issued.
+__device__ inline void wait_for_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wave_sync();
+}
+
+// SpMM, 16-bit storage.  Every row of B that a task needs - one per vector of its dense blocks, one per residual nonzero -
+// goes through the same LDS stage and the same instruction: 32 staged rows are the k dimension of v_mfma_f32_16x16x32, the
+// other operand is the 16 x 32 piece of A that belongs to them, built in registers from the block bitmaps (Section 4.4) or,
+// for residual nonzeros, with one value per column.  The sums stay in the accumulators until the task's rows are written.
+// A row's 16-byte pieces are fetched by consecutive lanes straight into LDS (no registers, no address per piece to keep), in
+// batches of ROWS rows; piece p of row r is kept at place p ^ 2 unit(r), so that the transposing reads of two lane groups
+// (eight rows, 32 bytes of each) touch all banks once.
+// Bound by the L2s: 128 channels of 64 bytes per clock are 18.7 TB/s, the power-law graph at N = 128 draws 6.5 M lines of 128
+// bytes from them (44 us at that rate).  Against fetching residual rows into registers and adding their products on the vector
+// ALUs (67 - 75 % busy with it; 24.7 -> 12.0 M wave instructions, power-law N = 128): power-law N = 32 / 64 / 128 44.7 / 43.7
+// / 65.5 -> 31.0 / 39.3 / 64.0 us, GAT graph N = 64 596 -> 555, irregular N = 32 1,888 -> 1,845, community N = 128 277 -> 268.
+// Two half-size stages in turn, 64 rows at N = 64 and seven or eight waves per SIMD at N <= 64 are each slower somewhere.
+template <int N>
+struct GatherStage {
+    static constexpr int ROW = 2 * N;                        // bytes of a staged row
+    static constexpr int PIECES = N / 8;                     // 16-byte pieces of a row = lanes that fetch it
+    static constexpr int RPL = WAVE / PIECES;                // rows per wave load
+    static constexpr int ROWS = N >= 64 ? 32 : 64;           // rows staged together
+    static constexpr int LOADS = ROWS / RPL;
+    static constexpr int BYTES = ROWS * ROW;
+    static_assert(N == 32 || N == 64 || N == 128, "piece widths");
+    __device__ static int unit(int row) {
+        return N == 128 ? (row & 3) | (row >> 1 & 4) : N == 64 ? (row >> 1 & 1) | (row >> 2 & 2) : row >> 3 & 1;
+    }
+    // rows ids[first .. first + count) of `base` (one id per lane of the wave) to the stage; whole loads, so up to RPL - 1 more
+    __device__ static void fetch(const char *base, uint32_t ld_bytes, int ids, int first, int count, lds_byte *stage) {
+        const int lane = threadIdx.x;
+        int id[LOADS];
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) id[i] = __builtin_amdgcn_ds_bpermute((first + i * RPL + lane / PIECES) * 4, ids);
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) asm volatile("" : "+v"(id[i]));          // all ids before the first fetch
+        auto load = [&](int i) {
+            const int piece = (lane % PIECES) ^ unit(i * RPL + lane / PIECES) << 1;
+            load_to_lds(base + ((uint64_t)(uint32_t)id[i] * ld_bytes + (uint32_t)piece * 16u), stage + i * RPL * ROW);
+        };
+        if (count > ROWS - RPL) {            // a whole batch, without a branch per load
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) load(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+                if (i * RPL < count) load(i);
+        }
+    }
+    // rows past the first `count` of an empty stage: the products take them times zero, so they have to be numbers
+    __device__ static void clear_rest(int count, lds_byte *stage) {
+        if (count > ROWS - RPL) return;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            if (i * RPL >= count) *reinterpret_cast<__attribute__((address_space(3))) word4_t *>(stage + i * RPL * ROW + threadIdx.x * 16) = word4_t{0u, 0u, 0u, 0u};
+    }
+    // B operand of columns 16 n .. 16 n + 15 and staged rows at .. at + 31: lane (g, j) gets column j of rows at + 8 g .. + 7.
+    // Lane i of a 16-lane group points at row i / 4, halves 4 (i % 4) .. + 3 of the 32-byte piece; the transposing read hands
+    // lane j the four rows' element j.
+    __device__ static uint4 operand(const lds_byte *stage, int at, int n, int g, int j) {
+        const int row = 8 * g + (j >> 2);
+        const lds_byte *p = stage + at * ROW + (row * ROW + ((n ^ unit(row)) * 32 + 8 * (j & 3)));
+        typedef short4_t __attribute__((address_space(3))) *lds_t;
+        const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)p), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(p + 4 * ROW));
+        uint4 r;
+        __builtin_memcpy(&r.x, &lo, 8);
+        __builtin_memcpy(&r.z, &hi, 8);
+        return r;
+    }
+};
+
 template <class T, int N>
-__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ? 4 : 6))) void spmm_task_kernel(SpmmArgs a) {
-    using E = Elem<T>;
-    typedef typename E::val_t val_t;
-    constexpr bool F32 = std::is_same<T, float>::value;        // fp32 storage: v_mfma_f32_16x16x4_f32, operands straight from the stage
-    constexpr bool DENSE = true;
-    constexpr int PL = E::PER_LANE;          // elements of a row per lane
-    constexpr int LPR = N / PL;              // lanes per row
-    constexpr int RPW = WAVE / LPR;          // lane groups per wave
-    static_assert(LPR >= 1 && LPR <= WAVE && WAVE % LPR == 0, "unsupported N");
-    constexpr int LDC = N + 4;               // fp32 tile row stride (floats)
-    constexpr int BPI = 1;                   // dense blocks staged in LDS at a time (the stage then fits inside the tile's bytes)
-    constexpr int LDBS = N + 16;             // stage row stride in elements: 4 consecutive 16-bit rows / 2 consecutive fp32 rows cover all 32 banks
-    constexpr int TILE_BYTES = W * LDC * 4;
-    constexpr int STAGE_BYTES = DENSE ? BPI * KB * LDBS * (int)sizeof(T) : 0;
-    constexpr int SMEM = TILE_BYTES > STAGE_BYTES ? TILE_BYTES : STAGE_BYTES;
-    constexpr int ECAP = 128;                // residual entries staged per round
-    constexpr int BCAP = 8;                  // dense blocks whose metadata is staged per round
-    constexpr int U = N >= 128 ? SPMM_U : SPMM_U / 2;   // B-row fetches in flight per lane group (narrow rows: fewer, for more waves)
-    // the B stage (dense phase) and the C tile (afterwards) share the same LDS bytes
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
-    __shared__ __attribute__((aligned(16))) uint32_t ent_lds[ECAP];          // the staged entries' words (column | row in window) ...
-    __shared__ __attribute__((aligned(16))) val_t val_lds[ECAP];             // ... and values
-    __shared__ __attribute__((aligned(16))) int32_t cols_lds[DENSE ? BCAP * KB : 4];
-    __shared__ __attribute__((aligned(16))) uint64_t bm_lds[DENSE ? WAVE : 2];   // BCAP * 4 words used
-    float *tile = reinterpret_cast<float *>(smem);
+__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ? 5 : 6))) void spmm_gather_kernel(SpmmArgs a) {
+    using S = GatherStage<N>;
+    constexpr int NT = N / 16;
+    constexpr int PAIRS = S::ROWS / (2 * KB);                // pairs of blocks per batch
+    constexpr int TILE_BYTES = W * N * 4;
+    constexpr int SMEM = TILE_BYTES > S::BYTES ? TILE_BYTES : S::BYTES;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];        // the stage, afterwards the C tile
+    __shared__ __attribute__((aligned(16))) uint16_t row_lds[WAVE], val_lds[WAVE];       // residual nonzeros: row in window, value bits
+    lds_byte *stage = (lds_byte *)smem;
 
     // workgroup b: die b mod 8, then the pieces of one task next to each other (they read the same plan data through
     // the same L2), then the die's next task
-    const unsigned round = blockIdx.x >> 3, piece = round % (unsigned)a.pieces;
-    const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + round / (unsigned)a.pieces];
-    const char *Bp = reinterpret_cast<const char *>(a.B) + (size_t)piece * N * sizeof(T);
+    unsigned round = blockIdx.x >> 3, piece = 0;
+    if (a.pieces > 1) {
+        piece = round % (unsigned)a.pieces;
+        round /= (unsigned)a.pieces;
+    }
+    DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + round];
+    asm volatile("" : "+s"(t.id), "+s"(t.blk_begin), "+s"(t.blk_end), "+s"(t.res_begin), "+s"(t.res_end), "+s"(t.masks));      // one load
+    const char *Bp = reinterpret_cast<const char *>(a.B) + (size_t)piece * S::ROW;
     float *Cp = a.C + (size_t)piece * N;
-    const int lane = threadIdx.x;
-    const int sub = lane % LPR;              // which PL-wide piece of a row
-    const int grp = lane / LPR;              // which lane group
+    const int lane = threadIdx.x, g = lane >> 4, j = lane & 15;
     const uint32_t atomic_mask = t.masks & 0xffffu, store_mask = t.masks >> 16;
-    const uint32_t out_mask = atomic_mask | store_mask;
     // The two-kernel mode (the paper's sequential schedule of Section 4.4.1: matrix-unit part, then scalar part) runs
     // the table twice.  Phase 1 takes the tasks that have blocks and writes all their rows; phase 2 takes the tasks that
     // have residual nonzeros or own rows that phase 1 did not write, and adds to rows that phase 1 wrote.
@@ -309,7 +289,219 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     const int L = a.phase == 1 ? 0 : t.res_end - t.res_begin;
     if (a.phase == 2 && nblk_all > 0 && L == 0) return;
     const bool add_to_c = a.phase == 2 && nblk_all > 0;
-    const uint32_t ldb_bytes = (uint32_t)a.ldb * (uint32_t)sizeof(T);
+    const uint32_t ldb_bytes = (uint32_t)a.ldb * 2u;
+
+    // ---- the task's first metadata of each kind in one round trip, from clamped (always valid) addresses ----
+    uint32_t word;
+    uint16_t val;
+    auto load_entries = [&](int e0) { load_blocked_entry(a.res_ent, (int64_t)(t.res_begin + max(min(e0 + lane, L - 1), 0)), word, val); };
+    int col;                            // lane l: column of slot l of the batch
+    uint64_t bits[PAIRS][4];            // bitmap of the block this lane's A elements come from, and its first packed value
+    uint32_t vptr[PAIRS];
+    auto load_blocks = [&](int b0) {
+        const int last = max(nblk - 1, 0);
+        col = a.blk_cols[(int64_t)(t.blk_begin + min(b0 + g, last)) * KB + j];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int64_t b = t.blk_begin + min(b0 + 2 * p + (g >> 1), last);
+            const uint64_t *bm = a.blk_bitmap + b * 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bits[p][k] = bm[k];
+            vptr[p] = (uint32_t)a.blk_valptr[b];
+        }
+    };
+    load_entries(0);
+    if (nblk > 0) load_blocks(0);
+
+    S::clear_rest(nblk > 0 ? nblk * KB : L, stage);
+    float4_t acc[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[n] = float4_t{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const uint4 &af, int at) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[n] = mfma_k32<T>(af, S::operand(stage, at, n, g, j), acc[n]);
+    };
+
+    // ---- dense blocks ----
+    for (int b0 = 0; b0 < nblk; b0 += 2 * PAIRS) {
+        // a padding slot fetches the row of its block's first slot (always a real one)
+        const int head = __builtin_amdgcn_ds_bpermute((lane & 48) * 4, col);
+        S::fetch(Bp, ldb_bytes, col >= 0 ? col : head, 0, (nblk - b0) * KB, stage);
+        // this lane's A elements: row j, slots 8 (g & 1) .. + 7 of block g / 2 of each pair.  Their values are loaded
+        // unconditionally (an unset slot reads a neighbouring value, at most 7 past the array's end, inside its 16 spare
+        // bytes) and selected when they have arrived.
+        uint32_t av[PAIRS][8], set[PAIRS];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int q = j >> 2, shift = (j & 3) * 16 + 8 * (g & 1);
+            const uint64_t w = q == 0 ? bits[p][0] : q == 1 ? bits[p][1] : q == 2 ? bits[p][2] : bits[p][3];
+            const int c0 = __popcll(bits[p][0]), c1 = __popcll(bits[p][1]), c2 = __popcll(bits[p][2]);
+            const int before = (q > 0 ? c0 : 0) + (q > 1 ? c1 : 0) + (q > 2 ? c2 : 0) + __popcll(w & ((1ull << shift) - 1ull));
+            set[p] = b0 + 2 * p + (g >> 1) < nblk ? (uint32_t)(w >> shift) & 0xffu : 0u;
+            uint32_t at = (vptr[p] + (uint32_t)before) * 2u;             // bytes: fewer than 2^32 for 31-bit counts
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                av[p][e] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(a.dense_val) + at);
+                at += (set[p] >> e & 1u) * 2u;
+            }
+        }
+        if (b0 + 2 * PAIRS < nblk) load_blocks(b0 + 2 * PAIRS);
+        wait_for_loads();
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) av[p][e] = set[p] >> e & 1u ? av[p][e] : 0u;
+            const uint4 af{av[p][0] | av[p][1] << 16, av[p][2] | av[p][3] << 16, av[p][4] | av[p][5] << 16, av[p][6] | av[p][7] << 16};
+            if (b0 + 2 * p < nblk) multiply(af, 2 * KB * p);
+        }
+        wait_for_lds();                  // the stage may be overwritten
+    }
+
+    // ---- residual nonzeros ----
+    for (int e0 = 0; e0 < L; e0 += WAVE) {
+        const int nE = min(WAVE, L - e0);
+        row_lds[lane] = (uint16_t)(word >> RES_ROW_SHIFT);
+        val_lds[lane] = lane < nE ? val : (uint16_t)0;
+        const int ids = (int)(word & RES_COL_MASK);
+#pragma unroll
+        for (int h = 0; h < WAVE; h += S::ROWS) {
+            if (h < nE) {
+                S::fetch(Bp, ldb_bytes, ids, h, nE - h, stage);
+                if (h == 0 && e0 + WAVE < L) load_entries(e0 + WAVE);        // they travel with the rows
+                wait_for_loads();
+#pragma unroll
+                for (int k0 = 0; k0 < S::ROWS; k0 += 32) {
+                    if (h + k0 < nE) {
+                        // A elements: nonzero 8 g + e of these 32 in its own row, nothing in the others, two per word: the value
+                        // times (1 - |row - j|, not below zero)
+                        typedef unsigned short ushort8_t __attribute__((ext_vector_type(8)));
+                        const uint4 rw = lds_read16((lds_byte *)row_lds + 2 * (h + k0 + 8 * g)), vw = lds_read16((lds_byte *)val_lds + 2 * (h + k0 + 8 * g));
+                        ushort8_t r, v;
+                        __builtin_memcpy(&r, &rw, 16);
+                        __builtin_memcpy(&v, &vw, 16);
+                        const ushort8_t one = (unsigned short)1;
+                        r = __builtin_elementwise_sub_sat(one, r ^ (unsigned short)j) * v;
+                        uint4 af;
+                        __builtin_memcpy(&af, &r, 16);
+                        multiply(af, k0);
+                    }
+                }
+                wait_for_lds();
+            }
+        }
+    }
+
+    // ---- the tile: accumulators to LDS (lane (g, j) holds rows 4g..4g+3, feature 16n + j), rows written once ----
+    lds_float *tile = reinterpret_cast<lds_float *>(stage);
+    float *cbase = Cp + (int64_t)t.id * W * a.ldc;
+    if (store_mask == 0 && (atomic_mask & (atomic_mask - 1u)) == 0) {
+        // one row, other writers beside this task (a segment of a decomposed row)
+        const int r = __builtin_ctz(atomic_mask | 1u << W);
+        if (r < W) {
+            if (g == r >> 2) {
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const float lo = r & 1 ? acc[n][1] : acc[n][0], hi = r & 1 ? acc[n][3] : acc[n][2];
+                    tile[16 * n + j] = r & 2 ? hi : lo;
+                }
+            }
+            wave_sync();
+            float *dst = cbase + (int64_t)r * a.ldc;
+#pragma unroll
+            for (int c = 0; c < N; c += WAVE)
+                if (N >= WAVE || lane < N) global_add(dst + c + lane, tile[c + lane]);
+        }
+        return;
+    }
+    auto at = [](int row, int c) { return row * N + (c ^ (row >> 2 & (NT - 1)) * 16); };        // four rows' 64-byte pieces in different banks
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) tile[at(4 * g + e, 16 * n + j)] = acc[n][e];
+    wave_sync();
+    constexpr int LPF = N / 4;                                   // lanes per tile row at 4 floats each
+    constexpr int RPP = WAVE / LPF;                              // tile rows per wave pass
+    const int rr = lane / LPF, cl = lane % LPF;
+    float *dst = cbase + (int64_t)rr * a.ldc + cl * 4;
+    const int64_t step = RPP * a.ldc;
+    if (atomic_mask == 0 && !add_to_c) {
+        // streaming stores: C is written once and not read again by this call
+        float4_t x[W / RPP];
+#pragma unroll
+        for (int k = 0; k < W / RPP; ++k) x[k] = *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(&tile[at(k * RPP + rr, cl * 4)]);
+#pragma unroll
+        for (int k = 0; k < W / RPP; ++k) {
+            if (store_mask >> (k * RPP + rr) & 1u) __builtin_nontemporal_store(x[k], reinterpret_cast<float4_t *>(dst));
+            dst += step;
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < W / RPP; ++k, dst += step) {
+        const int r = k * RPP + rr;
+        if (store_mask >> r & 1u) {
+            float4_t x = *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(&tile[at(r, cl * 4)]);
+            if (add_to_c) {           // stream order: phase 1 has written the row
+                const float4_t y = *reinterpret_cast<const float4_t *>(dst);
+                x[0] += y[0]; x[1] += y[1]; x[2] += y[2]; x[3] += y[3];
+            }
+            __builtin_nontemporal_store(x, reinterpret_cast<float4_t *>(dst));
+        } else if (atomic_mask >> r & 1u) {
+            // each atomic instruction covers LPF consecutive floats of the row
+#pragma unroll
+            for (int e = 0; e < 4; ++e) global_add(dst - cl * 4 + e * LPF + cl, tile[at(r, e * LPF + cl)]);
+        }
+    }
+}
+
+// SpMM, fp32 storage: a product on the matrix cores costs a full-rate FMA there (v_mfma_f32_16x16x4), so only the dense
+// blocks run on them and the residual nonzeros run on the vector ALUs.  The dense phase takes one block per round trip: the
+// 16 rows of B go through an LDS stage that shares its bytes with the C tile, a lane's four A elements are the four k-steps
+// of the product.  The accumulators are parked in the tile, and the residual nonzeros of the task, cut into equal contiguous
+// runs per lane group, are added to it.
+// Register budget: a 128-column task is held to four waves per SIMD by its LDS anyway; narrower ones gain from six, which
+// four fetches in flight per group allow.
+template <int N>
+__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ? 4 : 6))) void spmm_task_kernel_f32(SpmmArgs a) {
+    constexpr int PL = 4;                    // elements of a row per lane (16 bytes)
+    constexpr int LPR = N / PL;              // lanes per row
+    constexpr int RPW = WAVE / LPR;          // lane groups per wave
+    static_assert(LPR >= 1 && LPR <= WAVE && WAVE % LPR == 0, "unsupported N");
+    constexpr int LDC = N + 4;               // tile row stride (floats)
+    constexpr int LDBS = N + 16;             // stage row stride: 2 consecutive rows cover all 32 banks
+    constexpr int TILE_BYTES = W * LDC * 4;
+    constexpr int STAGE_BYTES = KB * LDBS * 4;
+    constexpr int SMEM = TILE_BYTES > STAGE_BYTES ? TILE_BYTES : STAGE_BYTES;
+    constexpr int ECAP = 128;                // residual entries staged per round
+    constexpr int BCAP = 8;                  // dense blocks whose metadata is staged per round
+    constexpr int U = N >= 128 ? 8 : 4;      // B-row fetches in flight per lane group (narrow rows: fewer, for more waves)
+    // the B stage (dense phase) and the C tile (afterwards) share the same LDS bytes
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+    __shared__ __attribute__((aligned(16))) uint32_t ent_lds[ECAP];          // the staged entries' words (column | row in window) ...
+    __shared__ __attribute__((aligned(16))) float val_lds[ECAP];             // ... and values
+    __shared__ __attribute__((aligned(16))) int32_t cols_lds[BCAP * KB];
+    __shared__ __attribute__((aligned(16))) uint64_t bm_lds[WAVE];           // BCAP * 4 words used
+    float *tile = reinterpret_cast<float *>(smem);
+
+    // workgroup b: die b mod 8, then the pieces of one task next to each other (they read the same plan data through
+    // the same L2), then the die's next task
+    const unsigned round = blockIdx.x >> 3, piece = round % (unsigned)a.pieces;
+    const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + round / (unsigned)a.pieces];
+    const char *Bp = reinterpret_cast<const char *>(a.B) + (size_t)piece * N * 4;
+    float *Cp = a.C + (size_t)piece * N;
+    const int lane = threadIdx.x;
+    const int sub = lane % LPR;              // which PL-wide piece of a row
+    const int grp = lane / LPR;              // which lane group
+    const uint32_t atomic_mask = t.masks & 0xffffu, store_mask = t.masks >> 16;
+    const uint32_t out_mask = atomic_mask | store_mask;
+    // two-kernel mode: see spmm_gather_kernel
+    const int nblk_all = t.blk_end - t.blk_begin;
+    if (a.phase == 1 && nblk_all == 0) return;
+    const int nblk = a.phase == 2 ? 0 : nblk_all;
+    const int L = a.phase == 1 ? 0 : t.res_end - t.res_begin;
+    if (a.phase == 2 && nblk_all > 0 && L == 0) return;
+    const bool add_to_c = a.phase == 2 && nblk_all > 0;
+    const uint32_t ldb_bytes = (uint32_t)a.ldb * 4u;
 
     // ---- round trip 2: all metadata of the task (first round of each kind) ----
     // Loads are issued unconditionally from clamped (always valid) addresses and unused results are
@@ -318,21 +510,19 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     {
         const int nE = min(L, ECAP), nb = min(nblk, BCAP);
         uint32_t tmp[ECAP / WAVE];
-        val_t tmp_val[ECAP / WAVE];
+        float tmp_val[ECAP / WAVE];
 #pragma unroll
         for (int k = 0; k < ECAP / WAVE; ++k)
             load_blocked_entry(a.res_ent, (int64_t)t.res_begin + max(min(k * WAVE + lane, nE - 1), 0), tmp[k], tmp_val[k]);
-        if constexpr (DENSE) {
-            const int32_t *csrc = a.blk_cols + (int64_t)t.blk_begin * KB;
-            int32_t c[BCAP * KB / WAVE];
+        const int32_t *csrc = a.blk_cols + (int64_t)t.blk_begin * KB;
+        int32_t c[BCAP * KB / WAVE];
 #pragma unroll
-            for (int k = 0; k < BCAP * KB / WAVE; ++k) c[k] = csrc[max(min(k * WAVE + lane, nb * KB - 1), 0)];
-            const uint64_t w = a.blk_bitmap[(int64_t)t.blk_begin * 4 + max(min(lane, nb * 4 - 1), 0)];
+        for (int k = 0; k < BCAP * KB / WAVE; ++k) c[k] = csrc[max(min(k * WAVE + lane, nb * KB - 1), 0)];
+        const uint64_t w = a.blk_bitmap[(int64_t)t.blk_begin * 4 + max(min(lane, nb * 4 - 1), 0)];
 #pragma unroll
-            for (int k = 0; k < BCAP * KB / WAVE; ++k) cols_lds[k * WAVE + lane] = c[k];
-            bm_lds[lane] = w;        // all 64 lanes write (the upper ones a copy of the last word): under a `lane < 32` branch
+        for (int k = 0; k < BCAP * KB / WAVE; ++k) cols_lds[k * WAVE + lane] = c[k];
+        bm_lds[lane] = w;            // all 64 lanes write (the upper ones a copy of the last word): under a `lane < 32` branch
                                      // the compiler moves the load there too and issues it only after the loads before it returned
-        }
 #pragma unroll
         for (int k = 0; k < ECAP / WAVE; ++k) {
             ent_lds[k * WAVE + lane] = tmp[k];
@@ -341,157 +531,94 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     }
     // later rounds of a task with more than BCAP blocks are fetched in place
     auto fetch_blocks = [&](int b0, int nb) {
-        if constexpr (DENSE) {
-            const int32_t *csrc = a.blk_cols + (int64_t)(t.blk_begin + b0) * KB;
-            int32_t c[BCAP * KB / WAVE];
+        const int32_t *csrc = a.blk_cols + (int64_t)(t.blk_begin + b0) * KB;
+        int32_t c[BCAP * KB / WAVE];
 #pragma unroll
-            for (int k = 0; k < BCAP * KB / WAVE; ++k) c[k] = csrc[min(k * WAVE + lane, nb * KB - 1)];
-            const uint64_t w = a.blk_bitmap[(int64_t)(t.blk_begin + b0) * 4 + min(lane, nb * 4 - 1)];
+        for (int k = 0; k < BCAP * KB / WAVE; ++k) c[k] = csrc[min(k * WAVE + lane, nb * KB - 1)];
+        const uint64_t w = a.blk_bitmap[(int64_t)(t.blk_begin + b0) * 4 + min(lane, nb * 4 - 1)];
 #pragma unroll
-            for (int k = 0; k < BCAP * KB / WAVE; ++k) cols_lds[k * WAVE + lane] = c[k];
-            bm_lds[lane] = w;        // all 64 lanes write (the upper ones a copy of the last word): under a `lane < 32` branch
-                                     // the compiler moves the load there too and issues it only after the loads before it returned
-        }
+        for (int k = 0; k < BCAP * KB / WAVE; ++k) cols_lds[k * WAVE + lane] = c[k];
+        bm_lds[lane] = w;
     };
     wave_sync();
 
     bool tile_ready = false;
-    if constexpr (DENSE) {
-        if (nblk > 0) {
-            tile_ready = true;
-            constexpr int NT = N / 16;
-            constexpr int PASSES = BPI * KB / RPW;               // wave loads per staged group of BPI blocks
-            constexpr int H = (N <= 128 && !F32) ? 2 : 1;        // staged groups per round trip (more costs registers, i.e. waves)
-            constexpr int FPI = BPI * H;                         // blocks fetched per round trip
-            static_assert(BPI * KB % RPW == 0 && PASSES >= 1, "stage shape");
-            typedef typename std::conditional<F32, float, uint16_t>::type stage_t;
-            stage_t *stage = reinterpret_cast<stage_t *>(smem);
-            const int g = lane >> 4, j = lane & 15;
-            float4_t acc[NT];
+    if (nblk > 0) {
+        tile_ready = true;
+        constexpr int NT = N / 16;
+        constexpr int PASSES = KB / RPW > 0 ? KB / RPW : 1;  // wave loads per block
+        static_assert(KB % RPW == 0, "stage shape");
+        float *stage = reinterpret_cast<float *>(smem);
+        const int g = lane >> 4, j = lane & 15;
+        float4_t acc[NT];
 #pragma unroll
-            for (int n = 0; n < NT; ++n) acc[n] = float4_t{0.f, 0.f, 0.f, 0.f};
-            int vbase = t.val_begin;                             // first packed value of the current block
-            for (int b0 = 0; b0 < nblk; b0 += BCAP) {
-                const int nbr = min(BCAP, nblk - b0);
-                if (b0 > 0) {
-                    wave_sync();
-                    fetch_blocks(b0, nbr);
-                    wave_sync();
-                }
-                for (int bb = 0; bb < nbr; bb += FPI) {
-                    const int nb = min(FPI, nbr - bb);
-                    // one round trip: the B rows of up to FPI blocks (padding slots become zero rows) ...
-                    typename E::raw_t raw[H][PASSES];
-                    int cc[H][PASSES];
-                    // all column ids first (LDS reads back to back), then all fetches
-#pragma unroll
-                    for (int h = 0; h < H; ++h)
-#pragma unroll
-                        for (int ps = 0; ps < PASSES; ++ps)
-                            cc[h][ps] = cols_lds[bb * KB + min(h * BPI * KB + ps * RPW + grp, nb * KB - 1)];
-#pragma unroll
-                    for (int h = 0; h < H; ++h)
-#pragma unroll
-                        for (int ps = 0; ps < PASSES; ++ps) {
-                            const int k = h * BPI * KB + ps * RPW + grp;
-                            const int c = cc[h][ps];
-                            // a padding slot fetches row 0 and is cleared by a mask the compiler cannot see through
-                            // (so that it keeps the fetch outside any branch)
-                            uint32_t keep = (k < nb * KB && c >= 0) ? 0xffffffffu : 0u;
-                            asm volatile("" : "+v"(keep));
-                            raw[h][ps] = E::load_row(Bp, keep ? c : 0, ldb_bytes, sub);
-                            E::mask(raw[h][ps], keep);
-                        }
-                    // ... and this lane's 4 A elements (row j, slots 4g..4g+3) of each block, decoded from its bitmap
-                    typedef typename std::conditional<F32, float, short>::type aval_t;
-                    typedef typename std::conditional<F32, float4_t, short4_t>::type afrag_t;
-                    // All value loads of the FPI blocks are issued before any of them is used: unconditional loads (an unset
-                    // slot reads a neighbouring value, at most 3 values past the array's end, inside its 16 spare bytes; a
-                    // block past the last one repeats the last one), and the selects afterwards.  With two blocks per round
-                    // trip an opaque move sits between the two: without it the compiler moves a load under its select's
-                    // condition and waits block by block (community N=128 261 -> 255 us with it, GAT graph N=64 624 -> 581 us
-                    // against the same code without it); with one block per round trip (fp32) it only forces the wait early
-                    // (community 388 -> 436 us) and is left out.
-                    afrag_t af[FPI];
-                    typedef typename std::conditional<F32, float, int>::type areg_t;
-                    areg_t av[FPI][4];
-                    unsigned nib[FPI];
-                    {
-                        int vb = vbase;
-#pragma unroll
-                        for (int x = 0; x < FPI; ++x) {
-                            const uint64_t *bm = &bm_lds[(bb + min(x, nb - 1)) * 4];
-                            const uint64_t w0 = bm[0], w1 = bm[1], w2 = bm[2], w3 = bm[3];
-                            const int q = j >> 2;
-                            const uint64_t word = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
-                            const int c0 = __popcll(w0), c1 = __popcll(w1), c2 = __popcll(w2), c3 = __popcll(w3);
-                            int prefix = (q > 0 ? c0 : 0) + (q > 1 ? c1 : 0) + (q > 2 ? c2 : 0);
-                            const int bitpos = (j & 3) * 16 + 4 * g;
-                            prefix += __popcll(word & ((1ull << bitpos) - 1ull));
-                            nib[x] = x < nb ? (unsigned)(word >> bitpos) & 0xFu : 0u;
-                            const aval_t *vals = reinterpret_cast<const aval_t *>(a.dense_val) + vb + prefix;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) av[x][e] = (areg_t)vals[__popc(nib[x] & ((1u << e) - 1u))];
-                            if (x + 1 < nb) vb += c0 + c1 + c2 + c3;       // the next block's values follow; a repeated block re-reads its own
-                            if (x < nb) vbase += c0 + c1 + c2 + c3;
-                        }
-                    }
-#pragma unroll
-                    for (int x = 0; x < FPI; ++x)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if constexpr (FPI > 1) asm volatile("" : "+v"(av[x][e]));
-#pragma unroll
-                    for (int x = 0; x < FPI; ++x)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) af[x][e] = (nib[x] >> e & 1u) ? (aval_t)av[x][e] : (aval_t)0;
-                    // the fetched rows go through the LDS stage BPI blocks at a time
-#pragma unroll
-                    for (int h = 0; h < H; ++h) {
-                        if (h * BPI < nb) {
-                            wave_sync();         // the previous operand reads are done
-#pragma unroll
-                            for (int ps = 0; ps < PASSES; ++ps) {
-                                const int k = ps * RPW + grp;
-                                *reinterpret_cast<typename E::raw_t *>(&stage[k * LDBS + sub * PL]) = raw[h][ps];
-                            }
-                            wave_sync();
-#pragma unroll
-                            for (int x = 0; x < BPI; ++x) {
-                                if (h * BPI + x < nb) {
-                                    if constexpr (F32) {
-                                        // k-step e of the 16x16x4 product takes column slot 4g + e from lane group g (the same
-                                        // slots as this lane's 4 A elements): B[4g+e][16n+j] is a plain 4-byte read
-                                        const float *src = &stage[(x * KB + 4 * g) * LDBS + j];
-#pragma unroll
-                                        for (int n = 0; n < NT; ++n)
-#pragma unroll
-                                            for (int e = 0; e < 4; ++e)
-                                                acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[h * BPI + x][e], src[e * LDBS + 16 * n], acc[n], 0, 0, 0);
-                                    } else {
-                                        // lane i of a 16-lane block points at row i/4, halves 4(i%4)..+3 of the 32-byte row piece;
-                                        // the transposing read hands lane j the four rows' element j: B[4g+e][16n+j], e = 0..3
-                                        const uint16_t *src = &stage[(x * KB + 4 * g + (j >> 2)) * LDBS + 4 * (j & 3)];
-#pragma unroll
-                                        for (int n = 0; n < NT; ++n) {
-                                            const short4_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                                (short4_t __attribute__((address_space(3))) *)(src + 16 * n));
-                                            acc[n] = mfma_k16<T>(af[h * BPI + x], r, acc[n]);
-                                        }
-                                    }
-                                }
-                            }
-                        }
-                    }
-                }
+        for (int n = 0; n < NT; ++n) acc[n] = float4_t{0.f, 0.f, 0.f, 0.f};
+        int vbase = t.val_begin;                             // first packed value of the current block
+        for (int b0 = 0; b0 < nblk; b0 += BCAP) {
+            const int nbr = min(BCAP, nblk - b0);
+            if (b0 > 0) {
+                wave_sync();
+                fetch_blocks(b0, nbr);
+                wave_sync();
             }
-            wave_sync();
-            // park the accumulators: lane (g, j) holds rows 4g..4g+3, feature 16n + j
+            for (int bb = 0; bb < nbr; ++bb) {
+                // one round trip: the B rows of a block (padding slots become zero rows) ...
+                float4_t raw[PASSES];
+                int cc[PASSES];
 #pragma unroll
-            for (int n = 0; n < NT; ++n)
+                for (int ps = 0; ps < PASSES; ++ps) cc[ps] = cols_lds[bb * KB + ps * RPW + grp];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) tile[(4 * g + e) * LDC + 16 * n + j] = acc[n][e];
+                for (int ps = 0; ps < PASSES; ++ps) {
+                    // a padding slot fetches row 0 and is cleared by a mask the compiler cannot see through
+                    // (so that it keeps the fetch outside any branch)
+                    uint32_t keep = cc[ps] >= 0 ? 0xffffffffu : 0u;
+                    asm volatile("" : "+v"(keep));
+                    raw[ps] = load_row4(Bp, keep ? cc[ps] : 0, ldb_bytes, sub);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[ps][e] = __uint_as_float(__float_as_uint(raw[ps][e]) & keep);
+                }
+                // ... and this lane's 4 A elements (row j, slots 4g..4g+3), decoded from the bitmap: unconditional loads (an
+                // unset slot reads a neighbouring value, at most 3 values past the array's end, inside its 16 spare bytes),
+                // and the selects afterwards
+                float4_t af;
+                {
+                    const uint64_t *bm = &bm_lds[bb * 4];
+                    const uint64_t w0 = bm[0], w1 = bm[1], w2 = bm[2], w3 = bm[3];
+                    const int q = j >> 2;
+                    const uint64_t word = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
+                    const int c0 = __popcll(w0), c1 = __popcll(w1), c2 = __popcll(w2), c3 = __popcll(w3);
+                    int prefix = (q > 0 ? c0 : 0) + (q > 1 ? c1 : 0) + (q > 2 ? c2 : 0);
+                    const int bitpos = (j & 3) * 16 + 4 * g;
+                    prefix += __popcll(word & ((1ull << bitpos) - 1ull));
+                    const unsigned nib = (unsigned)(word >> bitpos) & 0xFu;
+                    const float *vals = reinterpret_cast<const float *>(a.dense_val) + vbase + prefix;
+                    float av[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) av[e] = vals[__popc(nib & ((1u << e) - 1u))];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) af[e] = (nib >> e & 1u) ? av[e] : 0.f;
+                    vbase += c0 + c1 + c2 + c3;
+                }
+                wave_sync();         // the previous operand reads are done
+#pragma unroll
+                for (int ps = 0; ps < PASSES; ++ps) *reinterpret_cast<float4_t *>(&stage[(ps * RPW + grp) * LDBS + sub * PL]) = raw[ps];
+                wave_sync();
+                // k-step e of the 16x16x4 product takes column slot 4g + e from lane group g (the same slots as this lane's
+                // 4 A elements): B[4g+e][16n+j] is a plain 4-byte read
+                const float *src = &stage[4 * g * LDBS + j];
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[e], src[e * LDBS + 16 * n], acc[n], 0, 0, 0);
+            }
         }
+        wave_sync();
+        // park the accumulators: lane (g, j) holds rows 4g..4g+3, feature 16n + j
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tile[(4 * g + e) * LDC + 16 * n + j] = acc[n][e];
     }
     constexpr int LPF = N / 4;                                   // lanes per tile row at 4 floats each
     constexpr int RPP = WAVE / LPF >= 1 ? WAVE / LPF : 1;        // tile rows per wave pass
@@ -513,7 +640,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
         // the next round's entries go in flight now and wait in registers until this round is done
         const int nE_next = min(ECAP, L - e0 - ECAP);
         uint32_t next_ent[ECAP / WAVE];
-        val_t next_val[ECAP / WAVE];
+        float next_val[ECAP / WAVE];
         if (nE_next > 0) {
 #pragma unroll
             for (int k = 0; k < ECAP / WAVE; ++k)
@@ -530,50 +657,50 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
         // registers instead and adds it after the others, in group order, so the order of additions is fixed.
         bool first_is_shared = q0 > 0 && q0 < q1 && ((ent_lds[q0 - 1] ^ ent_lds[q0]) >> RES_ROW_SHIFT) == 0;
         int kept_row = -1;
-        float kept[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        float4_t kept = {0.f, 0.f, 0.f, 0.f};
         int cur = -1;
-        float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        auto add_to_tile = [&](int r, const float (&v)[8]) {
+        float4_t acc = {0.f, 0.f, 0.f, 0.f};
+        auto add_to_tile = [&](int r, const float4_t &v) {
+            float4_t *p = reinterpret_cast<float4_t *>(&tile[r * LDC + sub * PL]);
+            float4_t x = *p;
 #pragma unroll
-            for (int e = 0; e < PL; e += 4) {
-                float4_t *p = reinterpret_cast<float4_t *>(&tile[r * LDC + sub * PL + e]);
-                float4_t x = *p;
-                x[0] += v[e]; x[1] += v[e + 1]; x[2] += v[e + 2]; x[3] += v[e + 3];
-                *p = x;
-            }
+            for (int e = 0; e < 4; ++e) x[e] += v[e];
+            *p = x;
+        };
+        auto add_product = [&](float v, const float4_t &row) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(v, row[e], acc[e]);
         };
         auto flush = [&]() {
             if (first_is_shared) {
                 first_is_shared = false;
                 kept_row = cur;
-#pragma unroll
-                for (int e = 0; e < PL; ++e) kept[e] = acc[e];
+                kept = acc;
             } else {
                 add_to_tile(cur, acc);
             }
         };
         for (int q = q0; q < q1; q += U) {
             // all entry reads, then all row fetches, back to back
-            typename E::raw_t raw[U];
+            float4_t raw[U];
             const bool full = q + U <= q1;
             // U consecutive entries from one aligned base address; slots past the run hold valid entries whose fetch is
             // harmless and whose product is never formed
-            constexpr int VPW = E::VALS_PER_WORD;
             int ecol[U], erow[U];
             float eval[U];
             {
-                uint32_t cr[U], vw[U / VPW];
+                uint32_t cr[U], vw[U];
                 lds_words<U>(ent_lds + q, cr);
-                lds_words<U / VPW>(val_lds + q, vw);
+                lds_words<U>(val_lds + q, vw);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     ecol[u] = (int)(cr[u] & RES_COL_MASK);
                     erow[u] = (int)(cr[u] >> RES_ROW_SHIFT);
-                    eval[u] = (u % VPW) ? E::pair_hi(vw[u / VPW]) : E::pair_lo(vw[u / VPW]);
+                    eval[u] = __uint_as_float(vw[u]);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) raw[u] = E::load_row(Bp, ecol[u], ldb_bytes, sub);
+            for (int u = 0; u < U; ++u) raw[u] = load_row4(Bp, ecol[u], ldb_bytes, sub);
             bool one_row = full;
 #pragma unroll
             for (int u = 1; u < U; ++u) one_row = one_row && erow[u] == erow[0];
@@ -582,12 +709,11 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
                 const int r = erow[0];
                 if (r != cur) {
                     if (cur >= 0) flush();
-#pragma unroll
-                    for (int e = 0; e < PL; ++e) acc[e] = 0.f;
+                    acc = float4_t{0.f, 0.f, 0.f, 0.f};
                     cur = r;
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) E::fma(eval[u], raw[u], acc);
+                for (int u = 0; u < U; ++u) add_product(eval[u], raw[u]);
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -595,11 +721,10 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
                         const int r = erow[u];
                         if (r != cur) {
                             if (cur >= 0) flush();
-#pragma unroll
-                            for (int e = 0; e < PL; ++e) acc[e] = 0.f;
+                            acc = float4_t{0.f, 0.f, 0.f, 0.f};
                             cur = r;
                         }
-                        E::fma(eval[u], raw[u], acc);
+                        add_product(eval[u], raw[u]);
                     }
                 }
             }
@@ -693,26 +818,11 @@ __device__ inline float group_sum(float s) {
     return s;
 }
 
-// 16 bytes per lane from global memory to LDS, past the registers: lane l's piece lands at lds + 16 l.
-__device__ inline void load_to_lds(const void *src, unsigned char *lds) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
-}
-__device__ inline void wait_for_loads() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    wave_sync();
-}
-
 // 16-bit rows of Y come through LDS: a row's consecutive pieces are fetched by consecutive lanes, so that the address unit
 // handles 64 bytes per access (operand-shaped loads touch four rows with every four lanes: 544 M instead of 184 M accesses
 // for the segments of the GAT graph at K = 64, 910 instead of 690 us; window tasks of the community matrix K = 64 / 128
 // 222 / 372 -> 201 / 328 us).  Piece c of row r is kept
 // at place c ^ swizzle(r), which spreads the pieces that 16 lanes read together over all banks.
-// The stage's readers are done: fetches into it may be issued.
-__device__ inline void wait_for_lds() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    wave_sync();
-}
-
 template <int K>
 struct RowStage {
     static constexpr int ROW = 2 * K;                        // bytes of a row
@@ -723,7 +833,7 @@ struct RowStage {
     __device__ static int swizzle(int row) { return (row * PIECES / 16) & (PIECES - 1); }
     // rows ids[first], ids[first + 1], ... (one id per lane of the wave) of `base` to stage rows at, at + 1, ...
     template <int COUNT>
-    __device__ static void fetch(const void *base, int ids, int first, unsigned char *stage, int at) {
+    __device__ static void fetch(const void *base, int ids, int first, lds_byte *stage, int at) {
         const int lane = threadIdx.x % WAVE;
         int id[COUNT / RPL];
 #pragma unroll
@@ -737,8 +847,8 @@ struct RowStage {
         }
     }
     // operand of 16 staged rows from `at` on: piece g + 4 s of row j
-    __device__ static uint4 operand(const unsigned char *stage, int at, int g, int j, int s) {
-        return *reinterpret_cast<const uint4 *>(stage + (at + j) * ROW + ((g + 4 * s) ^ swizzle(at + j)) * 16);
+    __device__ static uint4 operand(const lds_byte *stage, int at, int g, int j, int s) {
+        return lds_read16(stage + (at + j) * ROW + ((g + 4 * s) ^ swizzle(at + j)) * 16);
     }
 };
 
@@ -750,7 +860,7 @@ struct RowStage {
 // stores that fall into the row-contiguous runs of the output instead of one 4-byte store per matrix-core lane (the
 // write-back of Section 4.4.2, with the popcount offsets resolved when the plan is built).
 template <class T, int K>
-__device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, unsigned char *stage) {
+__device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = RowStage<K>;
     constexpr int KS = K / 32;               // MFMA k-steps
     constexpr int RU = 4;                    // record loads in flight per lane
@@ -758,7 +868,7 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, u
     const int lane = threadIdx.x % WAVE;
     const int g = lane >> 4, j = lane & 15;
     const uint16_t *X = reinterpret_cast<const uint16_t *>(a.X);
-    float *products = reinterpret_cast<float *>(stage);
+    lds_float *products = reinterpret_cast<lds_float *>(stage);
     // A operand: row j of the window, k = 32*s + 8g .. +7 (rows past M repeat the last row; no record points at them)
     const int64_t xr = min((int64_t)t.id * W + j, a.M - 1);
     uint4 xa[KS];
@@ -915,12 +1025,12 @@ struct SegmentEntry {
 // f16, against that version: GAT graph K = 64 772 -> 680 us (648 us with segments of 128), power-law K = 32 35.4 -> 27.3,
 // community K = 32 177 -> 146, irregular 1,905 -> 1,770 us.  Fetching the next batch's entries early: no change.
 template <class T, int K>
-__device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, unsigned char *stage) {
+__device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = RowStage<K>;
     constexpr int KS = K / 32;                   // MFMA k-steps
     const int lane = threadIdx.x % WAVE;
     const int g = lane >> 4, j = lane & 15;
-    float *out_stage = reinterpret_cast<float *>(stage);
+    lds_float *out_stage = reinterpret_cast<lds_float *>(stage);
     for (int q0 = t.res_begin; q0 < t.res_end; q0 += WAVE) {
         SegmentEntry<T> ent;
         ent.load(a, min(q0 + lane, t.res_end - 1));
@@ -986,10 +1096,8 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, 
 // The same for fp32 storage, where the vector ALUs are the faster unit (v_mfma_f32_16x16x4 forms 16 products per column of
 // the tile to use one): K/4 lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.
 template <int K>
-__device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, float *stage) {
-    using E = Elem<float>;
-    constexpr int PL = E::PER_LANE;
-    constexpr int LPN = K / PL;              // lanes per nonzero
+__device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, lds_float *stage) {
+    constexpr int LPN = K / 4;              // lanes per nonzero
     constexpr int NPW = WAVE / LPN;          // nonzeros per wave pass
     constexpr int U = LPN <= 8 ? 8 : 4;      // passes in flight
     static_assert(LPN >= 4 && LPN % 4 == 0 && LPN <= WAVE, "unsupported K (whole quads per nonzero)");
@@ -1001,17 +1109,17 @@ __device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask 
         ent.load(a, q0 + min(lane, n - 1));
         const int col = ent.col(), row = ent.row(a);
         for (int e0 = 0; e0 < n; e0 += NPW * U) {
-            E::raw_t x[U], y[U];
+            float4_t x[U], y[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int from = (e0 + u * NPW + grp) * 4;
                 const int r = __builtin_amdgcn_ds_bpermute(from, row), c = __builtin_amdgcn_ds_bpermute(from, col);
-                x[u] = E::load(a.X, (int64_t)r * K + sub * PL);
-                y[u] = E::load(a.Y, (int64_t)c * K + sub * PL);
+                x[u] = load_row4(a.X, r, K * 4, sub);
+                y[u] = load_row4(a.Y, c, K * 4, sub);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float s = group_sum<LPN>(E::dot(x[u], y[u], 0.f));
+                const float s = group_sum<LPN>(dot4(x[u], y[u]));
                 if (sub == 0) stage[e0 + u * NPW + grp] = s;
             }
         }
@@ -1036,17 +1144,17 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K ==
     constexpr int PRODUCTS = DENSE ? SD_GROUP * 256 * 4 : WAVE * 4, ROWS = RowStage<K>::BYTES;
     constexpr int STAGE = F32 ? WAVE * 4 : PRODUCTS > ROWS ? PRODUCTS : ROWS;           // bytes per wave
     __shared__ __attribute__((aligned(16))) unsigned char stage_all[WPB * STAGE];
-    const unsigned wave = threadIdx.x / WAVE;
+    const unsigned wave = WPB == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const unsigned seq = (blockIdx.x >> 3) * WPB + wave;                // position in the die's part of the table
     if (seq >= (unsigned)a.tasks_per_die) return;
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + seq];
-    unsigned char *stage = stage_all + wave * STAGE;
+    lds_byte *stage = (lds_byte *)stage_all + wave * STAGE;
     if (DENSE && t.kind == LIBRA_TASK_WINDOW) {
         if constexpr (F32) sddmm_window_task_f32<K>(a, t);
         else sddmm_window_task<T, K>(a, t, stage);
         return;
     }
-    if constexpr (F32) sddmm_segment_task_f32<K>(a, t, reinterpret_cast<float *>(stage));
+    if constexpr (F32) sddmm_segment_task_f32<K>(a, t, reinterpret_cast<lds_float *>(stage));
     else sddmm_segment_task<T, K>(a, t, stage);
 }
 
@@ -1346,7 +1454,8 @@ inline int hip_rc(hipError_t e) { return e == hipSuccess ? LIBRA_OK : LIBRA_ERR_
 template <class T, int N>
 int launch_spmm(const SpmmArgs &a, int64_t ntasks, hipStream_t s) {
     if (ntasks == 0) return LIBRA_OK;
-    hipLaunchKernelGGL((spmm_task_kernel<T, N>), dim3((unsigned)(ntasks * a.pieces)), dim3(WAVE), 0, s, a);
+    if constexpr (std::is_same<T, float>::value) hipLaunchKernelGGL((spmm_task_kernel_f32<N>), dim3((unsigned)(ntasks * a.pieces)), dim3(WAVE), 0, s, a);
+    else hipLaunchKernelGGL((spmm_gather_kernel<T, N>), dim3((unsigned)(ntasks * a.pieces)), dim3(WAVE), 0, s, a);
     return hip_rc(hipGetLastError());
 }
 

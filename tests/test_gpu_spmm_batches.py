@@ -1,0 +1,58 @@
+"""The 16-bit SpMM task at the edges of its batches: windows with every combination of dense vectors around whole blocks and
+pairs of blocks and residual nonzeros around whole batches, each row owned, split or shared, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2506_22714_amd import binding as lb
+from paper_2506_22714_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+DENSE = (0, 1, 16, 17, 32, 33, 49)          # vectors of three or more nonzeros per window
+SINGLE = (0, 1, 31, 32, 33, 64, 65, 130)    # columns with one nonzero
+
+
+def edge_windows(seed=5, Kc=400):
+    rng = np.random.default_rng(seed)
+    D = np.zeros((16 * len(DENSE) * len(SINGLE) - 5, Kc), dtype=np.float32)
+    w = 0
+    for d in DENSE:
+        for r in SINGLE:
+            rows = np.arange(16 * w, min(16 * w + 16, D.shape[0]))
+            cols = rng.permutation(Kc)
+            for c in cols[:d]:
+                D[rng.choice(rows, size=rng.integers(3, rows.size + 1), replace=False), c] = 1.0
+            one_row = rng.random() < 0.3        # every third window: all its single nonzeros in one row, which is then split
+            D[rng.choice(rows) if one_row else rng.choice(rows, size=r), cols[d:d + r]] = 1.0
+            w += 1
+    A = wl.from_dense(D)
+    return wl.Csr(A.M, A.Kc, A.rowptr, A.col, wl.uniform_values(rng, A.nnz))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("N", [32, 64, 128, 224])
+def test_batch_edges(N, dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    A = edge_windows()
+    B = wl.dense_normal(A.Kc, N, seed=1, dtype=np.float32)
+    if dtype == "bf16":
+        B, val = wl.to_bf16_bits(B), wl.to_bf16_bits(A.val.astype(np.float32))
+        Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.bfloat16)
+    else:
+        B, val = B.astype(np.float16), A.val
+        Bd = torch.from_numpy(B).cuda()
+    ref, S = oracle.spmm(A.rowptr, A.col, val, B, bf16=dtype == "bf16")
+    deg = np.diff(A.rowptr).astype(np.float64)
+    limit = 16.0 * np.sqrt(deg.max()) * 2.0 ** -24      # exact products, deg - 1 fp32 additions
+    for opts in (dict(), dict(flags=lb.FLAG_NO_FILL_PADDING), dict(flags=lb.FLAG_NO_FILL_PADDING, cs=40, ts=2),
+                 dict(flags=lb.FLAG_TWO_KERNELS, cs=40), dict(mode=lb.MODE_SCALAR_ONLY), dict(mode=lb.MODE_DENSE_ONLY)):
+        p = lb.Plan.from_csr(A, val=val, val_dtype=lb.BF16 if dtype == "bf16" else None, **opts).upload()
+        C = torch.full((A.M, N), float("nan"), device="cuda")
+        got = p.spmm(Bd, out=C).cpu().numpy()
+        err = oracle.graded_error(got, ref, S, np.maximum(deg, 1)[:, None])
+        assert err <= limit, f"{dtype} N={N} {opts}: {err:.3e} > {limit:.3e}"
+        p.close()
