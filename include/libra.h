@@ -239,13 +239,16 @@ int libra_plan_upload(libra_plan_t *plan, void *dev_buf, size_t bytes, void *str
  *   C    device, M x N row-major fp32 with row stride ldc (ldc >= N, ldc % 4 == 0); fully overwritten
  *        (rows of A without nonzeros become zeros); must not alias B.
  *   N    multiple of 32 (fp16) or of 16 (fp32), 32 <= N <= 512
- * Dense blocks run on MFMA (operands of the plan's value type, fp32 accumulate), residual nonzeros on the VALU (fp32 FMA);
+ * Dense blocks, and with 16-bit storage residual nonzeros too, run on MFMA (operands of the plan's value type, fp32 accumulate),
+ * residual nonzeros of fp32 storage on the VALU (fp32 FMA);
  * rows with one writer are stored once, rows with several writers are cleared and accumulated with
  * fp32 atomics (their summation order is not deterministic).
- * B must hold finite numbers: a tile multiplies its empty places (zeros) by the gathered rows of B, so an Inf or NaN in
- * row j of B can reach every row of a window that has a nonzero in column j, not only the rows with that nonzero
- * (0 * Inf = NaN), where the definition would leave them untouched.  The same holds for
- * X and Y in libra_sddmm only for outputs that exist (an output is always a sampled product).
+ * 16-bit storage: an Inf or NaN in row j of B reaches the rows with a nonzero in column j and no others (a task that meets
+ * one forms its sums without the matrix cores, several times slower).  fp32 storage: B must hold finite numbers: a dense block
+ * multiplies the empty slots of its tile (zeros) by the gathered rows of B, so an Inf or NaN in row j of B reaches every row of
+ * a window that has a dense block with column j, not only the rows with a nonzero in column j (0 * Inf = NaN), where the
+ * definition would leave them untouched.  X and Y in libra_sddmm: only outputs that exist are affected (an output is always a
+ * sampled product).
  * ldb * (bytes per element) must be below 2^32.
  * Errors: NULL, SHAPE, UNSUPPORTED, NOT_UPLOADED, NOT_BUILT, HIP.
  */

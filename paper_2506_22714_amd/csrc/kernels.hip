@@ -256,6 +256,39 @@ struct GatherStage {
     }
 };
 
+// The sums of a task from its nonzeros alone, one at a time on the vector ALUs, into a tile of W x N: for rows of B that hold
+// an Inf or NaN, which must not meet the empty places of a matrix-core tile.
+template <class T, int N>
+__device__ inline void spmm_exact_sums(const SpmmArgs &a, const DevTask &t, int nblk, int L, const char *Bp, uint32_t ldb_bytes, lds_float *tile) {
+    const int lane = threadIdx.x;
+    constexpr int F = N >= WAVE ? WAVE : N;                  // features per pass; a narrower tile is done by the first lanes
+    for (int c = lane; c < W * N; c += WAVE) tile[c] = 0.f;
+    wave_sync();
+    auto add = [&](int row, int col, uint32_t value_bits) {
+        const uint16_t *src = reinterpret_cast<const uint16_t *>(Bp + (uint64_t)(uint32_t)col * ldb_bytes);
+        const float v = Elem<T>::word_val(value_bits);
+#pragma unroll
+        for (int c = 0; c < N; c += F)
+            if (F == WAVE || lane < F) tile[row * N + c + lane] = fmaf(v, Elem<T>::word_val(src[c + lane]), tile[row * N + c + lane]);
+    };
+    const uint16_t *vals = reinterpret_cast<const uint16_t *>(a.dense_val);
+    for (int b = t.blk_begin; b < t.blk_begin + nblk; ++b) {
+        int at = a.blk_valptr[b];
+        for (int q = 0; q < 4; ++q)
+            for (uint64_t w = a.blk_bitmap[(int64_t)b * 4 + q]; w; w &= w - 1) {
+                const int bit = __builtin_ctzll(w);
+                add(4 * q + (bit >> 4), a.blk_cols[(int64_t)b * KB + (bit & 15)], vals[at++]);
+            }
+    }
+    for (int i = 0; i < L; ++i) {
+        uint32_t word;
+        uint16_t val;
+        load_blocked_entry(a.res_ent, (int64_t)(t.res_begin + i), word, val);
+        add((int)(word >> RES_ROW_SHIFT), (int)(word & RES_COL_MASK), val);
+    }
+    wave_sync();
+}
+
 template <class T, int N>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ? 5 : 6))) void spmm_gather_kernel(SpmmArgs a) {
     using S = GatherStage<N>;
@@ -391,9 +424,25 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
         }
     }
 
-    // ---- the tile: accumulators to LDS (lane (g, j) holds rows 4g..4g+3, feature 16n + j), rows written once ----
     lds_float *tile = reinterpret_cast<lds_float *>(stage);
     float *cbase = Cp + (int64_t)t.id * W * a.ldc;
+    // An Inf or NaN among the staged rows is in every row of the accumulators (0 * Inf = NaN): such a task (and one whose sums
+    // overflow) forms its sums again from its nonzeros alone.
+    float probe = 0.f;
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) probe = fmaf(acc[n][e], 0.f, probe);
+    if (__any(probe != probe)) {
+        spmm_exact_sums<T, N>(a, t, nblk, L, Bp, ldb_bytes, tile);
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[n][e] = tile[(4 * g + e) * N + 16 * n + j];
+        wait_for_lds();
+    }
+
+    // ---- the tile: accumulators to LDS (lane (g, j) holds rows 4g..4g+3, feature 16n + j), rows written once ----
     if (store_mask == 0 && (atomic_mask & (atomic_mask - 1u)) == 0) {
         // one row, other writers beside this task (a segment of a decomposed row)
         const int r = __builtin_ctz(atomic_mask | 1u << W);

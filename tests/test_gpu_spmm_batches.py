@@ -56,3 +56,40 @@ def test_batch_edges(N, dtype):
         err = oracle.graded_error(got, ref, S, np.maximum(deg, 1)[:, None])
         assert err <= limit, f"{dtype} N={N} {opts}: {err:.3e} > {limit:.3e}"
         p.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("N", [32, 64, 128, 224])
+def test_inf_and_nan_reach_only_the_rows_that_refer_to_them(N, dtype):
+    """0 * Inf = NaN: an Inf or NaN in a row of B must not come into the sums through the empty places of a tile, nor subnormal
+    numbers be lost in it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    A = edge_windows(seed=6)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    B = torch.from_numpy(wl.dense_normal(A.Kc, N, seed=1, dtype=np.float32)).to(tdt)
+    B[::7] *= 2.0 ** (-130 if dtype == "bf16" else -16)           # subnormal
+    B[3, 0], B[50, N - 1], B[111, 5], B[200, N // 2] = float("inf"), -float("inf"), float("nan"), float("inf")
+    val = torch.from_numpy(A.val.astype(np.float32)).to(tdt)
+    rows = np.repeat(np.arange(A.M), np.diff(A.rowptr))
+    D = np.zeros((A.M, A.Kc))
+    D[rows, A.col] = val.double().numpy()
+    Bd = B.double().numpy()
+    want, scale = D @ np.where(np.isfinite(Bd), Bd, 0.0), np.abs(D) @ np.abs(np.where(np.isfinite(Bd), Bd, 0.0))
+    with np.errstate(invalid="ignore"):
+        for r, c in np.argwhere(~np.isfinite(Bd)):
+            hit = D[:, r] != 0
+            want[hit, c] += D[hit, r] * Bd[r, c]
+    finite = np.isfinite(want)
+    deg = np.diff(A.rowptr)
+    limit = deg.max() * 2.0 ** -24                                # deg - 1 fp32 additions of exact products
+    limit_abs = deg.max() * 2.0 ** -149                           # and of products below the normal range
+    for opts in (dict(), dict(flags=lb.FLAG_NO_FILL_PADDING), dict(cs=40, ts=2), dict(flags=lb.FLAG_TWO_KERNELS, cs=40),
+                 dict(mode=lb.MODE_SCALAR_ONLY), dict(mode=lb.MODE_DENSE_ONLY)):
+        p = lb.Plan.from_csr(A, val=val.view(torch.int16).numpy().view(np.uint16) if dtype == "bf16" else val.numpy(),
+                             val_dtype=lb.BF16 if dtype == "bf16" else None, **opts).upload()
+        got = p.spmm(B.cuda()).double().cpu().numpy()
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want), err_msg=str(opts))
+        np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)], err_msg=str(opts))
+        assert np.all(np.abs(got - np.where(finite, want, got))[finite] <= (limit * scale + limit_abs)[finite]), opts
+        p.close()
