@@ -1513,7 +1513,7 @@ int spmm_launch(const libra_plan_t *P, const SpmmArgs &a, int n, int64_t nt, hip
 // `pieces` adjacent pieces of n columns each, one launch
 int spmm_piece(const libra_plan_t *P, const void *B, int n, int pieces, int64_t ldb, float *C, int64_t ldc, hipStream_t s) {
     const SubPlan &sp = P->spmm;
-    const int64_t per_die = ((int64_t)sp.tasks.size() + LIBRA_XCDS - 1) / LIBRA_XCDS;
+    const int64_t per_die = (sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS;
     SpmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr, sp.dev.dense_val,
                sp.dev.res_ent, B, C, ldb, ldc, (int32_t)per_die, pieces, 0};
     if (sp.n.zero_rows) {
@@ -1693,8 +1693,9 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     const bool from_host = st && !da;
     auto H = [&](const void *p) { return from_host ? p : nullptr; };
     // ---- SpMM ----
-    if (st) st->tasks_a = pack_tasks(P, sa, true);
-    u.put(st ? (const void *)st->tasks_a.data() : nullptr, nullptr, task_slots(sa.n.tasks) * sizeof(DevTask), sa.dev.tasks);
+    const bool pack_a = st && !(da && da->write_tasks);
+    if (pack_a) st->tasks_a = pack_tasks(P, sa, true);
+    u.put(pack_a ? (const void *)st->tasks_a.data() : nullptr, nullptr, task_slots(sa.n.tasks) * sizeof(DevTask), sa.dev.tasks);
     u.put(H(sa.blk_cols.data()), da ? da->blk_cols : nullptr, (size_t)sa.n.col_slots * 4, sa.dev.blk_cols);
     u.put(H(sa.blk_bitmap.data()), da ? da->blk_bitmap : nullptr, (size_t)sa.n.bitmap_words * 8, sa.dev.blk_bitmap);
     u.put(H(sa.blk_valptr.data()), da ? da->blk_valptr : nullptr, P->o.build_spmm ? (size_t)(sa.n.blocks + 1) * 4 : 0, sa.dev.blk_valptr);
@@ -1717,8 +1718,9 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     u.put(H(sa.res_perm.data()), da ? da->res_perm : nullptr, nres * 4, sa.dev.res_perm);
     u.put(H(sa.zero_rows.data()), da ? da->zero_rows : nullptr, (size_t)sa.n.zero_rows * 4, sa.dev.zero_rows);
     // ---- SDDMM ----
-    if (st) st->tasks_d = pack_tasks(P, sd, false);
-    u.put(st ? (const void *)st->tasks_d.data() : nullptr, nullptr, task_slots(sd.n.tasks) * sizeof(DevTask), sd.dev.tasks);
+    const bool pack_d = st && !(dd && dd->write_tasks);
+    if (pack_d) st->tasks_d = pack_tasks(P, sd, false);
+    u.put(pack_d ? (const void *)st->tasks_d.data() : nullptr, nullptr, task_slots(sd.n.tasks) * sizeof(DevTask), sd.dev.tasks);
     u.put(H(sd.blk_cols.data()), dd ? dd->blk_cols : nullptr, (size_t)sd.n.col_slots * 4, sd.dev.blk_cols);
     u.put(H(sd.blk_bitmap.data()), dd ? dd->blk_bitmap : nullptr, (size_t)sd.n.bitmap_words * 8, sd.dev.blk_bitmap);
     u.put(H(sd.blk_valptr.data()), dd ? dd->blk_valptr : nullptr, P->o.build_sddmm ? (size_t)(sd.n.blocks + 1) * 4 : 0, sd.dev.blk_valptr);
@@ -1791,6 +1793,8 @@ int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const De
         layout(P, u, &st, &da, &dd);
         auto grid = [](int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1 << 16)); };
         const SubPlan &sa = P->spmm, &sd = P->sddmm;
+        if (da.write_tasks && sa.n.tasks) da.write_tasks(const_cast<DevTask *>(sa.dev.tasks), sa.n.tasks);
+        if (dd.write_tasks && sd.n.tasks) dd.write_tasks(const_cast<DevTask *>(sd.dev.tasks), sd.n.tasks);
         if (sa.n.res) {
             if (P->vdt == LIBRA_F32)
                 hipLaunchKernelGGL((pack_blocked_entries_kernel<float>), grid(sa.n.res), dim3(256), 0, s, da.res_col,
@@ -1910,8 +1914,8 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
     SddmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr,
                 reinterpret_cast<const uint2 *>(sp.dev.dense_pv), (int32_t)sp.n.dense,
                 sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, out, P->M, 0, pattern_only};
-    if (sp.tasks.empty()) return LIBRA_OK;
-    a.tasks_per_die = (int32_t)(((int64_t)sp.tasks.size() + LIBRA_XCDS - 1) / LIBRA_XCDS);
+    if (sp.n.tasks == 0) return LIBRA_OK;
+    a.tasks_per_die = (int32_t)((sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS);
     auto launch = [&](auto wpb, auto with_blocks) {
         constexpr int WPB = decltype(wpb)::value;
         constexpr bool DENSE = decltype(with_blocks)::value;

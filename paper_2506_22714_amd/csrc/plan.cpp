@@ -545,7 +545,7 @@ int libra::resolve_options(const libra_plan_opts_t *in, int vdt, Resolved &o) {
 
 // Shared tail of the host and the device planner: the flat SDDMM residual segments, the order of the task
 // tables and the statistics.  Expects the sub-plans with their tasks in window order.
-void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t *share) {
+void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t *share, const TableOrder &order) {
     const Resolved o = P->o;
     const int64_t M = P->M, nnz = P->nnz;
     const int32_t *rowptr = P->rowptr.data();
@@ -574,7 +574,7 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
         sa.count_host_arrays();
         sd.count_host_arrays();
     }
-    if (o.build_sddmm) {
+    if (o.build_sddmm && !order) {
         // scalar segments over the flat residual list (no atomics needed: each output has one writer)
         const int32_t nres = (int32_t)sd.n.res;
         const size_t nseg = ((size_t)nres + o.sddmm_Cs - 1) / o.sddmm_Cs;
@@ -590,7 +590,13 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
     // ---- ordering: heaviest first, so that the tail of the launch is made of light tasks ----
     st.neighbour_share = share ? (share[1] ? (double)share[0] / (double)share[1] : 1.0) : neighbour_share(M, rowptr, cols, o.W, o.threads);
     mark("neighbour share");
-    if (o.heavy_first) {
+    if (order) {
+        if (o.heavy_first) {
+            if (xcd < 0) P->o.xcd_order = xcd = st.neighbour_share <= LIBRA_SHARE_THRESHOLD;
+            st.xcd_order = xcd;
+        }
+        order(o.heavy_first, o.heavy_first && xcd, o.segments_by_column);
+    } else if (o.heavy_first) {
         auto heavier = [](const libra_task_t &a, const libra_task_t &b) { return a.cost > b.cost; };
         {
             // heaviest first, the segments' first columns travelling with their tasks
@@ -655,6 +661,7 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
     }
     mark("placement done");
     for (SubPlan *sp : {&sa, &sd}) {
+        if (order) break;
         for (auto &t : sp->tasks) (t.kind == LIBRA_TASK_WINDOW ? sp->n_window_tasks : sp->n_chunk_tasks)++;
         sp->n.tasks = (int64_t)sp->tasks.size();
     }
@@ -663,7 +670,7 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
     if (o.build_spmm) {
         st.spmm_dense_vectors = sa.dense_vectors; st.spmm_blocks = sa.n.blocks; st.spmm_pad_slots = sa.pad_slots;
         st.spmm_dense_nnz = sa.n.dense; st.spmm_res_nnz = sa.n.res;
-        st.spmm_tasks = (int64_t)sa.tasks.size(); st.spmm_chunk_tasks = sa.n_chunk_tasks;
+        st.spmm_tasks = sa.n.tasks; st.spmm_chunk_tasks = sa.n_chunk_tasks;
         st.spmm_zero_rows = sa.n.zero_rows;
         st.spmm_short_rows = sa.short_rows; st.spmm_long_rows = sa.long_rows; st.spmm_split_rows = sa.split_rows;
         st.spmm_gather_rows = sa.dense_vectors + st.spmm_res_nnz;
@@ -671,7 +678,7 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
     if (o.build_sddmm) {
         st.sddmm_dense_vectors = sd.dense_vectors; st.sddmm_blocks = sd.n.blocks; st.sddmm_pad_slots = sd.pad_slots;
         st.sddmm_dense_nnz = sd.n.dense; st.sddmm_res_nnz = sd.n.res;
-        st.sddmm_tasks = (int64_t)sd.tasks.size();
+        st.sddmm_tasks = sd.n.tasks;
         st.sddmm_gather_rows = sd.dense_vectors + (int64_t)o.W * sd.n.blocks + 2 * st.sddmm_res_nnz;
     }
 }

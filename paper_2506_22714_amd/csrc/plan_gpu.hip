@@ -19,7 +19,7 @@
 //
 // Sorting and prefix sums are rocPRIM device primitives; everything else is written here.
 // The arrays are produced in the host planner's format in the caller's workspace, copied to the
-// plan's host vectors, and the shared tail (task order, statistics) runs on the host.
+// plan's host vectors if a host copy is wanted; large task tables are ordered here, small ones by the host planner's tail.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -41,7 +41,7 @@ namespace {
 constexpr int W = 16, KB = 16;
 typedef unsigned long long u64;
 
-enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_COUNT };
+enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_COUNT };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -82,16 +82,32 @@ struct SubOut {      // one sub-plan in the host planner's format
     libra_task_t *tasks;
 };
 
+// Scratch of the task ordering: `items` entries per array (the longest region of either table).
+struct OrderScratch {
+    size_t items;
+    uint32_t *key_in, *key_out;
+    u64 *wide_in, *wide_out;
+    int32_t *ord, *ord2, *flag, *scan, *first, *rank, *base, *queue;
+    int32_t *meta;              // a few words that the host reads
+    int32_t *pieces;            // MAX_PIECES x {queue, first slot, first queue item}
+    int32_t *order_a, *order_d; // the ordered tables: task index, -1 for an empty task
+};
+constexpr int MAX_PIECES = 4096;
+
 struct Layout {
     int32_t *win_ptr, *spos, *hflag, *vid, *einfo, *ewin, *row_of, *rowbase;
     u64 *key_in, *key_out, *key2_in, *key2_out, *ctr;
     int32_t *vfirst, *vinfo, *vcol, *vwin, *sv, *srank, *scnt, *cum, *tflag, *taud, *win_vptr;
     int32_t *ntau, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
+    OrderScratch o;
     void *tmp;
     size_t tmp_bytes;
     size_t total;
 };
+
+size_t order_items(const Sizes &z) { return (size_t)std::max(z.tasks_a_max, std::max(z.tasks_d_max, z.segs_d_max)); }
+int64_t order_slots(int64_t tasks) { return 2 * tasks + 64; }      // the die-aware orders add empty tasks
 
 size_t rocprim_temp_bytes(const Sizes &z) {
     size_t best = 0, sz = 0;
@@ -102,6 +118,25 @@ size_t rocprim_temp_bytes(const Sizes &z) {
     sz = 0;
     (void)rocprim::exclusive_scan(nullptr, sz, (int32_t *)nullptr, (int32_t *)nullptr, (int32_t)0, (size_t)(z.n + z.nw + 2),
                             rocprim::plus<int32_t>());
+    best = std::max(best, sz);
+    const size_t m = order_items(z) + 16;
+    sz = 0;
+    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, m, 0, 32);
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 64);
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 32);
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::inclusive_scan(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, m, rocprim::maximum<u64>());
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::exclusive_scan(nullptr, sz, (int32_t *)nullptr, (int32_t *)nullptr, (int32_t)0, m, rocprim::plus<int32_t>());
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::exclusive_scan(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, (u64)0, m, rocprim::plus<u64>());
     best = std::max(best, sz);
     return best + 4096;
 }
@@ -165,6 +200,20 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
         s->ntasks = A.take<int32_t>(nw + 1);
         s->tbase = A.take<int32_t>(nw + 1);
         s->tasks = A.take<libra_task_t>((size_t)(s == &L.a ? z.tasks_a_max : z.tasks_d_max));
+    }
+    {
+        OrderScratch &o = L.o;
+        o.items = order_items(z);
+        const size_t m = o.items + 16;
+        o.key_in = A.take<uint32_t>(m);
+        o.key_out = A.take<uint32_t>(m);
+        o.wide_in = A.take<u64>(m);
+        o.wide_out = A.take<u64>(m);
+        for (int32_t **q : {&o.ord, &o.ord2, &o.flag, &o.scan, &o.first, &o.rank, &o.base, &o.queue}) *q = A.take<int32_t>(m);
+        o.meta = A.take<int32_t>(64);
+        o.pieces = A.take<int32_t>(3 * MAX_PIECES);
+        o.order_a = A.take<int32_t>((size_t)order_slots(z.tasks_a_max));
+        o.order_d = A.take<int32_t>((size_t)order_slots(z.tasks_d_max + z.segs_d_max));
     }
     L.tmp_bytes = rocprim_temp_bytes(z);
     L.tmp = A.take<uint8_t>(L.tmp_bytes);
@@ -519,6 +568,7 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
             if (n_short) atomicAdd(&ctr[C_SHORT], (u64)n_short);
             if (n_long) atomicAdd(&ctr[C_LONG], (u64)n_long);
             if (z.split) atomicAdd(&ctr[C_SPLIT], (u64)__popc(z.split));
+            if (nchunks) atomicAdd(&ctr[C_SEGMENTS], (u64)nchunks);
         } else {
             libra_task_t *out = tasks_a + tbase_a[t];
             int32_t *zr = zero_rows + zbase[t];
@@ -628,6 +678,211 @@ __global__ __launch_bounds__(256) void k_task_cols(const libra_task_t *tasks, in
 }
 
 // ------------------------------------------------------------------------------------------
+// Order of the task tables: the rules of finish_plan (heaviest first, segments by column, die-aware groups) as stable sorts
+// and prefix sums, with the same result.  A table is a list of task indices; SDDMM index nt + s is flat residual segment s.
+// ------------------------------------------------------------------------------------------
+constexpr int XC = LIBRA_XCDS;
+
+struct TaskView {
+    const libra_task_t *tasks;
+    int nt, cs, nres;                   // SDDMM segments: cs entries each of nres
+    __device__ u64 cost(int i) const {
+        if (i < nt) return tasks[i].cost;
+        return 2u * (unsigned)min(cs, nres - (i - nt) * cs);
+    }
+    __device__ bool empty(int i) const {          // writes nothing and reads nothing
+        if (i >= nt) return false;
+        const libra_task_t &t = tasks[i];
+        return t.cost == 0 && t.blk_begin == t.blk_end && t.res_begin == t.res_end && t.store_mask == 0 && t.atomic_mask == 0;
+    }
+    __device__ int group(int i) const {
+        if (i >= nt) return (i - nt) / LIBRA_LOCALITY_SEGMENTS;
+        return (tasks[i].kind == LIBRA_TASK_WINDOW ? tasks[i].id : tasks[i].id / W) / LIBRA_LOCALITY_WINDOWS;
+    }
+};
+// round r of the snake deal gives its p-th item to this queue
+__device__ inline int snake(int r) { return r / XC & 1 ? XC - 1 - r % XC : r % XC; }
+// how many of the first n items of the deal go to queue x
+__host__ __device__ inline int snake_count(int n, int x) { return n / XC + ((n / XC & 1 ? XC - 1 - x : x) < n % XC ? 1 : 0); }
+
+__global__ __launch_bounds__(256) void k_order_costs(TaskView v, int n, uint32_t *key) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) key[i] = (uint32_t)v.cost(i);
+}
+__global__ __launch_bounds__(256) void k_order_identity(int n, int first, int32_t *out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = first + i;
+}
+// flag = 1: the item goes by its column (SpMM: segments of decomposed rows; SDDMM: segments inside one row)
+__global__ __launch_bounds__(256) void k_order_by_column_flag(TaskView v, const int32_t *list, const int32_t *col, int n, int32_t *flag) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > n) return;
+    flag[i] = i < n && (list[i] < v.nt ? v.tasks[list[i]].kind == LIBRA_TASK_CHUNK : col[list[i] - v.nt] >= 0) ? 1 : 0;
+}
+// the flagged items with their columns, the others with their costs, each in list order
+__global__ __launch_bounds__(256) void k_order_split(TaskView v, const int32_t *list, const int32_t *col, const int32_t *flag, const int32_t *scan, int n,
+                                                     uint32_t *key, int32_t *placed, int32_t *other, uint32_t *other_cost) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int item = list[i], k = scan[i];
+    if (flag[i]) {
+        key[k] = (uint32_t)col[item < v.nt ? item : item - v.nt];
+        placed[k] = item;
+    } else {
+        other[i - k] = item;
+        other_cost[i - k] = (uint32_t)v.cost(item);
+    }
+}
+__global__ __launch_bounds__(256) void k_order_item_costs(TaskView v, const int32_t *list, int n, u64 *cost) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i <= n) cost[i] = i < n ? v.cost(list[i]) : 0;
+}
+// The die of segment k: LIBRA_XCDS runs of equal cost (run[k] = cost before it, run[n] = all).
+__device__ inline int run_of(const u64 *run, int k, int n) {
+    const u64 total = run[n] ? run[n] : 1;
+    const u64 x = run[k] * XC / total;
+    return x < XC - 1 ? (int)x : XC - 1;
+}
+__global__ void k_order_fill(int32_t *p, int n, int value) {
+    if ((int)threadIdx.x < n) p[threadIdx.x] = value;
+}
+// first segment of every die's run (start was filled with n)
+__global__ __launch_bounds__(256) void k_order_run_starts(const u64 *run, int n, int32_t *start) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const int x = run_of(run, k, n), before = k ? run_of(run, k - 1, n) : -1;
+    for (int y = before + 1; y <= x; ++y) start[y] = k;
+}
+// A die's queue merges its share of the others (descending cost) with its run of segments (column order): segment k comes
+// after the others of its die that cost no less than it or than a segment before it.  This counts the first kind; the maximum
+// over the run (the die in the high word restarts it) adds the second.
+__global__ __launch_bounds__(256) void k_order_others_before(TaskView v, const int32_t *seg, const u64 *run, int n, const uint32_t *other_cost, int no, u64 *before) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const uint32_t c = (uint32_t)v.cost(seg[k]);
+    int lo = 0, hi = no;                // others [0, lo) cost at least c
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (other_cost[mid] >= c) lo = mid + 1; else hi = mid;
+    }
+    const int x = run_of(run, k, n);
+    before[k] = (u64)x << 32 | (u64)snake_count(lo, x);
+}
+__global__ __launch_bounds__(256) void k_order_merge(const int32_t *seg, const u64 *before, const int32_t *start, int n, const int32_t *other, int no, int32_t *queue) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n + no) return;
+    const bool is_seg = i < n;
+    const int x = is_seg ? (int)(before[i] >> 32) : snake(i - n);
+    int off = start[x];                 // the queues one after another: runs and shares of the dies before
+    for (int y = 0; y < x; ++y) off += snake_count(no, y);
+    if (is_seg) {
+        queue[off + (i - start[x]) + (int)(before[i] & 0xffffffffull)] = seg[i];
+    } else {
+        const int r = (i - n) / XC, s0 = start[x], s1 = start[x + 1];
+        int lo = s0, hi = s1;           // segments [s0, lo) come before the die's r-th other
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if ((int)(before[mid] & 0xffffffffull) <= r) lo = mid + 1; else hi = mid;
+        }
+        queue[off + r + (lo - s0)] = other[i - n];
+    }
+}
+// SDDMM segments: those inside one row by column, cut into LIBRA_XCDS equal runs, then the others round-robin.
+__global__ __launch_bounds__(256) void k_order_sddmm_queues(const int32_t *placed, int n, const int32_t *other, int no, int32_t *queue) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n + no) return;
+    auto start = [&](int x) { return (int)(((int64_t)x * n + XC - 1) / XC); };
+    const int x = i < n ? (int)((int64_t)i * XC / n) : (i - n) % XC;
+    int off = start(x);
+    for (int y = 0; y < x; ++y) off += (no - y + XC - 1) / XC;
+    if (i < n) queue[off + i - start(x)] = placed[i];
+    else queue[off + start(x + 1) - start(x) + (i - n) / XC] = other[i - n];
+}
+// ---- die-aware groups ----
+__global__ __launch_bounds__(256) void k_order_groups(TaskView v, const int32_t *list, int n, uint32_t *key) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) key[i] = (uint32_t)v.group(list[i]);
+}
+__global__ __launch_bounds__(256) void k_order_heads(const uint32_t *key, int n, int32_t *flag) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i <= n) flag[i] = i < n && (i == 0 || key[i] != key[i - 1]) ? 1 : 0;
+}
+__global__ __launch_bounds__(256) void k_order_firsts(const int32_t *flag, const int32_t *scan, int n, int32_t *first) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > n) return;
+    if (i == n || flag[i]) first[scan[i]] = i;
+}
+__global__ __launch_bounds__(256) void k_order_group_costs(const u64 *run, const int32_t *first, int ng, u64 *cost) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < ng) cost[g] = run[first[g + 1]] - run[first[g]];
+}
+// groups heaviest first -> sizes in queue order, the queues one after another (`rounds` places each)
+__global__ __launch_bounds__(256) void k_order_deal(const int32_t *gord, const int32_t *first, int ng, int rounds, int32_t *size, int32_t *place) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r > rounds * XC) return;
+    if (r == rounds * XC) { size[r] = 0; return; }
+    const int at = snake(r) * rounds + r / XC;
+    size[at] = r < ng ? first[gord[r] + 1] - first[gord[r]] : 0;
+    if (r < ng) place[gord[r]] = at;
+}
+__global__ __launch_bounds__(256) void k_order_group_items(const int32_t *list, const int32_t *flag, const int32_t *scan, const int32_t *first, const int32_t *place,
+                                                           const int32_t *base, int n, int32_t *queue) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int g = scan[i] + flag[i] - 1;
+    queue[base[place[g]] + i - first[g]] = list[i];
+}
+__global__ void k_order_queue_starts(const int32_t *base, int rounds, int32_t *start) {
+    if (threadIdx.x <= XC) start[threadIdx.x] = base[threadIdx.x * rounds];
+}
+// Slot 8 j + x of the region is the j-th item of queue x, or an empty task; last = slots up to the last task that does something.
+__global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *queue, const int32_t *pieces, int4 p0, int4 p1, int np, int4 n0, int4 n1, int slots,
+                                                    int32_t *out, int32_t *last) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= slots) return;
+    const int x = i % XC, j = i / XC;
+    const int begin[XC + 1] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, np}, len[XC] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+    int b = 0, e = 0, n = 0;
+#pragma unroll
+    for (int y = 0; y < XC; ++y)
+        if (y == x) { b = begin[y]; e = begin[y + 1]; n = len[y]; }
+    int item = -1;
+    if (j < n) {
+        while (e - b > 1) {             // the piece that holds the j-th item
+            const int mid = (b + e) >> 1;
+            if (pieces[3 * mid + 1] <= j) b = mid; else e = mid;
+        }
+        item = queue[pieces[3 * b + 2] + j - pieces[3 * b + 1]];
+    }
+    out[i] = item;
+    if (item >= 0 && !v.empty(item)) atomicMax(last, i + 1);
+}
+// Device task records, die by die (see task_slot in the kernels); slots past the table's end and -1 hold empty tasks.
+__global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t *order, int n, int per_die, const int32_t *blk_valptr, int empty_kind, DevTask *out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= per_die * XC) return;
+    DevTask d{0, 0, 0, 0, 0, 0u, (uint32_t)empty_kind, 0};
+    const int item = i < n ? order[i] : -1;
+    if (item >= v.nt) {
+        const int q = (item - v.nt) * v.cs;
+        d.res_begin = q;
+        d.res_end = min(v.nres, q + v.cs);
+        d.kind = LIBRA_TASK_CHUNK;
+    } else if (item >= 0) {
+        const libra_task_t t = v.tasks[item];
+        const bool window = t.kind == LIBRA_TASK_WINDOW;
+        d = DevTask{t.id, t.blk_begin, t.blk_end, t.res_begin, t.res_end, (t.atomic_mask & 0xffffu) | (t.store_mask << 16), (uint32_t)t.kind,
+                    window ? blk_valptr[t.blk_begin] : 0};
+        if (!window) {                  // a segment of a decomposed row = a task of the row's window with one atomic output row
+            d.id = t.id / W;
+            d.blk_begin = d.blk_end = 0;
+            d.masks = 1u << (t.id % W);
+        }
+    }
+    out[(int64_t)(i % XC) * per_die + i / XC] = d;
+}
+
+// ------------------------------------------------------------------------------------------
 // host driver
 // ------------------------------------------------------------------------------------------
 struct Fail { int code; };
@@ -654,6 +909,165 @@ int32_t peek(const int32_t *p, hipStream_t s) {
     hip_ok(hipMemcpyAsync(&v, p, sizeof v, hipMemcpyDeviceToHost, s));
     hip_ok(hipStreamSynchronize(s));
     return v;
+}
+
+// ---- the order of one table region on the device ----
+struct Orderer {
+    const Layout &L;
+    hipStream_t s;
+    TaskView v;
+    const int32_t *col;                 // first columns: per SpMM task, per SDDMM segment
+    int colbits;
+
+    static int bits_for(int64_t max_value) { int b = 1; while (b < 32 && (max_value >> b)) ++b; return b; }
+    template <class F, class... A> void run(F *k, int64_t n, A... a) { hipLaunchKernelGGL(k, dim3(blocks_for(n, 256)), dim3(256), 0, s, a...); }
+    template <class T> void scan_sum(const T *in, T *out, size_t n) {
+        size_t sz = L.tmp_bytes;
+        hip_ok(rocprim::exclusive_scan(L.tmp, sz, in, out, (T)0, n, rocprim::plus<T>(), s));
+    }
+    void sort_by_key(const int32_t *in, int32_t *out, size_t n, int bits) {          // key_in -> key_out, stable
+        size_t sz = L.tmp_bytes;
+        hip_ok(rocprim::radix_sort_pairs(L.tmp, sz, L.o.key_in, L.o.key_out, in, out, n, 0u, (unsigned)bits, s));
+    }
+    // items 0 .. n-1 by descending cost, stable
+    void heaviest_first(int n, int32_t *out) {
+        if (n == 0) return;
+        run(k_order_costs, n, v, n, L.o.key_in);
+        size_t sz = L.tmp_bytes;
+        hip_ok(rocprim::radix_sort_pairs_desc(L.tmp, sz, L.o.key_in, L.o.key_out, rocprim::counting_iterator<int32_t>(0), out, (size_t)n, 0u, 32u, s));
+    }
+    void identity(int n, int first, int32_t *out) { if (n) run(k_order_identity, n, n, first, out); }
+    int copy(const int32_t *list, int n, int32_t *out) {
+        if (n) hip_ok(hipMemcpyAsync(out, list, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
+        return n;
+    }
+    // The queues lie one after another in L.o.queue, start[x] .. start[x + 1]: lengths levelled and interleaved as
+    // interleave_queues does it; returns the region's length.
+    int interleave(const int *start, int32_t *out) {
+        struct Piece { int from, n; };
+        std::vector<Piece> q[XC];
+        int len[XC];
+        for (int x = 0; x < XC; ++x) {
+            len[x] = start[x + 1] - start[x];
+            if (len[x]) q[x].push_back({start[x], len[x]});
+        }
+        for (;;) {
+            int lo = 0, hi = 0;
+            for (int x = 1; x < XC; ++x) {
+                if (len[x] < len[lo]) lo = x;
+                if (len[x] > len[hi]) hi = x;
+            }
+            if (len[hi] - len[lo] <= 1) break;
+            const int move = (len[hi] - len[lo]) / 2;
+            std::vector<Piece> tail;            // last pieces of the longest queue, in order
+            for (int left = move; left > 0;) {
+                Piece &b = q[hi].back();
+                const int take = std::min(left, b.n);
+                tail.push_back({b.from + b.n - take, take});
+                b.n -= take;
+                if (b.n == 0) q[hi].pop_back();
+                left -= take;
+            }
+            q[lo].insert(q[lo].end(), tail.rbegin(), tail.rend());
+            len[hi] -= move;
+            len[lo] += move;
+        }
+        std::vector<int32_t> table;
+        int begin[XC + 1], slots = 0;
+        for (int x = 0; x < XC; ++x) {
+            begin[x] = (int)table.size() / 3;
+            int at = 0;
+            for (const Piece &p : q[x]) {
+                table.insert(table.end(), {x, at, p.from});
+                at += p.n;
+            }
+            slots = std::max(slots, len[x] * XC);
+        }
+        begin[XC] = (int)table.size() / 3;
+        if (begin[XC] > MAX_PIECES) throw Fail{LIBRA_ERR_HIP};
+        hip_ok(hipMemcpyAsync(L.o.pieces, table.data(), table.size() * 4, hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(k_order_fill, dim3(1), dim3(64), 0, s, L.o.meta + 32, 1, 0);
+        run(k_order_emit, slots, v, (const int32_t *)L.o.queue, (const int32_t *)L.o.pieces, make_int4(begin[0], begin[1], begin[2], begin[3]),
+            make_int4(begin[4], begin[5], begin[6], begin[7]), begin[XC], make_int4(len[0], len[1], len[2], len[3]),
+            make_int4(len[4], len[5], len[6], len[7]), slots, out, L.o.meta + 32);
+        return peek(L.o.meta + 32, s);          // also keeps `table` alive until it has been copied
+    }
+    // Die-aware groups of `list` (place in the list breaks ties); `max_group` bounds the group numbers.
+    int grouped(const int32_t *list, int n, int64_t max_group, int32_t *out) {
+        if (n < 2 * XC) return copy(list, n, out);
+        const OrderScratch &o = L.o;
+        run(k_order_groups, n, v, list, n, o.key_in);
+        sort_by_key(list, o.ord2, (size_t)n, bits_for(max_group));
+        run(k_order_heads, n + 1, (const uint32_t *)o.key_out, n, o.flag);
+        scan_sum<int32_t>(o.flag, o.scan, (size_t)n + 1);
+        run(k_order_item_costs, n + 1, v, (const int32_t *)o.ord2, n, o.wide_in);
+        scan_sum<u64>(o.wide_in, o.wide_out, (size_t)n + 1);
+        run(k_order_firsts, n + 1, (const int32_t *)o.flag, (const int32_t *)o.scan, n, o.first);
+        const int ng = peek(o.scan + n, s), rounds = (ng + XC - 1) / XC;
+        run(k_order_group_costs, ng, (const u64 *)o.wide_out, (const int32_t *)o.first, ng, o.wide_in);
+        int32_t *gord = reinterpret_cast<int32_t *>(o.key_in), *size = reinterpret_cast<int32_t *>(o.key_out);
+        size_t sz = L.tmp_bytes;
+        hip_ok(rocprim::radix_sort_pairs_desc(L.tmp, sz, o.wide_in, o.wide_out, rocprim::counting_iterator<int32_t>(0), gord, (size_t)ng, 0u, 40u, s));
+        run(k_order_deal, rounds * XC + 1, (const int32_t *)gord, (const int32_t *)o.first, ng, rounds, size, o.rank);
+        scan_sum<int32_t>(size, o.base, (size_t)rounds * XC + 1);
+        run(k_order_group_items, n, (const int32_t *)o.ord2, (const int32_t *)o.flag, (const int32_t *)o.scan, (const int32_t *)o.first,
+            (const int32_t *)o.rank, (const int32_t *)o.base, n, o.queue);
+        hipLaunchKernelGGL(k_order_queue_starts, dim3(1), dim3(64), 0, s, (const int32_t *)o.base, rounds, o.meta);
+        int start[XC + 1];
+        hip_ok(hipMemcpyAsync(start, o.meta, sizeof start, hipMemcpyDeviceToHost, s));
+        hip_ok(hipStreamSynchronize(s));
+        return interleave(start, out);
+    }
+    // Segments by column; `list` is the whole SpMM table heaviest first, or the SDDMM segments in CSR order.
+    int by_column(const int32_t *list, int n, bool spmm, int32_t *out) {
+        const OrderScratch &o = L.o;
+        if (n == 0) return 0;
+        run(k_order_by_column_flag, n + 1, v, list, col, n, o.flag);
+        scan_sum<int32_t>(o.flag, o.scan, (size_t)n + 1);
+        const int ns = peek(o.scan + n, s), no = n - ns;
+        if (ns < 8 * XC) return copy(list, n, out);
+        int32_t *other = o.first, *placed = o.ord2, *sorted = o.base;
+        uint32_t *other_cost = reinterpret_cast<uint32_t *>(o.rank);
+        run(k_order_split, n, v, list, col, (const int32_t *)o.flag, (const int32_t *)o.scan, n, o.key_in, placed, other, other_cost);
+        sort_by_key(placed, sorted, (size_t)ns, colbits);
+        int start[XC + 1];
+        if (spmm) {
+            run(k_order_item_costs, ns + 1, v, (const int32_t *)sorted, ns, o.wide_in);
+            scan_sum<u64>(o.wide_in, o.wide_out, (size_t)ns + 1);
+            hipLaunchKernelGGL(k_order_fill, dim3(1), dim3(64), 0, s, o.meta, XC + 1, ns);
+            run(k_order_run_starts, ns, (const u64 *)o.wide_out, ns, o.meta);
+            run(k_order_others_before, ns, v, (const int32_t *)sorted, (const u64 *)o.wide_out, ns, (const uint32_t *)other_cost, no, o.wide_in);
+            size_t sz = L.tmp_bytes;
+            hip_ok(rocprim::inclusive_scan(L.tmp, sz, o.wide_in, o.wide_out, (size_t)ns, rocprim::maximum<u64>(), s));
+            run(k_order_merge, n, (const int32_t *)sorted, (const u64 *)o.wide_out, (const int32_t *)o.meta, ns, (const int32_t *)other, no, o.queue);
+            hip_ok(hipMemcpyAsync(start, o.meta, sizeof start, hipMemcpyDeviceToHost, s));
+            hip_ok(hipStreamSynchronize(s));
+            for (int x = 0, before = 0; x <= XC; ++x) {
+                start[x] += before;
+                if (x < XC) before += snake_count(no, x);
+            }
+        } else {
+            run(k_order_sddmm_queues, n, (const int32_t *)sorted, ns, (const int32_t *)other, no, o.queue);
+            for (int x = 0, before = 0; x <= XC; ++x) {
+                start[x] = (int)(((int64_t)x * ns + XC - 1) / XC) + before;
+                if (x < XC) before += (no - x + XC - 1) / XC;
+            }
+        }
+        return interleave(start, out);
+    }
+};
+
+// Tables of fewer tasks are ordered on the host: there a task costs 60 - 75 ns (copies both ways, radix sorts of 40-byte records,
+// merging), here the launches and waits cost 0.3 ms and a task 1 ns.  GAT graph (1.05 M tasks in both tables): 71 -> 1.5 ms,
+// the whole plan 86.7 -> 24.1 ms; a mini-batch (1,100 tasks) takes 0.09 ms on the host.
+constexpr int64_t DEVICE_ORDER_MIN = 8192;
+
+// Noops of a table as the host planner writes them.
+inline libra_task_t task_at(const std::vector<libra_task_t> &tasks, int item, int cs, int nres, int empty_kind) {
+    if (item < 0) return libra_task_t{empty_kind, 0, 0, 0, 0, 0, 0u, 0u, 0u, 0u};
+    if (item < (int)tasks.size()) return tasks[item];
+    const int q = (item - (int)tasks.size()) * cs, q1 = std::min(nres, q + cs);
+    return libra_task_t{LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, (uint32_t)(2 * (q1 - q))};
 }
 
 }  // namespace
@@ -880,16 +1294,17 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         const int nts[2] = {ntA, ntD}, nres2[2] = {nresA, nresD}, dn[2] = {dnnzA, dnnzD};
         SubPlan *hs[2] = {&sa, &sd};
         P->host_arrays = keep_host_copy != 0;
+        const bool order_here = (int64_t)ntA + ntD + nsegD >= DEVICE_ORDER_MIN;
         for (int k = 0; k < 2; ++k) {
             if (!(k == 0 ? o.build_spmm : o.build_sddmm)) continue;
             const SubOut &S = *subs[k];
             SubPlan &H = *hs[k];
             H.n.blocks = nbs[k]; H.n.col_slots = (int64_t)nbs[k] * KB; H.n.bitmap_words = (int64_t)nbs[k] * 4;
             H.n.dense = dn[k]; H.n.res = nres2[k]; H.n.zero_rows = k == 0 ? nz : 0;
-            fetch(H.tasks, S.tasks, (size_t)nts[k], s);
-            if (k == 0) fetch(H.task_col, L.task_col, (size_t)nts[k], s);
-            if (k == 1) fetch(H.seg_col, L.seg_col, (size_t)nsegD, s);
-            fetch(H.blk_valptr, S.blk_valptr, (size_t)nbs[k] + 1, s);
+            if (!order_here || keep_host_copy) fetch(H.tasks, S.tasks, (size_t)nts[k], s);
+            if (!order_here && k == 0) fetch(H.task_col, L.task_col, (size_t)nts[k], s);
+            if (!order_here && k == 1) fetch(H.seg_col, L.seg_col, (size_t)nsegD, s);
+            if (!order_here || keep_host_copy) fetch(H.blk_valptr, S.blk_valptr, (size_t)nbs[k] + 1, s);
             if (!keep_host_copy) continue;
             fetch(H.win_blkptr, S.blkptr, (size_t)nw + 1, s);
             fetch(H.blk_cols, S.blk_cols, (size_t)nbs[k] * KB, s);
@@ -913,15 +1328,69 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         P->stats.n_vectors_nnz1 = (int64_t)ctr[C_NNZ1];
         mark("copies to the host");
         const int64_t share[2] = {(int64_t)ctr[C_TOGETHER], (int64_t)ctr[C_APART]};
-        finish_plan(P, nullptr, share);
+        const TaskView va{L.a.tasks, ntA, 1, 0}, vd{L.d.tasks, ntD, o.sddmm_Cs, nresD};
+        auto order = [&](bool heavy_first, bool xcd, bool segments_by_column) {
+            int ends[2] = {0, 0};
+            const int64_t max_group = (nw - 1) / LIBRA_LOCALITY_WINDOWS;
+            if (o.build_spmm) {
+                Orderer a{L, s, va, L.task_col, colbits};
+                if (heavy_first) {
+                    a.heaviest_first(ntA, L.o.ord);
+                    ends[0] = xcd ? a.grouped(L.o.ord, ntA, max_group, L.o.order_a)
+                              : segments_by_column ? a.by_column(L.o.ord, ntA, true, L.o.order_a) : a.copy(L.o.ord, ntA, L.o.order_a);
+                } else {
+                    a.identity(ends[0] = ntA, 0, L.o.order_a);
+                }
+            }
+            if (o.build_sddmm) {
+                Orderer d{L, s, vd, L.seg_col, colbits};
+                if (heavy_first) {
+                    d.heaviest_first(ntD, L.o.ord);
+                    ends[1] = xcd ? d.grouped(L.o.ord, ntD, max_group, L.o.order_d) : d.copy(L.o.ord, ntD, L.o.order_d);
+                    d.identity(nsegD, ntD, L.o.ord);
+                    int32_t *segs = L.o.order_d + ends[1];
+                    ends[1] += xcd ? d.grouped(L.o.ord, nsegD, nsegD / LIBRA_LOCALITY_SEGMENTS, segs)
+                               : segments_by_column ? d.by_column(L.o.ord, nsegD, false, segs) : d.copy(L.o.ord, nsegD, segs);
+                } else {
+                    d.identity(ends[1] = ntD + nsegD, 0, L.o.order_d);
+                }
+            }
+            sa.n.tasks = ends[0];
+            sd.n.tasks = ends[1];
+            sa.n_window_tasks = ends[0] - (int64_t)ctr[C_SEGMENTS];        // empty tasks count as windows there, as segments here
+            sa.n_chunk_tasks = (int64_t)ctr[C_SEGMENTS];
+            sd.n_window_tasks = ntD;
+            sd.n_chunk_tasks = ends[1] - ntD;
+            if (!keep_host_copy) return;
+            for (int k = 0; k < 2; ++k) {
+                if (!(k == 0 ? o.build_spmm : o.build_sddmm)) continue;
+                SubPlan &H = *hs[k];
+                std::vector<int32_t> at;
+                fetch(at, k == 0 ? L.o.order_a : L.o.order_d, (size_t)ends[k], s);
+                hip_ok(hipStreamSynchronize(s));
+                std::vector<libra_task_t> out(at.size());
+                for (size_t i = 0; i < at.size(); ++i) out[i] = task_at(H.tasks, at[i], o.sddmm_Cs, nresD, k == 0 ? LIBRA_TASK_WINDOW : LIBRA_TASK_CHUNK);
+                H.tasks.swap(out);
+            }
+        };
+        if (order_here) finish_plan(P, nullptr, share, order);
+        else finish_plan(P, nullptr, share);
         mark("task order, statistics");
         if (plan_buf) {
             // the plan's device copy straight from the workspace: no round trip through host memory
-            auto src = [&](const SubOut &S, const int32_t *zero_rows) {
-                return DeviceSource{S.blk_cols, S.blk_valptr, S.dense_perm, S.res_perm, S.res_row, S.res_col, zero_rows,
-                                    reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val};
+            auto src = [&](const SubOut &S, const TaskView &v, const int32_t *list, int empty_kind, const int32_t *zero_rows) {
+                DeviceSource d{S.blk_cols, S.blk_valptr, S.dense_perm, S.res_perm, S.res_row, S.res_col, zero_rows,
+                               reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val, nullptr};
+                if (order_here)
+                    d.write_tasks = [&S, v, list, empty_kind, s](DevTask *out, int64_t n) {
+                        const int per_die = (int)((n + XC - 1) / XC);
+                        hipLaunchKernelGGL(k_order_records, dim3(blocks_for((int64_t)per_die * XC, 256)), dim3(256), 0, s, v, list, (int)n, per_die,
+                                           (const int32_t *)S.blk_valptr, empty_kind, out);
+                    };
+                return d;
             };
-            if (int rc = adopt_device_arrays(P, src(L.a, L.zero_rows), src(L.d, nullptr), plan_buf, plan_bytes, stream)) throw Fail{rc};
+            if (int rc = adopt_device_arrays(P, src(L.a, va, L.o.order_a, LIBRA_TASK_WINDOW, L.zero_rows), src(L.d, vd, L.o.order_d, LIBRA_TASK_CHUNK, nullptr),
+                                             plan_buf, plan_bytes, stream)) throw Fail{rc};
         }
         mark("plan buffer written");
         P->stats.plan_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

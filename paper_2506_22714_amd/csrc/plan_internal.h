@@ -82,6 +82,7 @@ struct DeviceSource {
     const int32_t *blk_cols, *blk_valptr, *dense_perm, *res_perm, *res_row, *res_col, *zero_rows;
     const uint64_t *blk_bitmap;
     const void *dense_val, *res_val;
+    std::function<void(DevTask *out, int64_t n)> write_tasks;      // set if the task table was ordered on the device: queues its records
 };
 
 struct SubPlan {
@@ -150,7 +151,10 @@ int resolve_options(const libra_plan_opts_t *in, int value_dtype, Resolved &out)
 // Shared tail of the host and the device planner (segments of the SDDMM residual list, task order, statistics).
 // `share` (optional): the two sums of the sampled column-sharing statistic {together, apart} if the caller has
 // already counted them; otherwise they are counted from `cols`.
-void finish_plan(libra_plan_s *plan, const ColumnFetch &cols, const int64_t *share = nullptr);
+// `order` (optional): orders both task tables in place of the host's sorts, sets the numbers of tasks and, where the plan has
+// host arrays, the host's tables.
+typedef std::function<void(bool heavy_first, bool xcd, bool segments_by_column)> TableOrder;
+void finish_plan(libra_plan_s *plan, const ColumnFetch &cols, const int64_t *share = nullptr, const TableOrder &order = nullptr);
 // The sample of that statistic: group k of `nsample` is sampled_group(k, ...) out of `ngroups` groups of
 // LIBRA_LOCALITY_WINDOWS windows.
 LIBRA_HD inline int64_t share_samples(int64_t ngroups) { return ngroups < 256 ? ngroups : 256; }

@@ -269,3 +269,46 @@ def test_device_planner_full_configs(name):
     one_writer = torch.ones(A.M, dtype=torch.bool, device="cuda")
     one_writer[torch.from_numpy(ph.export(0)["zero_rows"]).cuda().long()] = False
     assert torch.equal(ph.spmm(B)[one_writer], pr.spmm(B)[one_writer])
+
+
+ORDER_CASES = [
+    dict(cs=8, sddmm_cs=8),                                                        # segments by column
+    dict(cs=8, sddmm_cs=8, ts=2, spmm_min_vec_nnz=2, sddmm_min_blk_nnz=17, sddmm_ts=1),
+    dict(cs=8, sddmm_cs=8, flags=lb.FLAG_XCD_ORDER, sddmm_min_blk_nnz=17, sddmm_ts=1),
+    dict(cs=8, sddmm_cs=8, flags=lb.FLAG_NO_XCD_ORDER),
+    dict(cs=8, sddmm_cs=8, flags=lb.FLAG_SEGMENTS_BY_COST),
+    dict(cs=8, sddmm_cs=8, flags=lb.FLAG_NATURAL_ORDER),
+    dict(cs=4, flags=lb.FLAG_NO_SDDMM),
+    dict(sddmm_cs=4, flags=lb.FLAG_NO_SPMM | lb.FLAG_XCD_ORDER),
+    dict(mode=lb.MODE_SCALAR_ONLY, cs=1, sddmm_cs=1),
+]
+
+
+@pytest.mark.parametrize("name", ["rmat", "community", "short_rows", "hub_windows"])
+def test_large_task_tables_are_ordered_like_on_the_host(name):
+    """Tables of more than 8192 tasks are ordered on the GPU: the same tables as the host's, and a plan whose records never
+    were on the host computes what an uploaded one does."""
+    A = {"rmat": lambda: wl.rmat(scale=13, avg_degree=16, seed=3),
+         "community": lambda: wl.community(n_blocks=400, seed=2),                  # the die-aware order fires
+         "short_rows": lambda: wl.random_pattern(140_003, 300, 0.004, seed=4, empty_rows=0.3),   # no segments
+         # windows whose rows are all decomposed: empty tasks of cost 0 at the table's end
+         "hub_windows": lambda: wl.with_long_rows(wl.random_pattern(20_000, 2000, 0.003, seed=7), list(range(64, 96)) + [7], 1500, seed=8)}[name]()
+    B = torch.from_numpy(wl.dense_small_int(A.Kc, 32, seed=1)).cuda()
+    X = torch.from_numpy(wl.dense_small_int(A.M, 32, seed=2)).cuda()
+    ones = np.ones(A.nnz, dtype=np.float16)          # whole numbers: every order of additions gives the same sums
+    for kw in ORDER_CASES:
+        print(name, A.nnz, kw, flush=True)
+        fl = kw.get("flags", 0)
+        ph, pd = lb.Plan.from_csr(A, val=ones, **kw), device_plan(A, val=ones, **kw)
+        assert_same_plan(ph, pd, fl)
+        pd.close()
+        ph.upload()
+        pr = device_plan(A, val=ones, resident=True, keep_host_copy=False, **kw)
+        sh, sr = ph.stats(), pr.stats()
+        assert all(sh[k] == sr[k] for k in sh if k not in TIMES)
+        if not fl & lb.FLAG_NO_SPMM:
+            assert torch.equal(ph.spmm(B), pr.spmm(B))
+        if not fl & lb.FLAG_NO_SDDMM:
+            assert torch.equal(ph.sddmm(X, B), pr.sddmm(X, B))
+        ph.close()
+        pr.close()
