@@ -4,10 +4,10 @@
 // already in device memory.  The window-by-window loops of the host code become flat passes
 // over arrays plus prefix sums:
 //
-//   1. every nonzero gets the key (column, row inside the window); a segmented sort (segments =
-//      windows) puts the nonzeros of each column vector next to each other (the "census");
-//   2. head flags + a prefix sum number the vectors; a second segmented sort orders the vectors
-//      of a window by (NNZ descending, column ascending) - the order of the SDDMM blocks and of
+//   1. every nonzero finds its place in its window's (column, row) order by searching the window's
+//      other rows, which puts the nonzeros of each column vector next to each other (the "census");
+//   2. head flags + a prefix sum number the vectors; a sort of those with more than one nonzero
+//      gives the (NNZ descending, column ascending) order - the order of the SDDMM blocks and of
 //      the vectors that fill the padding of the last SpMM block;
 //   3. per window: how many vectors reach the SpMM threshold, how many fill padding, how many
 //      SDDMM blocks reach the block threshold (their NNZ never increases along the order, so a
@@ -17,7 +17,7 @@
 //   5. nonzeros outside the dense vectors are flagged in CSR order; prefix sums give residual
 //      positions; per window the load-balancing rule of Section 4.3 emits the task records.
 //
-// Sorting and prefix sums are rocPRIM device primitives; everything else is written here.
+// Radix sorts and prefix sums are rocPRIM device primitives; everything else is written here.
 // The arrays are produced in the host planner's format in the caller's workspace, copied to the
 // plan's host vectors if a host copy is wanted; large task tables are ordered here, small ones by the host planner's tail.
 #include <hip/hip_runtime.h>
@@ -95,9 +95,11 @@ struct OrderScratch {
 constexpr int MAX_PIECES = 4096;
 
 struct Layout {
-    int32_t *win_ptr, *spos, *hflag, *vid, *einfo, *ewin, *row_of, *rowbase;
-    u64 *key_in, *key_out, *key2_in, *key2_out, *ctr;
-    int32_t *vfirst, *vinfo, *vcol, *vwin, *sv, *srank, *scnt, *cum, *tflag, *taud, *win_vptr;
+    int32_t *win_ptr, *spos, *hflag, *vid, *einfo, *row_of, *rowbase;
+    u64 *key_out, *ctr;
+    uint32_t *mkey_in, *mkey_out;
+    int32_t *mflag, *mscan, *mvec_in, *mvec_out;
+    int32_t *vfirst, *vinfo, *vcol, *vwin, *srank, *scnt, *cum, *tflag, *taud, *win_vptr;
     int32_t *ntau, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
     OrderScratch o;
@@ -111,17 +113,13 @@ int64_t order_slots(int64_t tasks) { return 2 * tasks + 64; }      // the die-aw
 
 size_t rocprim_temp_bytes(const Sizes &z) {
     size_t best = 0, sz = 0;
-    const unsigned n = (unsigned)z.n, nw = (unsigned)z.nw;
-    (void)rocprim::segmented_radix_sort_pairs(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0),
-                                        (int32_t *)nullptr, n, nw, (int32_t *)nullptr, (int32_t *)nullptr, 0, 64);
-    best = std::max(best, sz);
-    sz = 0;
     (void)rocprim::exclusive_scan(nullptr, sz, (int32_t *)nullptr, (int32_t *)nullptr, (int32_t)0, (size_t)(z.n + z.nw + 2),
                             rocprim::plus<int32_t>());
     best = std::max(best, sz);
     const size_t m = order_items(z) + 16;
     sz = 0;
-    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, m, 0, 32);
+    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr,
+                              std::max(m, (size_t)z.n), 0, 32);
     best = std::max(best, sz);
     sz = 0;
     (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 64);
@@ -147,22 +145,23 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     const size_t n = (size_t)z.n, nw = (size_t)z.nw, nb = (size_t)z.nbmax;
     L.ctr = A.take<u64>(C_COUNT);
     L.win_ptr = A.take<int32_t>(nw + 1);
-    L.key_in = A.take<u64>(n);
     L.key_out = A.take<u64>(n);
     L.spos = A.take<int32_t>(n);
     L.hflag = A.take<int32_t>(n + 1);
     L.vid = A.take<int32_t>(n + 1);
     L.einfo = A.take<int32_t>(n);
-    L.ewin = A.take<int32_t>(n);
     L.row_of = A.take<int32_t>(n);
     L.rowbase = A.take<int32_t>((size_t)z.M + 1);
     L.vfirst = A.take<int32_t>(n);
     L.vinfo = A.take<int32_t>(n);
     L.vcol = A.take<int32_t>(n);
     L.vwin = A.take<int32_t>(n);
-    L.key2_in = A.take<u64>(n);
-    L.key2_out = A.take<u64>(n);
-    L.sv = A.take<int32_t>(n);
+    L.mkey_in = A.take<uint32_t>(n);
+    L.mkey_out = A.take<uint32_t>(n);
+    L.mflag = A.take<int32_t>(n + 1);
+    L.mscan = A.take<int32_t>(n + 1);
+    L.mvec_in = A.take<int32_t>(n);
+    L.mvec_out = A.take<int32_t>(n);
     L.srank = A.take<int32_t>(n);
     L.scnt = A.take<int32_t>(n + 1);
     L.cum = A.take<int32_t>(n + 1);
@@ -229,10 +228,14 @@ __global__ __launch_bounds__(256) void k_win_ptr(const int32_t *rowptr, int64_t 
     if (t <= nw) win_ptr[t] = rowptr[min((int64_t)M, t * W)];
 }
 
-// Per nonzero (CSR order): its row (bisection over rowptr; rows without nonzeros are skipped over), the sort key
-// (column, row in window), and the checks the host planner makes.
-__global__ __launch_bounds__(256) void k_keys(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n,
-                                              u64 *key_in, int32_t *row_of, u64 *ctr) {
+// Per nonzero (CSR order): its row (bisection over rowptr; rows without nonzeros are skipped over), the checks the host
+// planner makes, and its place in the window's (column, row) order.  A window's rows are sorted already, so that place is
+// found and not sorted for: its index in its own row plus, for each other row, the nonzeros that come before it there.
+// Neighbouring nonzeros take nearly the same path through a row, so the searches run from the L1s; four of them at a time,
+// because each is a chain of loads.  GAT graph (59.7 M nonzeros): 4.1 ms, against 7.4 ms for keys and a segmented radix sort with
+// one workgroup per window, which the hub windows hold up.
+__global__ __launch_bounds__(256) void k_ranks(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n,
+                                               u64 *key_out, int32_t *spos, int32_t *row_of, u64 *ctr) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     int64_t lo = 0, hi = M;                 // rowptr[lo] <= p < rowptr[hi]
@@ -241,32 +244,54 @@ __global__ __launch_bounds__(256) void k_keys(const int32_t *rowptr, const int32
         if (rowptr[mid] <= p) lo = mid; else hi = mid;
     }
     const int c = col[p];
+    const int row_start = rowptr[lo];
     unsigned bad = 0;
     if (c < 0 || c >= Kc) bad = 1u;
-    else if (p > rowptr[lo] && col[p - 1] >= c) bad = 2u;
-    key_in[p] = ((u64)(uint32_t)c << 4) | (u64)(lo & (W - 1));
+    else if (p > row_start && col[p - 1] >= c) bad = 2u;
     row_of[p] = (int32_t)lo;
     if (bad) atomicOr(&ctr[C_ERR], (u64)bad);
-}
-
-// largest w in [0, nw) with win_ptr[w] <= e   (win_ptr[0] = 0 <= e < win_ptr[nw])
-__device__ inline int window_of(const int32_t *win_ptr, int nw, int e) {
-    int lo = 0, hi = nw;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (win_ptr[mid] <= e) lo = mid; else hi = mid;
+    const int64_t r0 = lo - lo % W;
+    const int own = (int)(lo - r0), rows = (int)min((int64_t)W, M - r0);
+    const int start = rowptr[r0];
+    int rank = p - row_start;
+    constexpr int U = 4;
+    for (int q = 0; q < rows; q += U) {
+        int first[U], at[U], left[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = q + u;
+            const bool other = r < rows && r != own;
+            first[u] = at[u] = rowptr[r0 + min(r, rows - 1)];
+            left[u] = other ? rowptr[r0 + r + 1] - at[u] : 0;
+        }
+        while (left[0] | left[1] | left[2] | left[3]) {
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = (uint32_t)col[min(at[u] + (left[u] >> 1), n - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int half = left[u] >> 1;
+                // equal columns: the row above comes first
+                const bool before = left[u] > 0 && v[u] < (uint32_t)c + (q + u < own ? 1u : 0u);
+                at[u] = before ? at[u] + half + 1 : at[u];
+                left[u] = before ? left[u] - half - 1 : half;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) rank += at[u] - first[u];
     }
-    return lo;
+    // in range for any input: the index in the row plus at most the other rows' lengths
+    key_out[start + rank] = ((u64)(uint32_t)c << 4) | (u64)own;
+    spos[start + rank] = p;
 }
 
 // Per sorted nonzero: is it the first of its column vector; if so, the vector's NNZ and row mask.
-__global__ __launch_bounds__(256) void k_census(const u64 *skey, const int32_t *win_ptr, int nw, int n,
-                                                int32_t *hflag, int32_t *einfo, int32_t *ewin) {
+__global__ __launch_bounds__(256) void k_census(const u64 *skey, const int32_t *win_ptr, const int32_t *row_of, int n, int32_t *hflag, int32_t *einfo) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     const u64 key = skey[e];
     const u64 c = key >> 4;
-    const int w = window_of(win_ptr, nw, e);
+    const int w = row_of[e] / W;            // a place's window is that of the nonzero there in CSR order
     const int ws = win_ptr[w], we = win_ptr[w + 1];
     const bool head = e == ws || (skey[e - 1] >> 4) != c;
     int info = 0;
@@ -284,31 +309,33 @@ __global__ __launch_bounds__(256) void k_census(const u64 *skey, const int32_t *
     }
     hflag[e] = head ? 1 : 0;
     einfo[e] = info;
-    ewin[e] = w;
 }
 
+// (few workgroups, each over many nonzeros: one add to the shared counter per workgroup and not per 256 nonzeros - 233,000
+// adds to one address took 2.8 ms)
 __global__ __launch_bounds__(256) void k_vectors(const u64 *skey, const int32_t *hflag, const int32_t *vid, const int32_t *einfo,
-                                                 const int32_t *ewin, int n, int tau_a, int colbits,
-                                                 int32_t *vfirst, int32_t *vinfo, int32_t *vcol, int32_t *vwin, int32_t *tflag,
-                                                 u64 *key2, u64 *ctr) {
+                                                 const int32_t *row_of, int n, int tau_a,
+                                                 int32_t *vfirst, int32_t *vinfo, int32_t *vcol, int32_t *vwin, int32_t *tflag, int32_t *mflag, u64 *ctr) {
     __shared__ int ones;
     if (threadIdx.x == 0) ones = 0;
     __syncthreads();
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n && hflag[e]) {
-        const int v = vid[e];
-        const int info = einfo[e];
-        const int cnt = info & 0xff;
-        const int c = (int)(skey[e] >> 4);
-        vfirst[v] = e;
-        vinfo[v] = info;
-        vcol[v] = c;
-        vwin[v] = ewin[e];
-        tflag[v] = cnt >= tau_a ? 1 : 0;
-        key2[v] = ((u64)(W - cnt) << colbits) | (u64)(uint32_t)c;
-        if (cnt == 1) atomicAdd(&ones, 1);
+    int mine = 0;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        if (hflag[e]) {
+            const int v = vid[e];
+            const int info = einfo[e];
+            const int cnt = info & 0xff;
+            vfirst[v] = (int)e;
+            vinfo[v] = info;
+            vcol[v] = (int)(skey[e] >> 4);
+            vwin[v] = row_of[e] / W;
+            tflag[v] = cnt >= tau_a ? 1 : 0;
+            mflag[v] = cnt > 1 ? 1 : 0;
+            mine += cnt == 1;
+        }
+        if (e == n - 1) ctr[C_NV] = (u64)(vid[e] + hflag[e]);
     }
-    if (e == n - 1) ctr[C_NV] = (u64)(vid[e] + hflag[e]);
+    if (mine) atomicAdd(&ones, mine);
     __syncthreads();
     if (threadIdx.x == 0 && ones) atomicAdd(&ctr[C_NNZ1], (u64)ones);
 }
@@ -320,14 +347,32 @@ __global__ __launch_bounds__(256) void k_win_vptr(const int32_t *win_ptr, const 
     win_vptr[t] = p < n ? vid[p] : (int)ctr[C_NV];
 }
 
-// Per position of the (NNZ desc, column asc) order: the vector's NNZ; per vector: its rank in its window.
-__global__ __launch_bounds__(256) void k_sorted(const int32_t *sv, const int32_t *vinfo, const int32_t *vwin, const int32_t *win_vptr,
-                                                int nv, int32_t *scnt, int32_t *srank) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nv) return;
-    const int v = sv[k];
-    scnt[k] = vinfo[v] & 0xff;
-    srank[v] = k - win_vptr[vwin[v]];
+// The (NNZ descending, column ascending) order of a window's vectors: those of one nonzero - nine in ten of them on graphs -
+// are its end, already in column order; only the others are sorted, by (window, NNZ) with a stable sort (sorting all of them
+// by (NNZ, column) window by window, with one workgroup per window: 3.3 ms for 49 M vectors).
+__global__ __launch_bounds__(256) void k_multi_keys(const int32_t *mflag, const int32_t *mscan, const int32_t *vinfo, const int32_t *vwin, int nv,
+                                                    uint32_t *key, int32_t *vec) {
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= nv || !mflag[v]) return;
+    key[mscan[v]] = (uint32_t)vwin[v] << 4 | (uint32_t)(W - (vinfo[v] & 0xff));
+    vec[mscan[v]] = v;
+}
+// Per position of that order: the vector's NNZ; per vector: its rank in its window.
+__global__ __launch_bounds__(256) void k_sorted(const int32_t *mvec, int nm, const int32_t *mflag, const int32_t *mscan, const int32_t *vinfo, const int32_t *vwin,
+                                                const int32_t *win_vptr, int nv, int32_t *scnt, int32_t *srank) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nv) return;
+    if (i < nm) {
+        const int v = mvec[i], base = win_vptr[vwin[v]], rank = i - mscan[base];
+        scnt[base + rank] = vinfo[v] & 0xff;
+        srank[v] = rank;
+    }
+    if (!mflag[i]) {
+        const int w = vwin[i], base = win_vptr[w];
+        const int rank = mscan[win_vptr[w + 1]] - mscan[base] + (i - base) - (mscan[i] - mscan[base]);
+        scnt[base + rank] = 1;
+        srank[i] = rank;
+    }
 }
 
 // The sampled column-sharing statistic (one workgroup per sampled group of LIBRA_LOCALITY_WINDOWS windows): how
@@ -1057,9 +1102,9 @@ struct Orderer {
     }
 };
 
-// Tables of fewer tasks are ordered on the host: there a task costs 60 - 75 ns (copies both ways, radix sorts of 40-byte records,
-// merging), here the launches and waits cost 0.3 ms and a task 1 ns.  GAT graph (1.05 M tasks in both tables): 71 -> 1.5 ms,
-// the whole plan 86.7 -> 24.1 ms; a mini-batch (1,100 tasks) takes 0.09 ms on the host.
+// Tables of fewer tasks are ordered on the host: there a task costs 40 - 70 ns (copies both ways, radix sorts of 40-byte records,
+// merging), here the launches and waits cost 0.2 ms and a task 1 ns.  GAT graph (1.05 M tasks in both tables): 71 -> 1.5 ms,
+// the whole plan 86.7 -> 24.1 ms; 8,000 tasks without segments: 0.32 ms on the host, 0.21 here.
 constexpr int64_t DEVICE_ORDER_MIN = 8192;
 
 // Noops of a table as the host planner writes them.
@@ -1168,21 +1213,16 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         Rule R{o.mode, o.fill && o.mode == LIBRA_MODE_HYBRID ? 1 : 0, o.tau_sddmm, o.Ts, o.Cs, o.short_len, o.build_spmm ? 1 : 0, o.build_sddmm ? 1 : 0, o.sddmm_Ts};
         const int tau_a = o.mode == LIBRA_MODE_DENSE_ONLY ? 1 : o.mode == LIBRA_MODE_SCALAR_ONLY ? W + 1 : o.tau_spmm;
 
-        // ---- 1. census: sort the nonzeros of every window by (column, row) ----
+        // ---- 1. census: the nonzeros of every window in (column, row) order ----
         fill_bytes(L.ctr, 0, C_COUNT * sizeof(u64), s);
         hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr);
-        hipLaunchKernelGGL(k_keys, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_in, L.row_of, L.ctr);
-        {
-            size_t sz = L.tmp_bytes;
-            hip_ok(rocprim::segmented_radix_sort_pairs(L.tmp, sz, L.key_in, L.key_out, rocprim::counting_iterator<int32_t>(0), L.spos,
-                                                       (unsigned)n, (unsigned)nw, L.win_ptr, L.win_ptr + 1, 0, (unsigned)(colbits + 4), s));
-        }
+        hipLaunchKernelGGL(k_ranks, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_out, L.spos, L.row_of, L.ctr);
         // ---- 2. vectors ----
-        hipLaunchKernelGGL(k_census, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, nw, n, L.hflag, L.einfo, L.ewin);
+        hipLaunchKernelGGL(k_census, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, L.row_of, n, L.hflag, L.einfo);
         fill_bytes(L.hflag + n, 0, sizeof(int32_t), s);
         scan(L, L.hflag, L.vid, (size_t)n + 1, s);
-        hipLaunchKernelGGL(k_vectors, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.hflag, L.vid, L.einfo, L.ewin, n, tau_a, colbits,
-                           L.vfirst, L.vinfo, L.vcol, L.vwin, L.tflag, L.key2_in, L.ctr);
+        hipLaunchKernelGGL(k_vectors, dim3(std::min(blocks_for(n, 256), 4096u)), dim3(256), 0, s, L.key_out, L.hflag, L.vid, L.einfo, L.row_of, n, tau_a,
+                           L.vfirst, L.vinfo, L.vcol, L.vwin, L.tflag, L.mflag, L.ctr);
         hipLaunchKernelGGL(k_win_vptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, L.win_ptr, L.vid, nw, n, L.ctr, L.win_vptr);
         u64 ctr[C_COUNT];
         hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));
@@ -1192,14 +1232,20 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         if (ctr[C_ERR] & 2) throw Fail{LIBRA_ERR_UNSORTED};
         const int nv = (int)ctr[C_NV];
         if (nv < 1 || nv > n) throw Fail{LIBRA_ERR_HIP};
-        mark("census (sort 1, vectors)");
+        mark("census, vectors");
         // order of a window's vectors: NNZ descending, column ascending
-        {
+        const int nm = nv - (int)ctr[C_NNZ1];
+        if (nm < 0 || nm > nv) throw Fail{LIBRA_ERR_HIP};
+        fill_bytes(L.mflag + nv, 0, sizeof(int32_t), s);
+        scan(L, L.mflag, L.mscan, (size_t)nv + 1, s);
+        if (nm > 0) {
+            hipLaunchKernelGGL(k_multi_keys, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.mflag, L.mscan, L.vinfo, L.vwin, nv, L.mkey_in, L.mvec_in);
+            int winbits = 1;
+            while ((1ll << winbits) < nw) ++winbits;
             size_t sz = L.tmp_bytes;
-            hip_ok(rocprim::segmented_radix_sort_pairs(L.tmp, sz, L.key2_in, L.key2_out, rocprim::counting_iterator<int32_t>(0), L.sv,
-                                                       (unsigned)nv, (unsigned)nw, L.win_vptr, L.win_vptr + 1, 0, (unsigned)(colbits + 4), s));
+            hip_ok(rocprim::radix_sort_pairs(L.tmp, sz, L.mkey_in, L.mkey_out, L.mvec_in, L.mvec_out, (size_t)nm, 0u, (unsigned)(winbits + 4), s));
         }
-        hipLaunchKernelGGL(k_sorted, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.sv, L.vinfo, L.vwin, L.win_vptr, nv, L.scnt, L.srank);
+        hipLaunchKernelGGL(k_sorted, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.mvec_out, nm, L.mflag, L.mscan, L.vinfo, L.vwin, L.win_vptr, nv, L.scnt, L.srank);
         fill_bytes(L.scnt + nv, 0, sizeof(int32_t), s);
         fill_bytes(L.tflag + nv, 0, sizeof(int32_t), s);
         scan(L, L.scnt, L.cum, (size_t)nv + 1, s);
@@ -1224,7 +1270,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
         const int nbA = peek(L.a.blkptr + nw, s), nbD = peek(L.d.blkptr + nw, s);
         if (nbA < 0 || nbD < 0 || nbA > z.nbmax || nbD > z.nbmax) throw Fail{LIBRA_ERR_HIP};
-        mark("sort 2, window counts");
+        mark("vector order, window counts");
         // ---- 4. slots, blocks, packed values ----
         fill_bytes(L.a.slotvec, 0xff, (size_t)nbA * KB * sizeof(int32_t), s);
         fill_bytes(L.d.slotvec, 0xff, (size_t)nbD * KB * sizeof(int32_t), s);
@@ -1272,7 +1318,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);
         const int64_t ngroups = (nw + LIBRA_LOCALITY_WINDOWS - 1) / LIBRA_LOCALITY_WINDOWS, nsample = share_samples(ngroups);
-        hipLaunchKernelGGL(k_share, dim3((unsigned)nsample, 16), dim3(256), 0, s, L.win_vptr, L.vcol, nw, ngroups, nsample, L.ctr);
+        hipLaunchKernelGGL(k_share, dim3((unsigned)nsample, 64), dim3(256), 0, s, L.win_vptr, L.vcol, nw, ngroups, nsample, L.ctr);
         if (o.build_spmm)
             hipLaunchKernelGGL(k_row_bases, dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, L.resptr, M, nw, R, L.rowbase);
         hipLaunchKernelGGL(k_residual_fill, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_col, val, vsize, n, R, L.row_of,
