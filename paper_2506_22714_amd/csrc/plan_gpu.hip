@@ -103,6 +103,7 @@ struct Layout {
     int32_t *ntau, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
     OrderScratch o;
+    int32_t *sizes;
     void *tmp;
     size_t tmp_bytes;
     size_t total;
@@ -144,6 +145,7 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     Arena A{(char *)base};
     const size_t n = (size_t)z.n, nw = (size_t)z.nw, nb = (size_t)z.nbmax;
     L.ctr = A.take<u64>(C_COUNT);
+    L.sizes = A.take<int32_t>(64);
     L.win_ptr = A.take<int32_t>(nw + 1);
     L.key_out = A.take<u64>(n);
     L.spos = A.take<int32_t>(n);
@@ -586,7 +588,8 @@ __device__ inline void put_task(libra_task_t *t, int kind, int id, int b0, int b
 }
 
 // Per window: the hybrid load-balancing rule (Section 4.3).  FILL = false counts tasks, rows to clear and
-// residual nonzeros; FILL = true writes them at the offsets the prefix sums gave.
+// residual nonzeros, a window per thread; FILL = true writes them at the offsets the prefix sums gave, a window per wave: a hub
+// window has thousands of tasks (GAT graph: 800 us with a thread per window, 221 with a wave).
 template <bool FILL>
 __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, const int32_t *rescan_a, int64_t M, int nw, Rule R,
                                                       const int32_t *blkptr_a, const int32_t *blkmask_a, const int32_t *blkncols_a,
@@ -594,7 +597,8 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
                                                       int32_t *ntasks_a, int32_t *nzero, int32_t *nres, int32_t *ntasks_d, u64 *ctr,
                                                       const int32_t *tbase_a, const int32_t *zbase, const int32_t *resptr, const int32_t *tbase_d,
                                                       libra_task_t *tasks_a, int32_t *zero_rows, libra_task_t *tasks_d) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int LANES = FILL ? 64 : 1;
+    const int t = blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
     if (t >= nw) return;
     const int64_t r0 = (int64_t)t * W;
     if (R.build_a) {
@@ -621,26 +625,36 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
             auto touched = [&](int g0, int g1) { unsigned m = 0; for (int b = g0; b < g1; ++b) m |= (unsigned)blkmask_a[b]; return m; };
             auto cols_in = [&](int g0, int g1) { unsigned c = 0; for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_a[b]; return c; };
             if (many) {
-                for (int g0 = b0; g0 < b1; g0 += R.Ts) {
-                    const int g1 = min(b1, g0 + R.Ts);
-                    put_task(out++, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
+                const int groups = (b1 - b0 + R.Ts - 1) / R.Ts;
+                for (int g = lane; g < groups; g += LANES) {
+                    const int g0 = b0 + g * R.Ts, g1 = min(b1, g0 + R.Ts);
+                    put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
                 }
-                if (z.scalar) put_task(out++, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
-                for (int r = 0; r < z.nr; ++r) *zr++ = (int32_t)(r0 + r);
+                out += groups;
+                if (z.scalar) {
+                    if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
+                    ++out;
+                }
+                if (lane == 0)
+                    for (int r = 0; r < z.nr; ++r) *zr++ = (int32_t)(r0 + r);
             } else {
-                put_task(out++, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched(b0, b1), z.valid & ~z.split,
-                         cols_in(b0, b1) + (unsigned)(q1 - q0));
-                for (int r = 0; r < z.nr; ++r)
-                    if ((z.split >> r) & 1u) *zr++ = (int32_t)(r0 + r);
+                if (lane == 0) {
+                    put_task(out, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched(b0, b1), z.valid & ~z.split,
+                             cols_in(b0, b1) + (unsigned)(q1 - q0));
+                    for (int r = 0; r < z.nr; ++r)
+                        if ((z.split >> r) & 1u) *zr++ = (int32_t)(r0 + r);
+                }
+                ++out;
             }
             int q = q1;
             for (int r = 0; r < z.nr; ++r) {
                 if (!((z.split >> r) & 1u)) continue;
-                const int e = q + z.rlen[r];
-                for (; q < e; q += R.Cs) {
-                    const int qe = min(e, q + R.Cs);
-                    put_task(out++, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, q, qe, 0u, 0u, 0u, (unsigned)(qe - q));
+                const int n = (z.rlen[r] + R.Cs - 1) / R.Cs, e = q + z.rlen[r];
+                for (int k = lane; k < n; k += LANES) {
+                    const int qs = q + k * R.Cs, qe = min(e, qs + R.Cs);
+                    put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
                 }
+                out += n;
                 q = e;
             }
         }
@@ -653,11 +667,11 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
             ntasks_d[t] = (b1 - b0 + R.Ts_d - 1) / R.Ts_d;
         } else {
             libra_task_t *out = tasks_d + tbase_d[t];
-            for (int g0 = b0; g0 < b1; g0 += R.Ts_d) {
-                const int g1 = min(b1, g0 + R.Ts_d);
+            for (int g = lane; g < (b1 - b0 + R.Ts_d - 1) / R.Ts_d; g += LANES) {
+                const int g0 = b0 + g * R.Ts_d, g1 = min(b1, g0 + R.Ts_d);
                 unsigned c = 0;
                 for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
-                put_task(out++, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
+                put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
             }
         }
     } else if (!FILL) {
@@ -1115,6 +1129,21 @@ inline libra_task_t task_at(const std::vector<libra_task_t> &tasks, int item, in
     return libra_task_t{LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, (uint32_t)(2 * (q1 - q))};
 }
 
+// Several single words in one copy and one wait (each peek is a round trip of some 10 us).
+struct Words { const int32_t *at[7]; };
+__global__ void k_gather_words(Words w, int n, int32_t *out) {
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+        if (i < n && (int)threadIdx.x == i) out[i] = *w.at[i];
+}
+void peek_all(int32_t *scratch, std::initializer_list<const int32_t *> from, int32_t (&to)[7], hipStream_t s) {
+    Words w{};
+    std::copy(from.begin(), from.end(), w.at);
+    hipLaunchKernelGGL(k_gather_words, dim3(1), dim3(64), 0, s, w, (int)from.size(), scratch);
+    hip_ok(hipMemcpyAsync(to, scratch, from.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    hip_ok(hipStreamSynchronize(s));
+}
+
 }  // namespace
 
 extern "C" int libra_plan_device_workspace(int64_t M, int64_t nnz, const libra_plan_opts_t *opts, size_t *bytes) {
@@ -1268,7 +1297,9 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         fill_bytes(L.d.nb + nw, 0, sizeof(int32_t), s);
         scan(L, L.a.nb, L.a.blkptr, (size_t)nw + 1, s);
         scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
-        const int nbA = peek(L.a.blkptr + nw, s), nbD = peek(L.d.blkptr + nw, s);
+        int32_t size[7];
+        peek_all(L.sizes, {L.a.blkptr + nw, L.d.blkptr + nw}, size, s);
+        const int nbA = size[0], nbD = size[1];
         if (nbA < 0 || nbD < 0 || nbA > z.nbmax || nbD > z.nbmax) throw Fail{LIBRA_ERR_HIP};
         mark("vector order, window counts");
         // ---- 4. slots, blocks, packed values ----
@@ -1307,13 +1338,12 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         scan(L, L.nzero, L.zbase, (size_t)nw + 1, s);
         scan(L, L.nres, L.resptr, (size_t)nw + 1, s);
         scan(L, L.d.ntasks, L.d.tbase, (size_t)nw + 1, s);
-        const int ntA = peek(L.a.tbase + nw, s), ntD = peek(L.d.tbase + nw, s), nz = peek(L.zbase + nw, s);
-        const int nresA = peek(L.a.rescan + n, s), nresD = peek(L.d.rescan + n, s);
-        const int dnnzA = peek(L.a.blk_valptr + nbA, s), dnnzD = peek(L.d.blk_valptr + nbD, s);
+        peek_all(L.sizes, {L.a.tbase + nw, L.d.tbase + nw, L.zbase + nw, L.a.rescan + n, L.d.rescan + n, L.a.blk_valptr + nbA, L.d.blk_valptr + nbD}, size, s);
+        const int ntA = size[0], ntD = size[1], nz = size[2], nresA = size[3], nresD = size[4], dnnzA = size[5], dnnzD = size[6];
         if (ntA < 0 || ntA > z.tasks_a_max || ntD < 0 || ntD > z.tasks_d_max || nz < 0 || nz > M || nresA < 0 || nresA > n || nresD < 0 ||
             nresD > n || dnnzA < 0 || dnnzA > n || dnnzD < 0 || dnnzD > n)
             throw Fail{LIBRA_ERR_HIP};
-        hipLaunchKernelGGL((k_window_tasks<true>), dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
+        hipLaunchKernelGGL((k_window_tasks<true>), dim3(blocks_for(nw, 2)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
                            L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);
