@@ -4,8 +4,8 @@
 // already in device memory.  The window-by-window loops of the host code become flat passes
 // over arrays plus prefix sums:
 //
-//   1. every nonzero finds its place in its window's (column, row) order by searching the window's
-//      other rows, which puts the nonzeros of each column vector next to each other (the "census");
+//   1. the 16 sorted rows of a window are merged into (column, row) order in two passes in which
+//      every nonzero finds its place by searching the lists it is merged with, which puts the nonzeros of each column vector next to each other (the "census");
 //   2. head flags + a prefix sum number the vectors; a sort of those with more than one nonzero
 //      gives the (NNZ descending, column ascending) order - the order of the SDDMM blocks and of
 //      the vectors that fill the padding of the last SpMM block;
@@ -96,7 +96,7 @@ constexpr int MAX_PIECES = 4096;
 
 struct Layout {
     int32_t *win_ptr, *spos, *hflag, *vid, *einfo, *row_of, *rowbase;
-    u64 *key_out, *ctr;
+    u64 *key_in, *key_out, *ctr;
     uint32_t *mkey_in, *mkey_out;
     int32_t *mflag, *mscan, *mvec_in, *mvec_out;
     int32_t *vfirst, *vinfo, *vcol, *vwin, *srank, *scnt, *cum, *tflag, *taud, *win_vptr;
@@ -147,6 +147,7 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     L.ctr = A.take<u64>(C_COUNT);
     L.sizes = A.take<int32_t>(64);
     L.win_ptr = A.take<int32_t>(nw + 1);
+    L.key_in = A.take<u64>(n);
     L.key_out = A.take<u64>(n);
     L.spos = A.take<int32_t>(n);
     L.hflag = A.take<int32_t>(n + 1);
@@ -230,17 +231,52 @@ __global__ __launch_bounds__(256) void k_win_ptr(const int32_t *rowptr, int64_t 
     if (t <= nw) win_ptr[t] = rowptr[min((int64_t)M, t * W)];
 }
 
-// Per nonzero (CSR order): its row (bisection over rowptr; rows without nonzeros are skipped over), the checks the host
-// planner makes, and its place in the window's (column, row) order.  A window's rows are sorted already, so that place is
-// found and not sorted for: its index in its own row plus, for each other row, the nonzeros that come before it there.
-// Neighbouring nonzeros take nearly the same path through a row, so the searches run from the L1s; four of them at a time,
-// because each is a chain of loads.  GAT graph (59.7 M nonzeros): 4.1 ms, against 7.4 ms for keys and a segmented radix sort with
-// one workgroup per window, which the hub windows hold up.
-__global__ __launch_bounds__(256) void k_ranks(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n,
-                                               u64 *key_out, int32_t *spos, int32_t *row_of, u64 *ctr) {
+// The census: the nonzeros of every window in (column, row) order.  A window's rows are sorted already, so this is a merge of
+// 16 lists, done as two merges of four: a nonzero's place is its index in its own list plus, for each of the other three, how
+// many come before it there.  Neighbouring nonzeros take nearly the same path through a list, so the searches run from the L1s,
+// and the three go on together because each is a chain of loads.  Bound by the vector ALUs (some 30 instructions per step).  GAT
+// graph (59.7 M nonzeros): 1.4 + 1.6 ms; one pass with searches in all 15 other rows 4.1, keys and a segmented radix sort with one
+// workgroup per window, which the hub windows hold up, 7.4 ms.
+constexpr int MERGE = 4;
+static_assert(W == MERGE * MERGE, "two merges of MERGE lists");
+// sum over the lists of the elements for which less(value) holds (they come first); list u is values[first[u] .. + left[u])
+template <class T, class Less>
+__device__ inline int places_before(const T *values, int n, const int (&first)[MERGE], int (&left)[MERGE], Less less) {
+    int at[MERGE], sum = 0;
+#pragma unroll
+    for (int u = 0; u < MERGE; ++u) at[u] = first[u];
+    static_assert(MERGE == 4, "the loop's condition");
+    while (left[0] | left[1] | left[2] | left[3]) {
+        T v[MERGE];
+#pragma unroll
+        for (int u = 0; u < MERGE; ++u) v[u] = values[min(at[u] + (left[u] >> 1), n - 1)];
+#pragma unroll
+        for (int u = 0; u < MERGE; ++u) {
+            const int half = left[u] >> 1;
+            const bool before = left[u] > 0 && less(u, v[u]);
+            at[u] = before ? at[u] + half + 1 : at[u];
+            left[u] = before ? left[u] - half - 1 : half;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < MERGE; ++u) sum += at[u] - first[u];
+    return sum;
+}
+// First merge, from CSR order: groups of MERGE rows.  Also a nonzero's row and the checks the host planner makes.
+__global__ __launch_bounds__(256) void k_merge_rows(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n,
+                                                    u64 *key_out, int32_t *pos_out, int32_t *row_of, u64 *ctr) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
-    int64_t lo = 0, hi = M;                 // rowptr[lo] <= p < rowptr[hi]
+    // the rows of the wave's first and last nonzero once per wave (rowptr[lo] <= p < rowptr[lo + 1]), then between them
+    const int p0 = __builtin_amdgcn_readfirstlane(p), p1 = (int)min((int64_t)p0 + 63, (int64_t)n - 1);
+    int64_t lo = 0, hi = M;
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (rowptr[mid] <= p0) lo = mid; else hi = mid;
+    }
+    int64_t step = 1;
+    while (lo + step < M && rowptr[lo + step] <= p1) step <<= 1;
+    hi = min(M, lo + step);                 // rowptr[hi] > p1
     while (hi - lo > 1) {
         const int64_t mid = (lo + hi) >> 1;
         if (rowptr[mid] <= p) lo = mid; else hi = mid;
@@ -252,39 +288,41 @@ __global__ __launch_bounds__(256) void k_ranks(const int32_t *rowptr, const int3
     else if (p > row_start && col[p - 1] >= c) bad = 2u;
     row_of[p] = (int32_t)lo;
     if (bad) atomicOr(&ctr[C_ERR], (u64)bad);
-    const int64_t r0 = lo - lo % W;
-    const int own = (int)(lo - r0), rows = (int)min((int64_t)W, M - r0);
-    const int start = rowptr[r0];
-    int rank = p - row_start;
-    constexpr int U = 4;
-    for (int q = 0; q < rows; q += U) {
-        int first[U], at[U], left[U];
+    const int64_t r0 = lo - lo % MERGE;
+    const int own = (int)(lo - r0);
+    int first[MERGE + 1], left[MERGE];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = q + u;
-            const bool other = r < rows && r != own;
-            first[u] = at[u] = rowptr[r0 + min(r, rows - 1)];
-            left[u] = other ? rowptr[r0 + r + 1] - at[u] : 0;
-        }
-        while (left[0] | left[1] | left[2] | left[3]) {
-            uint32_t v[U];
+    for (int u = 0; u <= MERGE; ++u) first[u] = rowptr[min(r0 + u, M)];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = (uint32_t)col[min(at[u] + (left[u] >> 1), n - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int half = left[u] >> 1;
-                // equal columns: the row above comes first
-                const bool before = left[u] > 0 && v[u] < (uint32_t)c + (q + u < own ? 1u : 0u);
-                at[u] = before ? at[u] + half + 1 : at[u];
-                left[u] = before ? left[u] - half - 1 : half;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) rank += at[u] - first[u];
-    }
+    for (int u = 0; u < MERGE; ++u) left[u] = u == own ? 0 : first[u + 1] - first[u];
+    const int f[MERGE] = {first[0], first[1], first[2], first[3]};
+    // equal columns: the row above comes first
+    const int to = first[0] + (p - row_start) + places_before((const uint32_t *)col, n, f, left, [&](int u, uint32_t v) { return v < (uint32_t)c + (u < own ? 1u : 0u); });
     // in range for any input: the index in the row plus at most the other rows' lengths
-    key_out[start + rank] = ((u64)(uint32_t)c << 4) | (u64)own;
-    spos[start + rank] = p;
+    key_out[to] = ((u64)(uint32_t)c << 4) | (u64)(lo % W);
+    pos_out[to] = p;
+}
+// Second merge: the groups of a window.  Keys (column, row in window) differ.
+__global__ __launch_bounds__(256) void k_merge_groups(const int32_t *rowptr, int64_t M, const u64 *key, const int32_t *pos, const int32_t *row_of, int n,
+                                                      u64 *key_out, int32_t *spos) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n) return;
+    const u64 k = key[e];
+    const int64_t r = row_of[e], r0 = r - r % W;           // a place's window and group are those of the nonzero there in CSR order
+    const int own = (int)(r % W) / MERGE;
+    int first[MERGE + 1], left[MERGE];
+#pragma unroll
+    for (int u = 0; u <= MERGE; ++u) first[u] = rowptr[min(r0 + u * MERGE, M)];
+    int own_first = first[0];
+#pragma unroll
+    for (int u = 0; u < MERGE; ++u) {
+        left[u] = u == own ? 0 : first[u + 1] - first[u];
+        own_first = u == own ? first[u] : own_first;
+    }
+    const int f[MERGE] = {first[0], first[1], first[2], first[3]};
+    const int to = first[0] + (e - own_first) + places_before(key, n, f, left, [&](int, u64 v) { return v < k; });
+    key_out[to] = k;
+    spos[to] = pos[e];
 }
 
 // Per sorted nonzero: is it the first of its column vector; if so, the vector's NNZ and row mask.
@@ -391,17 +429,36 @@ __global__ __launch_bounds__(256) void k_share(const int32_t *win_vptr, const in
     // the group's vectors are dealt to the gridDim.y workgroups of the group
     for (int v = v0 + (int)(blockIdx.y * blockDim.x + threadIdx.x); v < v1; v += (int)(blockDim.x * gridDim.y)) {
         const int c = vcol[v];
-        bool seen = false;
-        for (int w = w0; w < w1 && !seen; ++w) {
-            const int a = win_vptr[w], b = win_vptr[w + 1];
-            if (b > v) break;                     // only the windows before the vector's own
-            int lo = a, hi = b;                   // first position with column >= c
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (vcol[mid] < c) lo = mid + 1; else hi = mid;
-            }
-            seen = lo < b && vcol[lo] == c;
+        // first position with column >= c in each window before the vector's own, together: the searches are chains of loads
+        constexpr int E = LIBRA_LOCALITY_WINDOWS - 1;
+        int at[E], left[E], end[E];
+        bool more = false;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int w = min(w0 + u, w1 - 1);
+            at[u] = win_vptr[w];
+            end[u] = win_vptr[w + 1];
+            left[u] = w0 + u < w1 && end[u] <= v ? end[u] - at[u] : 0;
+            if (left[u] == 0) end[u] = at[u];
+            more = more || left[u];
         }
+        while (more) {
+            int x[E];
+#pragma unroll
+            for (int u = 0; u < E; ++u) x[u] = vcol[min(at[u] + (left[u] >> 1), v)];
+            more = false;
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const int half = left[u] >> 1;
+                const bool before = left[u] > 0 && x[u] < c;
+                at[u] = before ? at[u] + half + 1 : at[u];
+                left[u] = before ? left[u] - half - 1 : half;
+                more = more || left[u];
+            }
+        }
+        bool seen = false;
+#pragma unroll
+        for (int u = 0; u < E; ++u) seen = seen || (at[u] < end[u] && vcol[at[u]] == c);
         mine += seen ? 0 : 1;
     }
     if (mine) atomicAdd(&together, mine);
@@ -914,7 +971,9 @@ __global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *q
         item = queue[pieces[3 * b + 2] + j - pieces[3 * b + 1]];
     }
     out[i] = item;
-    if (item >= 0 && !v.empty(item)) atomicMax(last, i + 1);
+    // the last such slot of the wave
+    const u64 used = __ballot(item >= 0 && !v.empty(item));
+    if (used && (int)(threadIdx.x & 63) == 63 - __builtin_clzll(used)) atomicMax(last, i + 1);
 }
 // Device task records, die by die (see task_slot in the kernels); slots past the table's end and -1 hold empty tasks.
 __global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t *order, int n, int per_die, const int32_t *blk_valptr, int empty_kind, DevTask *out) {
@@ -1245,7 +1304,8 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         // ---- 1. census: the nonzeros of every window in (column, row) order ----
         fill_bytes(L.ctr, 0, C_COUNT * sizeof(u64), s);
         hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr);
-        hipLaunchKernelGGL(k_ranks, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_out, L.spos, L.row_of, L.ctr);
+        hipLaunchKernelGGL(k_merge_rows, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_in, L.mvec_in, L.row_of, L.ctr);
+        hipLaunchKernelGGL(k_merge_groups, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, M, L.key_in, L.mvec_in, L.row_of, n, L.key_out, L.spos);
         // ---- 2. vectors ----
         hipLaunchKernelGGL(k_census, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, L.row_of, n, L.hflag, L.einfo);
         fill_bytes(L.hflag + n, 0, sizeof(int32_t), s);
