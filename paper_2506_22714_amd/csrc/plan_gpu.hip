@@ -328,6 +328,7 @@ __global__ __launch_bounds__(256) void k_merge_groups(const int32_t *rowptr, int
 // Per sorted nonzero: is it the first of its column vector; if so, the vector's NNZ and row mask.
 __global__ __launch_bounds__(256) void k_census(const u64 *skey, const int32_t *win_ptr, const int32_t *row_of, int n, int32_t *hflag, int32_t *einfo) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e == n) hflag[n] = 0;               // the scans take one entry more, here and below
     if (e >= n) return;
     const u64 key = skey[e];
     const u64 c = key >> 4;
@@ -373,7 +374,12 @@ __global__ __launch_bounds__(256) void k_vectors(const u64 *skey, const int32_t 
             mflag[v] = cnt > 1 ? 1 : 0;
             mine += cnt == 1;
         }
-        if (e == n - 1) ctr[C_NV] = (u64)(vid[e] + hflag[e]);
+        if (e == n - 1) {
+            const int nv = vid[e] + hflag[e];
+            ctr[C_NV] = (u64)nv;
+            tflag[nv] = 0;
+            mflag[nv] = 0;
+        }
     }
     if (mine) atomicAdd(&ones, mine);
     __syncthreads();
@@ -401,6 +407,7 @@ __global__ __launch_bounds__(256) void k_multi_keys(const int32_t *mflag, const 
 __global__ __launch_bounds__(256) void k_sorted(const int32_t *mvec, int nm, const int32_t *mflag, const int32_t *mscan, const int32_t *vinfo, const int32_t *vwin,
                                                 const int32_t *win_vptr, int nv, int32_t *scnt, int32_t *srank) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == nv) scnt[nv] = 0;
     if (i >= nv) return;
     if (i < nm) {
         const int v = mvec[i], base = win_vptr[vwin[v]], rank = i - mscan[base];
@@ -477,6 +484,7 @@ struct Rule {
 __global__ __launch_bounds__(256) void k_window_counts(const int32_t *win_vptr, const int32_t *taud, const int32_t *cum, int nw, Rule R,
                                                        int32_t *ntau_o, int32_t *ndv_a, int32_t *nb_a, int32_t *ndv_d, int32_t *nb_d, u64 *ctr) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == nw) { nb_a[nw] = 0; nb_d[nw] = 0; }
     if (t >= nw) return;
     const int base = win_vptr[t], nvw = win_vptr[t + 1] - base;
     int ntau = 0, ndv = 0, nb = 0;
@@ -545,6 +553,7 @@ __global__ __launch_bounds__(256) void k_blocks(const int32_t *slotvec, const in
     const int b = (int)(gid >> 4), s = (int)(gid & 15);
     const int grp = (threadIdx.x & 63) >> 4;
     const bool live = b < nb;
+    if (gid == 0) blknnz[nb] = 0;
     const int v = live ? slotvec[(int64_t)b * KB + s] : -1;
     const unsigned mask = v >= 0 ? ((unsigned)vinfo[v] >> 8) & 0xffffu : 0u;
     if (live) blk_cols[(int64_t)b * KB + s] = v >= 0 ? vcol[v] : -1;
@@ -600,6 +609,7 @@ __global__ __launch_bounds__(256) void k_block_values(const int32_t *slotvec, co
 __global__ __launch_bounds__(256) void k_entry_flags(const int32_t *hflag, const int32_t *vid, const int32_t *spos, const uint8_t *dflag_a,
                                                      const uint8_t *dflag_d, int n, Rule R, int32_t *resf_a, int32_t *resf_d) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e == n) { resf_a[n] = 0; resf_d[n] = 0; }
     if (e >= n) return;
     const int v = vid[e] + hflag[e] - 1;
     const int p = spos[e];
@@ -656,6 +666,7 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
                                                       libra_task_t *tasks_a, int32_t *zero_rows, libra_task_t *tasks_d) {
     constexpr int LANES = FILL ? 64 : 1;
     const int t = blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
+    if (!FILL && t == nw) { ntasks_a[nw] = 0; nzero[nw] = 0; nres[nw] = 0; ntasks_d[nw] = 0; }
     if (t >= nw) return;
     const int64_t r0 = (int64_t)t * W;
     if (R.build_a) {
@@ -954,7 +965,7 @@ __global__ void k_order_queue_starts(const int32_t *base, int rounds, int32_t *s
 // Slot 8 j + x of the region is the j-th item of queue x, or an empty task; last = slots up to the last task that does something.
 __global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *queue, const int32_t *pieces, int4 p0, int4 p1, int np, int4 n0, int4 n1, int slots,
                                                     int32_t *out, int32_t *last) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;      // the end first: the others then leave `last` alone
     if (i >= slots) return;
     const int x = i % XC, j = i / XC;
     const int begin[XC + 1] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, np}, len[XC] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
@@ -973,7 +984,7 @@ __global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *q
     out[i] = item;
     // the last such slot of the wave
     const u64 used = __ballot(item >= 0 && !v.empty(item));
-    if (used && (int)(threadIdx.x & 63) == 63 - __builtin_clzll(used)) atomicMax(last, i + 1);
+    if (used && (int)(threadIdx.x & 63) == 63 - __builtin_clzll(used) && __hip_atomic_load(last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= i) atomicMax(last, i + 1);
 }
 // Device task records, die by die (see task_slot in the kernels); slots past the table's end and -1 hold empty tasks.
 __global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t *order, int n, int per_die, const int32_t *blk_valptr, int empty_kind, DevTask *out) {
@@ -1307,8 +1318,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         hipLaunchKernelGGL(k_merge_rows, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_in, L.mvec_in, L.row_of, L.ctr);
         hipLaunchKernelGGL(k_merge_groups, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, M, L.key_in, L.mvec_in, L.row_of, n, L.key_out, L.spos);
         // ---- 2. vectors ----
-        hipLaunchKernelGGL(k_census, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, L.row_of, n, L.hflag, L.einfo);
-        fill_bytes(L.hflag + n, 0, sizeof(int32_t), s);
+        hipLaunchKernelGGL(k_census, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, L.row_of, n, L.hflag, L.einfo);
         scan(L, L.hflag, L.vid, (size_t)n + 1, s);
         hipLaunchKernelGGL(k_vectors, dim3(std::min(blocks_for(n, 256), 4096u)), dim3(256), 0, s, L.key_out, L.hflag, L.vid, L.einfo, L.row_of, n, tau_a,
                            L.vfirst, L.vinfo, L.vcol, L.vwin, L.tflag, L.mflag, L.ctr);
@@ -1325,7 +1335,6 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         // order of a window's vectors: NNZ descending, column ascending
         const int nm = nv - (int)ctr[C_NNZ1];
         if (nm < 0 || nm > nv) throw Fail{LIBRA_ERR_HIP};
-        fill_bytes(L.mflag + nv, 0, sizeof(int32_t), s);
         scan(L, L.mflag, L.mscan, (size_t)nv + 1, s);
         if (nm > 0) {
             hipLaunchKernelGGL(k_multi_keys, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.mflag, L.mscan, L.vinfo, L.vwin, nv, L.mkey_in, L.mvec_in);
@@ -1334,13 +1343,11 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             size_t sz = L.tmp_bytes;
             hip_ok(rocprim::radix_sort_pairs(L.tmp, sz, L.mkey_in, L.mkey_out, L.mvec_in, L.mvec_out, (size_t)nm, 0u, (unsigned)(winbits + 4), s));
         }
-        hipLaunchKernelGGL(k_sorted, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.mvec_out, nm, L.mflag, L.mscan, L.vinfo, L.vwin, L.win_vptr, nv, L.scnt, L.srank);
-        fill_bytes(L.scnt + nv, 0, sizeof(int32_t), s);
-        fill_bytes(L.tflag + nv, 0, sizeof(int32_t), s);
+        hipLaunchKernelGGL(k_sorted, dim3(blocks_for((int64_t)nv + 1, 256)), dim3(256), 0, s, L.mvec_out, nm, L.mflag, L.mscan, L.vinfo, L.vwin, L.win_vptr, nv, L.scnt, L.srank);
         scan(L, L.scnt, L.cum, (size_t)nv + 1, s);
         scan(L, L.tflag, L.taud, (size_t)nv + 1, s);
         // ---- 3. per window: dense vectors and blocks ----
-        hipLaunchKernelGGL(k_window_counts, dim3(blocks_for(nw, 256)), dim3(256), 0, s, L.win_vptr, L.taud, L.cum, nw, R,
+        hipLaunchKernelGGL(k_window_counts, dim3(blocks_for((int64_t)nw + 1, 256)), dim3(256), 0, s, L.win_vptr, L.taud, L.cum, nw, R,
                            L.ntau, L.a.ndv, L.a.nb, L.d.ndv, L.d.nb, L.ctr);
         if (o.build_sddmm && o.mode == LIBRA_MODE_HYBRID && o.sddmm_min_dense_pct > 0) {
             // the whole-matrix utilisation rule: too small a dense share sends the whole SDDMM sub-plan to the scalar path
@@ -1353,8 +1360,6 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
                 fill_bytes(L.ctr + C_DV_D, 0, 2 * sizeof(u64), s);              // C_DV_D and C_PAD_D are neighbours
             }
         }
-        fill_bytes(L.a.nb + nw, 0, sizeof(int32_t), s);
-        fill_bytes(L.d.nb + nw, 0, sizeof(int32_t), s);
         scan(L, L.a.nb, L.a.blkptr, (size_t)nw + 1, s);
         scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
         int32_t size[7];
@@ -1377,23 +1382,20 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             if (nb > 0)
                 hipLaunchKernelGGL(k_blocks, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vcol, L.vinfo, nb,
                                    S.blk_cols, S.bitmap, S.blknnz, S.blkmask, S.blkncols);
-            fill_bytes(S.blknnz + nb, 0, sizeof(int32_t), s);
+            if (nb == 0) fill_bytes(S.blknnz, 0, sizeof(int32_t), s);
             scan(L, S.blknnz, S.blk_valptr, (size_t)nb + 1, s);
             if (nb > 0)
                 hipLaunchKernelGGL(k_block_values, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vfirst, L.vinfo, S.bitmap,
                                    S.blk_valptr, L.spos, val, vsize, nb, S.dense_perm, S.dense_val);
         }
         // ---- 5. residual nonzeros and tasks ----
-        hipLaunchKernelGGL(k_entry_flags, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.hflag, L.vid, L.spos, L.a.dflag, L.d.dflag, n, R, L.a.resf, L.d.resf);
-        fill_bytes(L.a.resf + n, 0, sizeof(int32_t), s);
-        fill_bytes(L.d.resf + n, 0, sizeof(int32_t), s);
+        hipLaunchKernelGGL(k_entry_flags, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, s, L.hflag, L.vid, L.spos, L.a.dflag, L.d.dflag, n, R, L.a.resf, L.d.resf);
         scan(L, L.a.resf, L.a.rescan, (size_t)n + 1, s);
         scan(L, L.d.resf, L.d.rescan, (size_t)n + 1, s);
-        hipLaunchKernelGGL((k_window_tasks<false>), dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
+        hipLaunchKernelGGL((k_window_tasks<false>), dim3(blocks_for((int64_t)nw + 1, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
                            L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);
-        for (int32_t *p : {L.a.ntasks, L.nzero, L.nres, L.d.ntasks}) fill_bytes(p + nw, 0, sizeof(int32_t), s);
         scan(L, L.a.ntasks, L.a.tbase, (size_t)nw + 1, s);
         scan(L, L.nzero, L.zbase, (size_t)nw + 1, s);
         scan(L, L.nres, L.resptr, (size_t)nw + 1, s);
