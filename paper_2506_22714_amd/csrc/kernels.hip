@@ -1351,7 +1351,7 @@ struct SoftmaxRows {
     uint32_t medium_blocks, short_blocks;
 };
 __host__ inline SoftmaxRows softmax_rows(const libra_plan_t *P) {
-    SoftmaxRows r{P->d_rowptr, P->d_long_rows, P->d_medium_rows, P->M, (int32_t)P->long_rows.size(), (int32_t)P->medium_rows.size(), 0u, 0u};
+    SoftmaxRows r{P->d_rowptr, P->d_long_rows, P->d_medium_rows, P->M, (int32_t)P->long_rows.size(), (int32_t)P->n_medium_rows, 0u, 0u};
     r.medium_blocks = ((uint32_t)r.nmedium + 256u / MEDIUM_LANES - 1u) / (256u / MEDIUM_LANES);
     r.short_blocks = (uint32_t)std::min<int64_t>((P->M * SHORT_LANES + 255) / 256, 1 << 18);
     return r;
@@ -1685,9 +1685,10 @@ __global__ __launch_bounds__(WAVE) void pack_sddmm_sorted_records_kernel(const D
 // st == nullptr: size pass.  da/dd == nullptr: the arrays come from the plan's host vectors; otherwise from
 // device memory, and the packed record arrays are only reserved here (adopt_device_arrays fills them).
 void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, const DeviceSource *dd) {
-    u.put(st ? (const void *)P->rowptr.data() : nullptr, nullptr, (size_t)(P->M + 1) * 4, P->d_rowptr);
+    u.put(st && !da ? (const void *)P->rowptr.data() : nullptr, da ? da->rowptr : nullptr, (size_t)(P->M + 1) * 4, P->d_rowptr);
     u.putv(P->long_rows, P->d_long_rows);
-    u.putv(P->medium_rows, P->d_medium_rows);
+    const bool listed = da && da->medium_rows;
+    u.put(st && !listed ? (const void *)P->medium_rows.data() : nullptr, listed ? da->medium_rows : nullptr, (size_t)P->n_medium_rows * 4, P->d_medium_rows);
     SubPlan &sa = P->spmm, &sd = P->sddmm;
     const size_t vs = (size_t)P->vsize;
     const bool from_host = st && !da;

@@ -548,7 +548,7 @@ int libra::resolve_options(const libra_plan_opts_t *in, int vdt, Resolved &o) {
 void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t *share, const TableOrder &order) {
     const Resolved o = P->o;
     const int64_t M = P->M, nnz = P->nnz;
-    const int32_t *rowptr = P->rowptr.data();
+    const int32_t *rowptr = P->rowptr.empty() ? nullptr : P->rowptr.data();
     SubPlan &sa = P->spmm, &sd = P->sddmm;
     libra_stats_t &st = P->stats;
     const int64_t nwin = (M + o.W - 1) / o.W;
@@ -559,15 +559,18 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
         if (trace) std::fprintf(stderr, "[finish_plan] %-34s %8.3f ms\n", what,
                                 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
     };
-    for (int64_t i = 0; i < M; ++i) {       // row lists of the edge softmax
+    for (int64_t i = 0; rowptr && i < M; ++i) {       // row lists of the edge softmax
         const int32_t n = rowptr[i + 1] - rowptr[i];
         if (n > LIBRA_SOFTMAX_LONG_ROW) P->long_rows.push_back((int32_t)i);
         else if (n > 64) P->medium_rows.push_back((int32_t)i);
     }
     // longest first: one workgroup takes a long row, and the longest one sets the time of the whole class
-    std::stable_sort(P->long_rows.begin(), P->long_rows.end(), [&](int32_t a, int32_t b) {
-        return rowptr[a + 1] - rowptr[a] > rowptr[b + 1] - rowptr[b];
-    });
+    if (rowptr) {
+        std::stable_sort(P->long_rows.begin(), P->long_rows.end(), [&](int32_t a, int32_t b) {
+            return rowptr[a + 1] - rowptr[a] > rowptr[b + 1] - rowptr[b];
+        });
+        P->n_medium_rows = (int64_t)P->medium_rows.size();
+    }
     if (!o.build_spmm) sa = SubPlan();
     if (!o.build_sddmm) sd = SubPlan();
     if (P->host_arrays) {

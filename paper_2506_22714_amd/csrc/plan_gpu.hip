@@ -41,6 +41,10 @@ namespace {
 constexpr int W = 16, KB = 16;
 typedef unsigned long long u64;
 
+// Matrices of fewer rows have rowptr checked and the rows of the edge softmax listed on the host, where a row costs 1.2 ns; here
+// the launches and the extra wait cost some 60 us (2^20 rows, plan and one step of the GAT graph: 13.15 -> 12.05 ms).
+constexpr int64_t DEVICE_ROWS_MIN = 1 << 17;
+
 enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_COUNT };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -103,12 +107,17 @@ struct Layout {
     int32_t *ntau, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
     OrderScratch o;
-    int32_t *sizes;
+    int32_t *sizes, *medium_rows, *long_rows, *long_lens;
     void *tmp;
     size_t tmp_bytes;
     size_t total;
 };
 
+struct RowsOfLength {                   // more than `above` and at most `most` nonzeros
+    const int32_t *rowptr;
+    int above, most;
+    __device__ bool operator()(int32_t i) const { const int n = rowptr[i + 1] - rowptr[i]; return n > above && n <= most; }
+};
 size_t order_items(const Sizes &z) { return (size_t)std::max(z.tasks_a_max, std::max(z.tasks_d_max, z.segs_d_max)); }
 int64_t order_slots(int64_t tasks) { return 2 * tasks + 64; }      // the die-aware orders add empty tasks
 
@@ -137,6 +146,9 @@ size_t rocprim_temp_bytes(const Sizes &z) {
     sz = 0;
     (void)rocprim::exclusive_scan(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, (u64)0, m, rocprim::plus<u64>());
     best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::select(nullptr, sz, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, (int32_t *)nullptr, (size_t)z.M, RowsOfLength{nullptr, 0, 0});
+    best = std::max(best, sz);
     return best + 4096;
 }
 
@@ -146,6 +158,9 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     const size_t n = (size_t)z.n, nw = (size_t)z.nw, nb = (size_t)z.nbmax;
     L.ctr = A.take<u64>(C_COUNT);
     L.sizes = A.take<int32_t>(64);
+    L.medium_rows = A.take<int32_t>((size_t)z.M);
+    L.long_rows = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
+    L.long_lens = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
     L.win_ptr = A.take<int32_t>(nw + 1);
     L.key_in = A.take<u64>(n);
     L.key_out = A.take<u64>(n);
@@ -229,6 +244,16 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
 __global__ __launch_bounds__(256) void k_win_ptr(const int32_t *rowptr, int64_t M, int nw, int32_t *win_ptr) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t <= nw) win_ptr[t] = rowptr[min((int64_t)M, t * W)];
+}
+
+__global__ __launch_bounds__(256) void k_check_rowptr(const int32_t *rowptr, int64_t M, int n, u64 *ctr) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool bad = i < M ? rowptr[i + 1] < rowptr[i] : i == M && (rowptr[0] != 0 || rowptr[M] != n);
+    if (bad) atomicOr(&ctr[C_ERR], (u64)4);
+}
+__global__ __launch_bounds__(256) void k_row_lengths(const int32_t *rowptr, const int32_t *rows, int n, int32_t *len) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) len[i] = rowptr[rows[i] + 1] - rowptr[rows[i]];
 }
 
 // The census: the nonzeros of every window in (column, row) order.  A window's rows are sorted already, so this is a merge of
@@ -1284,11 +1309,45 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
     try {
         P->M = M; P->Kc = Kc; P->nnz = nnz; P->vdt = val_dtype; P->vsize = val_dtype == LIBRA_F32 ? 4 : 2;
         P->o = o;
-        fetch(P->rowptr, d_rowptr, (size_t)M + 1, s);
-        hip_ok(hipStreamSynchronize(s));
-        if (P->rowptr[0] != 0 || P->rowptr[M] != nnz) throw Fail{LIBRA_ERR_ROWPTR};
-        for (int64_t i = 0; i < M; ++i)
-            if (P->rowptr[i + 1] < P->rowptr[i]) throw Fail{LIBRA_ERR_ROWPTR};
+        const bool rows_here = M >= DEVICE_ROWS_MIN && !keep_host_copy && nnz > 0 && !((uintptr_t)workspace & 255) &&
+                               workspace_bytes >= make_layout(make_sizes(M, nnz, o), P->vsize, workspace).total;
+        if (rows_here) {
+            const Layout L = make_layout(make_sizes(M, nnz, o), P->vsize, workspace);
+            u64 bad = 0;
+            fill_bytes(L.ctr, 0, C_COUNT * sizeof(u64), s);
+            hipLaunchKernelGGL(k_check_rowptr, dim3(blocks_for(M + 1, 256)), dim3(256), 0, s, d_rowptr, M, (int)nnz, L.ctr);
+            hip_ok(hipMemcpyAsync(&bad, L.ctr + C_ERR, sizeof bad, hipMemcpyDeviceToHost, s));
+            hip_ok(hipStreamSynchronize(s));
+            if (bad) throw Fail{LIBRA_ERR_ROWPTR};
+            // longest first: one workgroup takes a long row, and the longest one sets the time of the whole class
+            auto select = [&](int above, int most, int32_t *to, int32_t *count) {
+                size_t sz = L.tmp_bytes;
+                hip_ok(rocprim::select(L.tmp, sz, rocprim::counting_iterator<int32_t>(0), to, count, (size_t)M, RowsOfLength{d_rowptr, above, most}, s));
+            };
+            select(64, LIBRA_SOFTMAX_LONG_ROW, L.medium_rows, L.sizes);
+            select(LIBRA_SOFTMAX_LONG_ROW, INT32_MAX, L.long_rows, L.sizes + 1);
+            int32_t count[2];
+            hip_ok(hipMemcpyAsync(count, L.sizes, sizeof count, hipMemcpyDeviceToHost, s));
+            hip_ok(hipStreamSynchronize(s));
+            P->n_medium_rows = count[0];
+            if (count[1] > 0) {
+                std::vector<int32_t> rows, len, by(count[1]);
+                hipLaunchKernelGGL(k_row_lengths, dim3(blocks_for(count[1], 256)), dim3(256), 0, s, d_rowptr, L.long_rows, count[1], L.long_lens);
+                fetch(rows, L.long_rows, (size_t)count[1], s);
+                fetch(len, L.long_lens, (size_t)count[1], s);
+                hip_ok(hipStreamSynchronize(s));
+                for (int i = 0; i < count[1]; ++i) by[i] = i;
+                std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return len[a] > len[b]; });
+                P->long_rows.resize(by.size());
+                for (size_t i = 0; i < by.size(); ++i) P->long_rows[i] = rows[by[i]];
+            }
+        } else {
+            fetch(P->rowptr, d_rowptr, (size_t)M + 1, s);
+            hip_ok(hipStreamSynchronize(s));
+            if (P->rowptr[0] != 0 || P->rowptr[M] != nnz) throw Fail{LIBRA_ERR_ROWPTR};
+            for (int64_t i = 0; i < M; ++i)
+                if (P->rowptr[i + 1] < P->rowptr[i]) throw Fail{LIBRA_ERR_ROWPTR};
+        }
         if (nnz == 0) {
             // nothing to sort or scan: the plan of a matrix without nonzeros (one empty task per window) needs no device work
             const std::vector<int32_t> rp = P->rowptr;
@@ -1300,7 +1359,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             }
             return rc;
         }
-        mark("rowptr on the host, checked");
+        mark("rowptr checked");
         const Sizes z = make_sizes(M, nnz, o);
         const Layout L = make_layout(z, P->vsize, workspace);
         if (((uintptr_t)workspace & 255) || workspace_bytes < L.total) throw Fail{LIBRA_ERR_BUFFER};
@@ -1518,7 +1577,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             // the plan's device copy straight from the workspace: no round trip through host memory
             auto src = [&](const SubOut &S, const TaskView &v, const int32_t *list, int empty_kind, const int32_t *zero_rows) {
                 DeviceSource d{S.blk_cols, S.blk_valptr, S.dense_perm, S.res_perm, S.res_row, S.res_col, zero_rows,
-                               reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val, nullptr};
+                               reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val, d_rowptr, rows_here ? L.medium_rows : nullptr, nullptr};
                 if (order_here)
                     d.write_tasks = [&S, v, list, empty_kind, s](DevTask *out, int64_t n) {
                         const int per_die = (int)((n + XC - 1) / XC);

@@ -82,6 +82,7 @@ struct DeviceSource {
     const int32_t *blk_cols, *blk_valptr, *dense_perm, *res_perm, *res_row, *res_col, *zero_rows;
     const uint64_t *blk_bitmap;
     const void *dense_val, *res_val;
+    const int32_t *rowptr, *medium_rows;        // of the matrix (medium_rows: nullptr = the plan's host list)
     std::function<void(DevTask *out, int64_t n)> write_tasks;      // set if the task table was ordered on the device: queues its records
 };
 
@@ -130,9 +131,10 @@ struct libra_plan_s {
     int vdt = LIBRA_F16;
     int vsize = 2;
     libra::Resolved o{};
-    std::vector<int32_t> rowptr;
+    std::vector<int32_t> rowptr;        // empty if the device planner checked it and listed the rows
     std::vector<int32_t> long_rows;     // rows with more than LIBRA_SOFTMAX_LONG_ROW nonzeros (edge softmax)
-    std::vector<int32_t> medium_rows;   // rows with 65 .. LIBRA_SOFTMAX_LONG_ROW nonzeros
+    std::vector<int32_t> medium_rows;   // rows with 65 .. LIBRA_SOFTMAX_LONG_ROW nonzeros; empty if the device planner listed them
+    int64_t n_medium_rows = 0;
     libra::SubPlan spmm, sddmm;
     bool host_arrays = true;            // false: built on the device without a host copy (nothing to export or upload)
     libra_stats_t stats{};

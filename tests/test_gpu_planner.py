@@ -312,3 +312,29 @@ def test_large_task_tables_are_ordered_like_on_the_host(name):
             assert torch.equal(ph.sddmm(X, B), pr.sddmm(X, B))
         ph.close()
         pr.close()
+
+
+def test_rows_of_large_matrices_are_checked_and_listed_on_the_device():
+    """From 2^17 rows on rowptr stays on the GPU (plans without a host copy): the row classes of the edge softmax at their edges
+    (64, 65, 2048, 2049 nonzeros) against the host-planned result, and a broken rowptr is refused."""
+    M, Kc = (1 << 17) + 3, 4096
+    A = wl.random_pattern(M, 64, 0.03, seed=4, empty_rows=0.3)
+    A = wl.Csr(M, Kc, A.rowptr, A.col, A.val)
+    for k, n in enumerate((64, 65, 2048, 2049, 2600)):
+        A = wl.with_long_rows(A, [0 if n == 2600 else 100 * k + 7, 70_000 + k, M - 1 - k], n, seed=k)
+    ones = np.ones(A.nnz, dtype=np.float16)
+    ph, pd = lb.Plan.from_csr(A, val=ones).upload(), device_plan(A, val=ones, resident=True, keep_host_copy=False)
+    scores = torch.randn(A.nnz, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    ah, ad = ph.edge_softmax(scores, 0.5, out=torch.empty_like(scores)), pd.edge_softmax(scores, 0.5, out=torch.full_like(scores, float("nan")))
+    assert torch.equal(ah, ad)
+    dalpha = torch.randn(A.nnz, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    assert torch.equal(ph.edge_softmax_backward(ah, dalpha, 0.5), pd.edge_softmax_backward(ad, dalpha, 0.5))
+    ph.close()
+    pd.close()
+    col, val = torch.from_numpy(A.col.astype(np.int32)).cuda(), torch.from_numpy(ones).cuda()
+    for at, by in ((0, 1), (M // 2, 100_000), (M, -1)):
+        rowptr = A.rowptr.astype(np.int32).copy()
+        rowptr[at] += by
+        with pytest.raises(lb.LibraError) as e:
+            lb.Plan.from_device_csr(M, Kc, torch.from_numpy(rowptr).cuda(), col, val, resident=True, keep_host_copy=False)
+        assert e.value.code == lb.ERR["ROWPTR"]
