@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t
     if (item >= v.nt) {
         const int q = (item - v.nt) * v.cs;
         d.res_begin = q;
-        d.res_end = min(v.nres, q + v.cs);
+        d.res_end = piece_end(q, v.nres, v.cs);
         d.kind = LIBRA_TASK_CHUNK;
     } else if (item >= 0) {
         const libra_task_t t = v.tasks[item];
@@ -1220,8 +1220,8 @@ constexpr int64_t DEVICE_ORDER_MIN = 8192;
 inline libra_task_t task_at(const std::vector<libra_task_t> &tasks, int item, int cs, int nres, int empty_kind) {
     if (item < 0) return libra_task_t{empty_kind, 0, 0, 0, 0, 0, 0u, 0u, 0u, 0u};
     if (item < (int)tasks.size()) return tasks[item];
-    const int q = (item - (int)tasks.size()) * cs, q1 = std::min(nres, q + cs);
-    return libra_task_t{LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, (uint32_t)(2 * (q1 - q))};
+    const int q = (item - (int)tasks.size()) * cs, q1 = piece_end(q, nres, cs);
+    return libra_task_t{LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, 2u * (uint32_t)(q1 - q)};
 }
 
 // Several single words in one copy and one wait (each peek is a round trip of some 10 us).
@@ -1477,7 +1477,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
                            L.d.resf, L.d.rescan, L.d.res_perm, L.d.res_row, L.d.res_col, L.d.res_val);
         if (o.build_spmm && ntA > 0)
             hipLaunchKernelGGL(k_task_cols, dim3(blocks_for(ntA, 256)), dim3(256), 0, s, L.a.tasks, ntA, L.a.res_col, L.task_col);
-        const int nsegD = o.build_sddmm ? (nresD + o.sddmm_Cs - 1) / o.sddmm_Cs : 0;
+        const int nsegD = o.build_sddmm ? piece_count(nresD, o.sddmm_Cs) : 0;
         if (nsegD > 0)
             hipLaunchKernelGGL(k_segment_cols, dim3(blocks_for(nsegD, 256)), dim3(256), 0, s, L.d.res_row, L.d.res_col, nresD, o.sddmm_Cs, nsegD, L.seg_col);
         hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));

@@ -22,6 +22,11 @@
 
 namespace libra {
 
+// n items cut into pieces of at most `size` items: how many, and where the piece that begins at q ends.  `size` is an option and
+// may be anything up to 2^31 - 1 ("do not cut"), so neither forms a sum with it that could leave 32 bits.
+LIBRA_HD inline int32_t piece_count(int32_t n, int32_t size) { return n > 0 ? (n - 1) / size + 1 : 0; }
+LIBRA_HD inline int32_t piece_end(int32_t q, int32_t end, int32_t size) { return end - q > size ? q + size : end; }
+
 // Task record as the kernels read it (32 bytes).  SpMM: a decomposed-row segment is stored
 // as a window task without blocks whose only output row is the atomic one.
 struct DevTask {

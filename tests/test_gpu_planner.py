@@ -314,6 +314,34 @@ def test_large_task_tables_are_ordered_like_on_the_host(name):
         pr.close()
 
 
+@pytest.mark.parametrize("sddmm_cs", [2**31 - 1, 2**31 - 2, 2**30, 204_356, 204_355])
+def test_segments_longer_than_the_residual_list(sddmm_cs):
+    """sddmm_cs may be anything up to 2^31 - 1 ("do not cut"): one segment, or two, over the whole residual list, in a table
+    ordered on the GPU and (small matrix, two or three residual nonzeros) in one ordered on the host."""
+    A = wl.rmat(scale=13, avg_degree=16, seed=3)
+    assert A.nnz == 204_356
+    ones = np.ones(A.nnz, dtype=np.float16)
+    kw = dict(mode=lb.MODE_SCALAR_ONLY, cs=8, sddmm_cs=sddmm_cs)
+    ph, pd = lb.Plan.from_csr(A, val=ones, **kw), device_plan(A, val=ones, **kw)
+    assert ph.stats()["spmm_tasks"] > 8192 and ph.stats()["sddmm_tasks"] == 1 + (sddmm_cs < A.nnz)
+    assert_same_plan(ph, pd)
+    pd.close()
+    ph.upload()
+    pr = device_plan(A, val=ones, resident=True, keep_host_copy=False, **kw)
+    X, Y = (torch.from_numpy(wl.dense_small_int(n, 32, seed=k)).cuda() for k, n in ((1, A.M), (2, A.Kc)))
+    out = torch.full((A.nnz,), float("nan"), device="cuda")
+    pr.sddmm(X, Y, out=out)
+    assert torch.equal(out, ph.sddmm(X, Y))
+    ph.close()
+    pr.close()
+    for nnz in (1, 2, 3, 4):
+        S = wl.Csr(5, 9, np.minimum(np.arange(6), nnz).astype(np.int32), np.arange(nnz, dtype=np.int32), ones[:nnz])
+        ph, pd = lb.Plan.from_csr(S, **kw), device_plan(S, **kw)
+        assert_same_plan(ph, pd)
+        ph.close()
+        pd.close()
+
+
 def test_rows_of_large_matrices_are_checked_and_listed_on_the_device():
     """From 2^17 rows on rowptr stays on the GPU (plans without a host copy): the row classes of the edge softmax at their edges
     (64, 65, 2048, 2049 nonzeros) against the host-planned result, and a broken rowptr is refused."""
