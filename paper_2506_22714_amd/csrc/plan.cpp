@@ -194,8 +194,8 @@ void plan_range(const Ctx &c, int64_t w0, int64_t w1, Part &out) {
                 return n;
             };
             if (b1 - b0 > o.Ts) {
-                for (int32_t g0 = b0; g0 < b1; g0 += o.Ts) {
-                    int32_t g1 = std::min(b1, g0 + o.Ts);
+                for (int32_t g0 = b0, g1; g0 < b1; g0 = g1) {
+                    g1 = piece_end(g0, b1, o.Ts);
                     sa.tasks.push_back({LIBRA_TASK_WINDOW, (int32_t)w, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1)});
                     sa.task_col.push_back(-1);
                 }
@@ -217,12 +217,11 @@ void plan_range(const Ctx &c, int64_t w0, int64_t w1, Part &out) {
                 for (int r = 0; r < (int)(r1 - r0); ++r) {
                     if (!(split_mask >> r & 1)) continue;
                     const int32_t e = q + rlen[r];
-                    for (; q < e; q += o.Cs) {
-                        int32_t qe = std::min(e, q + o.Cs);
+                    for (int32_t qe; q < e; q = qe) {
+                        qe = piece_end(q, e, o.Cs);
                         sa.tasks.push_back({LIBRA_TASK_CHUNK, (int32_t)(r0 + r), 0, 0, q, qe, 0u, 0u, 0u, (uint32_t)(qe - q)});
                         sa.task_col.push_back(sa.res_col[q]);            // first column of the segment
                     }
-                    q = e;
                 }
             }
             sa.win_resptr.push_back((int32_t)sa.res_perm.size());
@@ -247,8 +246,8 @@ void plan_range(const Ctx &c, int64_t w0, int64_t w1, Part &out) {
             }
             const int32_t b1 = (int32_t)sd.n_blocks();
             sd.win_blkptr.push_back(b1);
-            for (int32_t g0 = b0; g0 < b1; g0 += o.sddmm_Ts) {
-                int32_t g1 = std::min(b1, g0 + o.sddmm_Ts);
+            for (int32_t g0 = b0, g1; g0 < b1; g0 = g1) {
+                g1 = piece_end(g0, b1, o.sddmm_Ts);
                 uint32_t ncols = 0;
                 for (int32_t b = g0; b < g1; ++b)
                     for (int s = 0; s < KB; ++s) ncols += sd.blk_cols[(size_t)b * KB + s] >= 0;
@@ -580,12 +579,12 @@ void libra::finish_plan(libra_plan_t *P, const ColumnFetch &cols, const int64_t 
     if (o.build_sddmm && !order) {
         // scalar segments over the flat residual list (no atomics needed: each output has one writer)
         const int32_t nres = (int32_t)sd.n.res;
-        const size_t nseg = ((size_t)nres + o.sddmm_Cs - 1) / o.sddmm_Cs;
+        const size_t nseg = (size_t)piece_count(nres, o.sddmm_Cs);
         const bool derive = sd.seg_col.size() != nseg && P->host_arrays;
         if (sd.seg_col.size() != nseg) sd.seg_col.assign(nseg, -1);
-        for (int32_t q = 0; q < nres; q += o.sddmm_Cs) {
-            int32_t q1 = std::min(nres, q + o.sddmm_Cs);
-            sd.tasks.push_back({LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, (uint32_t)(2 * (q1 - q))});
+        for (int32_t q = 0, q1; q < nres; q = q1) {
+            q1 = piece_end(q, nres, o.sddmm_Cs);
+            sd.tasks.push_back({LIBRA_TASK_CHUNK, 0, 0, 0, q, q1, 0u, 0u, 0u, 2u * (uint32_t)(q1 - q)});
             if (derive && sd.res_row[q] == sd.res_row[q1 - 1]) sd.seg_col[q / o.sddmm_Cs] = sd.res_col[q];
         }
     }

@@ -701,9 +701,9 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
         const bool many = b1 - b0 > R.Ts;
         int nchunks = 0;
         for (int r = 0; r < z.nr; ++r)
-            if ((z.split >> r) & 1u) nchunks += (z.rlen[r] + R.Cs - 1) / R.Cs;
+            if ((z.split >> r) & 1u) nchunks += piece_count(z.rlen[r], R.Cs);
         if (!FILL) {
-            const int nwt = many ? (b1 - b0 + R.Ts - 1) / R.Ts + (z.scalar ? 1 : 0) : 1;
+            const int nwt = many ? piece_count(b1 - b0, R.Ts) + (z.scalar ? 1 : 0) : 1;
             ntasks_a[t] = nwt + nchunks;
             nzero[t] = many ? z.nr : __popc(z.split);
             nres[t] = z.q_unsplit + z.q_split;
@@ -718,9 +718,9 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
             auto touched = [&](int g0, int g1) { unsigned m = 0; for (int b = g0; b < g1; ++b) m |= (unsigned)blkmask_a[b]; return m; };
             auto cols_in = [&](int g0, int g1) { unsigned c = 0; for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_a[b]; return c; };
             if (many) {
-                const int groups = (b1 - b0 + R.Ts - 1) / R.Ts;
+                const int groups = piece_count(b1 - b0, R.Ts);
                 for (int g = lane; g < groups; g += LANES) {
-                    const int g0 = b0 + g * R.Ts, g1 = min(b1, g0 + R.Ts);
+                    const int g0 = b0 + g * R.Ts, g1 = piece_end(g0, b1, R.Ts);
                     put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
                 }
                 out += groups;
@@ -742,9 +742,9 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
             int q = q1;
             for (int r = 0; r < z.nr; ++r) {
                 if (!((z.split >> r) & 1u)) continue;
-                const int n = (z.rlen[r] + R.Cs - 1) / R.Cs, e = q + z.rlen[r];
+                const int n = piece_count(z.rlen[r], R.Cs), e = q + z.rlen[r];
                 for (int k = lane; k < n; k += LANES) {
-                    const int qs = q + k * R.Cs, qe = min(e, qs + R.Cs);
+                    const int qs = q + k * R.Cs, qe = piece_end(qs, e, R.Cs);
                     put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
                 }
                 out += n;
@@ -757,11 +757,11 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
     if (R.build_d) {
         const int b0 = blkptr_d[t], b1 = blkptr_d[t + 1];
         if (!FILL) {
-            ntasks_d[t] = (b1 - b0 + R.Ts_d - 1) / R.Ts_d;
+            ntasks_d[t] = piece_count(b1 - b0, R.Ts_d);
         } else {
             libra_task_t *out = tasks_d + tbase_d[t];
-            for (int g = lane; g < (b1 - b0 + R.Ts_d - 1) / R.Ts_d; g += LANES) {
-                const int g0 = b0 + g * R.Ts_d, g1 = min(b1, g0 + R.Ts_d);
+            for (int g = lane; g < piece_count(b1 - b0, R.Ts_d); g += LANES) {
+                const int g0 = b0 + g * R.Ts_d, g1 = piece_end(g0, b1, R.Ts_d);
                 unsigned c = 0;
                 for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
                 put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);

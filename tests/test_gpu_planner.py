@@ -65,6 +65,8 @@ CASES = [
     dict(spmm_min_vec_nnz=16, sddmm_min_blk_nnz=200),
     dict(sddmm_min_blk_nnz=20, sddmm_min_dense_pct=30),
     dict(sddmm_min_blk_nnz=20, sddmm_min_dense_pct=85),
+    dict(sddmm_min_blk_nnz=17, ts=2**31 - 1, cs=2**31 - 1, sddmm_cs=2**31 - 1, sddmm_ts=2**31 - 1),      # nothing is cut
+    dict(mode=lb.MODE_DENSE_ONLY, sddmm_ts=2**31 - 2),
 ]
 
 

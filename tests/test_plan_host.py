@@ -167,6 +167,8 @@ CASES = [
     dict(flags=lb.FLAG_NATURAL_ORDER, ts=2, cs=6),
     dict(sddmm_min_blk_nnz=20, sddmm_min_dense_pct=30),         # the dense-share rule: fires on some of the matrices
     dict(sddmm_min_blk_nnz=20, sddmm_min_dense_pct=85),
+    dict(sddmm_min_blk_nnz=17, ts=2**31 - 1, cs=2**31 - 1, sddmm_cs=2**31 - 1, sddmm_ts=2**31 - 1),      # nothing is cut
+    dict(mode=lb.MODE_DENSE_ONLY, sddmm_ts=2**31 - 2),
 ]
 
 
