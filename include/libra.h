@@ -244,7 +244,7 @@ int libra_plan_upload(libra_plan_t *plan, void *dev_buf, size_t bytes, void *str
  * rows with one writer are stored once, rows with several writers are cleared and accumulated with
  * fp32 atomics (their summation order is not deterministic).
  * 16-bit storage: an Inf or NaN in row j of B reaches the rows with a nonzero in column j and no others (a task that meets
- * one forms its sums without the matrix cores, several times slower).  fp32 storage: B must hold finite numbers: a dense block
+ * one, or whose sums overflow, goes over its rows a second time: a call takes 2 to 5 times as long if all of them do).  fp32 storage: B must hold finite numbers: a dense block
  * multiplies the empty slots of its tile (zeros) by the gathered rows of B, so an Inf or NaN in row j of B reaches every row of
  * a window that has a dense block with column j, not only the rows with a nonzero in column j (0 * Inf = NaN), where the
  * definition would leave them untouched.  X and Y in libra_sddmm: only outputs that exist are affected (an output is always a

@@ -256,37 +256,141 @@ struct GatherStage {
     }
 };
 
-// The sums of a task from its nonzeros alone, one at a time on the vector ALUs, into a tile of W x N: for rows of B that hold
-// an Inf or NaN, which must not meet the empty places of a matrix-core tile.
-template <class T, int N>
-__device__ inline void spmm_exact_sums(const SpmmArgs &a, const DevTask &t, int nblk, int L, const char *Bp, uint32_t ldb_bytes, lds_float *tile) {
-    const int lane = threadIdx.x;
-    constexpr int F = N >= WAVE ? WAVE : N;                  // features per pass; a narrower tile is done by the first lanes
-    for (int c = lane; c < W * N; c += WAVE) tile[c] = 0.f;
-    wave_sync();
-    auto add = [&](int row, int col, uint32_t value_bits) {
-        const uint16_t *src = reinterpret_cast<const uint16_t *>(Bp + (uint64_t)(uint32_t)col * ldb_bytes);
-        const float v = Elem<T>::word_val(value_bits);
-#pragma unroll
-        for (int c = 0; c < N; c += F)
-            if (F == WAVE || lane < F) tile[row * N + c + lane] = fmaf(v, Elem<T>::word_val(src[c + lane]), tile[row * N + c + lane]);
+// An Inf or NaN among staged rows must not meet the empty places of the A piece (0 * Inf = NaN).  What it gives where A does
+// have a nonzero is counted on the matrix cores instead: per product +Inf counts 1, -Inf 64 and NaN at least 4160, which is
+// the sum of two products of small numbers,
+//   positive value: (1, 0), negative: (0, 1), stored zero: (64, 64), no value: (0, 0)
+//   +Inf: (1, 64), -Inf: (64, 1), NaN: (8192, 8192), a number: (0, 0);
+// 32 products without a NaN give at most 32 * 64, exact in binary32.  The sums themselves take +-1 in place of the Inf or NaN:
+// nothing comes from empty places, and an infinite value of A keeps the sign of its product.
+template <class T>
+struct NonFinite {
+    static constexpr bool F16 = std::is_same<T, half_t>::value;
+    static constexpr uint32_t INF = F16 ? 0x7c00u : 0x7f80u;
+    // 1, 64 and 8192 in both halves of a word; two 16-bit numbers are handled at once
+    static constexpr uint32_t ONE = F16 ? 0x3c003c00u : 0x3f803f80u, P64 = F16 ? 0x54005400u : 0x42804280u, P8192 = F16 ? 0x70007000u : 0x46004600u;
+    static constexpr float NANS = 64.f * 65.f;
+    // per half: all ones if the sign bit is set; if the number without its sign is at least `least` (as bits)
+    __device__ static uint32_t spread(uint32_t x) {
+        typedef short short2_t __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, x) >> (short2_t)(short)15);
+    }
+    __device__ static uint32_t above(uint32_t w, uint32_t least) { return spread((w & 0x7fff7fffu) + (0x8000u - least) * 0x00010001u); }
+    struct Pair {                                   // of B
+        uint32_t w, infinite, nan, negative;
+        __device__ explicit Pair(uint32_t x) : w(x), infinite(above(x, INF)), nan(above(x, INF + 1u)), negative(spread(x)) { infinite &= ~nan; }
+        __device__ uint32_t finite() const { return (w & ~(infinite | nan)) | ((infinite | nan) & ((w & 0x80008000u) | ONE)); }
+        // what it counts for values of a sign
+        __device__ uint32_t for_positive() const { return (infinite & ((~negative & ONE) | (negative & P64))) | (nan & P8192); }
+        __device__ uint32_t for_negative() const { return (infinite & ((negative & ONE) | (~negative & P64))) | (nan & P8192); }
     };
+    // of A: what positive values count (`present`: the places that hold a value), and negative ones from that
+    __device__ static uint32_t weight(uint32_t w, uint32_t present) {
+        const uint32_t number = above(w, 1u);
+        return present & ((number & ~spread(w) & ONE) | (~number & P64));
+    }
+    __device__ static uint32_t other_sign(uint32_t weight, uint32_t w) { return weight ^ (above(w, 1u) & ONE); }
+    __device__ static float fold(float sum, float counts) {
+        const int c = (int)fminf(counts, NANS);
+        if (c & 63) sum += __builtin_huge_valf();
+        if (c >> 6) sum -= __builtin_huge_valf();
+        return counts >= NANS ? __builtin_nanf("") : sum;
+    }
+};
+
+// The sums of a task that met an Inf or NaN, once more: 32 rows at a time as in the kernel, one batch after the other.  Bound by
+// the chain of each 16 columns (LDS, some 100 vector instructions, three products), which go one after the other so that the
+// kernel needs no more registers than without this.  All of B Inf, default options: power-law N = 128 310 us (finite 65), community
+// N = 128 578 (263); one Inf, in the most referenced row: 135 and 267.  One nonzero at a time on the vector ALUs: 525, 2,060, 461
+// and 322.
+template <class T, int N>
+__device__ inline void spmm_careful_sums(const SpmmArgs &a, const DevTask &t, int nblk, int L, const char *Bp, uint32_t ldb_bytes, lds_byte *stage,
+                                         uint16_t *row_lds, uint16_t *val_lds, float4_t (&acc)[N / 16]) {
+    using S = GatherStage<N>;
+    typedef NonFinite<T> F;
+    typedef typename F::Pair Pair;
+    const int lane = threadIdx.x, g = lane >> 4, j = lane & 15;
+#pragma unroll
+    for (int n = 0; n < N / 16; ++n) acc[n] = float4_t{0.f, 0.f, 0.f, 0.f};
     const uint16_t *vals = reinterpret_cast<const uint16_t *>(a.dense_val);
-    for (int b = t.blk_begin; b < t.blk_begin + nblk; ++b) {
-        int at = a.blk_valptr[b];
-        for (int q = 0; q < 4; ++q)
-            for (uint64_t w = a.blk_bitmap[(int64_t)b * 4 + q]; w; w &= w - 1) {
-                const int bit = __builtin_ctzll(w);
-                add(4 * q + (bit >> 4), a.blk_cols[(int64_t)b * KB + (bit & 15)], vals[at++]);
+    const int pairs = piece_count(nblk, 2), batches = pairs + piece_count(L, 32);          // dense blocks, then residual nonzeros
+    for (int i = 0; i < batches; ++i) {
+        uint32_t v[4], present[4];                          // this lane's A elements, and all ones where there is one
+        if (i < pairs) {
+            const int col = a.blk_cols[(int64_t)(t.blk_begin + min(2 * i + (g & 1), nblk - 1)) * KB + j];
+            const int head = __builtin_amdgcn_ds_bpermute((lane & 48) * 4, col);
+            S::fetch(Bp, ldb_bytes, col >= 0 ? col : head, 0, 2 * KB, stage);
+            const int b = t.blk_begin + min(2 * i + (g >> 1), nblk - 1);
+            int at = a.blk_valptr[b];
+            const int q = j >> 2, shift = (j & 3) * 16 + 8 * (g & 1);
+            for (int k = 0; k < q; ++k) at += __popcll(a.blk_bitmap[(int64_t)b * 4 + k]);
+            const uint64_t w = a.blk_bitmap[(int64_t)b * 4 + q];
+            at += __popcll(w & ((1ull << shift) - 1ull));
+            const uint32_t set = 2 * i + (g >> 1) < nblk ? (uint32_t)(w >> shift) & 0xffu : 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = present[k] = 0;
+#pragma unroll
+                for (int e = 2 * k; e < 2 * k + 2; ++e)
+                    if (set >> e & 1u) {
+                        v[k] |= (uint32_t)vals[at++] << (e & 1) * 16;
+                        present[k] |= 0xffffu << (e & 1) * 16;
+                    }
             }
+        } else {
+            const int e0 = (i - pairs) * 32, n = min(32, L - e0);
+            uint32_t word;
+            uint16_t val;
+            load_blocked_entry(a.res_ent, (int64_t)(t.res_begin + e0 + min(lane, n - 1)), word, val);
+            S::fetch(Bp, ldb_bytes, (int)(word & RES_COL_MASK), 0, 32, stage);
+            row_lds[lane] = lane < n ? (uint16_t)(word >> RES_ROW_SHIFT) : (uint16_t)W;
+            val_lds[lane] = val;
+            wave_sync();
+            const uint4 rw = lds_read16((lds_byte *)row_lds + 16 * g), vw = lds_read16((lds_byte *)val_lds + 16 * g);
+            const uint32_t r[4] = {rw.x, rw.y, rw.z, rw.w}, x[4] = {vw.x, vw.y, vw.z, vw.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                present[k] = ~F::above(r[k] ^ (uint32_t)j * 0x00010001u, 1u);
+                v[k] = x[k] & present[k];
+            }
+        }
+        uint32_t weight[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) weight[k] = F::weight(v[k], present[k]);
+        wait_for_loads();
+#pragma unroll
+        for (int n = 0; n < N / 16; ++n) {
+            __builtin_amdgcn_sched_barrier(0);              // one after the other, so that the kernel needs no more registers for this
+            int l = lane;
+            asm volatile("" : "+v"(l));                   // the addresses are formed again, not kept
+            const uint4 op = S::operand(stage, 0, n, l >> 4, l & 15);
+            uint32_t b[4] = {op.x, op.y, op.z, op.w}, x[4], any = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const Pair p(b[k]);
+                x[k] = p.finite();
+                any |= p.infinite | p.nan;
+                asm volatile("" : "+v"(b[k]));              // nor are these
+            }
+            acc[n] = mfma_k32<T>(uint4{v[0], v[1], v[2], v[3]}, uint4{x[0], x[1], x[2], x[3]}, acc[n]);
+            if (__any(any != 0)) {
+                float4_t counts = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = Pair(b[k]).for_positive();
+                counts = mfma_k32<T>(uint4{weight[0], weight[1], weight[2], weight[3]}, uint4{x[0], x[1], x[2], x[3]}, counts);
+                uint32_t w[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    w[k] = F::other_sign(weight[k], v[k]);
+                    x[k] = Pair(b[k]).for_negative();
+                }
+                counts = mfma_k32<T>(uint4{w[0], w[1], w[2], w[3]}, uint4{x[0], x[1], x[2], x[3]}, counts);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[n][e] = F::fold(acc[n][e], counts[e]);
+            }
+        }
+        wait_for_lds();
     }
-    for (int i = 0; i < L; ++i) {
-        uint32_t word;
-        uint16_t val;
-        load_blocked_entry(a.res_ent, (int64_t)(t.res_begin + i), word, val);
-        add((int)(word >> RES_ROW_SHIFT), (int)(word & RES_COL_MASK), val);
-    }
-    wave_sync();
 }
 
 template <class T, int N>
@@ -427,20 +531,13 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     lds_float *tile = reinterpret_cast<lds_float *>(stage);
     float *cbase = Cp + (int64_t)t.id * W * a.ldc;
     // An Inf or NaN among the staged rows is in every row of the accumulators (0 * Inf = NaN): such a task (and one whose sums
-    // overflow) forms its sums again from its nonzeros alone.
+    // overflow) forms its sums again.
     float probe = 0.f;
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
         for (int e = 0; e < 4; ++e) probe = fmaf(acc[n][e], 0.f, probe);
-    if (__any(probe != probe)) {
-        spmm_exact_sums<T, N>(a, t, nblk, L, Bp, ldb_bytes, tile);
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[n][e] = tile[(4 * g + e) * N + 16 * n + j];
-        wait_for_lds();
-    }
+    if (__builtin_expect(__any(probe != probe), 0)) spmm_careful_sums<T, N>(a, t, nblk, L, Bp, ldb_bytes, stage, row_lds, val_lds, acc);
 
     // ---- the tile: accumulators to LDS (lane (g, j) holds rows 4g..4g+3, feature 16n + j), rows written once ----
     if (store_mask == 0 && (atomic_mask & (atomic_mask - 1u)) == 0) {
