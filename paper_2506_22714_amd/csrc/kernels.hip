@@ -1867,8 +1867,9 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     u.put(from_host ? (const void *)st->sd_res_base.data() : nullptr, nullptr, nblocks * 4, sd.dev.res_base);
     u.put(H(sd.res_row.data()), dd ? dd->res_row : nullptr, nrd * 4, sd.dev.res_row);
     // the residual list is ascending in CSR position: if it is the whole matrix, entry i is nonzero i
-    if ((int64_t)nrd == P->nnz) sd.dev.res_perm = nullptr;
-    else u.put(H(sd.res_perm.data()), dd ? dd->res_perm : nullptr, nrd * 4, sd.dev.res_perm);
+    if ((int64_t)nrd == P->nnz) {
+        if (st) sd.dev.res_perm = nullptr;      // the size pass writes nothing: another thread may be computing with the plan
+    } else u.put(H(sd.res_perm.data()), dd ? dd->res_perm : nullptr, nrd * 4, sd.dev.res_perm);
 }
 }  // namespace
 

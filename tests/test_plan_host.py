@@ -3,6 +3,8 @@ symbol the header declares, validates its input, and its planner output is
 bit-identical to the reference planner's."""
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -107,6 +109,32 @@ def test_compute_calls_without_device_copy_fail_cleanly():
         p2.export(1)
     assert e.value.code == lb.ERR["NOT_BUILT"]
     assert lb.libra_plan_device_bytes(p.handle) > 0
+
+
+READ_ONLY_PLAN = """
+import ctypes, mmap
+from paper_2506_22714_amd import binding as lb
+from paper_2506_22714_amd import workloads as wl
+L = lb.lib()
+p = lb.Plan.from_csr(wl.random_pattern(200, 150, 0.08, seed=1), mode=lb.MODE_SCALAR_ONLY)      # every nonzero is in the residual lists
+n, page = ctypes.c_size_t(), mmap.PAGESIZE
+start = p.handle.value // page * page
+assert p.handle.value - start < 64, "the plan does not start a mapping of its own"
+assert ctypes.CDLL(None).mprotect(ctypes.c_void_p(start), page, 1) == 0         # PROT_READ
+rc = L.libra_plan_device_bytes(p.handle, ctypes.byref(n))
+assert ctypes.CDLL(None).mprotect(ctypes.c_void_p(start), page, 3) == 0
+print(rc, n.value, flush=True)
+"""
+
+
+def test_asking_for_the_size_does_not_write_to_the_plan():
+    """libra_plan_device_bytes takes a const plan, which another thread may be computing with: the plan's memory (a mapping of its
+    own with a small malloc threshold) is read-only during the call."""
+    r = subprocess.run([sys.executable, "-c", READ_ONLY_PLAN], cwd=ROOT, env=dict(os.environ, MALLOC_MMAP_THRESHOLD_="512"),
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+    rc, n = r.stdout.split()
+    assert rc == "0" and int(n) > 0
 
 
 # ------------------------------------------------- plan == reference planner
