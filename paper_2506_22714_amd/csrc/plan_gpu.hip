@@ -1074,7 +1074,17 @@ struct Orderer {
     int colbits;
 
     static int bits_for(int64_t max_value) { int b = 1; while (b < 32 && (max_value >> b)) ++b; return b; }
-    template <class F, class... A> void run(F *k, int64_t n, A... a) { hipLaunchKernelGGL(k, dim3(blocks_for(n, 256)), dim3(256), 0, s, a...); }
+    template <class F, class... A> void launch(F *k, unsigned blocks, unsigned threads, A... a) {
+        hipLaunchKernelGGL(k, dim3(blocks), dim3(threads), 0, s, a...);
+        hip_ok(hipGetLastError());
+    }
+    template <class F, class... A> void run(F *k, int64_t n, A... a) { launch(k, blocks_for(n, 256), 256, a...); }
+    // numbers that come back from the device become launch sizes and indexes: they are not used out of their range
+    static void check(bool ok) { if (!ok) throw Fail{LIBRA_ERR_HIP}; }
+    static void check_queues(const int *start, int n) {
+        check(start[0] == 0 && start[XC] == n);
+        for (int x = 0; x < XC; ++x) check(start[x] <= start[x + 1]);
+    }
     template <class T> void scan_sum(const T *in, T *out, size_t n) {
         size_t sz = L.tmp_bytes;
         hip_ok(rocprim::exclusive_scan(L.tmp, sz, in, out, (T)0, n, rocprim::plus<T>(), s));
@@ -1140,11 +1150,13 @@ struct Orderer {
         begin[XC] = (int)table.size() / 3;
         if (begin[XC] > MAX_PIECES) throw Fail{LIBRA_ERR_HIP};
         hip_ok(hipMemcpyAsync(L.o.pieces, table.data(), table.size() * 4, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(k_order_fill, dim3(1), dim3(64), 0, s, L.o.meta + 32, 1, 0);
+        launch(k_order_fill, 1, 64, L.o.meta + 32, 1, 0);
         run(k_order_emit, slots, v, (const int32_t *)L.o.queue, (const int32_t *)L.o.pieces, make_int4(begin[0], begin[1], begin[2], begin[3]),
             make_int4(begin[4], begin[5], begin[6], begin[7]), begin[XC], make_int4(len[0], len[1], len[2], len[3]),
             make_int4(len[4], len[5], len[6], len[7]), slots, out, L.o.meta + 32);
-        return peek(L.o.meta + 32, s);          // also keeps `table` alive until it has been copied
+        const int end = peek(L.o.meta + 32, s);         // also keeps `table` alive until it has been copied
+        check(end >= 0 && end <= slots);
+        return end;
     }
     // Die-aware groups of `list` (place in the list breaks ties); `max_group` bounds the group numbers.
     int grouped(const int32_t *list, int n, int64_t max_group, int32_t *out) {
@@ -1158,6 +1170,7 @@ struct Orderer {
         scan_sum<u64>(o.wide_in, o.wide_out, (size_t)n + 1);
         run(k_order_firsts, n + 1, (const int32_t *)o.flag, (const int32_t *)o.scan, n, o.first);
         const int ng = peek(o.scan + n, s), rounds = (ng + XC - 1) / XC;
+        check(ng > 0 && ng <= n);
         run(k_order_group_costs, ng, (const u64 *)o.wide_out, (const int32_t *)o.first, ng, o.wide_in);
         int32_t *gord = reinterpret_cast<int32_t *>(o.key_in), *size = reinterpret_cast<int32_t *>(o.key_out);
         size_t sz = L.tmp_bytes;
@@ -1166,10 +1179,11 @@ struct Orderer {
         scan_sum<int32_t>(size, o.base, (size_t)rounds * XC + 1);
         run(k_order_group_items, n, (const int32_t *)o.ord2, (const int32_t *)o.flag, (const int32_t *)o.scan, (const int32_t *)o.first,
             (const int32_t *)o.rank, (const int32_t *)o.base, n, o.queue);
-        hipLaunchKernelGGL(k_order_queue_starts, dim3(1), dim3(64), 0, s, (const int32_t *)o.base, rounds, o.meta);
+        launch(k_order_queue_starts, 1, 64, (const int32_t *)o.base, rounds, o.meta);
         int start[XC + 1];
         hip_ok(hipMemcpyAsync(start, o.meta, sizeof start, hipMemcpyDeviceToHost, s));
         hip_ok(hipStreamSynchronize(s));
+        check_queues(start, n);
         return interleave(start, out);
     }
     // Segments by column; `list` is the whole SpMM table heaviest first, or the SDDMM segments in CSR order.
@@ -1179,6 +1193,7 @@ struct Orderer {
         run(k_order_by_column_flag, n + 1, v, list, col, n, o.flag);
         scan_sum<int32_t>(o.flag, o.scan, (size_t)n + 1);
         const int ns = peek(o.scan + n, s), no = n - ns;
+        check(ns >= 0 && ns <= n);
         if (ns < 8 * XC) return copy(list, n, out);
         int32_t *other = o.first, *placed = o.ord2, *sorted = o.base;
         uint32_t *other_cost = reinterpret_cast<uint32_t *>(o.rank);
@@ -1188,7 +1203,7 @@ struct Orderer {
         if (spmm) {
             run(k_order_item_costs, ns + 1, v, (const int32_t *)sorted, ns, o.wide_in);
             scan_sum<u64>(o.wide_in, o.wide_out, (size_t)ns + 1);
-            hipLaunchKernelGGL(k_order_fill, dim3(1), dim3(64), 0, s, o.meta, XC + 1, ns);
+            launch(k_order_fill, 1, 64, o.meta, XC + 1, ns);
             run(k_order_run_starts, ns, (const u64 *)o.wide_out, ns, o.meta);
             run(k_order_others_before, ns, v, (const int32_t *)sorted, (const u64 *)o.wide_out, ns, (const uint32_t *)other_cost, no, o.wide_in);
             size_t sz = L.tmp_bytes;
@@ -1207,6 +1222,7 @@ struct Orderer {
                 if (x < XC) before += (no - x + XC - 1) / XC;
             }
         }
+        check_queues(start, n);
         return interleave(start, out);
     }
 };
