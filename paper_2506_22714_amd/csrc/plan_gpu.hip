@@ -681,7 +681,8 @@ __device__ inline void put_task(libra_task_t *t, int kind, int id, int b0, int b
 
 // Per window: the hybrid load-balancing rule (Section 4.3).  FILL = false counts tasks, rows to clear and
 // residual nonzeros, a window per thread; FILL = true writes them at the offsets the prefix sums gave, a window per wave: a hub
-// window has thousands of tasks (GAT graph: 800 us with a thread per window, 221 with a wave).
+// window has thousands of tasks (GAT graph: 800 us with a thread per window, 221 with a wave).  A launch has fewer than 2^32
+// threads, so from 2^23 windows on a wave takes several.
 template <bool FILL>
 __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, const int32_t *rescan_a, int64_t M, int nw, Rule R,
                                                       const int32_t *blkptr_a, const int32_t *blkmask_a, const int32_t *blkncols_a,
@@ -690,85 +691,87 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
                                                       const int32_t *tbase_a, const int32_t *zbase, const int32_t *resptr, const int32_t *tbase_d,
                                                       libra_task_t *tasks_a, int32_t *zero_rows, libra_task_t *tasks_d) {
     constexpr int LANES = FILL ? 64 : 1;
-    const int t = blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
+    const int lane = threadIdx.x % LANES;
+    int t = blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES;
     if (!FILL && t == nw) { ntasks_a[nw] = 0; nzero[nw] = 0; nres[nw] = 0; ntasks_d[nw] = 0; }
-    if (t >= nw) return;
-    const int64_t r0 = (int64_t)t * W;
-    if (R.build_a) {
-        int n_short, n_long;
-        const WinRows z = window_rows(rowptr, rescan_a, M, t, R, &n_short, &n_long);
-        const int b0 = blkptr_a[t], b1 = blkptr_a[t + 1];
-        const bool many = b1 - b0 > R.Ts;
-        int nchunks = 0;
-        for (int r = 0; r < z.nr; ++r)
-            if ((z.split >> r) & 1u) nchunks += piece_count(z.rlen[r], R.Cs);
-        if (!FILL) {
-            const int nwt = many ? piece_count(b1 - b0, R.Ts) + (z.scalar ? 1 : 0) : 1;
-            ntasks_a[t] = nwt + nchunks;
-            nzero[t] = many ? z.nr : __popc(z.split);
-            nres[t] = z.q_unsplit + z.q_split;
-            if (n_short) atomicAdd(&ctr[C_SHORT], (u64)n_short);
-            if (n_long) atomicAdd(&ctr[C_LONG], (u64)n_long);
-            if (z.split) atomicAdd(&ctr[C_SPLIT], (u64)__popc(z.split));
-            if (nchunks) atomicAdd(&ctr[C_SEGMENTS], (u64)nchunks);
-        } else {
-            libra_task_t *out = tasks_a + tbase_a[t];
-            int32_t *zr = zero_rows + zbase[t];
-            const int q0 = resptr[t], q1 = q0 + z.q_unsplit;
-            auto touched = [&](int g0, int g1) { unsigned m = 0; for (int b = g0; b < g1; ++b) m |= (unsigned)blkmask_a[b]; return m; };
-            auto cols_in = [&](int g0, int g1) { unsigned c = 0; for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_a[b]; return c; };
-            if (many) {
-                const int groups = piece_count(b1 - b0, R.Ts);
-                for (int g = lane; g < groups; g += LANES) {
-                    const int g0 = b0 + g * R.Ts, g1 = piece_end(g0, b1, R.Ts);
-                    put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
-                }
-                out += groups;
-                if (z.scalar) {
-                    if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
+    for (; t < nw; t += gridDim.x * (blockDim.x / LANES)) {
+        const int64_t r0 = (int64_t)t * W;
+        if (R.build_a) {
+            int n_short, n_long;
+            const WinRows z = window_rows(rowptr, rescan_a, M, t, R, &n_short, &n_long);
+            const int b0 = blkptr_a[t], b1 = blkptr_a[t + 1];
+            const bool many = b1 - b0 > R.Ts;
+            int nchunks = 0;
+            for (int r = 0; r < z.nr; ++r)
+                if ((z.split >> r) & 1u) nchunks += piece_count(z.rlen[r], R.Cs);
+            if (!FILL) {
+                const int nwt = many ? piece_count(b1 - b0, R.Ts) + (z.scalar ? 1 : 0) : 1;
+                ntasks_a[t] = nwt + nchunks;
+                nzero[t] = many ? z.nr : __popc(z.split);
+                nres[t] = z.q_unsplit + z.q_split;
+                if (n_short) atomicAdd(&ctr[C_SHORT], (u64)n_short);
+                if (n_long) atomicAdd(&ctr[C_LONG], (u64)n_long);
+                if (z.split) atomicAdd(&ctr[C_SPLIT], (u64)__popc(z.split));
+                if (nchunks) atomicAdd(&ctr[C_SEGMENTS], (u64)nchunks);
+            } else {
+                libra_task_t *out = tasks_a + tbase_a[t];
+                int32_t *zr = zero_rows + zbase[t];
+                const int q0 = resptr[t], q1 = q0 + z.q_unsplit;
+                auto touched = [&](int g0, int g1) { unsigned m = 0; for (int b = g0; b < g1; ++b) m |= (unsigned)blkmask_a[b]; return m; };
+                auto cols_in = [&](int g0, int g1) { unsigned c = 0; for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_a[b]; return c; };
+                if (many) {
+                    const int groups = piece_count(b1 - b0, R.Ts);
+                    for (int g = lane; g < groups; g += LANES) {
+                        const int g0 = b0 + g * R.Ts, g1 = piece_end(g0, b1, R.Ts);
+                        put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
+                    }
+                    out += groups;
+                    if (z.scalar) {
+                        if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
+                        ++out;
+                    }
+                    if (lane == 0)
+                        for (int r = 0; r < z.nr; ++r) *zr++ = (int32_t)(r0 + r);
+                } else {
+                    if (lane == 0) {
+                        put_task(out, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched(b0, b1), z.valid & ~z.split,
+                                 cols_in(b0, b1) + (unsigned)(q1 - q0));
+                        for (int r = 0; r < z.nr; ++r)
+                            if ((z.split >> r) & 1u) *zr++ = (int32_t)(r0 + r);
+                    }
                     ++out;
                 }
-                if (lane == 0)
-                    for (int r = 0; r < z.nr; ++r) *zr++ = (int32_t)(r0 + r);
+                int q = q1;
+                for (int r = 0; r < z.nr; ++r) {
+                    if (!((z.split >> r) & 1u)) continue;
+                    const int n = piece_count(z.rlen[r], R.Cs), e = q + z.rlen[r];
+                    for (int k = lane; k < n; k += LANES) {
+                        const int qs = q + k * R.Cs, qe = piece_end(qs, e, R.Cs);
+                        put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
+                    }
+                    out += n;
+                    q = e;
+                }
+            }
+        } else if (!FILL) {
+            ntasks_a[t] = 0; nzero[t] = 0; nres[t] = 0;
+        }
+        if (R.build_d) {
+            const int b0 = blkptr_d[t], b1 = blkptr_d[t + 1];
+            if (!FILL) {
+                ntasks_d[t] = piece_count(b1 - b0, R.Ts_d);
             } else {
-                if (lane == 0) {
-                    put_task(out, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched(b0, b1), z.valid & ~z.split,
-                             cols_in(b0, b1) + (unsigned)(q1 - q0));
-                    for (int r = 0; r < z.nr; ++r)
-                        if ((z.split >> r) & 1u) *zr++ = (int32_t)(r0 + r);
+                libra_task_t *out = tasks_d + tbase_d[t];
+                for (int g = lane; g < piece_count(b1 - b0, R.Ts_d); g += LANES) {
+                    const int g0 = b0 + g * R.Ts_d, g1 = piece_end(g0, b1, R.Ts_d);
+                    unsigned c = 0;
+                    for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
+                    put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
                 }
-                ++out;
             }
-            int q = q1;
-            for (int r = 0; r < z.nr; ++r) {
-                if (!((z.split >> r) & 1u)) continue;
-                const int n = piece_count(z.rlen[r], R.Cs), e = q + z.rlen[r];
-                for (int k = lane; k < n; k += LANES) {
-                    const int qs = q + k * R.Cs, qe = piece_end(qs, e, R.Cs);
-                    put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
-                }
-                out += n;
-                q = e;
-            }
+        } else if (!FILL) {
+            ntasks_d[t] = 0;
         }
-    } else if (!FILL) {
-        ntasks_a[t] = 0; nzero[t] = 0; nres[t] = 0;
-    }
-    if (R.build_d) {
-        const int b0 = blkptr_d[t], b1 = blkptr_d[t + 1];
-        if (!FILL) {
-            ntasks_d[t] = piece_count(b1 - b0, R.Ts_d);
-        } else {
-            libra_task_t *out = tasks_d + tbase_d[t];
-            for (int g = lane; g < piece_count(b1 - b0, R.Ts_d); g += LANES) {
-                const int g0 = b0 + g * R.Ts_d, g1 = piece_end(g0, b1, R.Ts_d);
-                unsigned c = 0;
-                for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
-                put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
-            }
-        }
-    } else if (!FILL) {
-        ntasks_d[t] = 0;
     }
 }
 
@@ -1480,7 +1483,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         if (ntA < 0 || ntA > z.tasks_a_max || ntD < 0 || ntD > z.tasks_d_max || nz < 0 || nz > M || nresA < 0 || nresA > n || nresD < 0 ||
             nresD > n || dnnzA < 0 || dnnzA > n || dnnzD < 0 || dnnzD > n)
             throw Fail{LIBRA_ERR_HIP};
-        hipLaunchKernelGGL((k_window_tasks<true>), dim3(blocks_for(nw, 2)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
+        hipLaunchKernelGGL((k_window_tasks<true>), dim3(std::min(blocks_for(nw, 2), 1u << 22)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
                            L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);

@@ -368,3 +368,33 @@ def test_rows_of_large_matrices_are_checked_and_listed_on_the_device():
         with pytest.raises(lb.LibraError) as e:
             lb.Plan.from_device_csr(M, Kc, torch.from_numpy(rowptr).cuda(), col, val, resident=True, keep_host_copy=False)
         assert e.value.code == lb.ERR["ROWPTR"]
+
+
+@pytest.mark.parametrize("M,flags", [((1 << 27) + 1605, 0), ((1 << 30) + 37, lb.FLAG_NO_SPMM)])
+def test_more_windows_than_one_launch_has_waves(M, flags):
+    """A wave writes the tasks of a window; with more than 2^23 windows a wave takes several, and 2^30 rows at a wave per window
+    would be more threads than a launch can have.  A few rows with nonzeros among many empty ones, the last row among them."""
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs some 40 GiB")
+    nw = (M + 15) // 16
+    rows = np.unique(np.array([0, 5, 16 * 70, (1 << 27) - 1, 1 << 27, (1 << 27) + 1600, M // 2, M - 18, M - 1]))
+    rows = rows[rows < M]
+    per_row = 20
+    rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    for r in rows.tolist():
+        rowptr[r + 1:] += per_row
+    col = torch.arange(per_row, dtype=torch.int32, device="cuda").repeat(rows.size) * 3
+    val = torch.ones(col.numel(), dtype=torch.float16, device="cuda")
+    p = lb.Plan.from_device_csr(M, 64, rowptr, col, val, flags=flags | lb.FLAG_NATURAL_ORDER, sddmm_min_blk_nnz=16, sddmm_ts=1)
+    windows = np.unique(rows // 16)
+    tasks = p.export(1)["tasks"]                # blocks of 16 columns, the rest residual
+    dense = tasks[tasks["kind"] == lb.TASK_WINDOW]
+    assert np.array_equal(np.unique(dense["id"]), windows)
+    st = p.stats()
+    assert st["n_windows"] == nw and st["sddmm_dense_nnz"] + st["sddmm_res_nnz"] == st["nnz"] == per_row * rows.size
+    if not flags & lb.FLAG_NO_SPMM:
+        tasks = p.export(0)["tasks"]
+        assert np.array_equal(tasks["id"], np.arange(nw))
+        assert np.all(tasks["store_mask"][:-1] == 0xffff) and tasks["store_mask"][-1] == (1 << (M - 16 * (nw - 1))) - 1
+        assert np.array_equal(np.flatnonzero(tasks["res_end"] > tasks["res_begin"]), windows)
+    p.close()
