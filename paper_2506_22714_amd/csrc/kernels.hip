@@ -945,6 +945,7 @@ struct SddmmArgs {
     float *out;
     int64_t M;
     int32_t tasks_per_die;      // as in SpmmArgs
+    int32_t tasks_left;         // of a die, from `tasks` on
     int32_t pattern_only;       // nonzero: out_p = <X_i, Y_j>, A's values are not applied
 };
 
@@ -1292,7 +1293,7 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K ==
     __shared__ __attribute__((aligned(16))) unsigned char stage_all[WPB * STAGE];
     const unsigned wave = WPB == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const unsigned seq = (blockIdx.x >> 3) * WPB + wave;                // position in the die's part of the table
-    if (seq >= (unsigned)a.tasks_per_die) return;
+    if (seq >= (unsigned)a.tasks_left) return;
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + seq];
     lds_byte *stage = (lds_byte *)stage_all + wave * STAGE;
     if (DENSE && t.kind == LIBRA_TASK_WINDOW) {
@@ -1597,12 +1598,21 @@ __global__ __launch_bounds__(256) void scatter_blocked_values_kernel(const T *sr
 
 inline int hip_rc(hipError_t e) { return e == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP; }
 
+// A launch has fewer than 2^32 threads (one of more is cut short without an error): a table with a wave per task takes several
+// launches from LAUNCH_WAVES waves on.  In launches of whole rounds (a task of each die) the next one starts further into a.tasks.
+constexpr int64_t LAUNCH_WAVES = 1 << 25;
+
 template <class T, int N>
-int launch_spmm(const SpmmArgs &a, int64_t ntasks, hipStream_t s) {
-    if (ntasks == 0) return LIBRA_OK;
-    if constexpr (std::is_same<T, float>::value) hipLaunchKernelGGL((spmm_task_kernel_f32<N>), dim3((unsigned)(ntasks * a.pieces)), dim3(WAVE), 0, s, a);
-    else hipLaunchKernelGGL((spmm_gather_kernel<T, N>), dim3((unsigned)(ntasks * a.pieces)), dim3(WAVE), 0, s, a);
-    return hip_rc(hipGetLastError());
+int launch_spmm(const SpmmArgs &all, int64_t ntasks, hipStream_t s) {
+    SpmmArgs a = all;
+    const int64_t rounds = ntasks / LIBRA_XCDS, most = LAUNCH_WAVES / LIBRA_XCDS / a.pieces;
+    for (int64_t r = 0; r < rounds; r += most, a.tasks += most) {
+        const dim3 grid((unsigned)(std::min(most, rounds - r) * LIBRA_XCDS * a.pieces));
+        if constexpr (std::is_same<T, float>::value) hipLaunchKernelGGL((spmm_task_kernel_f32<N>), grid, dim3(WAVE), 0, s, a);
+        else hipLaunchKernelGGL((spmm_gather_kernel<T, N>), grid, dim3(WAVE), 0, s, a);
+        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
+    }
+    return LIBRA_OK;
 }
 
 int spmm_launch(const libra_plan_t *P, const SpmmArgs &a, int n, int64_t nt, hipStream_t s);
@@ -1914,10 +1924,12 @@ int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const De
             if (P->vdt == LIBRA_F32)
                 hipLaunchKernelGGL((pack_sddmm_values_kernel<uint32_t>), grid(sd.n.dense), dim3(256), 0, s, dd.dense_perm,
                                    (const uint32_t *)dd.dense_val, sd.n.dense, (SdPv *)sd.dev.dense_pv);
-            else if (sorted_records(P))       // reads the task table that layout() has just queued for copying on this stream
-                hipLaunchKernelGGL(pack_sddmm_sorted_records_kernel, dim3((unsigned)task_slots(sd.n.tasks)), dim3(WAVE), 0, s, sd.dev.tasks,
-                                   dd.blk_bitmap, dd.blk_valptr, dd.dense_perm, (const uint16_t *)dd.dense_val, (SdPv *)sd.dev.dense_pv);
-            else
+            else if (sorted_records(P)) {     // reads the task table that has just been queued for writing on this stream
+                const int64_t slots = (int64_t)task_slots(sd.n.tasks);
+                for (int64_t k = 0; k < slots; k += LAUNCH_WAVES)
+                    hipLaunchKernelGGL(pack_sddmm_sorted_records_kernel, dim3((unsigned)std::min(LAUNCH_WAVES, slots - k)), dim3(WAVE), 0, s, sd.dev.tasks + k,
+                                       dd.blk_bitmap, dd.blk_valptr, dd.dense_perm, (const uint16_t *)dd.dense_val, (SdPv *)sd.dev.dense_pv);
+            } else
                 hipLaunchKernelGGL((pack_sddmm_values_kernel<uint16_t>), grid(sd.n.dense), dim3(256), 0, s, dd.dense_perm,
                                    (const uint16_t *)dd.dense_val, sd.n.dense, (SdPv *)sd.dev.dense_pv);
         }
@@ -2012,13 +2024,14 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
     const SubPlan &sp = P->sddmm;
     SddmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr,
                 reinterpret_cast<const uint2 *>(sp.dev.dense_pv), (int32_t)sp.n.dense,
-                sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, out, P->M, 0, pattern_only};
+                sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, out, P->M, 0, 0, pattern_only};
     if (sp.n.tasks == 0) return LIBRA_OK;
-    a.tasks_per_die = (int32_t)((sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS);
+    a.tasks_per_die = a.tasks_left = (int32_t)((sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS);
+    constexpr int32_t most = LAUNCH_WAVES / LIBRA_XCDS;      // rounds of a launch: whole workgroups
     auto launch = [&](auto wpb, auto with_blocks) {
         constexpr int WPB = decltype(wpb)::value;
         constexpr bool DENSE = decltype(with_blocks)::value;
-        const dim3 grid((unsigned)((a.tasks_per_die + WPB - 1) / WPB * LIBRA_XCDS)), block(WAVE * WPB);
+        const dim3 grid((unsigned)((std::min(a.tasks_left, most) + WPB - 1) / WPB * LIBRA_XCDS)), block(WAVE * WPB);
         auto width = [&](auto tag) {
             typedef decltype(tag) T;
             switch (K) {
@@ -2035,9 +2048,11 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
         if (P->o.xcd_order == 1) launch(std::integral_constant<int, 4>{}, with_blocks);
         else launch(std::integral_constant<int, 1>{}, with_blocks);
     };
-    if (sp.n_window_tasks > 0) shape(std::true_type{});
-    else shape(std::false_type{});
-    if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
+    for (; a.tasks_left > 0; a.tasks += most, a.tasks_left -= most) {
+        if (sp.n_window_tasks > 0) shape(std::true_type{});
+        else shape(std::false_type{});
+        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
+    }
     return LIBRA_OK;
 }
 }  // namespace

@@ -398,3 +398,35 @@ def test_more_windows_than_one_launch_has_waves(M, flags):
         assert np.all(tasks["store_mask"][:-1] == 0xffff) and tasks["store_mask"][-1] == (1 << (M - 16 * (nw - 1))) - 1
         assert np.array_equal(np.flatnonzero(tasks["res_end"] > tasks["res_begin"]), windows)
     p.close()
+
+
+@pytest.mark.parametrize("flags", [lb.FLAG_XCD_ORDER, lb.FLAG_NATURAL_ORDER])
+def test_more_tasks_than_one_launch_has_waves(flags):
+    """A launch has fewer than 2^32 threads, i.e. 2^26 waves with a task each: tables of more tasks (segments of one nonzero) take
+    several launches.  Values and operands are whole numbers, so every order of additions gives the same sums."""
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs some 60 GiB")
+    M, deg, N = (1 << 20) + 5, 65, 32
+    nnz = M * deg
+    assert nnz > 1 << 26
+    rowptr = torch.arange(M + 1, dtype=torch.int32, device="cuda") * deg
+    first = torch.arange(M, dtype=torch.int32, device="cuda") % 128                # row i: 65 consecutive columns
+    col = (first[:, None] + torch.arange(deg, dtype=torch.int32, device="cuda")).reshape(-1)
+    val = torch.ones(nnz, dtype=torch.float16, device="cuda")
+    p = lb.Plan.from_device_csr(M, 192, rowptr, col, val, resident=True, keep_host_copy=False, mode=lb.MODE_SCALAR_ONLY, cs=1, sddmm_cs=1,
+                                flags=flags, ts=1 << 20, sddmm_ts=1 << 20)
+    st = p.stats()
+    assert st["spmm_tasks"] > 1 << 26 and st["sddmm_tasks"] > 1 << 26
+    gen = torch.Generator("cuda").manual_seed(1)
+    B = torch.randint(-3, 4, (192, N), device="cuda", generator=gen).half()
+    X = torch.randint(-3, 4, (M, N), device="cuda", generator=gen).half()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    p.spmm(B, out=C)
+    sums = torch.cat([torch.zeros((1, N), device="cuda"), B.float().cumsum(0)])
+    f = first.long()
+    assert torch.equal(C, sums[f + deg] - sums[f])
+    out = torch.full((nnz,), float("nan"), device="cuda")
+    p.sddmm(X, B, out=out)
+    want = (X.float() @ B.float().T).gather(1, col.reshape(M, deg).long())
+    assert torch.equal(out.reshape(M, deg), want)
+    p.close()
