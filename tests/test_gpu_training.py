@@ -56,6 +56,26 @@ def test_transposed_pattern_matches_the_definition():
     assert rp_t.cpu().tolist() == [0] * 7 and col_t.numel() == 0
 
 
+@pytest.mark.parametrize("M", [(1 << 28) + 37, (1 << 30) + 37])
+def test_transposed_pattern_of_more_rows_than_one_launch_has_waves(M):
+    """A wave lists 16 rows; from 2^28 rows on it takes several groups of them, and 2^30 rows at a wave per group would be more
+    threads than a launch can have.  A few rows with nonzeros, the last one among them."""
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs some 10 GiB")
+    rows = [0, 17, (1 << 28) - 1, 1 << 28, (1 << 28) + 36, M // 2, M - 2, M - 1]
+    rows = np.unique([r for r in rows if r < M])
+    rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    for k, r in enumerate(rows.tolist()):
+        rowptr[r + 1:] += 3
+    col = np.stack([np.arange(3) * 5 + k % 4 for k in range(rows.size)]).astype(np.int32).reshape(-1)
+    rp_t, col_t, perm_t = lb.transpose_csr(M, 16, rowptr, torch.from_numpy(col).cuda())
+    order = np.lexsort((np.arange(col.size), col))
+    assert np.array_equal(perm_t.cpu().numpy(), order)
+    assert np.array_equal(col_t.cpu().numpy(), np.repeat(rows, 3)[order])
+    assert np.array_equal(rp_t.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col, minlength=16))]))
+
+
+
 @pytest.mark.parametrize("K", [32, 128])
 def test_sddmm_without_values(K):
     A = graft(None)
