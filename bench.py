@@ -37,6 +37,16 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_measured.json")
 SOURCE_DIRS = (os.path.join(ROOT, "paper_2506_22714_amd", "csrc"), os.path.join(ROOT, "include"))
 
 
+# The kernels of a libra_spmm call: 16-bit storage, fp32 storage, and the one that clears rows with several writers.
+SPMM_TASK_KERNELS = ("spmm_gather_kernel", "spmm_task_kernel_f32")
+
+
+def spmm_kernel_name(dtype: str, N: int) -> str:
+    """The task kernel of an SpMM of N columns; wide operands are cut into pieces of 128 columns, the rest into powers of two."""
+    width = 1 << (min(N, 128).bit_length() - 1)
+    return f"spmm_task_kernel_f32<{width}>" if dtype == "f32" else f"spmm_gather_kernel<{dtype},{width}>"
+
+
 def source_digest() -> str:
     """sha256 over the library's sources (names and contents, sorted): what a traffic measurement is valid for."""
     import hashlib
@@ -94,7 +104,9 @@ def record_traffic(directory: str, key: str) -> int:
         cal_kib = max(cal.values())                                   # the copy kernel is the only large one in that run
         scale = copy_bytes / (cal_kib * 1024.0)
         run = _counter_means(os.path.join(directory, what), counter)
-        kib = sum(v for k, v in run.items() if "spmm_task_kernel" in k or "zero_rows_kernel" in k)
+        if not any(name in k for k in run for name in SPMM_TASK_KERNELS):
+            raise SystemExit(f"no SpMM task kernel ({', '.join(SPMM_TASK_KERNELS)}) in the {counter} run under {directory}")
+        kib = sum(v for k, v in run.items() if any(name in k for name in SPMM_TASK_KERNELS + ("zero_rows_kernel",)))
         entry[what + "_kib_raw"] = round(kib, 1)
         entry[what + "_scale"] = round(scale, 4)
         entry[what + "_bytes"] = int(kib * 1024.0 * scale)
@@ -358,7 +370,7 @@ def main() -> int:
         "config": {"workload": f"{args.workload}{'-small' if args.small else ''}: M={A.M} nnz={A.nnz} SpMM N={N} + SDDMM K={K}",
                    "M": A.M, "nnz": A.nnz, "N": N, "K": K, "mode": args.mode,
                    "options": "tuner table" if tuned else "library defaults"},
-        "roofline": {"bound": "hbm", "kernel": f"spmm_task_kernel<{args.dtype},{min(N, 256)}>", "achieved": round(achieved, 1),
+        "roofline": {"bound": "hbm", "kernel": spmm_kernel_name(args.dtype, N), "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "algorithmic_bytes": bytes_spmm, "avg_us": round(spmm_avg_s * 1e6, 2),
                      "frac_of_measured_copy": round(achieved / copy_gbs, 4), "measured_copy_GBs": round(copy_gbs, 1),
