@@ -187,8 +187,8 @@ int libra_plan(int64_t M, int64_t Kc, const int32_t *rowptr, const int32_t *col,
 
 /*
  * libra_plan_device - the same plan, bit for bit, built on the GPU from a CSR matrix that is already in device
- * memory (the paper's GPU-accelerated preprocessing, Section 4.5, Algorithm 1: per-window census by sorting,
- * prefix sums for every offset).  Only the kernels' shape is supported (window_rows = block_cols = 16).
+ * memory (the paper's GPU-accelerated preprocessing, Section 4.5, Algorithm 1: per-window census by merging the
+ * window's sorted rows, prefix sums for every offset).  Only the kernels' shape is supported (window_rows = block_cols = 16).
  *   d_rowptr, d_col, d_val   device, as in libra_plan; nnz must equal d_rowptr[M]
  *   workspace                device, 256-byte aligned, at least libra_plan_device_workspace() bytes; only used
  *                            during the call, the caller may free it afterwards
@@ -201,8 +201,9 @@ int libra_plan(int64_t M, int64_t Kc, const int32_t *rowptr, const int32_t *col,
  *                            libra_plan_export and libra_plan_upload work as for a host-built plan.  Zero (only
  *                            with plan_buf): they are not; those two calls then return LIBRA_ERR_NOT_BUILT.
  *   stream                   the passes are enqueued on it; the call synchronises it several times
- * The task tables always pass through the host: their order and the statistics are made by the same code as in
- * libra_plan.  A matrix without nonzeros needs no device pass.
+ * Task tables of 8,192 or more tasks (both operators together) are ordered on the GPU and come to the host only with
+ * keep_host_copy; smaller ones pass through the host and the code of libra_plan, which also forms the statistics.  The
+ * order is the same either way.  A matrix without nonzeros needs no device pass.
  * Errors: as libra_plan, plus UNSUPPORTED (window shape), BUFFER (workspace or plan buffer too small or
  * misaligned), HIP.
  */

@@ -146,16 +146,16 @@ template <> __device__ inline bf16_t to_storage<bf16_t>(float x) {
 
 // Workgroup b of a launch runs on die b mod 8, so the records of the tasks that one die runs are stored next to each
 // other: a 128-byte line of the table then serves four consecutive workgroups of one die instead of four dies.
-static_assert(LIBRA_XCDS == 8, "task_slot divides by the number of dies with a shift");
-__device__ inline int64_t task_slot(unsigned b, int per_die) { return (int64_t)(b & (LIBRA_XCDS - 1)) * per_die + (b >> 3); }
+constexpr unsigned DIE_SHIFT = 3;
+static_assert(LIBRA_XCDS == 1 << DIE_SHIFT, "workgroup b takes record (b mod dies) * tasks_per_die + b / dies");
 
 // ---------------------------------------------------------------------------------------
 // SpMM.  N = feature columns handled by this launch, T = storage type of values and B.
 //
 // A task is latency-bound unless few dependent memory round trips carry many row fetches, so
 // the kernel is organised around round trips: (1) the task record; (2) all the metadata of the
-// task at once - residual entries, block column ids, block bitmaps - staged in LDS; (3..) the
-// B-row fetches in large batches whose addresses come from LDS, never from another global load.
+// task at once - residual entries, block column ids, block bitmaps; (3..) the
+// B-row fetches in large batches whose addresses are at hand, never from another global load.
 // ---------------------------------------------------------------------------------------
 
 // Orders the LDS accesses of one wavefront (the hardware runs a wave's LDS instructions in order;
@@ -196,10 +196,12 @@ __device__ inline void wait_for_lds() {
 // A row's 16-byte pieces are fetched by consecutive lanes straight into LDS (no registers, no address per piece to keep), in
 // batches of ROWS rows; piece p of row r is kept at place p ^ 2 unit(r), so that the transposing reads of two lane groups
 // (eight rows, 32 bytes of each) touch all banks once.
-// Bound by the L2s: 128 channels of 64 bytes per clock are 18.7 TB/s, the power-law graph at N = 128 draws 6.5 M lines of 128
-// bytes from them (44 us at that rate).  Against fetching residual rows into registers and adding their products on the vector
-// ALUs (67 - 75 % busy with it; 24.7 -> 12.0 M wave instructions, power-law N = 128): power-law N = 32 / 64 / 128 44.7 / 43.7
-// / 65.5 -> 31.0 / 39.3 / 64.0 us, GAT graph N = 64 596 -> 555, irregular N = 32 1,888 -> 1,845, community N = 128 277 -> 268.
+// Bound by the way from the L2s to the L1s (the data return units are busy 78 % of the kernel on the power-law graph at N = 128, 97
+// % on the GAT graph): the power-law graph draws 6.5 M lines of 128 bytes, 39 us at the 21 TB/s of a bare gather that always hits;
+// a quarter of them miss.  The irregular graph is bound behind the L2s, by 94 M lines at 54 G lines per second.  Against fetching
+// residual rows into registers and adding their products on the vector ALUs (65 - 76 % busy with it, now 27 - 35 %; 24.7 -> 9.8 M
+// wave instructions, power-law N = 128): power-law N = 32 / 64 / 128 44.7 / 43.7 / 65.5 -> 31.0 / 39.3 / 64.0 us, GAT graph
+// N = 64 596 -> 555, irregular N = 32 1,888 -> 1,845, community N = 128 277 -> 268.
 // Two half-size stages in turn, 64 rows at N = 64 and seven or eight waves per SIMD at N <= 64 are each slower somewhere.
 template <int N>
 struct GatherStage {
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
 
     // workgroup b: die b mod 8, then the pieces of one task next to each other (they read the same plan data through
     // the same L2), then the die's next task
-    unsigned round = blockIdx.x >> 3, piece = 0;
+    unsigned round = blockIdx.x >> DIE_SHIFT, piece = 0;
     if (a.pieces > 1) {
         piece = round % (unsigned)a.pieces;
         round /= (unsigned)a.pieces;
@@ -631,7 +633,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
 
     // workgroup b: die b mod 8, then the pieces of one task next to each other (they read the same plan data through
     // the same L2), then the die's next task
-    const unsigned round = blockIdx.x >> 3, piece = round % (unsigned)a.pieces;
+    const unsigned round = blockIdx.x >> DIE_SHIFT, piece = round % (unsigned)a.pieces;
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + round / (unsigned)a.pieces];
     const char *Bp = reinterpret_cast<const char *>(a.B) + (size_t)piece * N * 4;
     float *Cp = a.C + (size_t)piece * N;
@@ -966,10 +968,9 @@ __device__ inline float group_sum(float s) {
 }
 
 // 16-bit rows of Y come through LDS: a row's consecutive pieces are fetched by consecutive lanes, so that the address unit
-// handles 64 bytes per access (operand-shaped loads touch four rows with every four lanes: 544 M instead of 184 M accesses
-// for the segments of the GAT graph at K = 64, 910 instead of 690 us; window tasks of the community matrix K = 64 / 128
-// 222 / 372 -> 201 / 328 us).  Piece c of row r is kept
-// at place c ^ swizzle(r), which spreads the pieces that 16 lanes read together over all banks.
+// handles 64 bytes per access, where operand-shaped loads touch four rows with every four lanes (window tasks of the community
+// matrix K = 64 / 128 222 / 372 -> 201 / 328 us; K = 32, blocks only: 65.0 -> 34.5 M accesses of the L1s).  Piece c of row r is
+// kept at place c ^ swizzle(r), which spreads the pieces that 16 lanes read together over all banks.
 template <int K>
 struct RowStage {
     static constexpr int ROW = 2 * K;                        // bytes of a row
@@ -1167,10 +1168,11 @@ struct SegmentEntry {
 // consecutive rows (nearly always) the A operand is those rows of X, fetched once and not once per nonzero, and the products
 // are the elements (row slot of j, j) of the tile; otherwise slot i of A is the row of nonzero i and the products are the
 // diagonal.  Nothing is widened or summed across lanes.
-// Bound by the address and data-return units of the L1s (96 % busy when every nonzero fetched its two rows with K/8 lanes and
-// the vector ALUs formed the dot product): X once per batch and 6 instead of 16 bytes per entry take that to one row of Y.
-// f16, against that version: GAT graph K = 64 772 -> 680 us (648 us with segments of 128), power-law K = 32 35.4 -> 27.3,
-// community K = 32 177 -> 146, irregular 1,905 -> 1,770 us.  Fetching the next batch's entries early: no change.
+// Bound by the data return units of the L1s (97 % busy on the GAT graph at K = 64, their address units 64 %).  When every nonzero
+// fetched its two rows with K/8 lanes and the vector ALUs formed the dot product it was 97 and 86 %: X once per batch and 6
+// instead of 16 bytes per entry halve the accesses (322 -> 172 M).  f16, against that version: GAT graph K = 64 772 -> 680 us
+// (648 us with segments of 128), power-law K = 32 35.4 -> 27.3, community K = 32 177 -> 146, irregular 1,905 -> 1,770 us (98 M
+// lines from behind the L2s, at the rate at which they come).  Fetching the next batch's entries early: no change.
 template <class T, int K>
 __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = RowStage<K>;
@@ -1292,7 +1294,7 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K ==
     constexpr int STAGE = F32 ? WAVE * 4 : PRODUCTS > ROWS ? PRODUCTS : ROWS;           // bytes per wave
     __shared__ __attribute__((aligned(16))) unsigned char stage_all[WPB * STAGE];
     const unsigned wave = WPB == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const unsigned seq = (blockIdx.x >> 3) * WPB + wave;                // position in the die's part of the table
+    const unsigned seq = (blockIdx.x >> DIE_SHIFT) * WPB + wave;                // position in the die's part of the table
     if (seq >= (unsigned)a.tasks_left) return;
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + seq];
     lds_byte *stage = (lds_byte *)stage_all + wave * STAGE;
@@ -1698,7 +1700,7 @@ struct Uploader {
 // Slots of the device task table: the table's length rounded up to whole rounds of the dies.
 size_t task_slots(int64_t ntasks) { return (size_t)((ntasks + LIBRA_XCDS - 1) / LIBRA_XCDS) * LIBRA_XCDS; }
 
-// Device task records, die by die (see task_slot); the slots past the last task hold empty tasks.
+// Device task records, die by die (see DIE_SHIFT); the slots past the last task hold empty tasks.
 std::vector<DevTask> pack_tasks(const libra_plan_t *P, const SubPlan &sp, bool spmm) {
     const size_t per_die = task_slots((int64_t)sp.tasks.size()) / LIBRA_XCDS;
     const DevTask empty{0, 0, 0, 0, 0, 0u, (uint32_t)(spmm ? LIBRA_TASK_WINDOW : LIBRA_TASK_CHUNK), 0};

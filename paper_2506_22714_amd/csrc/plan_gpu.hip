@@ -5,7 +5,8 @@
 // over arrays plus prefix sums:
 //
 //   1. the 16 sorted rows of a window are merged into (column, row) order in two passes in which
-//      every nonzero finds its place by searching the lists it is merged with, which puts the nonzeros of each column vector next to each other (the "census");
+//      every nonzero finds its place by searching the lists it is merged with, which puts the
+//      nonzeros of each column vector next to each other (the "census");
 //   2. head flags + a prefix sum number the vectors; a sort of those with more than one nonzero
 //      gives the (NNZ descending, column ascending) order - the order of the SDDMM blocks and of
 //      the vectors that fill the padding of the last SpMM block;
@@ -19,7 +20,8 @@
 //
 // Radix sorts and prefix sums are rocPRIM device primitives; everything else is written here.
 // The arrays are produced in the host planner's format in the caller's workspace, copied to the
-// plan's host vectors if a host copy is wanted; large task tables are ordered here, small ones by the host planner's tail.
+// plan's host vectors if a host copy is wanted; large task tables are ordered here, small ones
+// by the host planner's tail.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -41,8 +43,9 @@ namespace {
 constexpr int W = 16, KB = 16;
 typedef unsigned long long u64;
 
-// Matrices of fewer rows have rowptr checked and the rows of the edge softmax listed on the host, where a row costs 1.2 ns; here
-// the launches and the extra wait cost some 60 us (2^20 rows, plan and one step of the GAT graph: 13.15 -> 12.05 ms).
+// Matrices of fewer rows have rowptr checked and the rows of the edge softmax listed on the host; here the launches and the extra
+// wait cost some 80 us.  A plan of 8 nonzeros per row, host / here: 2^14 rows 585 / 665 us, 2^16 745 / 780, 98,304 813 / 820, 2^17
+// level; 2^20 rows (plan and one step of the GAT graph) 13.15 / 12.05 ms.
 constexpr int64_t DEVICE_ROWS_MIN = 1 << 17;
 
 enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_COUNT };
@@ -1014,7 +1017,7 @@ __global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *q
     const u64 used = __ballot(item >= 0 && !v.empty(item));
     if (used && (int)(threadIdx.x & 63) == 63 - __builtin_clzll(used) && __hip_atomic_load(last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= i) atomicMax(last, i + 1);
 }
-// Device task records, die by die (see task_slot in the kernels); slots past the table's end and -1 hold empty tasks.
+// Device task records, die by die (as the host packs them); slots past the table's end and -1 hold empty tasks.
 __global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t *order, int n, int per_die, const int32_t *blk_valptr, int empty_kind, DevTask *out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= per_die * XC) return;
@@ -1505,7 +1508,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         P->stats.device_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         mark("blocks, residual, tasks");
 
-        // ---- sizes; the task tables always come to the host (their order is made there); the big arrays only on request ----
+        // ---- sizes; small task tables come to the host, which orders them; large ones and the big arrays only on request ----
         SubPlan &sa = P->spmm, &sd = P->sddmm;
         const int nts[2] = {ntA, ntD}, nres2[2] = {nresA, nresD}, dn[2] = {dnnzA, dnnzD};
         SubPlan *hs[2] = {&sa, &sd};
