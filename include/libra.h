@@ -6,7 +6,8 @@
  *     column that holds a nonzero is an m x 1 nonzero column vector, and
  *     vectors are condensed k at a time into dense blocks.
  *   - Section 4.2 (Eq. 2-6): nonzeros are split between a matrix-unit path
- *     (here MFMA) and a scalar path (here VALU) by data reuse and utilisation.
+ *     (here MFMA) and a scalar path (here the VALU for fp32 storage; for 16-bit storage one row of the operand per
+ *     nonzero, also through MFMA tiles) by data reuse and utilisation.
  *   - Section 4.3: heavy windows and long rows are decomposed into bounded
  *     segments; decomposed segments accumulate with atomics.
  *   - Section 4.4: bitmap-encoded dense blocks decoded in registers, popcount
@@ -54,8 +55,8 @@ extern "C" {
 #define LIBRA_ERR_NOMEM         -14   /* host allocation failed */
 
 /* ---- value types (storage type of A's values and of the dense operands) ---- */
-#define LIBRA_F16   0    /* IEEE binary16 in, fp32 accumulate (MFMA + VALU) */
-#define LIBRA_BF16  1    /* bfloat16 in, fp32 accumulate (MFMA + VALU); beside the paper's FP16 / TF32 inputs (Section 4.4) */
+#define LIBRA_F16   0    /* IEEE binary16 in, fp32 accumulate (MFMA) */
+#define LIBRA_BF16  1    /* bfloat16 in, fp32 accumulate (MFMA); beside the paper's FP16 / TF32 inputs (Section 4.4) */
 #define LIBRA_F32   2    /* binary32 in, fp32 accumulate (MFMA 16x16x4 f32 + VALU): the paper's TF32 & FP32 mode with unrounded inputs */
 
 /* ---- distribution modes (Section 5.3.2: matrix-unit-only, scalar-only, hybrid) ---- */
@@ -79,8 +80,8 @@ extern "C" {
                                            die fetches dense-operand rows of one column range only and its L2 holds eight
                                            times as many distinct hot rows; the flat SDDMM segments that lie inside one row are
                                            placed the same way */
-#define LIBRA_FLAG_TWO_KERNELS    128u  /* libra_spmm runs the task table twice on the stream: first the dense blocks (MFMA), then the
-                                           residual nonzeros (VALU), which add to what the first launch wrote - the paper's
+#define LIBRA_FLAG_TWO_KERNELS    128u  /* libra_spmm runs the task table twice on the stream: first the dense blocks, then the
+                                           residual nonzeros, which add to what the first launch wrote - the paper's
                                            sequential schedule of its two kernels (Section 4.4.1).  Same results up to the order
                                            of additions; for debugging and as the baseline the fused task is measured against */
 

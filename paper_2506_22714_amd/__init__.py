@@ -1,5 +1,5 @@
 """MI355X-native SpMM / SDDMM with a 2D-aware split between an MFMA dense-tile
-path and a VALU scalar path (after arXiv 2506.22714, "Libra").
+path and a per-nonzero path (after arXiv 2506.22714, "Libra").
 
 The work is done by a C-ABI shared library built from ``csrc/`` (see
 ``include/libra.h``); :mod:`.binding` marshals arguments to it and nothing else.

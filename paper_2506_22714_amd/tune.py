@@ -56,8 +56,8 @@ ABLATION = [
     ("window order instead of heaviest first", dict(flags=8)),
     ("heaviest first, nothing die-aware", dict(flags=32 | 256)),
     ("padding slots not filled", dict(flags=1)),
-    ("matrix cores only", dict(mode=1)),
-    ("vector ALUs only", dict(mode=2)),
+    ("dense blocks only", dict(mode=1)),
+    ("residual nonzeros only", dict(mode=2)),
 ]
 
 
