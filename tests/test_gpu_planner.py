@@ -280,7 +280,7 @@ ORDER_CASES = [
     dict(cs=8, sddmm_cs=8, flags=lb.FLAG_NO_XCD_ORDER),
     dict(cs=8, sddmm_cs=8, flags=lb.FLAG_SEGMENTS_BY_COST),
     dict(cs=8, sddmm_cs=8, flags=lb.FLAG_NATURAL_ORDER),
-    dict(cs=4, flags=lb.FLAG_NO_SDDMM),
+    dict(cs=4, ts=1, flags=lb.FLAG_NO_SDDMM),
     dict(sddmm_cs=4, flags=lb.FLAG_NO_SPMM | lb.FLAG_XCD_ORDER),
     dict(mode=lb.MODE_SCALAR_ONLY, cs=1, sddmm_cs=1),
 ]
@@ -291,7 +291,7 @@ def test_large_task_tables_are_ordered_like_on_the_host(name):
     """Tables of more than 8192 tasks are ordered on the GPU: the same tables as the host's, and a plan whose records never
     were on the host computes what an uploaded one does."""
     A = {"rmat": lambda: wl.rmat(scale=13, avg_degree=16, seed=3),
-         "community": lambda: wl.community(n_blocks=400, seed=2),                  # the die-aware order fires
+         "community": lambda: wl.community(n_blocks=500, seed=2),                  # the die-aware order fires
          "short_rows": lambda: wl.random_pattern(140_003, 300, 0.004, seed=4, empty_rows=0.3),   # no segments
          # windows whose rows are all decomposed: empty tasks of cost 0 at the table's end
          "hub_windows": lambda: wl.with_long_rows(wl.random_pattern(20_000, 2000, 0.003, seed=7), list(range(64, 96)) + [7], 1500, seed=8)}[name]()
@@ -302,6 +302,7 @@ def test_large_task_tables_are_ordered_like_on_the_host(name):
         print(name, A.nnz, kw, flush=True)
         fl = kw.get("flags", 0)
         ph, pd = lb.Plan.from_csr(A, val=ones, **kw), device_plan(A, val=ones, **kw)
+        assert ph.stats()["spmm_tasks"] + ph.stats()["sddmm_tasks"] > 8192 + 100      # beside the few empty tasks of the die-aware order
         assert_same_plan(ph, pd, fl)
         pd.close()
         ph.upload()
