@@ -919,13 +919,17 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     }
 }
 
-// Clear the rows that several tasks accumulate into.
+// Clear the rows that several tasks accumulate into, n4 16-byte pieces each (at most 512 columns): CLEAR_ROWS rows per workgroup.
+// Once per call and not per column piece: some 5 us each, most of it the launch (power-law graph of 200,003 rows, N = 256 200.8 ->
+// 198.8 us; 4, 16 or 32 rows per workgroup are level).
+constexpr int CLEAR_ROWS = 8;
 __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *rows, int64_t nrows, float *C, int64_t ldc, int n4) {
-    const int64_t total = nrows * n4;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / n4;
-        const int c4 = (int)(i - r * n4);
-        *reinterpret_cast<float4_t *>(C + (int64_t)rows[r] * ldc + c4 * 4) = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int64_t r0 = (int64_t)blockIdx.x * CLEAR_ROWS; r0 < nrows; r0 += (int64_t)gridDim.x * CLEAR_ROWS) {
+        const unsigned pieces = (unsigned)min((int64_t)CLEAR_ROWS, nrows - r0) * (unsigned)n4;
+        for (unsigned i = threadIdx.x; i < pieces; i += 256) {
+            const unsigned r = i / (unsigned)n4, c4 = i - r * (unsigned)n4;
+            *reinterpret_cast<float4_t *>(C + (int64_t)rows[r0 + r] * ldc + c4 * 4) = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
     }
 }
 
@@ -1625,13 +1629,6 @@ int spmm_piece(const libra_plan_t *P, const void *B, int n, int pieces, int64_t 
     const int64_t per_die = (sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS;
     SpmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr, sp.dev.dense_val,
                sp.dev.res_ent, B, C, ldb, ldc, (int32_t)per_die, pieces, 0};
-    if (sp.n.zero_rows) {
-        const int n4 = n * pieces / 4;
-        const int64_t total = sp.n.zero_rows * n4;
-        const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
-        hipLaunchKernelGGL(zero_rows_kernel, dim3(blocks), dim3(256), 0, s, sp.dev.zero_rows, sp.n.zero_rows, C, ldc, n4);
-        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
-    }
     const int64_t nt = per_die * LIBRA_XCDS;         // every slot of the table (the last few may hold empty tasks)
     if (P->o.two_kernels && a.phase == 0) {
         // ablation / debugging schedule: the matrix-unit part and the scalar part as two launches on the stream
@@ -1986,6 +1983,11 @@ extern "C" int libra_spmm(const libra_plan_t *P, const void *B, int32_t N, int64
     if (((uintptr_t)B & 15) || ((uintptr_t)C & 15)) return LIBRA_ERR_BUFFER;
     hipStream_t s = (hipStream_t)stream;
     const int esz = P->vsize;
+    if (const int64_t nz = P->spmm.n.zero_rows) {
+        const unsigned blocks = (unsigned)std::min<int64_t>((nz + CLEAR_ROWS - 1) / CLEAR_ROWS, 1 << 16);
+        hipLaunchKernelGGL(zero_rows_kernel, dim3(blocks), dim3(256), 0, s, P->spmm.dev.zero_rows, nz, C, ldc, N / 4);
+        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
+    }
     // the feature dimension is cut into pieces the kernels are instantiated for; at most 128 columns, the widest
     // piece whose tile leaves four waves per SIMD (a 256-column piece ran at two and took 2.5x the time of a 128-column one)
     for (int n0 = 0; n0 < N;) {
