@@ -258,6 +258,18 @@ int libra_spmm(const libra_plan_t *plan, const void *B, int32_t N, int64_t ldb,
                float *C, int64_t ldc, void *stream);
 
 /*
+ * libra_spmm_rounded - libra_spmm with the result in the plan's value type (16-bit plans): every element is the fp32 sum of
+ * libra_spmm rounded once to nearest even.  What a training step that keeps its gradients in 16 bits asks for: the fp32 matrix is
+ * neither written nor read again, but for the rows with several writers.
+ *   R        device, M x N row-major in the plan's value type with row stride ldr (ldr >= N, ldr % 8 == 0); fully overwritten
+ *   scratch  device, M x N fp32 with row stride lds (as C of libra_spmm; none of B, R); its contents afterwards mean nothing.
+ *            May be NULL if no row has several writers (spmm_zero_rows = 0 in the statistics) and the plan is not in two-kernel mode
+ * Errors: as libra_spmm; DTYPE for an fp32 plan.
+ */
+int libra_spmm_rounded(const libra_plan_t *plan, const void *B, int32_t N, int64_t ldb,
+                       void *R, int64_t ldr, float *scratch, int64_t lds, void *stream);
+
+/*
  * libra_sddmm - out[p] = val[p] * <X[i,:], Y[col[p],:]> for every nonzero p of row i (Section 2.2; Eq. 4).
  *   X    device, M x K row-major, contiguous, plan's value type
  *   Y    device, Kc x K row-major, contiguous, plan's value type

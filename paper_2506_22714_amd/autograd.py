@@ -54,7 +54,7 @@ class _SpMM(torch.autograd.Function):
         dvals = dB = None
         if ctx.needs_input_grad[2]:
             sm.plan_t.set_values(vals.detach()[sm.perm_t].contiguous(), lb.OP_SPMM)
-            dB = sm.plan_t.spmm(dC16).to(B.dtype)
+            dB = sm.plan_t.spmm_rounded(dC16).to(B.dtype)
         if ctx.needs_input_grad[1]:
             if not _feature_ok(B.shape[1]):
                 raise RuntimeError("gradient with respect to the sparse values needs N in {32, 64, 128}")
@@ -79,10 +79,10 @@ class _SDDMM(torch.autograd.Function):
         dvals = dX = dY = None
         if ctx.needs_input_grad[2]:
             sm.plan.set_values(g, lb.OP_SPMM)
-            dX = sm.plan.spmm(Yc).to(X.dtype)
+            dX = sm.plan.spmm_rounded(Yc).to(X.dtype)
         if ctx.needs_input_grad[3]:
             sm.plan_t.set_values(g[sm.perm_t].contiguous(), lb.OP_SPMM)
-            dY = sm.plan_t.spmm(Xc).to(Y.dtype)
+            dY = sm.plan_t.spmm_rounded(Xc).to(Y.dtype)
         if ctx.needs_input_grad[1]:
             dvals = (dout * sm.plan.sddmm(Xc, Yc, pattern_only=True)).to(vals.dtype)
         return None, dvals, dX, dY

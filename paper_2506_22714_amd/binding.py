@@ -102,6 +102,7 @@ def lib() -> C.CDLL:
         L.libra_plan_device_bytes.argtypes = [vp, C.POINTER(sz)]
         L.libra_plan_upload.argtypes = [vp, vp, sz, vp]
         L.libra_spmm.argtypes = [vp, vp, i32, i64, vp, i64, vp]
+        L.libra_spmm_rounded.argtypes = [vp, vp, i32, i64, vp, i64, vp, i64, vp]
         L.libra_sddmm.argtypes = [vp, vp, vp, i32, vp, vp]
         L.libra_sddmm_pattern.argtypes = [vp, vp, vp, i32, vp, vp]
         L.libra_edge_softmax.argtypes = [vp, vp, C.c_float, vp, C.c_int, vp]
@@ -205,6 +206,11 @@ def libra_plan_upload(plan, dev_ptr: int, nbytes: int, stream: int = 0):
 
 def libra_spmm(plan, B_ptr: int, N: int, ldb: int, C_ptr: int, ldc: int, stream: int = 0):
     _check(lib().libra_spmm(plan, C.c_void_p(B_ptr), N, ldb, C.c_void_p(C_ptr), ldc, C.c_void_p(stream)), "libra_spmm")
+
+
+def libra_spmm_rounded(plan, B_ptr: int, N: int, ldb: int, R_ptr: int, ldr: int, scratch_ptr: int, lds: int, stream: int = 0):
+    _check(lib().libra_spmm_rounded(plan, C.c_void_p(B_ptr), N, ldb, C.c_void_p(R_ptr), ldr, C.c_void_p(scratch_ptr), lds, C.c_void_p(stream)),
+           "libra_spmm_rounded")
 
 
 def libra_sddmm(plan, X_ptr: int, Y_ptr: int, K: int, out_ptr: int, stream: int = 0):
@@ -371,7 +377,7 @@ class Plan:
         opts = _with_tuned(opts, tuned, self.val_dtype, N, K)
         self.handle = libra_plan(self.M, self.Kc, rowptr, col, val, PlanOpts(**opts) if opts else None,
                                  val_dtype=self.val_dtype)
-        self.nnz = libra_plan_stats(self.handle)["nnz"]
+        self._facts(opts)
         self._buf = None
 
     @classmethod
@@ -405,8 +411,14 @@ class Plan:
                                         self._buf.data_ptr() if resident else 0, self._buf.numel() if resident else 0,
                                         keep_host_copy or not resident, torch.cuda.current_stream().cuda_stream)
         del ws
-        self.nnz = libra_plan_stats(self.handle)["nnz"]
+        self._facts(opts)
         return self
+
+    def _facts(self, opts):
+        stats = libra_plan_stats(self.handle)
+        self.nnz = stats["nnz"]
+        # rows that a call with rounded results sums up in fp32 memory: those with several writers, all of them in two-kernel mode
+        self._fp32_rows = stats["spmm_zero_rows"] > 0 or bool(opts.get("flags", 0) & FLAG_TWO_KERNELS)
 
     @classmethod
     def from_csr(cls, csr, val=None, val_dtype: int | None = None, tuned=None, N: int | None = None, K: int | None = None, **opts):
@@ -481,6 +493,19 @@ class Plan:
             raise ValueError("out: on another device than B")
         libra_spmm(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), out.stride(0),
                    torch.cuda.current_stream().cuda_stream)
+        return out
+
+    def spmm_rounded(self, B):
+        """``spmm(B)`` in the plan's value type: the fp32 sums rounded once."""
+        import torch
+        if self.val_dtype == F32:
+            return self.spmm(B)
+        self._operand(B, "B", self._torch_dtype(), shape=(self.Kc, None), rows_contiguous=True)
+        N = int(B.shape[1])
+        out = torch.empty((self.M, N), dtype=B.dtype, device=B.device)
+        scratch = torch.empty((self.M, N), dtype=torch.float32, device=B.device) if self._fp32_rows else None
+        libra_spmm_rounded(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), N, scratch.data_ptr() if scratch is not None else 0, N,
+                           torch.cuda.current_stream().cuda_stream)
         return out
 
     def sddmm(self, X, Y, out=None, pattern_only: bool = False):

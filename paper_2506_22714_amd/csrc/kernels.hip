@@ -61,6 +61,8 @@ struct SpmmArgs {
     int32_t tasks_per_die;  // the table holds die k's tasks (dispatch positions k, k + 8, ...) contiguously from k * tasks_per_die on
     int32_t pieces;         // the launch covers `pieces` adjacent column pieces of N features each: every task runs once per piece
     int32_t phase;          // 0: a task does all its work; 1: dense blocks only; 2: residual nonzeros only, added to what phase 1 wrote
+    void *R;                // kernels with rounded output: where a row with one writer goes, in the storage type (phase 0 only)
+    int64_t ldr;
 };
 
 // Per storage type: a residual entry's value as it is stored and as a number.
@@ -142,6 +144,20 @@ template <> __device__ inline bf16_t to_storage<bf16_t>(float x) {
     if ((u & 0x7fffffffu) > 0x7f800000u) return bf16_t{(uint16_t)((u >> 16) | 0x40u)};      // NaN stays NaN
     u += 0x7fffu + ((u >> 16) & 1u);
     return bf16_t{(uint16_t)(u >> 16)};
+}
+
+template <class T>
+__device__ inline uint4 round8(const float4_t &lo, const float4_t &hi) {
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const T a = to_storage<T>(k < 2 ? lo[2 * k] : hi[2 * k - 4]), b = to_storage<T>(k < 2 ? lo[2 * k + 1] : hi[2 * k - 3]);
+        uint16_t x, y;
+        __builtin_memcpy(&x, &a, 2);
+        __builtin_memcpy(&y, &b, 2);
+        w[k] = (uint32_t)x | (uint32_t)y << 16;
+    }
+    return uint4{w[0], w[1], w[2], w[3]};
 }
 
 // Workgroup b of a launch runs on die b mod 8, so the records of the tasks that one die runs are stored next to each
@@ -395,7 +411,11 @@ __device__ inline void spmm_careful_sums(const SpmmArgs &a, const DevTask &t, in
     }
 }
 
-template <class T, int N>
+// ROUNDED: a row with one writer leaves in the storage type, rounded once from its fp32 sums, instead of as an fp32 row of C that
+// another pass reads and rounds (a write of 4, a read of 4 and a write of 2 bytes per element become the last one).  A training
+// step with attention on a power-law graph of 500,009 rows, bf16, N = K = 64, three such products: 1,697 -> 1,573 us; with fixed
+// weights on an irregular graph of 300,007 rows, fp16, N = 128, one: 940 -> 897 us.
+template <class T, int N, bool ROUNDED>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ? 5 : 6))) void spmm_gather_kernel(SpmmArgs a) {
     using S = GatherStage<N>;
     constexpr int NT = N / 16;
@@ -572,7 +592,22 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
     const int rr = lane / LPF, cl = lane % LPF;
     float *dst = cbase + (int64_t)rr * a.ldc + cl * 4;
     const int64_t step = RPP * a.ldc;
-    if (atomic_mask == 0 && !add_to_c) {
+    if constexpr (ROUNDED) {
+        // eight values of a row per lane; rows with other writers are added to C below and rounded when they are whole
+        constexpr int LPR = N / 8, RPR = WAVE / LPR;
+        const int r0 = lane / LPR, c = lane % LPR * 8;
+        T *rdst = reinterpret_cast<T *>(a.R) + (int64_t)piece * N + ((int64_t)t.id * W + r0) * a.ldr + c;
+#pragma unroll
+        for (int k = 0; k < W / RPR; ++k, rdst += RPR * a.ldr) {
+            if (!(store_mask >> (k * RPR + r0) & 1u)) continue;
+            const lds_float *src = &tile[at(k * RPR + r0, c)];
+            const float4_t lo = *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(src);
+            const float4_t hi = *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(src + 4);
+            *reinterpret_cast<uint4 *>(rdst) = round8<T>(lo, hi);
+        }
+        if (atomic_mask == 0) return;
+    }
+    if (!ROUNDED && atomic_mask == 0 && !add_to_c) {
         // streaming stores: C is written once and not read again by this call
         float4_t x[W / RPP];
 #pragma unroll
@@ -587,7 +622,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(N >= 128 ?
 #pragma unroll
     for (int k = 0; k < W / RPP; ++k, dst += step) {
         const int r = k * RPP + rr;
-        if (store_mask >> r & 1u) {
+        if (!ROUNDED && (store_mask >> r & 1u)) {
             float4_t x = *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(&tile[at(r, cl * 4)]);
             if (add_to_c) {           // stream order: phase 1 has written the row
                 const float4_t y = *reinterpret_cast<const float4_t *>(dst);
@@ -929,6 +964,20 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *rows, int
         for (unsigned i = threadIdx.x; i < pieces; i += 256) {
             const unsigned r = i / (unsigned)n4, c4 = i - r * (unsigned)n4;
             *reinterpret_cast<float4_t *>(C + (int64_t)rows[r0 + r] * ldc + c4 * 4) = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+}
+
+// fp32 rows of C to the storage type: the listed rows, or all of them (rows = nullptr); n8 groups of eight values each.
+template <class T>
+__global__ __launch_bounds__(256) void round_rows_kernel(const int32_t *rows, int64_t nrows, const float *C, int64_t ldc, T *R, int64_t ldr, int n8) {
+    for (int64_t r0 = (int64_t)blockIdx.x * CLEAR_ROWS; r0 < nrows; r0 += (int64_t)gridDim.x * CLEAR_ROWS) {
+        const unsigned groups = (unsigned)min((int64_t)CLEAR_ROWS, nrows - r0) * (unsigned)n8;
+        for (unsigned i = threadIdx.x; i < groups; i += 256) {
+            const unsigned k = i / (unsigned)n8, c = (i - k * (unsigned)n8) * 8u;
+            const int64_t r = rows ? (int64_t)rows[r0 + k] : r0 + k;
+            const float4_t *src = reinterpret_cast<const float4_t *>(C + r * ldc + c);
+            *reinterpret_cast<uint4 *>(R + r * ldr + c) = round8<T>(src[0], src[1]);
         }
     }
 }
@@ -1608,14 +1657,14 @@ inline int hip_rc(hipError_t e) { return e == hipSuccess ? LIBRA_OK : LIBRA_ERR_
 // launches from LAUNCH_WAVES waves on.  In launches of whole rounds (a task of each die) the next one starts further into a.tasks.
 constexpr int64_t LAUNCH_WAVES = 1 << 25;
 
-template <class T, int N>
+template <class T, int N, bool ROUNDED = false>
 int launch_spmm(const SpmmArgs &all, int64_t ntasks, hipStream_t s) {
     SpmmArgs a = all;
     const int64_t rounds = ntasks / LIBRA_XCDS, most = LAUNCH_WAVES / LIBRA_XCDS / a.pieces;
     for (int64_t r = 0; r < rounds; r += most, a.tasks += most) {
         const dim3 grid((unsigned)(std::min(most, rounds - r) * LIBRA_XCDS * a.pieces));
         if constexpr (std::is_same<T, float>::value) hipLaunchKernelGGL((spmm_task_kernel_f32<N>), grid, dim3(WAVE), 0, s, a);
-        else hipLaunchKernelGGL((spmm_gather_kernel<T, N>), grid, dim3(WAVE), 0, s, a);
+        else hipLaunchKernelGGL((spmm_gather_kernel<T, N, ROUNDED>), grid, dim3(WAVE), 0, s, a);
         if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
     }
     return LIBRA_OK;
@@ -1624,11 +1673,11 @@ int launch_spmm(const SpmmArgs &all, int64_t ntasks, hipStream_t s) {
 int spmm_launch(const libra_plan_t *P, const SpmmArgs &a, int n, int64_t nt, hipStream_t s);
 
 // `pieces` adjacent pieces of n columns each, one launch
-int spmm_piece(const libra_plan_t *P, const void *B, int n, int pieces, int64_t ldb, float *C, int64_t ldc, hipStream_t s) {
+int spmm_piece(const libra_plan_t *P, const void *B, int n, int pieces, int64_t ldb, float *C, int64_t ldc, void *R, int64_t ldr, hipStream_t s) {
     const SubPlan &sp = P->spmm;
     const int64_t per_die = (sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS;
     SpmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr, sp.dev.dense_val,
-               sp.dev.res_ent, B, C, ldb, ldc, (int32_t)per_die, pieces, 0};
+               sp.dev.res_ent, B, C, ldb, ldc, (int32_t)per_die, pieces, 0, R, ldr};
     const int64_t nt = per_die * LIBRA_XCDS;         // every slot of the table (the last few may hold empty tasks)
     if (P->o.two_kernels && a.phase == 0) {
         // ablation / debugging schedule: the matrix-unit part and the scalar part as two launches on the stream
@@ -1643,18 +1692,19 @@ int spmm_piece(const libra_plan_t *P, const void *B, int n, int pieces, int64_t 
 }
 
 int spmm_launch(const libra_plan_t *P, const SpmmArgs &a, int n, int64_t nt, hipStream_t s) {
-    if (P->vdt == LIBRA_F16) {
+    auto width16 = [&](auto tag, auto rounded) {
+        typedef decltype(tag) T;
+        constexpr bool ROUNDED = decltype(rounded)::value;
         switch (n) {
-        case 32: return launch_spmm<half_t, 32>(a, nt, s);
-        case 64: return launch_spmm<half_t, 64>(a, nt, s);
-        case 128: return launch_spmm<half_t, 128>(a, nt, s);
+        case 32: return launch_spmm<T, 32, ROUNDED>(a, nt, s);
+        case 64: return launch_spmm<T, 64, ROUNDED>(a, nt, s);
+        case 128: return launch_spmm<T, 128, ROUNDED>(a, nt, s);
         }
-    } else if (P->vdt == LIBRA_BF16) {
-        switch (n) {
-        case 32: return launch_spmm<bf16_t, 32>(a, nt, s);
-        case 64: return launch_spmm<bf16_t, 64>(a, nt, s);
-        case 128: return launch_spmm<bf16_t, 128>(a, nt, s);
-        }
+        return (int)LIBRA_ERR_UNSUPPORTED;
+    };
+    if (P->vdt != LIBRA_F32) {
+        if (P->vdt == LIBRA_F16) return a.R ? width16(half_t{}, std::true_type{}) : width16(half_t{}, std::false_type{});
+        return a.R ? width16(bf16_t{}, std::true_type{}) : width16(bf16_t{}, std::false_type{});
     } else {
         switch (n) {
         case 16: return launch_spmm<float, 16>(a, nt, s);
@@ -1969,8 +2019,9 @@ extern "C" int libra_plan_upload(libra_plan_t *plan, void *dev_buf, size_t bytes
     return LIBRA_OK;
 }
 
-extern "C" int libra_spmm(const libra_plan_t *P, const void *B, int32_t N, int64_t ldb, float *C, int64_t ldc, void *stream) {
-    if (!P || !B || !C) return LIBRA_ERR_NULL;
+namespace {
+// R: a second output of 16-bit rows (libra_spmm_rounded); nullptr: C is the output.
+int spmm_call(const libra_plan_t *P, const void *B, int32_t N, int64_t ldb, float *C, int64_t ldc, void *R, int64_t ldr, void *stream) {
     if (!P->o.build_spmm) return LIBRA_ERR_NOT_BUILT;
     if (!P->dev_base) return LIBRA_ERR_NOT_UPLOADED;
     if (P->o.W != W || P->o.KB != KB) return LIBRA_ERR_UNSUPPORTED;
@@ -1983,11 +2034,14 @@ extern "C" int libra_spmm(const libra_plan_t *P, const void *B, int32_t N, int64
     if (((uintptr_t)B & 15) || ((uintptr_t)C & 15)) return LIBRA_ERR_BUFFER;
     hipStream_t s = (hipStream_t)stream;
     const int esz = P->vsize;
-    if (const int64_t nz = P->spmm.n.zero_rows) {
-        const unsigned blocks = (unsigned)std::min<int64_t>((nz + CLEAR_ROWS - 1) / CLEAR_ROWS, 1 << 16);
-        hipLaunchKernelGGL(zero_rows_kernel, dim3(blocks), dim3(256), 0, s, P->spmm.dev.zero_rows, nz, C, ldc, N / 4);
+    auto row_blocks = [](int64_t n) { return dim3((unsigned)std::min<int64_t>((n + CLEAR_ROWS - 1) / CLEAR_ROWS, 1 << 16)); };
+    const int64_t nz = P->spmm.n.zero_rows;
+    if (nz) {
+        hipLaunchKernelGGL(zero_rows_kernel, row_blocks(nz), dim3(256), 0, s, P->spmm.dev.zero_rows, nz, C, ldc, N / 4);
         if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
     }
+    // the two-kernel mode adds its second launch to the rows of C: all of them are rounded afterwards
+    const bool all_rows = R && P->o.two_kernels;
     // the feature dimension is cut into pieces the kernels are instantiated for; at most 128 columns, the widest
     // piece whose tile leaves four waves per SIMD (a 256-column piece ran at two and took 2.5x the time of a 128-column one)
     for (int n0 = 0; n0 < N;) {
@@ -1998,11 +2052,38 @@ extern "C" int libra_spmm(const libra_plan_t *P, const void *B, int32_t N, int64
         // tail; community N=256: 535 -> 508 us).  Elsewhere they run one after the other: together they would compete for
         // the L2 with twice the rows of B (power-law N=512: 267 us apart, 354 us together).
         const int pieces = (n == 128 && P->o.xcd_order == 1) ? (N - n0) / 128 : 1;
-        int rc = spmm_piece(P, (const char *)B + (size_t)n0 * esz, n, pieces, ldb, C + n0, ldc, s);
+        int rc = spmm_piece(P, (const char *)B + (size_t)n0 * esz, n, pieces, ldb, C + n0, ldc, R && !all_rows ? (char *)R + (size_t)n0 * esz : nullptr, ldr, s);
         if (rc != LIBRA_OK) return rc;
         n0 += n * pieces;
     }
+    if (R && (nz || all_rows)) {
+        auto run = [&](auto tag) {
+            typedef decltype(tag) T;
+            const int64_t rows = all_rows ? P->M : nz;
+            hipLaunchKernelGGL((round_rows_kernel<T>), row_blocks(rows), dim3(256), 0, s, all_rows ? nullptr : P->spmm.dev.zero_rows, rows, C, ldc,
+                               reinterpret_cast<T *>(R), ldr, N / 8);
+        };
+        if (P->vdt == LIBRA_F16) run(half_t{});
+        else run(bf16_t{});
+        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
+    }
     return LIBRA_OK;
+}
+}  // namespace
+
+extern "C" int libra_spmm(const libra_plan_t *P, const void *B, int32_t N, int64_t ldb, float *C, int64_t ldc, void *stream) {
+    if (!P || !B || !C) return LIBRA_ERR_NULL;
+    return spmm_call(P, B, N, ldb, C, ldc, nullptr, 0, stream);
+}
+
+extern "C" int libra_spmm_rounded(const libra_plan_t *P, const void *B, int32_t N, int64_t ldb, void *R, int64_t ldr, float *scratch, int64_t lds, void *stream) {
+    if (!P || !B || !R) return LIBRA_ERR_NULL;
+    if (!scratch && (P->spmm.n.zero_rows || P->o.two_kernels)) return LIBRA_ERR_NULL;
+    if (P->vdt == LIBRA_F32) return LIBRA_ERR_DTYPE;
+    if (ldr < N) return LIBRA_ERR_SHAPE;
+    if (ldr % 8) return LIBRA_ERR_UNSUPPORTED;
+    if ((uintptr_t)R & 15) return LIBRA_ERR_BUFFER;
+    return spmm_call(P, B, N, ldb, scratch, lds, R, ldr, stream);
 }
 
 namespace {
