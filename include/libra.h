@@ -288,6 +288,12 @@ int libra_sddmm_pattern(const libra_plan_t *plan, const void *X, const void *Y, 
                         float *out, void *stream);
 
 /*
+ * libra_sddmm_pattern_rounded - libra_sddmm_pattern with the result in the plan's value type (16-bit plans), rounded once.
+ *   out  device, nnz values of the plan's type.  Errors: as libra_sddmm_pattern; DTYPE for an fp32 plan.
+ */
+int libra_sddmm_pattern_rounded(const libra_plan_t *plan, const void *X, const void *Y, int32_t K, void *out, void *stream);
+
+/*
  * libra_edge_softmax - row-wise softmax over CSR-ordered scores (the step between SDDMM and SpMM in an
  * attention layer, Section 5.5): vals_out[p] = exp(scale*s[p] - mx_i) / sum_row exp(scale*s[q] - mx_i).
  *   scores    device, fp32[nnz], CSR order
@@ -307,6 +313,18 @@ int libra_edge_softmax(const libra_plan_t *plan, const float *scores, float scal
  */
 int libra_edge_softmax_backward(const libra_plan_t *plan, const void *alpha, int alpha_dtype, const float *dalpha,
                                 float scale, float *dscores, void *stream);
+
+/* The same with alpha and dalpha both in `dtype`. */
+int libra_edge_softmax_backward_rounded(const libra_plan_t *plan, const void *alpha, const void *dalpha, int dtype,
+                                        float scale, float *dscores, void *stream);
+
+/*
+ * libra_value_products - out[p] = factors[p] * vals[p], formed in fp32 and rounded once to `dtype` (LIBRA_F16 or LIBRA_BF16):
+ * the coefficients of the SDDMM's backward products (A o dout).
+ *   vals, out  device, n values of `dtype`;  factors  device, fp32[n];  out may be vals
+ * Errors: NULL, SHAPE, DTYPE, BUFFER (an array not aligned to its elements), HIP.
+ */
+int libra_value_products(const void *vals, const float *factors, int64_t n, int dtype, void *out, void *stream);
 
 /*
  * libra_csr_transpose_device - CSR pattern of the transposed matrix, on the device (the backward pass of SpMM,

@@ -58,7 +58,7 @@ class _SpMM(torch.autograd.Function):
         if ctx.needs_input_grad[1]:
             if not _feature_ok(B.shape[1]):
                 raise RuntimeError("gradient with respect to the sparse values needs N in {32, 64, 128}")
-            dvals = sm.plan.sddmm(dC16, B.detach().contiguous(), pattern_only=True).to(vals.dtype)
+            dvals = sm.plan.sddmm_pattern_rounded(dC16, B.detach().contiguous()).to(vals.dtype)
         return None, dvals, dB
 
 
@@ -75,7 +75,7 @@ class _SDDMM(torch.autograd.Function):
         sm = ctx.sm
         vals, X, Y = ctx.saved_tensors
         Xc, Yc = X.detach().contiguous(), Y.detach().contiguous()
-        g = (dout * vals.detach().float()).to(sm.dtype).contiguous()
+        g = sm.plan.value_products(vals.detach().contiguous(), dout.float().contiguous())
         dvals = dX = dY = None
         if ctx.needs_input_grad[2]:
             sm.plan.set_values(g, lb.OP_SPMM)
@@ -100,7 +100,7 @@ class _EdgeSoftmax(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dalpha):
         (alpha,) = ctx.saved_tensors
-        return None, ctx.sm.plan.edge_softmax_backward(alpha, dalpha.float().contiguous(), ctx.scale), None
+        return None, ctx.sm.plan.edge_softmax_backward_rounded(alpha, dalpha.to(alpha.dtype).contiguous(), ctx.scale), None
 
 
 def spmm(sm: SparseMatrix, vals: torch.Tensor, B: torch.Tensor) -> torch.Tensor:

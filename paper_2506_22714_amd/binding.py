@@ -107,6 +107,9 @@ def lib() -> C.CDLL:
         L.libra_sddmm_pattern.argtypes = [vp, vp, vp, i32, vp, vp]
         L.libra_edge_softmax.argtypes = [vp, vp, C.c_float, vp, C.c_int, vp]
         L.libra_edge_softmax_backward.argtypes = [vp, vp, C.c_int, vp, C.c_float, vp, vp]
+        L.libra_sddmm_pattern_rounded.argtypes = [vp, vp, vp, i32, vp, vp]
+        L.libra_edge_softmax_backward_rounded.argtypes = [vp, vp, vp, C.c_int, C.c_float, vp, vp]
+        L.libra_value_products.argtypes = [vp, vp, i64, C.c_int, vp, vp]
         L.libra_probe_coissue.argtypes = [C.c_int, vp, C.POINTER(C.c_float * 3), vp]
         L.libra_probe_gather.argtypes = [vp, i64, i32, vp, i64, vp, vp]
         L.libra_probe_gather_hub.argtypes = [vp, i64, i32, vp, i64, vp, i32, vp, vp]
@@ -227,6 +230,21 @@ def libra_edge_softmax_backward(plan, alpha_ptr: int, alpha_dtype: int, dalpha_p
                                 stream: int = 0):
     _check(lib().libra_edge_softmax_backward(plan, C.c_void_p(alpha_ptr), alpha_dtype, C.c_void_p(dalpha_ptr), C.c_float(scale),
                                              C.c_void_p(dscores_ptr), C.c_void_p(stream)), "libra_edge_softmax_backward")
+
+
+def libra_sddmm_pattern_rounded(plan, X_ptr: int, Y_ptr: int, K: int, out_ptr: int, stream: int = 0):
+    _check(lib().libra_sddmm_pattern_rounded(plan, C.c_void_p(X_ptr), C.c_void_p(Y_ptr), K, C.c_void_p(out_ptr), C.c_void_p(stream)),
+           "libra_sddmm_pattern_rounded")
+
+
+def libra_edge_softmax_backward_rounded(plan, alpha_ptr: int, dalpha_ptr: int, dtype: int, scale: float, dscores_ptr: int, stream: int = 0):
+    _check(lib().libra_edge_softmax_backward_rounded(plan, C.c_void_p(alpha_ptr), C.c_void_p(dalpha_ptr), dtype, C.c_float(scale),
+                                                     C.c_void_p(dscores_ptr), C.c_void_p(stream)), "libra_edge_softmax_backward_rounded")
+
+
+def libra_value_products(vals_ptr: int, factors_ptr: int, n: int, dtype: int, out_ptr: int, stream: int = 0):
+    _check(lib().libra_value_products(C.c_void_p(vals_ptr), C.c_void_p(factors_ptr), n, dtype, C.c_void_p(out_ptr), C.c_void_p(stream)),
+           "libra_value_products")
 
 
 def libra_probe_coissue(iters: int, sink_ptr: int, stream: int = 0):
@@ -521,6 +539,20 @@ class Plan:
                                                                torch.cuda.current_stream().cuda_stream)
         return out
 
+    def sddmm_pattern_rounded(self, X, Y):
+        """``sddmm(X, Y, pattern_only=True)`` in the plan's value type, rounded once."""
+        import torch
+        if self.val_dtype == F32:
+            return self.sddmm(X, Y, pattern_only=True)
+        self._operand(X, "X", self._torch_dtype(), shape=(self.M, None))
+        self._operand(Y, "Y", self._torch_dtype(), shape=(self.Kc, int(X.shape[1])))
+        if Y.device != X.device:
+            raise ValueError("X and Y must be on one device")
+        out = torch.empty(self.nnz, dtype=X.dtype, device=X.device)
+        libra_sddmm_pattern_rounded(self.handle, X.data_ptr(), Y.data_ptr(), X.shape[1], out.data_ptr(),
+                                    torch.cuda.current_stream().cuda_stream)
+        return out
+
     def edge_softmax(self, scores, scale: float, out=None):
         import torch
         self._operand(scores, "scores", torch.float32, numel=self.nnz)
@@ -546,6 +578,33 @@ class Plan:
             raise ValueError("alpha, dalpha and out must be on one device")
         libra_edge_softmax_backward(self.handle, alpha.data_ptr(), code, dalpha.data_ptr(), scale, out.data_ptr(),
                                     torch.cuda.current_stream().cuda_stream)
+        return out
+
+    def edge_softmax_backward_rounded(self, alpha, dalpha, scale: float):
+        """``edge_softmax_backward`` of a ``dalpha`` in alpha's type."""
+        import torch
+        code = self._value_code(alpha, "alpha")
+        self._operand(alpha, "alpha", None, numel=self.nnz)
+        self._operand(dalpha, "dalpha", alpha.dtype, numel=self.nnz)
+        if dalpha.device != alpha.device:
+            raise ValueError("alpha and dalpha must be on one device")
+        out = torch.empty(self.nnz, dtype=torch.float32, device=alpha.device)
+        libra_edge_softmax_backward_rounded(self.handle, alpha.data_ptr(), dalpha.data_ptr(), code, scale, out.data_ptr(),
+                                            torch.cuda.current_stream().cuda_stream)
+        return out
+
+    def value_products(self, vals, factors):
+        """``(factors * vals.float())`` in the plan's value type, rounded once: values of A (CSR order) times fp32 factors."""
+        import torch
+        if self.val_dtype == F32:
+            return factors * vals
+        self._operand(vals, "vals", self._torch_dtype(), numel=self.nnz)
+        self._operand(factors, "factors", torch.float32, numel=self.nnz)
+        if factors.device != vals.device:
+            raise ValueError("vals and factors must be on one device")
+        out = torch.empty(self.nnz, dtype=vals.dtype, device=vals.device)
+        libra_value_products(vals.data_ptr(), factors.data_ptr(), self.nnz, self.val_dtype, out.data_ptr(),
+                             torch.cuda.current_stream().cuda_stream)
         return out
 
     def set_values(self, vals, ops: int = OP_SPMM | OP_SDDMM, one_call: bool = False):

@@ -1003,6 +1003,12 @@ struct SddmmArgs {
     int32_t tasks_left;         // of a die, from `tasks` on
     int32_t pattern_only;       // nonzero: out_p = <X_i, Y_j>, A's values are not applied
 };
+// ROUNDED: `out` holds values of the storage type (a template argument: as a flag it took 0.3 % off the fp32 calls)
+template <class T, bool ROUNDED>
+__device__ inline void put_output(const SddmmArgs &a, int32_t pos, float v) {
+    if constexpr (ROUNDED) reinterpret_cast<T *>(a.out)[pos] = to_storage<T>(v);
+    else a.out[pos] = v;
+}
 
 // Sum over the LPN consecutive lanes of a group; every lane of the group gets the total.
 // Steps inside a 16-lane row are DPP moves (no LDS traffic); wider groups finish with wave shuffles.
@@ -1060,7 +1066,7 @@ struct RowStage {
 // plan time in ascending CSR position inside every group - are then read by consecutive lanes: coalesced record loads, and
 // stores that fall into the row-contiguous runs of the output instead of one 4-byte store per matrix-core lane (the
 // write-back of Section 4.4.2, with the popcount offsets resolved when the plan is built).
-template <class T, int K>
+template <class T, int K, bool ROUNDED>
 __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = RowStage<K>;
     constexpr int KS = K / 32;               // MFMA k-steps
@@ -1115,7 +1121,7 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, l
 #pragma unroll
             for (int u = 0; u < RU; ++u)
                 if (q + u * WAVE + lane < v1)
-                    a.out[(int32_t)rec[u].x] = (a.pattern_only ? 1.f : Elem<T>::word_val(rec[u].y)) * products[rec[u].y >> 16];
+                    put_output<T, ROUNDED>(a, (int32_t)rec[u].x, (a.pattern_only ? 1.f : Elem<T>::word_val(rec[u].y)) * products[rec[u].y >> 16]);
         }
         wait_for_lds();                      // the next group overwrites the stage
     }
@@ -1226,7 +1232,7 @@ struct SegmentEntry {
 // instead of 16 bytes per entry halve the accesses (322 -> 172 M).  f16, against that version: GAT graph K = 64 772 -> 680 us
 // (648 us with segments of 128), power-law K = 32 35.4 -> 27.3, community K = 32 177 -> 146, irregular 1,905 -> 1,770 us (98 M
 // lines from behind the L2s, at the rate at which they come).  Fetching the next batch's entries early: no change.
-template <class T, int K>
+template <class T, int K, bool ROUNDED>
 __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = RowStage<K>;
     constexpr int KS = K / 32;                   // MFMA k-steps
@@ -1290,7 +1296,7 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, 
         for (int x = 0; x < 4; ++x)
             if (mine[x]) out_stage[x * 16 + j] = v[x];
         wave_sync();
-        if (q0 + lane < t.res_end) a.out[ent.pos] = (a.pattern_only ? 1.f : ent.value()) * out_stage[lane];
+        if (q0 + lane < t.res_end) put_output<T, ROUNDED>(a, ent.pos, (a.pattern_only ? 1.f : ent.value()) * out_stage[lane]);
         wait_for_lds();                          // the next batch overwrites the stage
     }
 }
@@ -1340,7 +1346,7 @@ __device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask 
 // graph 31.0 vs 32.3 us: a workgroup's slots are only free again when its slowest wave has finished).
 // DENSE = false: the table has no window task (a plan without dense blocks).  At K = 64 the LDS allows five waves per SIMD
 // and the registers are held to that (GAT 688 -> 674 us, power-law 41.9 -> 40.4); at K = 128 it would spill (327 -> 373).
-template <class T, int K, int WPB, bool DENSE>
+template <class T, int K, int WPB, bool DENSE, bool ROUNDED>
 __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K == 64 && !std::is_same<T, float>::value ? 5 : 1))) void sddmm_task_kernel(SddmmArgs a) {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int PRODUCTS = DENSE ? SD_GROUP * 256 * 4 : WAVE * 4, ROWS = RowStage<K>::BYTES;
@@ -1353,11 +1359,11 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K ==
     lds_byte *stage = (lds_byte *)stage_all + wave * STAGE;
     if (DENSE && t.kind == LIBRA_TASK_WINDOW) {
         if constexpr (F32) sddmm_window_task_f32<K>(a, t);
-        else sddmm_window_task<T, K>(a, t, stage);
+        else sddmm_window_task<T, K, ROUNDED>(a, t, stage);
         return;
     }
     if constexpr (F32) sddmm_segment_task_f32<K>(a, t, reinterpret_cast<lds_float *>(stage));
-    else sddmm_segment_task<T, K>(a, t, stage);
+    else sddmm_segment_task<T, K, ROUNDED>(a, t, stage);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1517,13 +1523,15 @@ __global__ __launch_bounds__(256) void edge_softmax_kernel(SoftmaxRows r, const 
     else edge_softmax_short_rows<TO>(b - (unsigned)r.nlong - r.medium_blocks, r.short_blocks, r.rowptr, r.M, score, scale, out);
 }
 
+// TD: dalpha in alpha's 16-bit type or fp32.  Together with SDDMM results and value products that leave in 16 bits (no fp32 arrays and
+// conversions between the steps) a training step with attention, 500,009 rows, bf16, K = 64 went from 1,573 to 1,487 us.
 // Backward of the edge softmax: dscore_p = scale * alpha_p * (dalpha_p - sum_row alpha_q dalpha_q).  Same three row
 // classes as the forward kernels.
 template <class TA> __device__ inline float from_storage(TA x) { return (float)x; }
 template <> __device__ inline float from_storage<bf16_t>(bf16_t x) { return __uint_as_float((uint32_t)x.bits << 16); }
 
-template <class TA>
-__device__ inline void edge_softmax_bwd_short_rows(unsigned block, unsigned nblocks, const int32_t *rowptr, int64_t M, const TA *alpha, const float *dalpha, float scale, float *dscore) {
+template <class TA, class TD>
+__device__ inline void edge_softmax_bwd_short_rows(unsigned block, unsigned nblocks, const int32_t *rowptr, int64_t M, const TA *alpha, const TD *dalpha, float scale, float *dscore) {
     constexpr int SL = SHORT_LANES, KPL = SHORT_LOADS;
     const int l = threadIdx.x % SL;
     const int64_t group = ((int64_t)block * blockDim.x + threadIdx.x) / SL;
@@ -1533,16 +1541,18 @@ __device__ inline void edge_softmax_bwd_short_rows(unsigned block, unsigned nblo
         if (n == 0 || n > 64) continue;
         // clamped addresses, all loads in flight together; the padding contributes zero
         TA ar[KPL];
+        TD gr[KPL];
         float a[KPL], g[KPL], dot = 0.f;
 #pragma unroll
         for (int k = 0; k < KPL; ++k) {
             const int q = s + min(l + SL * k, n - 1);
             ar[k] = alpha[q];
-            g[k] = dalpha[q];
+            gr[k] = dalpha[q];
         }
 #pragma unroll
         for (int k = 0; k < KPL; ++k) {
             a[k] = l + SL * k < n ? from_storage<TA>(ar[k]) : 0.f;
+            g[k] = from_storage<TD>(gr[k]);
             dot += a[k] * g[k];
         }
         dot = group_sum<SL>(dot);
@@ -1554,8 +1564,8 @@ __device__ inline void edge_softmax_bwd_short_rows(unsigned block, unsigned nblo
 
 // MEDIUM_LANES lanes per listed row (65 .. LIBRA_SOFTMAX_LONG_ROW nonzeros), or one 256-thread workgroup per listed long row;
 // UNR pairs per thread and round, as in the forward kernel
-template <class TA, int THREADS, int UNR>
-__device__ inline void edge_softmax_bwd_listed_row(unsigned block, const int32_t *rowptr, const int32_t *rows, int nrows, const TA *alpha, const float *dalpha, float scale, float *dscore) {
+template <class TA, class TD, int THREADS, int UNR>
+__device__ inline void edge_softmax_bwd_listed_row(unsigned block, const int32_t *rowptr, const int32_t *rows, int nrows, const TA *alpha, const TD *dalpha, float scale, float *dscore) {
     __shared__ float red[4];
     static_assert(THREADS == 256 || (THREADS <= WAVE && WAVE % THREADS == 0), "a workgroup per row, or whole groups of lanes inside a wave");
     const int tid = (int)threadIdx.x % THREADS;
@@ -1566,14 +1576,18 @@ __device__ inline void edge_softmax_bwd_listed_row(unsigned block, const int32_t
     float a[UNR], g[UNR];
     auto fetch = [&](int q0) {          // clamped addresses; padding contributes zero
         TA ar[UNR];
+        TD gr[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int q = min(q0 + u * THREADS + tid, n - 1);
             ar[u] = alpha[s + q];
-            g[u] = dalpha[s + q];
+            gr[u] = dalpha[s + q];
         }
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) a[u] = q0 + u * THREADS + tid < n ? from_storage<TA>(ar[u]) : 0.f;
+        for (int u = 0; u < UNR; ++u) {
+            a[u] = q0 + u * THREADS + tid < n ? from_storage<TA>(ar[u]) : 0.f;
+            g[u] = from_storage<TD>(gr[u]);
+        }
     };
     float dot = 0.f;
     for (int q0 = 0; q0 < n; q0 += THREADS * UNR) {
@@ -1593,12 +1607,35 @@ __device__ inline void edge_softmax_bwd_listed_row(unsigned block, const int32_t
     }
 }
 
-template <class TA>
-__global__ __launch_bounds__(256) void edge_softmax_bwd_kernel(SoftmaxRows r, const TA *alpha, const float *dalpha, float scale, float *dscore) {
+template <class TA, class TD>
+__global__ __launch_bounds__(256) void edge_softmax_bwd_kernel(SoftmaxRows r, const TA *alpha, const TD *dalpha, float scale, float *dscore) {
     const unsigned b = blockIdx.x;
-    if (b < (unsigned)r.nlong) edge_softmax_bwd_listed_row<TA, 256, 8>(b, r.rowptr, r.long_rows, r.nlong, alpha, dalpha, scale, dscore);
-    else if (b < (unsigned)r.nlong + r.medium_blocks) edge_softmax_bwd_listed_row<TA, MEDIUM_LANES, 8>(b - (unsigned)r.nlong, r.rowptr, r.medium_rows, r.nmedium, alpha, dalpha, scale, dscore);
-    else edge_softmax_bwd_short_rows<TA>(b - (unsigned)r.nlong - r.medium_blocks, r.short_blocks, r.rowptr, r.M, alpha, dalpha, scale, dscore);
+    if (b < (unsigned)r.nlong) edge_softmax_bwd_listed_row<TA, TD, 256, 8>(b, r.rowptr, r.long_rows, r.nlong, alpha, dalpha, scale, dscore);
+    else if (b < (unsigned)r.nlong + r.medium_blocks) edge_softmax_bwd_listed_row<TA, TD, MEDIUM_LANES, 8>(b - (unsigned)r.nlong, r.rowptr, r.medium_rows, r.nmedium, alpha, dalpha, scale, dscore);
+    else edge_softmax_bwd_short_rows<TA, TD>(b - (unsigned)r.nlong - r.medium_blocks, r.short_blocks, r.rowptr, r.M, alpha, dalpha, scale, dscore);
+}
+
+// out[p] = factor[p] * val[p], rounded once, in one pass (bound by memory: 8 bytes per nonzero; as conversion, product and
+// rounding it was 26); eight per thread where the three arrays lie on 16-byte boundaries.
+template <class T>
+__global__ __launch_bounds__(256) void value_products_kernel(const T *val, const float *factor, int64_t n, T *out, bool whole) {
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nthreads = (int64_t)gridDim.x * blockDim.x;
+    const int64_t groups = whole ? n / 8 : 0;
+    for (int64_t g = tid; g < groups; g += nthreads) {
+        const uint4 raw = reinterpret_cast<const uint4 *>(val)[g];
+        const float4_t f0 = reinterpret_cast<const float4_t *>(factor)[2 * g], f1 = reinterpret_cast<const float4_t *>(factor)[2 * g + 1];
+        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        float4_t lo, hi;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            lo[2 * k] = f0[2 * k] * Elem<T>::word_val(w[k] & 0xffffu);
+            lo[2 * k + 1] = f0[2 * k + 1] * Elem<T>::word_val(w[k] >> 16);
+            hi[2 * k] = f1[2 * k] * Elem<T>::word_val(w[k + 2] & 0xffffu);
+            hi[2 * k + 1] = f1[2 * k + 1] * Elem<T>::word_val(w[k + 2] >> 16);
+        }
+        reinterpret_cast<uint4 *>(out)[g] = round8<T>(lo, hi);
+    }
+    for (int64_t i = groups * 8 + tid; i < n; i += nthreads) out[i] = to_storage<T>(factor[i] * from_storage<T>(val[i]));
 }
 
 // dst[i * stride + offset] (as T) = src[perm[i]]: new values into a packed array or into entry records
@@ -2087,16 +2124,20 @@ extern "C" int libra_spmm_rounded(const libra_plan_t *P, const void *B, int32_t 
 }
 
 namespace {
-int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, float *out, void *stream, int pattern_only);
+int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, void *out, void *stream, int pattern_only, int rounded);
 }
 extern "C" int libra_sddmm(const libra_plan_t *P, const void *X, const void *Y, int32_t K, float *out, void *stream) {
-    return sddmm_call(P, X, Y, K, out, stream, 0);
+    return sddmm_call(P, X, Y, K, out, stream, 0, 0);
 }
 extern "C" int libra_sddmm_pattern(const libra_plan_t *P, const void *X, const void *Y, int32_t K, float *out, void *stream) {
-    return sddmm_call(P, X, Y, K, out, stream, 1);
+    return sddmm_call(P, X, Y, K, out, stream, 1, 0);
+}
+extern "C" int libra_sddmm_pattern_rounded(const libra_plan_t *P, const void *X, const void *Y, int32_t K, void *out, void *stream) {
+    if (P && P->vdt == LIBRA_F32) return LIBRA_ERR_DTYPE;
+    return sddmm_call(P, X, Y, K, out, stream, 1, 1);
 }
 namespace {
-int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, float *out, void *stream, int pattern_only) {
+int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, void *out, void *stream, int pattern_only, int rounded) {
     if (!P || !X || !Y) return LIBRA_ERR_NULL;
     if (!out && P->nnz > 0) return LIBRA_ERR_NULL;           // a matrix without nonzeros has no output
     if (!P->o.build_sddmm) return LIBRA_ERR_NOT_BUILT;
@@ -2104,12 +2145,12 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
     if (P->o.W != W || P->o.KB != KB) return LIBRA_ERR_UNSUPPORTED;
     if (K <= 0) return LIBRA_ERR_SHAPE;
     if (K != 32 && K != 64 && K != 128) return LIBRA_ERR_UNSUPPORTED;
-    if (((uintptr_t)X & 15) || ((uintptr_t)Y & 15) || ((uintptr_t)out & 3)) return LIBRA_ERR_BUFFER;
+    if (((uintptr_t)X & 15) || ((uintptr_t)Y & 15) || ((uintptr_t)out & (rounded ? 1 : 3))) return LIBRA_ERR_BUFFER;
     hipStream_t s = (hipStream_t)stream;
     const SubPlan &sp = P->sddmm;
     SddmmArgs a{sp.dev.tasks, sp.dev.blk_cols, sp.dev.blk_bitmap, sp.dev.blk_valptr,
                 reinterpret_cast<const uint2 *>(sp.dev.dense_pv), (int32_t)sp.n.dense,
-                sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, out, P->M, 0, 0, pattern_only};
+                sp.dev.res_ent, sp.dev.res_base, sp.dev.res_row, sp.dev.res_perm, X, Y, (float *)out, P->M, 0, 0, pattern_only};
     if (sp.n.tasks == 0) return LIBRA_OK;
     a.tasks_per_die = a.tasks_left = (int32_t)((sp.n.tasks + LIBRA_XCDS - 1) / LIBRA_XCDS);
     constexpr int32_t most = LAUNCH_WAVES / LIBRA_XCDS;      // rounds of a launch: whole workgroups
@@ -2117,17 +2158,18 @@ int sddmm_call(const libra_plan_t *P, const void *X, const void *Y, int32_t K, f
         constexpr int WPB = decltype(wpb)::value;
         constexpr bool DENSE = decltype(with_blocks)::value;
         const dim3 grid((unsigned)((std::min(a.tasks_left, most) + WPB - 1) / WPB * LIBRA_XCDS)), block(WAVE * WPB);
-        auto width = [&](auto tag) {
+        auto width = [&](auto tag, auto round) {
             typedef decltype(tag) T;
+            constexpr bool ROUNDED = decltype(round)::value;
             switch (K) {
-            case 32: hipLaunchKernelGGL((sddmm_task_kernel<T, 32, WPB, DENSE>), grid, block, 0, s, a); break;
-            case 64: hipLaunchKernelGGL((sddmm_task_kernel<T, 64, WPB, DENSE>), grid, block, 0, s, a); break;
-            case 128: hipLaunchKernelGGL((sddmm_task_kernel<T, 128, WPB, DENSE>), grid, block, 0, s, a); break;
+            case 32: hipLaunchKernelGGL((sddmm_task_kernel<T, 32, WPB, DENSE, ROUNDED>), grid, block, 0, s, a); break;
+            case 64: hipLaunchKernelGGL((sddmm_task_kernel<T, 64, WPB, DENSE, ROUNDED>), grid, block, 0, s, a); break;
+            case 128: hipLaunchKernelGGL((sddmm_task_kernel<T, 128, WPB, DENSE, ROUNDED>), grid, block, 0, s, a); break;
             }
         };
-        if (P->vdt == LIBRA_F16) width(half_t{});
-        else if (P->vdt == LIBRA_BF16) width(bf16_t{});
-        else width(float{});
+        if (P->vdt == LIBRA_F32) width(float{}, std::false_type{});
+        else if (P->vdt == LIBRA_F16) rounded ? width(half_t{}, std::true_type{}) : width(half_t{}, std::false_type{});
+        else rounded ? width(bf16_t{}, std::true_type{}) : width(bf16_t{}, std::false_type{});
     };
     auto shape = [&](auto with_blocks) {
         if (P->o.xcd_order == 1) launch(std::integral_constant<int, 4>{}, with_blocks);
@@ -2161,8 +2203,9 @@ extern "C" int libra_edge_softmax(const libra_plan_t *P, const float *scores, fl
     return hip_rc(hipGetLastError());
 }
 
-extern "C" int libra_edge_softmax_backward(const libra_plan_t *P, const void *alpha, int alpha_dtype, const float *dalpha, float scale,
-                                           float *dscores, void *stream) {
+namespace {
+// `same`: dalpha has alpha's type, otherwise fp32
+int softmax_backward(const libra_plan_t *P, const void *alpha, int alpha_dtype, const void *dalpha, bool same, float scale, float *dscores, void *stream) {
     if (!P) return LIBRA_ERR_NULL;
     if ((!alpha || !dalpha || !dscores) && P->nnz > 0) return LIBRA_ERR_NULL;
     if (alpha_dtype != LIBRA_F16 && alpha_dtype != LIBRA_BF16 && alpha_dtype != LIBRA_F32) return LIBRA_ERR_DTYPE;
@@ -2171,13 +2214,42 @@ extern "C" int libra_edge_softmax_backward(const libra_plan_t *P, const void *al
     if (P->nnz == 0) return LIBRA_OK;
     const SoftmaxRows r = softmax_rows(P);
     const unsigned blocks = (unsigned)r.nlong + r.medium_blocks + r.short_blocks;
-    auto run = [&](auto tag) {
+    auto run = [&](auto tag, auto dtag) {
         typedef decltype(tag) TA;
-        hipLaunchKernelGGL((edge_softmax_bwd_kernel<TA>), dim3(blocks), dim3(256), 0, s, r, reinterpret_cast<const TA *>(alpha), dalpha, scale, dscores);
+        typedef decltype(dtag) TD;
+        hipLaunchKernelGGL((edge_softmax_bwd_kernel<TA, TD>), dim3(blocks), dim3(256), 0, s, r, reinterpret_cast<const TA *>(alpha),
+                           reinterpret_cast<const TD *>(dalpha), scale, dscores);
     };
-    if (alpha_dtype == LIBRA_F16) run(half_t{});
-    else if (alpha_dtype == LIBRA_BF16) run(bf16_t{});
-    else run(float{});
+    if (alpha_dtype == LIBRA_F16) same ? run(half_t{}, half_t{}) : run(half_t{}, float{});
+    else if (alpha_dtype == LIBRA_BF16) same ? run(bf16_t{}, bf16_t{}) : run(bf16_t{}, float{});
+    else run(float{}, float{});
+    return hip_rc(hipGetLastError());
+}
+}  // namespace
+extern "C" int libra_edge_softmax_backward(const libra_plan_t *P, const void *alpha, int alpha_dtype, const float *dalpha, float scale,
+                                           float *dscores, void *stream) {
+    return softmax_backward(P, alpha, alpha_dtype, dalpha, false, scale, dscores, stream);
+}
+extern "C" int libra_edge_softmax_backward_rounded(const libra_plan_t *P, const void *alpha, const void *dalpha, int dtype, float scale,
+                                                   float *dscores, void *stream) {
+    return softmax_backward(P, alpha, dtype, dalpha, true, scale, dscores, stream);
+}
+
+extern "C" int libra_value_products(const void *vals, const float *factors, int64_t n, int dtype, void *out, void *stream) {
+    if (n < 0) return LIBRA_ERR_SHAPE;
+    if ((!vals || !factors || !out) && n > 0) return LIBRA_ERR_NULL;
+    if (dtype != LIBRA_F16 && dtype != LIBRA_BF16) return LIBRA_ERR_DTYPE;
+    if (((uintptr_t)vals & 1) || ((uintptr_t)factors & 3) || ((uintptr_t)out & 1)) return LIBRA_ERR_BUFFER;
+    if (n == 0) return LIBRA_OK;
+    const bool whole = !(((uintptr_t)vals | (uintptr_t)factors | (uintptr_t)out) & 15);
+    const unsigned blocks = (unsigned)std::min<int64_t>(((whole ? n / 8 : n) + 255) / 256 + 1, 1 << 16);
+    auto run = [&](auto tag) {
+        typedef decltype(tag) T;
+        hipLaunchKernelGGL((value_products_kernel<T>), dim3(blocks), dim3(256), 0, (hipStream_t)stream, reinterpret_cast<const T *>(vals), factors, n,
+                           reinterpret_cast<T *>(out), whole);
+    };
+    if (dtype == LIBRA_F16) run(half_t{});
+    else run(bf16_t{});
     return hip_rc(hipGetLastError());
 }
 

@@ -62,3 +62,49 @@ def test_spmm_rounded_of_infinities_and_overflow():
     assert torch.isinf(want).any() and torch.isnan(want).any()
     assert torch.equal(got.nan_to_num(1.0, 2.0, 3.0), want.nan_to_num(1.0, 2.0, 3.0)) and torch.equal(got.isnan(), want.isnan())
     p.close()
+
+
+@pytest.mark.parametrize("K", [32, 64, 128])
+@pytest.mark.parametrize("dtype", list(DTYPES))
+def test_sddmm_pattern_rounded(dtype, K):
+    A, dt = matrix(), DTYPES[dtype]
+    X, Y = whole((A.M, K), dt, 1), whole((A.Kc, K), dt, 2)
+    for opts in (dict(), dict(sddmm_min_blk_nnz=8), dict(mode=lb.MODE_SCALAR_ONLY), dict(sddmm_min_blk_nnz=8, flags=lb.FLAG_XCD_ORDER)):
+        p = plan(A, dt, **opts)
+        want = p.sddmm(X, Y, pattern_only=True)
+        assert want.abs().max() > 2048
+        got = p.sddmm_pattern_rounded(X, Y)
+        assert got.dtype == dt and torch.equal(got, want.to(dt)), opts
+        with pytest.raises((ValueError, lb.LibraError)):
+            p.sddmm_pattern_rounded(X, Y[:, :16])
+        p.close()
+
+
+@pytest.mark.parametrize("dtype", list(DTYPES))
+def test_edge_softmax_backward_of_a_rounded_gradient(dtype):
+    """A 16-bit gradient is widened exactly: the result is that of the fp32 call on the widened one, bit for bit."""
+    A, dt = wl.make("gat", small=True), DTYPES[dtype]        # rows of every length class
+    p = plan(A, dt)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    alpha = p.edge_softmax(torch.randn(A.nnz, device="cuda", generator=g), 0.7)
+    d = torch.randn(A.nnz, device="cuda", generator=g).to(dt)
+    assert torch.equal(p.edge_softmax_backward_rounded(alpha, d, 0.7), p.edge_softmax_backward(alpha, d.float(), 0.7))
+    for bad in (d.float(), d[1:]):
+        with pytest.raises(ValueError):
+            p.edge_softmax_backward_rounded(alpha, bad, 0.7)
+    p.close()
+
+
+@pytest.mark.parametrize("dtype", list(DTYPES))
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 4099])
+def test_value_products(dtype, n):
+    """Groups of eight, remainders, and arrays that are only aligned to their elements."""
+    dt = DTYPES[dtype]
+    g = torch.Generator(device="cuda").manual_seed(n)
+    for shift in ((0, 0), (1, 0), (0, 1), (3, 2)):
+        vals = torch.randn(n + 8, device="cuda", generator=g).to(dt)[shift[0]:shift[0] + n]
+        factors = (torch.randn(n + 8, device="cuda", generator=g) * 100)[shift[1]:shift[1] + n]
+        out = torch.empty_like(vals)
+        lb.libra_value_products(vals.data_ptr(), factors.data_ptr(), n, lb.F16 if dtype == "f16" else lb.BF16, out.data_ptr(),
+                                torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(out, (factors * vals.float()).to(dt)), shift
