@@ -416,6 +416,22 @@ int libra_plan_set_values(libra_plan_t *plan, const void *vals_csr_dev, int dtyp
 #define LIBRA_OP_SDDMM 2
 int libra_plan_set_values_for(libra_plan_t *plan, const void *vals_csr_dev, int dtype, int ops, void *stream);
 
+/*
+ * libra_plan_set_values_ordered - new values for the SpMM arrays that come in another order of the same nonzeros: nonzero p of the
+ * plan's matrix takes vals[perm[p]].  A training step multiplies by A^T with the values of A (Section 5.5): its plan takes them in
+ * A's order, through the permutation that libra_csr_transpose_device gives.  libra_value_order turns the permutation into the form
+ * the call reads, once per plan and permutation; libra_value_order_bytes gives the sizes of that form, of the workspace for making
+ * it (free afterwards) and of the call's scratch memory (may be 0: NULL then).
+ *   perm     device, int32[nnz], a permutation of 0 .. nnz - 1 (SHAPE if a place is out of range or a chunk of them not covered)
+ *   order    device, 256-byte aligned;  workspace  device, 256-byte aligned;  libra_value_order synchronises the stream
+ *   vals     device, nnz values of the plan's type;  scratch  device, aligned to a value
+ * Errors: NULL, SHAPE, DTYPE, BUFFER, NOT_BUILT, NOT_UPLOADED, HIP.
+ */
+int libra_value_order_bytes(const libra_plan_t *plan, size_t *order_bytes, size_t *workspace_bytes, size_t *scratch_bytes);
+int libra_value_order(const libra_plan_t *plan, const int32_t *perm, void *order, size_t order_bytes,
+                      void *workspace, size_t workspace_bytes, void *stream);
+int libra_plan_set_values_ordered(libra_plan_t *plan, const void *vals, int dtype, const void *order, void *scratch, void *stream);
+
 /* Host views for checkers; pointers stay valid until libra_plan_destroy.  which: 0 = SpMM, 1 = SDDMM. */
 int libra_plan_export(const libra_plan_t *plan, int which, libra_subplan_view_t *view);
 int libra_plan_stats(const libra_plan_t *plan, libra_stats_t *stats);

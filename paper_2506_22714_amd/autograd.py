@@ -26,8 +26,18 @@ class SparseMatrix:
         ones = torch.ones(self.nnz, dtype=dtype, device=col.device)
         self.plan = lb.Plan.from_device_csr(M, Kc, rowptr, col, ones, resident=True, keep_host_copy=False, **opts)
         rowptr_t, col_t, perm_t = lb.transpose_csr(M, Kc, rowptr, col)
-        self.perm_t = perm_t.long()
+        self._perm_t = perm_t
         self.plan_t = lb.Plan.from_device_csr(Kc, M, rowptr_t, col_t, ones, resident=True, keep_host_copy=False, **opts)
+        self._order_t = self.plan_t.value_order(perm_t)
+
+    @property
+    def perm_t(self) -> torch.Tensor:
+        """CSR position in A of every nonzero of A^T."""
+        return self._perm_t.long()
+
+    def set_transposed(self, vals: torch.Tensor):
+        """Values of A (CSR order) into the SpMM arrays of the plan of A^T."""
+        self.plan_t.set_values_ordered(vals, self._order_t)
 
     def close(self):
         self.plan.close()
@@ -53,7 +63,7 @@ class _SpMM(torch.autograd.Function):
         dC16 = dC.to(sm.dtype).contiguous()
         dvals = dB = None
         if ctx.needs_input_grad[2]:
-            sm.plan_t.set_values(vals.detach()[sm.perm_t].contiguous(), lb.OP_SPMM)
+            sm.set_transposed(vals.detach().contiguous())
             dB = sm.plan_t.spmm_rounded(dC16).to(B.dtype)
         if ctx.needs_input_grad[1]:
             if not _feature_ok(B.shape[1]):
@@ -81,7 +91,7 @@ class _SDDMM(torch.autograd.Function):
             sm.plan.set_values(g, lb.OP_SPMM)
             dX = sm.plan.spmm_rounded(Yc).to(X.dtype)
         if ctx.needs_input_grad[3]:
-            sm.plan_t.set_values(g[sm.perm_t].contiguous(), lb.OP_SPMM)
+            sm.set_transposed(g)
             dY = sm.plan_t.spmm_rounded(Xc).to(Y.dtype)
         if ctx.needs_input_grad[1]:
             dvals = (dout * sm.plan.sddmm(Xc, Yc, pattern_only=True)).to(vals.dtype)

@@ -118,6 +118,9 @@ def lib() -> C.CDLL:
         L.libra_csr_transpose_device_static.argtypes = [i64, i64, i64, vp, vp, vp, vp, vp, vp]
         L.libra_plan_set_values.argtypes = [vp, vp, C.c_int, vp]
         L.libra_plan_set_values_for.argtypes = [vp, vp, C.c_int, C.c_int, vp]
+        L.libra_value_order_bytes.argtypes = [vp, C.POINTER(sz), C.POINTER(sz), C.POINTER(sz)]
+        L.libra_value_order.argtypes = [vp, vp, vp, sz, vp, sz, vp]
+        L.libra_plan_set_values_ordered.argtypes = [vp, vp, C.c_int, vp, vp, vp]
         L.libra_plan_export.argtypes = [vp, C.c_int, C.POINTER(SubplanView)]
         L.libra_plan_stats.argtypes = [vp, C.POINTER(Stats)]
         L.libra_plan_destroy.argtypes = [vp]
@@ -329,6 +332,23 @@ def libra_plan_set_values(plan, vals_ptr: int, dtype: int, stream: int = 0):
 def libra_plan_set_values_for(plan, vals_ptr: int, dtype: int, ops: int, stream: int = 0):
     _check(lib().libra_plan_set_values_for(plan, C.c_void_p(vals_ptr), dtype, ops, C.c_void_p(stream)),
            "libra_plan_set_values_for")
+
+
+def libra_value_order_bytes(plan) -> tuple:
+    """(order, workspace, scratch) in bytes."""
+    n = [C.c_size_t() for _ in range(3)]
+    _check(lib().libra_value_order_bytes(plan, *(C.byref(x) for x in n)), "libra_value_order_bytes")
+    return tuple(int(x.value) for x in n)
+
+
+def libra_value_order(plan, perm_ptr: int, order_ptr: int, order_bytes: int, ws_ptr: int, ws_bytes: int, stream: int = 0):
+    _check(lib().libra_value_order(plan, C.c_void_p(perm_ptr), C.c_void_p(order_ptr), order_bytes, C.c_void_p(ws_ptr), ws_bytes,
+                                   C.c_void_p(stream)), "libra_value_order")
+
+
+def libra_plan_set_values_ordered(plan, vals_ptr: int, dtype: int, order_ptr: int, scratch_ptr: int, stream: int = 0):
+    _check(lib().libra_plan_set_values_ordered(plan, C.c_void_p(vals_ptr), dtype, C.c_void_p(order_ptr), C.c_void_p(scratch_ptr),
+                                               C.c_void_p(stream)), "libra_plan_set_values_ordered")
 
 
 def libra_plan_destroy(plan):
@@ -618,3 +638,25 @@ class Plan:
             libra_plan_set_values(self.handle, vals.data_ptr(), self.val_dtype, torch.cuda.current_stream().cuda_stream)
         else:
             libra_plan_set_values_for(self.handle, vals.data_ptr(), self.val_dtype, ops, torch.cuda.current_stream().cuda_stream)
+
+    def value_order(self, perm):
+        """The form of a permutation of the nonzeros (int32) that :meth:`set_values_ordered` reads; belongs to this plan."""
+        import torch
+        self._operand(perm, "perm", torch.int32, numel=self.nnz)
+        order_bytes, ws_bytes, scratch_bytes = libra_value_order_bytes(self.handle)
+        order = torch.empty(order_bytes, dtype=torch.uint8, device=perm.device)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=perm.device)
+        libra_value_order(self.handle, perm.data_ptr(), order.data_ptr(), order_bytes, ws.data_ptr(), ws_bytes,
+                          torch.cuda.current_stream().cuda_stream)
+        return order, scratch_bytes
+
+    def set_values_ordered(self, vals, order):
+        """SpMM values from ``vals`` in the order that ``order`` (of :meth:`value_order`) stands for: nonzero p takes vals[perm[p]]."""
+        import torch
+        self._operand(vals, "vals", self._torch_dtype(), numel=self.nnz)
+        order, scratch_bytes = order
+        if order.device != vals.device:
+            raise ValueError("vals: on another device than order")
+        scratch = torch.empty(scratch_bytes, dtype=torch.uint8, device=vals.device) if scratch_bytes else None
+        libra_plan_set_values_ordered(self.handle, vals.data_ptr(), self.val_dtype, order.data_ptr(),
+                                      scratch.data_ptr() if scratch is not None else 0, torch.cuda.current_stream().cuda_stream)

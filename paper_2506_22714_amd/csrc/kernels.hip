@@ -46,7 +46,6 @@ constexpr int SD_GROUP = 4;
 __host__ __device__ inline int sd_stage_slot(int block_in_group, int row, int slot) {
     return block_in_group * 256 + (row % 4) * 64 + (row / 4) * 16 + slot;
 }
-inline bool sorted_records(const libra_plan_t *P) { return P->vdt != LIBRA_F32 && P->o.W == W && P->o.KB == KB; }
 
 struct SpmmArgs {
     const DevTask *tasks;
@@ -1638,56 +1637,6 @@ __global__ __launch_bounds__(256) void value_products_kernel(const T *val, const
     for (int64_t i = groups * 8 + tid; i < n; i += nthreads) out[i] = to_storage<T>(factor[i] * from_storage<T>(val[i]));
 }
 
-// dst[i * stride + offset] (as T) = src[perm[i]]: new values into a packed array or into entry records
-template <class T>
-__global__ __launch_bounds__(256) void scatter_values_kernel(const T *src, const int32_t *perm, int64_t n, void *dst, int stride, int offset) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        *reinterpret_cast<T *>(reinterpret_cast<char *>(dst) + i * stride + offset) = src[perm[i]];
-}
-
-// new values into the 16-bit SDDMM output records, which carry their own CSR position (and keep their stage slot)
-__global__ __launch_bounds__(256) void refresh_record_values_kernel(const uint16_t *src, int64_t n, SdPv *rec) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        rec[i].val = (rec[i].val & 0xffff0000u) | src[rec[i].perm];
-}
-
-// the same into the value runs of the blocked entry layout
-// 16-bit values, eight consecutive destinations per thread: the permutation arrives as two 16-byte loads and the values
-// leave as one 16-byte store (a group of eight never straddles a block of the blocked layout: 64 values per block).
-// BLOCKED: the value runs of the blocked SpMM entries; otherwise a plain array of 16-bit values.
-template <bool BLOCKED>
-__global__ __launch_bounds__(256) void scatter_values16_x8_kernel(const uint16_t *src, const int32_t *perm, int64_t n, unsigned char *dst) {
-    static_assert(RES_BLOCK % 8 == 0, "a group of eight values stays inside one block");
-    const int64_t groups = n / 8;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nthreads = (int64_t)gridDim.x * blockDim.x;
-    auto where = [&](int64_t i) {
-        return BLOCKED ? dst + (i / RES_BLOCK) * (RES_BLOCK * 6) + RES_BLOCK * 4 + (i % RES_BLOCK) * 2 : dst + i * 2;
-    };
-    if (!perm) {                            // destination i takes value i
-        const bool whole = ((uintptr_t)src & 15) == 0;
-        for (int64_t g = tid; g < groups; g += nthreads) {
-            uint4 v;
-            if (whole) v = reinterpret_cast<const uint4 *>(src)[g];
-            else __builtin_memcpy(&v, src + g * 8, 16);
-            *reinterpret_cast<uint4 *>(where(g * 8)) = v;
-        }
-        for (int64_t i = groups * 8 + tid; i < n; i += nthreads) *reinterpret_cast<uint16_t *>(where(i)) = src[i];
-        return;
-    }
-    for (int64_t g = tid; g < groups; g += nthreads) {
-        const int4 p0 = reinterpret_cast<const int4 *>(perm)[2 * g], p1 = reinterpret_cast<const int4 *>(perm)[2 * g + 1];
-        const uint32_t v0 = src[p0.x], v1 = src[p0.y], v2 = src[p0.z], v3 = src[p0.w];
-        const uint32_t v4 = src[p1.x], v5 = src[p1.y], v6 = src[p1.z], v7 = src[p1.w];
-        *reinterpret_cast<uint4 *>(where(g * 8)) = uint4{v0 | v1 << 16, v2 | v3 << 16, v4 | v5 << 16, v6 | v7 << 16};
-    }
-    for (int64_t i = groups * 8 + tid; i < n; i += nthreads) *reinterpret_cast<uint16_t *>(where(i)) = src[perm[i]];
-}
-template <class T>
-__global__ __launch_bounds__(256) void scatter_blocked_values_kernel(const T *src, const int32_t *perm, int64_t n, unsigned char *dst) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        reinterpret_cast<T *>(dst + (i / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(T))) + RES_BLOCK * 4)[i % RES_BLOCK] = src[perm ? perm[i] : i];
-}
-
 inline int hip_rc(hipError_t e) { return e == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP; }
 
 // A launch has fewer than 2^32 threads (one of more is cut short without an error): a table with a wave per task takes several
@@ -2251,46 +2200,4 @@ extern "C" int libra_value_products(const void *vals, const float *factors, int6
     if (dtype == LIBRA_F16) run(half_t{});
     else run(bf16_t{});
     return hip_rc(hipGetLastError());
-}
-
-extern "C" int libra_plan_set_values(libra_plan_t *P, const void *vals, int dtype, void *stream) {
-    return libra_plan_set_values_for(P, vals, dtype, LIBRA_OP_SPMM | LIBRA_OP_SDDMM, stream);
-}
-
-extern "C" int libra_plan_set_values_for(libra_plan_t *P, const void *vals, int dtype, int ops, void *stream) {
-    if (!P) return LIBRA_ERR_NULL;
-    if (!(ops & (LIBRA_OP_SPMM | LIBRA_OP_SDDMM)) || (ops & ~(LIBRA_OP_SPMM | LIBRA_OP_SDDMM))) return LIBRA_ERR_OPTION;
-    if (!vals && P->nnz > 0) return LIBRA_ERR_NULL;
-    if (dtype != P->vdt) return LIBRA_ERR_DTYPE;
-    if (!P->dev_base) return LIBRA_ERR_NOT_UPLOADED;
-    hipStream_t s = (hipStream_t)stream;
-    const bool f16 = dtype != LIBRA_F32;       // 16-bit values are moved as raw bits
-    const int vs = P->vsize;
-    struct Seg { const int32_t *perm; void *dst; int64_t n; int stride, offset; };
-    const SubPlan &sa = P->spmm, &sd = P->sddmm;
-    const Seg segs[4] = {
-        {sa.dev.dense_perm, sa.dev.dense_val, sa.n.dense, vs, 0},
-        {sa.dev.res_perm, sa.dev.res_ent, sa.n.res, 0, 0},                  // stride 0: the blocked entry layout
-        {sd.dev.dense_perm, sd.dev.dense_pv, sd.n.dense, (int)sizeof(SdPv), 4},
-        {sd.dev.res_perm, sd.dev.res_ent, sd.n.res, 0, 0}};
-    for (int k = 0; k < 4; ++k) {
-        const Seg &g = segs[k];
-        if (g.n == 0 || !(ops & (k < 2 ? LIBRA_OP_SPMM : LIBRA_OP_SDDMM))) continue;
-        const unsigned blocks = (unsigned)std::min<int64_t>((g.n + 255) / 256, 1 << 16);
-        const unsigned blocks8 = (unsigned)std::min<int64_t>((g.n / 8 + 255) / 256 + 1, 1 << 16);
-        if (k == 2 && sorted_records(P))
-            hipLaunchKernelGGL(refresh_record_values_kernel, dim3(blocks), dim3(256), 0, s, (const uint16_t *)vals, g.n, (SdPv *)g.dst);
-        else if (g.stride == 0 && f16)
-            hipLaunchKernelGGL((scatter_values16_x8_kernel<true>), dim3(blocks8), dim3(256), 0, s, (const uint16_t *)vals, g.perm, g.n, (unsigned char *)g.dst);
-        else if (g.stride == 2 && g.offset == 0 && f16)
-            hipLaunchKernelGGL((scatter_values16_x8_kernel<false>), dim3(blocks8), dim3(256), 0, s, (const uint16_t *)vals, g.perm, g.n, (unsigned char *)g.dst);
-        else if (g.stride == 0)
-            hipLaunchKernelGGL((scatter_blocked_values_kernel<float>), dim3(blocks), dim3(256), 0, s, (const float *)vals, g.perm, g.n, (unsigned char *)g.dst);
-        else if (f16)
-            hipLaunchKernelGGL((scatter_values_kernel<uint16_t>), dim3(blocks), dim3(256), 0, s, (const uint16_t *)vals, g.perm, g.n, g.dst, g.stride, g.offset);
-        else
-            hipLaunchKernelGGL((scatter_values_kernel<float>), dim3(blocks), dim3(256), 0, s, (const float *)vals, g.perm, g.n, g.dst, g.stride, g.offset);
-        if (hipGetLastError() != hipSuccess) return LIBRA_ERR_HIP;
-    }
-    return LIBRA_OK;
 }

@@ -1630,7 +1630,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
 // Transposition of a CSR pattern on the device (the backward pass of SpMM multiplies by the transposed matrix).
 // ------------------------------------------------------------------------------------------
 namespace {
-// one wave per 16 rows: key = (column, CSR position); a sort by key lists the nonzeros column by column, rows ascending
+// one wave per 16 rows: key = (column, CSR position); a stable sort by the column (the positions ascend already) lists the nonzeros column by column, rows ascending
 __global__ __launch_bounds__(64) void k_transpose_keys(const int32_t *rowptr, const int32_t *col, int64_t M, u64 *key, int32_t *row_of) {
     const int lane = threadIdx.x;
     for (int64_t w = blockIdx.x; w * W < M; w += gridDim.x) {
@@ -1700,7 +1700,7 @@ int transpose_passes(int64_t M, int64_t Kc, int n, const int32_t *d_rowptr, cons
     // a launch has fewer than 2^32 threads: of large matrices a wave takes several groups of rows
     hipLaunchKernelGGL(k_transpose_keys, dim3((unsigned)std::min<int64_t>(nw, 1 << 24)), dim3(64), 0, s, d_rowptr, d_col, M, L.key_in, L.row_of);
     size_t sz = L.tmp_bytes;
-    if (rocprim::radix_sort_keys(L.tmp, sz, L.key_in, L.key_out, (size_t)n, 0, (unsigned)(32 + colbits), s) != hipSuccess) return LIBRA_ERR_HIP;
+    if (rocprim::radix_sort_keys(L.tmp, sz, L.key_in, L.key_out, (size_t)n, 32u, (unsigned)(32 + colbits), s) != hipSuccess) return LIBRA_ERR_HIP;
     hipLaunchKernelGGL(k_transpose_fill, dim3(blocks_for(n, 256)), dim3(256), 0, s, L.key_out, L.row_of, n, d_col_t, d_perm_t);
     hipLaunchKernelGGL(k_transpose_rowptr, dim3(blocks_for(Kc + 1, 256)), dim3(256), 0, s, L.key_out, n, Kc, d_rowptr_t);
     return hipGetLastError() == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP;

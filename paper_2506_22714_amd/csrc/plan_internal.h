@@ -168,6 +168,8 @@ LIBRA_HD inline int64_t share_samples(int64_t ngroups) { return ngroups < 256 ? 
 LIBRA_HD inline int64_t sampled_group(int64_t k, int64_t ngroups, int64_t nsample) { return k * ngroups / nsample; }
 // Lay the plan out in `dev_buf` taking the big arrays from device memory (device planner) instead of the host vectors.
 int adopt_device_arrays(libra_plan_s *plan, const DeviceSource &spmm, const DeviceSource &sddmm, void *dev_buf, size_t bytes, void *stream);
+// Are the SDDMM output records sorted by CSR position and do they carry a stage slot (16-bit values, the kernels' window and block)?
+inline bool sorted_records(const libra_plan_s *P) { return P->vdt != LIBRA_F32 && P->o.W == 16 && P->o.KB == 16; }
 // Bytes libra_plan_upload / adopt_device_arrays need for a plan with these array sizes.
 size_t plan_buffer_bytes(const libra_plan_s *plan);
 }  // namespace libra

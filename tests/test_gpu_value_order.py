@@ -1,0 +1,108 @@
+"""Values that come in another order of the nonzeros: the plan's contents, and so every product, are those of set_values with the
+permuted values.  Whole numbers make every sum exact in any order, so the comparison is bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2506_22714_amd import binding as lb
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+DTYPES = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}
+PASSES_MIN = (5 << 20) // 2         # from this many 16-bit nonzeros on the values are permuted in two passes (fp32: half as many)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def random_csr(M, Kc, nnz, seed, clustered):
+    """nnz distinct places; clustered: most of them in few columns of each window, so that both paths hold many."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    keys = torch.zeros(0, dtype=torch.int64, device="cuda")
+    while keys.numel() < nnz:
+        r = torch.randint(M, (nnz,), device="cuda", generator=g)
+        c = torch.randint(Kc, (nnz,), device="cuda", generator=g)
+        if clustered:
+            c = torch.where(torch.rand(nnz, device="cuda", generator=g) < 0.7, (r // 16 * 37 + c % 64) % Kc, c)
+        keys = torch.unique(torch.cat([keys, r * Kc + c]))
+    keys = keys[torch.randperm(keys.numel(), device="cuda", generator=g)[:nnz]].sort().values
+    rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(keys // Kc, minlength=M), 0)
+    return rowptr, (keys % Kc).int()
+
+
+def values(n, dt, seed):
+    return torch.randint(-4, 5, (n,), device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed)).to(dt)
+
+
+@pytest.mark.parametrize("dtype", list(DTYPES))
+@pytest.mark.parametrize("nnz", [1, 7, 1000, PASSES_MIN - 1, PASSES_MIN, PASSES_MIN + 32768 * 3 + 5])
+def test_ordered_values_are_permuted_values(nnz, dtype):
+    dt = DTYPES[dtype]
+    nnz = nnz - PASSES_MIN // 2 if dtype == "f32" and nnz > 1000 else nnz
+    M, Kc = (40, 50) if nnz < 1000 else (301, 203) if nnz == 1000 else (40_003, 30_011)
+    B = values(Kc * 32, dt, 5).view(Kc, 32)
+    for opts, clustered in ((dict(), True), (dict(mode=lb.MODE_SCALAR_ONLY), False), (dict(mode=lb.MODE_DENSE_ONLY), True)):
+        rowptr, col = random_csr(M, Kc, nnz, nnz, clustered)
+        p = lb.Plan.from_device_csr(M, Kc, rowptr, col, values(nnz, dt, 1), resident=True, keep_host_copy=False, flags=lb.FLAG_NO_SDDMM, **opts)
+        if nnz >= 1000 and not opts:
+            s = p.stats()
+            assert s["spmm_dense_nnz"] > 0 and s["spmm_res_nnz"] > 0
+        g = torch.Generator(device="cuda").manual_seed(2)
+        for perm in (torch.randperm(nnz, device="cuda", generator=g), torch.arange(nnz - 1, -1, -1, device="cuda")):
+            order = p.value_order(perm.int())
+            for shift in (0, 1):                         # also an array that is only aligned to its elements
+                vals = values(nnz + 1, dt, 3 + shift)[shift:shift + nnz]
+                p.set_values(vals[perm].contiguous(), lb.OP_SPMM)
+                want = p.spmm(B)
+                p.set_values(torch.zeros_like(vals), lb.OP_SPMM)
+                p.set_values_ordered(vals, order)
+                assert torch.equal(p.spmm(B), want), (opts, shift)
+        p.close()
+
+
+def test_transposed_order_of_a_skewed_matrix():
+    """The permutation of a transposition, rows and columns of very different lengths (empty tiles of a chunk, whole-chunk runs)."""
+    M, Kc, nnz = 20_000, 70_001, PASSES_MIN + 12_345
+    g = torch.Generator(device="cuda").manual_seed(7)
+    keys = torch.zeros(0, dtype=torch.int64, device="cuda")
+    while keys.numel() < nnz:
+        r = (torch.rand(nnz, device="cuda", generator=g) ** 4 * M).long()
+        c = (torch.rand(nnz, device="cuda", generator=g) ** 3 * Kc).long()
+        keys = torch.unique(torch.cat([keys, r * Kc + c]))
+    keys = keys[:nnz]
+    rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(keys // Kc, minlength=M), 0)
+    col = (keys % Kc).int()
+    rowptr_t, col_t, perm_t = lb.transpose_csr(M, Kc, rowptr, col)
+    p = lb.Plan.from_device_csr(Kc, M, rowptr_t, col_t, values(nnz, torch.float16, 1), resident=True, keep_host_copy=False)
+    vals, B = values(nnz, torch.float16, 2), values(M * 32, torch.float16, 3).view(M, 32)
+    p.set_values(vals[perm_t.long()].contiguous(), lb.OP_SPMM)
+    want = p.spmm(B)
+    p.set_values_ordered(vals, p.value_order(perm_t))
+    assert torch.equal(p.spmm(B), want)
+    p.close()
+
+
+@pytest.mark.parametrize("nnz", [1000, PASSES_MIN])
+def test_orders_that_are_no_permutations_are_refused(nnz):
+    M, Kc = (301, 203) if nnz == 1000 else (40_003, 30_011)
+    rowptr, col = random_csr(M, Kc, nnz, 1, False)
+    p = lb.Plan.from_device_csr(M, Kc, rowptr, col, values(nnz, torch.float16, 1), resident=True, keep_host_copy=False)
+    good = torch.arange(nnz, dtype=torch.int32, device="cuda")
+    p.value_order(good)
+    for at, to in ((0, nnz), (nnz - 1, -1)) + (((5, 40_000),) if nnz == PASSES_MIN else ()):
+        bad = good.clone()
+        bad[at] = to
+        with pytest.raises(lb.LibraError) as e:
+            p.value_order(bad)
+        assert e.value.code == lb.ERR["SHAPE"]
+    order = p.value_order(good)
+    for vals in (values(nnz, torch.float32, 1), values(nnz - 1, torch.float16, 1)):
+        with pytest.raises(ValueError):
+            p.set_values_ordered(vals, order)
+    p.close()
