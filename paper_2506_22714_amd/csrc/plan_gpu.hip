@@ -4,19 +4,17 @@
 // already in device memory.  The window-by-window loops of the host code become flat passes
 // over arrays plus prefix sums:
 //
-//   1. the 16 sorted rows of a window are merged into (column, row) order in two passes in which
-//      every nonzero finds its place by searching the lists it is merged with, which puts the
-//      nonzeros of each column vector next to each other (the "census");
-//   2. head flags + a prefix sum number the vectors; a sort of those with more than one nonzero
-//      gives the (NNZ descending, column ascending) order - the order of the SDDMM blocks and of
-//      the vectors that fill the padding of the last SpMM block;
-//   3. per window: how many vectors reach the SpMM threshold, how many fill padding, how many
-//      SDDMM blocks reach the block threshold (their NNZ never increases along the order, so a
-//      binary search finds the cut); prefix sums give block offsets;
-//   4. vectors are scattered to their slots, blocks build bitmaps by ballots, packed values go
+//   1. the nonzeros of every window are sorted by (column, row), a tile of them at a time in LDS, which
+//      puts the nonzeros of each column vector next to each other (the "census"); a vector is named by
+//      the place of its first nonzero.  The vectors of each NNZ are counted per window;
+//   2. per window, from those counts: how many vectors reach the SpMM threshold, how many fill padding,
+//      how many SDDMM blocks reach the block threshold (their NNZ never increases along the order
+//      (NNZ descending, column ascending), so a binary search finds the cut); prefix sums give block offsets;
+//   3. the vectors in dense blocks go to their slots (the order is that of the SDDMM blocks and of the vectors
+//      that fill the padding of the last SpMM block), blocks build bitmaps by ballots, packed values go
 //      to the position given by the popcount of the bits below theirs;
-//   5. nonzeros outside the dense vectors are flagged in CSR order; prefix sums give residual
-//      positions; per window the load-balancing rule of Section 4.3 emits the task records.
+//   4. nonzeros outside the dense vectors are numbered in CSR order by prefix sums; per window the
+//      load-balancing rule of Section 4.3 emits the task records.
 //
 // Radix sorts and prefix sums are rocPRIM device primitives; everything else is written here.
 // The arrays are produced in the host planner's format in the caller's workspace, copied to the
@@ -83,8 +81,8 @@ Sizes make_sizes(int64_t M, int64_t n, const Resolved &o) {
 struct SubOut {      // one sub-plan in the host planner's format
     int32_t *slotvec, *blk_cols, *blknnz, *blk_valptr, *blkmask, *blkncols, *dense_perm;
     u64 *bitmap;
-    uint8_t *dense_val, *res_val, *dflag;
-    int32_t *resf, *rescan, *res_perm, *res_row, *res_col;
+    uint8_t *dense_val, *res_val;
+    int32_t *rescan, *res_perm, *res_row, *res_col;
     int32_t *nb, *ndv, *blkptr, *ntasks, *tbase;
     libra_task_t *tasks;
 };
@@ -101,13 +99,24 @@ struct OrderScratch {
 };
 constexpr int MAX_PIECES = 4096;
 
+// Tiles of the census (see k_tile_sort).
+constexpr int TILE_THREADS = 256, TILE_EACH = 7;             // an odd number of places per thread: their LDS accesses fall into different banks
+constexpr int TILE_CAP = TILE_THREADS * TILE_EACH, TILE_STEP = TILE_CAP - W;
+inline int tile_count(int64_t n) { return (int)((n + TILE_STEP - 1) / TILE_STEP); }
+struct Tiles {
+    int32_t *pos;       // per boundary: its place,
+    int32_t *win;       // its window,
+    int32_t *split;     // and per row of the window the first nonzero (CSR position) that lies behind it
+    int32_t *tail;      // per tile: the vectors of each NNZ in the part of the next boundary's window that it holds
+};
+
 struct Layout {
-    int32_t *win_ptr, *spos, *hflag, *vid, *einfo, *row_of, *rowbase;
-    u64 *key_in, *key_out, *ctr;
-    uint32_t *mkey_in, *mkey_out;
-    int32_t *mflag, *mscan, *mvec_in, *mvec_out;
-    int32_t *vfirst, *vinfo, *vcol, *vwin, *srank, *scnt, *cum, *tflag, *taud, *win_vptr;
-    int32_t *ntau, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
+    int32_t *win_ptr, *row_of, *rowbase, *scol, *spos;
+    uint16_t *vmask;
+    uint8_t *dense;
+    u64 *ctr;
+    Tiles tiles;
+    int32_t *hist, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
     OrderScratch o;
     int32_t *sizes, *medium_rows, *long_rows, *long_lens;
@@ -121,6 +130,10 @@ struct RowsOfLength {                   // more than `above` and at most `most` 
     int above, most;
     __device__ bool operator()(int32_t i) const { const int n = rowptr[i + 1] - rowptr[i]; return n > above && n <= most; }
 };
+struct NotDense {                       // of a nonzero's bits in `dense` (1: in a block of the SpMM sub-plan, 2: of the SDDMM one)
+    unsigned bit;
+    __host__ __device__ int32_t operator()(uint8_t f) const { return f & bit ? 0 : 1; }
+};
 size_t order_items(const Sizes &z) { return (size_t)std::max(z.tasks_a_max, std::max(z.tasks_d_max, z.segs_d_max)); }
 int64_t order_slots(int64_t tasks) { return 2 * tasks + 64; }      // the die-aware orders add empty tasks
 
@@ -131,8 +144,11 @@ size_t rocprim_temp_bytes(const Sizes &z) {
     best = std::max(best, sz);
     const size_t m = order_items(z) + 16;
     sz = 0;
-    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr,
-                              std::max(m, (size_t)z.n), 0, 32);
+    (void)rocprim::exclusive_scan(nullptr, sz, rocprim::make_transform_iterator((const uint8_t *)nullptr, NotDense{1}), (int32_t *)nullptr, (int32_t)0, (size_t)(z.n + 1),
+                            rocprim::plus<int32_t>());
+    best = std::max(best, sz);
+    sz = 0;
+    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, m, 0, 32);
     best = std::max(best, sz);
     sz = 0;
     (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 64);
@@ -165,31 +181,18 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     L.long_rows = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
     L.long_lens = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
     L.win_ptr = A.take<int32_t>(nw + 1);
-    L.key_in = A.take<u64>(n);
-    L.key_out = A.take<u64>(n);
+    const size_t boundaries = (size_t)tile_count(z.n) + 1;
+    L.tiles.pos = A.take<int32_t>(boundaries);
+    L.tiles.win = A.take<int32_t>(boundaries);
+    L.tiles.split = A.take<int32_t>(boundaries * W);
+    L.tiles.tail = A.take<int32_t>(boundaries * W);
+    L.hist = A.take<int32_t>(nw * W);
+    L.scol = A.take<int32_t>(n);
     L.spos = A.take<int32_t>(n);
-    L.hflag = A.take<int32_t>(n + 1);
-    L.vid = A.take<int32_t>(n + 1);
-    L.einfo = A.take<int32_t>(n);
+    L.vmask = A.take<uint16_t>(n);
+    L.dense = A.take<uint8_t>(n + 1);
     L.row_of = A.take<int32_t>(n);
     L.rowbase = A.take<int32_t>((size_t)z.M + 1);
-    L.vfirst = A.take<int32_t>(n);
-    L.vinfo = A.take<int32_t>(n);
-    L.vcol = A.take<int32_t>(n);
-    L.vwin = A.take<int32_t>(n);
-    L.mkey_in = A.take<uint32_t>(n);
-    L.mkey_out = A.take<uint32_t>(n);
-    L.mflag = A.take<int32_t>(n + 1);
-    L.mscan = A.take<int32_t>(n + 1);
-    L.mvec_in = A.take<int32_t>(n);
-    L.mvec_out = A.take<int32_t>(n);
-    L.srank = A.take<int32_t>(n);
-    L.scnt = A.take<int32_t>(n + 1);
-    L.cum = A.take<int32_t>(n + 1);
-    L.tflag = A.take<int32_t>(n + 1);
-    L.taud = A.take<int32_t>(n + 1);
-    L.win_vptr = A.take<int32_t>(nw + 1);
-    L.ntau = A.take<int32_t>(nw);
     L.nzero = A.take<int32_t>(nw + 1);
     L.zbase = A.take<int32_t>(nw + 1);
     L.nres = A.take<int32_t>(nw + 1);
@@ -207,8 +210,6 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
         s->blkncols = A.take<int32_t>(nb);
         s->dense_perm = A.take<int32_t>(n);
         s->dense_val = A.take<uint8_t>(n * vsize);
-        s->dflag = A.take<uint8_t>(n);
-        s->resf = A.take<int32_t>(n + 1);
         s->rescan = A.take<int32_t>(n + 1);
         s->res_perm = A.take<int32_t>(n);
         s->res_row = A.take<int32_t>(n);
@@ -259,273 +260,453 @@ __global__ __launch_bounds__(256) void k_row_lengths(const int32_t *rowptr, cons
     if (i < n) len[i] = rowptr[rows[i] + 1] - rowptr[rows[i]];
 }
 
-// The census: the nonzeros of every window in (column, row) order.  A window's rows are sorted already, so this is a merge of
-// 16 lists, done as two merges of four: a nonzero's place is its index in its own list plus, for each of the other three, how
-// many come before it there.  Neighbouring nonzeros take nearly the same path through a list, so the searches run from the L1s,
-// and the three go on together because each is a chain of loads.  Bound by the vector ALUs (some 30 instructions per step).  GAT
-// graph (59.7 M nonzeros): 1.4 + 1.6 ms; one pass with searches in all 15 other rows 4.1, keys and a segmented radix sort with one
-// workgroup per window, which the hub windows hold up, 7.4 ms.
-constexpr int MERGE = 4;
-static_assert(W == MERGE * MERGE, "two merges of MERGE lists");
-// sum over the lists of the elements for which less(value) holds (they come first); list u is values[first[u] .. + left[u])
-template <class T, class Less>
-__device__ inline int places_before(const T *values, int n, const int (&first)[MERGE], int (&left)[MERGE], Less less) {
-    int at[MERGE], sum = 0;
-#pragma unroll
-    for (int u = 0; u < MERGE; ++u) at[u] = first[u];
-    static_assert(MERGE == 4, "the loop's condition");
-    while (left[0] | left[1] | left[2] | left[3]) {
-        T v[MERGE];
-#pragma unroll
-        for (int u = 0; u < MERGE; ++u) v[u] = values[min(at[u] + (left[u] >> 1), n - 1)];
-#pragma unroll
-        for (int u = 0; u < MERGE; ++u) {
-            const int half = left[u] >> 1;
-            const bool before = left[u] > 0 && less(u, v[u]);
-            at[u] = before ? at[u] + half + 1 : at[u];
-            left[u] = before ? left[u] - half - 1 : half;
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < MERGE; ++u) sum += at[u] - first[u];
-    return sum;
-}
-// First merge, from CSR order: groups of MERGE rows.  Also a nonzero's row and the checks the host planner makes.
-__global__ __launch_bounds__(256) void k_merge_rows(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n,
-                                                    u64 *key_out, int32_t *pos_out, int32_t *row_of, u64 *ctr) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    // the rows of the wave's first and last nonzero once per wave (rowptr[lo] <= p < rowptr[lo + 1]), then between them
-    const int p0 = __builtin_amdgcn_readfirstlane(p), p1 = (int)min((int64_t)p0 + 63, (int64_t)n - 1);
+// The checks of the host planner on the columns, and every nonzero's row.  A workgroup takes ROWS_CHUNK nonzeros: the rows that
+// begin among them mark their first nonzero in LDS (of rows that begin at one place the last one counts, the others are empty), and a
+// nonzero's row is the largest mark up to it.  GAT graph: 217 us; a search through rowptr per wave of 64 nonzeros 601.
+constexpr int ROWS_EACH = 8, ROWS_CHUNK = 256 * ROWS_EACH;
+__global__ __launch_bounds__(256) void k_rows(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n, int32_t *row_of, u64 *ctr) {
+    __shared__ __attribute__((aligned(16))) int32_t mark[ROWS_CHUNK];
+    __shared__ int32_t wave_max[4];
+    const int base = (int)(blockIdx.x * (unsigned)ROWS_CHUNK), end = (int)min((int64_t)base + ROWS_CHUNK, (int64_t)n), tid = threadIdx.x;
+    for (int i = tid; i < ROWS_CHUNK; i += 256) mark[i] = -1;
+    // first and last row, the same search in every lane: rowptr[lo] <= base < rowptr[lo + 1], and for end - 1
     int64_t lo = 0, hi = M;
     while (hi - lo > 1) {
         const int64_t mid = (lo + hi) >> 1;
-        if (rowptr[mid] <= p0) lo = mid; else hi = mid;
+        if (rowptr[mid] <= base) lo = mid; else hi = mid;
     }
     int64_t step = 1;
-    while (lo + step < M && rowptr[lo + step] <= p1) step <<= 1;
-    hi = min(M, lo + step);                 // rowptr[hi] > p1
+    while (lo + step < M && rowptr[lo + step] <= end - 1) step <<= 1;
+    int64_t last = lo;
+    hi = min(M, lo + step);                 // rowptr[hi] > end - 1
+    while (hi - last > 1) {
+        const int64_t mid = (last + hi) >> 1;
+        if (rowptr[mid] <= end - 1) last = mid; else hi = mid;
+    }
+    __syncthreads();
+    if (tid == 0) mark[0] = (int32_t)lo;
+    for (int64_t r = lo + 1 + tid; r <= last; r += 256) atomicMax(&mark[rowptr[r] - base], (int32_t)r);      // 0 < place < end - base
+    __syncthreads();
+    int row[ROWS_EACH], top = -1;
+#pragma unroll
+    for (int j = 0; j < ROWS_EACH; ++j) {
+        top = max(top, mark[tid * ROWS_EACH + j]);
+        row[j] = top;
+    }
+    int scan = top;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const int x = __shfl_up(scan, m, 64);
+        if (tid % 64 >= m) scan = max(scan, x);
+    }
+    if (tid % 64 == 63) wave_max[tid / 64] = scan;
+    int before = __shfl_up(scan, 1, 64);
+    if (tid % 64 == 0) before = -1;
+    __syncthreads();
+    for (int v = 0; v < tid / 64; ++v) before = max(before, wave_max[v]);
+#pragma unroll
+    for (int j = 0; j < ROWS_EACH; ++j) mark[tid * ROWS_EACH + j] = max(row[j], before);
+    __syncthreads();
+    unsigned bad = 0;
+#pragma unroll
+    for (int j = 0; j < ROWS_EACH; ++j) {
+        const int i = tid + j * 256, p = base + i;
+        if (p >= end) continue;
+        const int r = mark[i], c = col[p];
+        row_of[p] = r;
+        if (c < 0 || c >= Kc) bad |= 1u;
+        else if (p > 0 && col[p - 1] >= c && (i > 0 ? mark[i - 1] == r : rowptr[r] < p)) bad |= 2u;
+    }
+    if (bad) atomicOr(&ctr[C_ERR], (u64)bad);
+}
+
+// 16 lanes per boundary, one per row: the largest column with at most `target` of the window's nonzeros before it, by bisection;
+// every lane keeps the part of its row between the columns that bound it.
+__global__ __launch_bounds__(256) void k_tile_splits(const int32_t *rowptr, const int32_t *col, const int32_t *win_ptr, int64_t M, int64_t Kc, int n, int nw, int tiles, Tiles T) {
+    const int k = (int)((blockIdx.x * blockDim.x + threadIdx.x) / W), r = threadIdx.x % W;
+    if (k > tiles) return;
+    if (k == tiles) {
+        if (r == 0) { T.pos[k] = n; T.win[k] = nw; }
+        T.split[(int64_t)k * W + r] = n;
+        return;
+    }
+    const int at = k * TILE_STEP;           // < n
+    int w = 0, end = nw;                    // win_ptr[w] <= at < win_ptr[end]
+    while (end - w > 1) {
+        const int mid = (w + end) >> 1;
+        if (win_ptr[mid] <= at) w = mid; else end = mid;
+    }
+    const int64_t row = (int64_t)w * W + r;
+    const int first = rowptr[min(row, M)], target = at - win_ptr[w];
+    int a = first, b = rowptr[min(row + 1, M)];
+    int64_t lo = 0, hi = Kc;                // nonzeros before column lo: at most target; before hi: more
+    auto sum = [](int x) {
+#pragma unroll
+        for (int m = 1; m < W; m <<= 1) x += __shfl_xor(x, m, W);
+        return x;
+    };
     while (hi - lo > 1) {
         const int64_t mid = (lo + hi) >> 1;
-        if (rowptr[mid] <= p) lo = mid; else hi = mid;
-    }
-    const int c = col[p];
-    const int row_start = rowptr[lo];
-    unsigned bad = 0;
-    if (c < 0 || c >= Kc) bad = 1u;
-    else if (p > row_start && col[p - 1] >= c) bad = 2u;
-    row_of[p] = (int32_t)lo;
-    if (bad) atomicOr(&ctr[C_ERR], (u64)bad);
-    const int64_t r0 = lo - lo % MERGE;
-    const int own = (int)(lo - r0);
-    int first[MERGE + 1], left[MERGE];
-#pragma unroll
-    for (int u = 0; u <= MERGE; ++u) first[u] = rowptr[min(r0 + u, M)];
-#pragma unroll
-    for (int u = 0; u < MERGE; ++u) left[u] = u == own ? 0 : first[u + 1] - first[u];
-    const int f[MERGE] = {first[0], first[1], first[2], first[3]};
-    // equal columns: the row above comes first
-    const int to = first[0] + (p - row_start) + places_before((const uint32_t *)col, n, f, left, [&](int u, uint32_t v) { return v < (uint32_t)c + (u < own ? 1u : 0u); });
-    // in range for any input: the index in the row plus at most the other rows' lengths
-    key_out[to] = ((u64)(uint32_t)c << 4) | (u64)(lo % W);
-    pos_out[to] = p;
-}
-// Second merge: the groups of a window.  Keys (column, row in window) differ.
-__global__ __launch_bounds__(256) void k_merge_groups(const int32_t *rowptr, int64_t M, const u64 *key, const int32_t *pos, const int32_t *row_of, int n,
-                                                      u64 *key_out, int32_t *spos) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const u64 k = key[e];
-    const int64_t r = row_of[e], r0 = r - r % W;           // a place's window and group are those of the nonzero there in CSR order
-    const int own = (int)(r % W) / MERGE;
-    int first[MERGE + 1], left[MERGE];
-#pragma unroll
-    for (int u = 0; u <= MERGE; ++u) first[u] = rowptr[min(r0 + u * MERGE, M)];
-    int own_first = first[0];
-#pragma unroll
-    for (int u = 0; u < MERGE; ++u) {
-        left[u] = u == own ? 0 : first[u + 1] - first[u];
-        own_first = u == own ? first[u] : own_first;
-    }
-    const int f[MERGE] = {first[0], first[1], first[2], first[3]};
-    const int to = first[0] + (e - own_first) + places_before(key, n, f, left, [&](int, u64 v) { return v < k; });
-    key_out[to] = k;
-    spos[to] = pos[e];
-}
-
-// Per sorted nonzero: is it the first of its column vector; if so, the vector's NNZ and row mask.
-__global__ __launch_bounds__(256) void k_census(const u64 *skey, const int32_t *win_ptr, const int32_t *row_of, int n, int32_t *hflag, int32_t *einfo) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e == n) hflag[n] = 0;               // the scans take one entry more, here and below
-    if (e >= n) return;
-    const u64 key = skey[e];
-    const u64 c = key >> 4;
-    const int w = row_of[e] / W;            // a place's window is that of the nonzero there in CSR order
-    const int ws = win_ptr[w], we = win_ptr[w + 1];
-    const bool head = e == ws || (skey[e - 1] >> 4) != c;
-    int info = 0;
-    if (head) {
-        int cnt = 1;
-        unsigned mask = 1u << (unsigned)(key & 15);
-        for (int k = 1; k < W; ++k) {
-            if (e + k >= we) break;
-            const u64 kk = skey[e + k];
-            if ((kk >> 4) != c) break;
-            ++cnt;
-            mask |= 1u << (unsigned)(kk & 15);
+        int x = a, y = b;
+        while (x < y) {
+            const int z = (x + y) >> 1;
+            if ((int64_t)col[z] < mid) x = z + 1; else y = z;
         }
-        info = cnt | (int)(mask << 8);
+        const int before = sum(x - first);
+        if (before <= target) { lo = mid; a = x; } else { hi = mid; b = x; }
+        if (before == target) break;
     }
-    hflag[e] = head ? 1 : 0;
-    einfo[e] = info;
+    const int before = sum(a - first);
+    if (r == 0) { T.pos[k] = at - target + before; T.win[k] = w; }
+    T.split[(int64_t)k * W + r] = a;
 }
 
-// (few workgroups, each over many nonzeros: one add to the shared counter per workgroup and not per 256 nonzeros - 233,000
-// adds to one address took 2.8 ms)
-__global__ __launch_bounds__(256) void k_vectors(const u64 *skey, const int32_t *hflag, const int32_t *vid, const int32_t *einfo,
-                                                 const int32_t *row_of, int n, int tau_a,
-                                                 int32_t *vfirst, int32_t *vinfo, int32_t *vcol, int32_t *vwin, int32_t *tflag, int32_t *mflag, u64 *ctr) {
-    __shared__ int ones;
-    if (threadIdx.x == 0) ones = 0;
-    __syncthreads();
-    int mine = 0;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        if (hflag[e]) {
-            const int v = vid[e];
-            const int info = einfo[e];
-            const int cnt = info & 0xff;
-            vfirst[v] = (int)e;
-            vinfo[v] = info;
-            vcol[v] = (int)(skey[e] >> 4);
-            vwin[v] = row_of[e] / W;
-            tflag[v] = cnt >= tau_a ? 1 : 0;
-            mflag[v] = cnt > 1 ? 1 : 0;
-            mine += cnt == 1;
+// The lanes of a wave that are `valid` and have the same 4-bit `cls` as `mine`.
+struct ClassPlanes {
+    u64 plane[4], valid;
+    __device__ ClassPlanes(int cls, bool ok) {
+        valid = __ballot(ok);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) plane[k] = __ballot(cls >> k & 1);
+    }
+    __device__ u64 same(int cls) const {
+        u64 m = valid;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m &= cls >> k & 1 ? plane[k] : ~plane[k];
+        return m;
+    }
+};
+
+// A workgroup per tile.  The nonzeros of equal row number in their windows form a list that is sorted by (window, column): the tile is 16
+// such lists, merged in four rounds of pairs; in a round a thread finds where its places begin in the two lists by bisection and
+// merges from there.  Bound by the vector ALUs and LDS.  GAT graph (59.7 M nonzeros), rows, boundaries and sort: 0.22 + 0.15 + 0.64 ms (0.76
+// with the masks and counts); two merges of four lists with a search through the other lists per nonzero took 3.06 ms, one pass over all
+// 16 rows 4.1, keys and a segmented radix sort 7.4.
+__global__ __launch_bounds__(TILE_THREADS) void k_tile_sort(const int32_t *rowptr, const int32_t *col, const int32_t *win_ptr, const int32_t *row_of, int64_t M, Tiles T,
+                                                            const u64 *ctr, int32_t *scol, int32_t *spos, uint16_t *vmask, int32_t *hist) {
+    __shared__ u64 key[TILE_CAP];
+    __shared__ int32_t pos[TILE_CAP];
+    __shared__ int32_t run_first[2 * W + 1], run_at[2 * W + 2];
+    __shared__ int32_t list[W + 1], wave_count[TILE_THREADS / 64][W], tail[W];
+    if (ctr[C_ERR]) return;                 // unsorted rows: nothing below would hold (the host has the error before it reads on)
+    const int k = blockIdx.x, tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    const int w0 = T.win[k], w1 = T.win[k + 1], out = T.pos[k], count = min(T.pos[k + 1] - out, TILE_CAP);
+    if (tid < 64) {
+        // up to 33 stretches of CSR positions: rows of the first window, whole windows, rows of the last window
+        int from = 0, to = 0;
+        if (tid < W) {
+            from = T.split[(int64_t)k * W + tid];
+            to = w0 == w1 ? T.split[(int64_t)(k + 1) * W + tid] : rowptr[min((int64_t)w0 * W + tid + 1, M)];
+        } else if (tid == W && w1 > w0) {
+            from = win_ptr[w0 + 1];
+            to = win_ptr[w1];
+        } else if (tid > W && tid <= 2 * W && w1 > w0) {
+            from = rowptr[min((int64_t)w1 * W + (tid - W - 1), M)];
+            to = T.split[(int64_t)(k + 1) * W + (tid - W - 1)];
         }
-        if (e == n - 1) {
-            const int nv = vid[e] + hflag[e];
-            ctr[C_NV] = (u64)nv;
-            tflag[nv] = 0;
-            mflag[nv] = 0;
+        int sum = to - from;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int x = __shfl_up(sum, m, 64);
+            if (lane >= m) sum += x;
+        }
+        if (tid <= 2 * W) {
+            run_first[tid] = from;
+            run_at[tid + 1] = sum;
+        }
+        if (tid == 0) run_at[0] = 0;
+    }
+    __syncthreads();
+    // a wave takes 448 neighbouring nonzeros, and counts those of equal row number before each
+    u64 kk[TILE_EACH];
+    int pp[TILE_EACH], rank[TILE_EACH], seen = 0;            // seen: lane c < 16, of row number c
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int i = wave * (64 * TILE_EACH) + j * 64 + lane;
+        const bool ok = i < count;
+        int lo = 0, hi = 2 * W + 1;         // run_at[lo] <= i < run_at[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (run_at[mid] <= i) lo = mid; else hi = mid;
+        }
+        const int p = ok ? run_first[lo] + (i - run_at[lo]) : run_first[0];
+        pp[j] = p;
+    }
+    {
+        int rows[TILE_EACH], cols[TILE_EACH];
+#pragma unroll
+        for (int j = 0; j < TILE_EACH; ++j) {
+            const bool ok = wave * (64 * TILE_EACH) + j * 64 + lane < count;
+            rows[j] = ok ? row_of[pp[j]] : 0;
+            cols[j] = ok ? col[pp[j]] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < TILE_EACH; ++j) {
+            const bool ok = wave * (64 * TILE_EACH) + j * 64 + lane < count;
+            const int cls = rows[j] % W;
+            kk[j] = (u64)(rows[j] / W - w0) << 36 | (u64)(uint32_t)cols[j] << 4 | (u64)cls;
+            const ClassPlanes planes(cls, ok);
+            rank[j] = __popcll(planes.same(cls) & ((1ull << lane) - 1ull)) + __shfl(seen, cls, 64);
+            seen += lane < W ? __popcll(planes.same(lane)) : 0;
         }
     }
-    if (mine) atomicAdd(&ones, mine);
+    if (lane < W) wave_count[wave][lane] = seen;
     __syncthreads();
-    if (threadIdx.x == 0 && ones) atomicAdd(&ctr[C_NNZ1], (u64)ones);
-}
-
-__global__ __launch_bounds__(256) void k_win_vptr(const int32_t *win_ptr, const int32_t *vid, int nw, int n, const u64 *ctr, int32_t *win_vptr) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t > nw) return;
-    const int p = win_ptr[t];
-    win_vptr[t] = p < n ? vid[p] : (int)ctr[C_NV];
-}
-
-// The (NNZ descending, column ascending) order of a window's vectors: those of one nonzero - nine in ten of them on graphs -
-// are its end, already in column order; only the others are sorted, by (window, NNZ) with a stable sort (sorting all of them
-// by (NNZ, column) window by window, with one workgroup per window: 3.3 ms for 49 M vectors).
-__global__ __launch_bounds__(256) void k_multi_keys(const int32_t *mflag, const int32_t *mscan, const int32_t *vinfo, const int32_t *vwin, int nv,
-                                                    uint32_t *key, int32_t *vec) {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nv || !mflag[v]) return;
-    key[mscan[v]] = (uint32_t)vwin[v] << 4 | (uint32_t)(W - (vinfo[v] & 0xff));
-    vec[mscan[v]] = v;
-}
-// Per position of that order: the vector's NNZ; per vector: its rank in its window.
-__global__ __launch_bounds__(256) void k_sorted(const int32_t *mvec, int nm, const int32_t *mflag, const int32_t *mscan, const int32_t *vinfo, const int32_t *vwin,
-                                                const int32_t *win_vptr, int nv, int32_t *scnt, int32_t *srank) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == nv) scnt[nv] = 0;
-    if (i >= nv) return;
-    if (i < nm) {
-        const int v = mvec[i], base = win_vptr[vwin[v]], rank = i - mscan[base];
-        scnt[base + rank] = vinfo[v] & 0xff;
-        srank[v] = rank;
+    if (tid < 64) {
+        int total = 0;
+        if (tid < W)
+            for (int v = 0; v < TILE_THREADS / 64; ++v) {
+                const int x = wave_count[v][tid];
+                wave_count[v][tid] = total;
+                total += x;
+            }
+        int sum = total;
+#pragma unroll
+        for (int m = 1; m < W; m <<= 1) {
+            const int x = __shfl_up(sum, m, 64);
+            if (lane >= m) sum += x;
+        }
+        if (tid < W) list[tid + 1] = sum;
+        if (tid == 0) list[0] = 0;
     }
-    if (!mflag[i]) {
-        const int w = vwin[i], base = win_vptr[w];
-        const int rank = mscan[win_vptr[w + 1]] - mscan[base] + (i - base) - (mscan[i] - mscan[base]);
-        scnt[base + rank] = 1;
-        srank[i] = rank;
-    }
-}
-
-// The sampled column-sharing statistic (one workgroup per sampled group of LIBRA_LOCALITY_WINDOWS windows): how
-// many distinct columns the windows have together (a vector counts unless an earlier window of the group has its
-// column) and one by one.
-__global__ __launch_bounds__(256) void k_share(const int32_t *win_vptr, const int32_t *vcol, int nw, int64_t ngroups, int64_t nsample, u64 *ctr) {
-    __shared__ int together;
-    if (threadIdx.x == 0) together = 0;
     __syncthreads();
-    const int64_t g = sampled_group(blockIdx.x, ngroups, nsample);
-    const int w0 = (int)(g * LIBRA_LOCALITY_WINDOWS), w1 = (int)min((int64_t)nw, (g + 1) * LIBRA_LOCALITY_WINDOWS);
-    const int v0 = win_vptr[w0], v1 = win_vptr[w1];
-    int mine = 0;
-    // the group's vectors are dealt to the gridDim.y workgroups of the group
-    for (int v = v0 + (int)(blockIdx.y * blockDim.x + threadIdx.x); v < v1; v += (int)(blockDim.x * gridDim.y)) {
-        const int c = vcol[v];
-        // first position with column >= c in each window before the vector's own, together: the searches are chains of loads
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        if (wave * (64 * TILE_EACH) + j * 64 + lane < count) {
+            const int cls = (int)(kk[j] & 15), to = list[cls] + wave_count[wave][cls] + rank[j];
+            key[to] = kk[j];
+            pos[to] = pp[j];
+        }
+    }
+    __syncthreads();
+    const int o0 = tid * TILE_EACH;
+#pragma unroll 1
+    for (int width = 1; width < W; width <<= 1) {
+        int g = 0;                          // the pair of lists that this thread's first place lies in
+        while (g + 2 * width < W && list[g + 2 * width] <= o0) g += 2 * width;
+        int s = list[g], m = list[g + width], e = list[g + 2 * width];
+        int ia = s, ib = m;
+        if (o0 < count) {
+            const int d = o0 - s;
+            int lo = max(0, d - (e - m)), hi = min(d, m - s);
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (key[s + mid] < key[m + d - 1 - mid]) lo = mid + 1; else hi = mid;
+            }
+            ia = s + lo;
+            ib = m + d - lo;
+        }
+        constexpr u64 NONE = ~0ull;
+        u64 ka = o0 < count && ia < m ? key[ia] : NONE, kb = o0 < count && ib < e ? key[ib] : NONE;
+#pragma unroll
+        for (int j = 0; j < TILE_EACH; ++j) {
+            if (o0 + j < count) {
+                if (o0 + j == e) {          // on to the next pair that holds something
+                    do {
+                        g += 2 * width;
+                        s = list[g]; m = list[g + width]; e = list[g + 2 * width];
+                    } while (e == o0 + j);
+                    ia = s; ib = m;
+                    ka = ia < m ? key[ia] : NONE;
+                    kb = ib < e ? key[ib] : NONE;
+                }
+                const bool first = ka < kb;
+                kk[j] = first ? ka : kb;
+                pp[j] = pos[first ? ia : ib];
+                if (first) {
+                    ++ia;
+                    ka = ia < m ? key[ia] : NONE;
+                } else {
+                    ++ib;
+                    kb = ib < e ? key[ib] : NONE;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TILE_EACH; ++j)
+            if (o0 + j < count) {
+                key[o0 + j] = kk[j];
+                pos[o0 + j] = pp[j];
+            }
+        __syncthreads();
+    }
+    // The places leave with what the rest of the planner asks of them: column, CSR position and, at the first place of a column vector,
+    // the rows it holds.
+    int cls[TILE_EACH], rel[TILE_EACH];     // of a vector's first place: NNZ - 1 and window; otherwise -1
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int i = tid + j * TILE_THREADS;
+        cls[j] = -1;
+        rel[j] = 0;
+        if (i >= count) continue;
+        const u64 mine = key[i], vec = mine >> 4;
+        unsigned rows = 0;
+        if (i == 0 || key[i - 1] >> 4 != vec) {
+            rows = 1u << (unsigned)(mine & 15);
+            for (int q = i + 1; q < count && key[q] >> 4 == vec; ++q) rows |= 1u << (unsigned)(key[q] & 15);
+            cls[j] = __popc(rows) - 1;
+            rel[j] = (int)(mine >> 36);
+        }
+        scol[out + i] = (int32_t)(uint32_t)vec;
+        spos[out + i] = pos[i];
+        vmask[out + i] = (uint16_t)rows;
+    }
+    __syncthreads();
+    // vectors of each NNZ per window, in LDS (over `pos`) if the tile's windows are few enough, which they are unless most are nearly empty
+    const int last = w1 - w0, windows = last + 1;
+    const bool here = windows <= TILE_CAP / W;
+    if (here)
+        for (int i = tid; i < windows * W; i += TILE_THREADS) pos[i] = 0;
+    if (tid < W) tail[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        // the vectors of one nonzero in the wave's first window, most of all, are added as one
+        const int rel0 = __builtin_amdgcn_readfirstlane(rel[j]);
+        const bool single = cls[j] == 0 && rel[j] == rel0;
+        const u64 singles = __ballot(single);
+        const int add = single ? (lane == __ffsll(singles) - 1 ? __popcll(singles) : 0) : 1;
+        if (cls[j] < 0 || add == 0) continue;
+        if (here) {
+            atomicAdd(&pos[rel[j] * W + cls[j]], add);
+        } else {
+            atomicAdd(&hist[((int64_t)w0 + rel[j]) * W + cls[j]], add);
+            if (rel[j] == last) atomicAdd(&tail[cls[j]], add);
+        }
+    }
+    __syncthreads();
+    if (here) {
+        for (int i = tid; i < windows * W; i += TILE_THREADS) {
+            const int v = pos[i], w = i / W;
+            if (v == 0) continue;
+            if (w > 0 && w < last) hist[(int64_t)w0 * W + i] = v;          // the whole window is in this tile
+            else atomicAdd(&hist[(int64_t)w0 * W + i], v);
+        }
+        if (tid < W) tail[tid] = pos[last * W + tid];
+        __syncthreads();
+    }
+    if (tid < W) T.tail[(int64_t)k * W + tid] = tail[tid];
+}
+
+// The sampled column-sharing statistic: how many distinct columns the windows of each sampled group of LIBRA_LOCALITY_WINDOWS windows
+// have together (a vector counts unless an earlier window of the group has its column) and one by one.  The places of all sampled
+// groups are one list, dealt to the threads: a hub's group has more of them than all others together.  GAT graph: 223 us, with 64
+// workgroups for each group 493.
+constexpr int SHARE_SAMPLES = 256;
+__global__ __launch_bounds__(SHARE_SAMPLES) void k_share(const int32_t *win_ptr, const int32_t *scol, const uint16_t *vmask, int nw, int64_t ngroups, int nsample, u64 *ctr) {
+    __shared__ int64_t at[SHARE_SAMPLES + 1], wave_sum[SHARE_SAMPLES / 64];
+    __shared__ int32_t first_window[SHARE_SAMPLES];
+    __shared__ int together, apart;
+    const int tid = threadIdx.x;
+    {
+        const int w0 = (int)(sampled_group(min(tid, nsample - 1), ngroups, nsample) * LIBRA_LOCALITY_WINDOWS);
+        first_window[tid] = w0;
+        int64_t sum = tid < nsample ? win_ptr[min(w0 + LIBRA_LOCALITY_WINDOWS, nw)] - win_ptr[w0] : 0;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int64_t x = __shfl_up(sum, m, 64);
+            if (tid % 64 >= m) sum += x;
+        }
+        if (tid % 64 == 63) wave_sum[tid / 64] = sum;
+        if (tid == 0) { together = apart = 0; at[0] = 0; }
+        __syncthreads();
+        for (int v = 0; v < tid / 64; ++v) sum += wave_sum[v];
+        at[tid + 1] = sum;
+        __syncthreads();
+    }
+    int mine = 0, all = 0;
+    for (int64_t i = (int64_t)blockIdx.x * SHARE_SAMPLES + tid; i < at[SHARE_SAMPLES]; i += (int64_t)gridDim.x * SHARE_SAMPLES) {
+        int lo = 0, hi = SHARE_SAMPLES;     // at[lo] <= i < at[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (at[mid] <= i) lo = mid; else hi = mid;
+        }
+        const int w0 = first_window[lo], w1 = min(w0 + LIBRA_LOCALITY_WINDOWS, nw), v = win_ptr[w0] + (int)(i - at[lo]);
+        if (vmask[v] == 0) continue;
+        ++all;
+        const int c = scol[v];
+        // first place with column >= c in each window before the vector's own, together: the searches are chains of loads
         constexpr int E = LIBRA_LOCALITY_WINDOWS - 1;
-        int at[E], left[E], end[E];
+        int from[E], left[E], end[E];
         bool more = false;
 #pragma unroll
         for (int u = 0; u < E; ++u) {
             const int w = min(w0 + u, w1 - 1);
-            at[u] = win_vptr[w];
-            end[u] = win_vptr[w + 1];
-            left[u] = w0 + u < w1 && end[u] <= v ? end[u] - at[u] : 0;
-            if (left[u] == 0) end[u] = at[u];
+            from[u] = win_ptr[w];
+            end[u] = win_ptr[w + 1];
+            left[u] = w0 + u < w1 && end[u] <= v ? end[u] - from[u] : 0;
+            if (left[u] == 0) end[u] = from[u];
             more = more || left[u];
         }
         while (more) {
             int x[E];
 #pragma unroll
-            for (int u = 0; u < E; ++u) x[u] = vcol[min(at[u] + (left[u] >> 1), v)];
+            for (int u = 0; u < E; ++u) x[u] = scol[min(from[u] + (left[u] >> 1), v)];
             more = false;
 #pragma unroll
             for (int u = 0; u < E; ++u) {
                 const int half = left[u] >> 1;
                 const bool before = left[u] > 0 && x[u] < c;
-                at[u] = before ? at[u] + half + 1 : at[u];
+                from[u] = before ? from[u] + half + 1 : from[u];
                 left[u] = before ? left[u] - half - 1 : half;
                 more = more || left[u];
             }
         }
         bool seen = false;
 #pragma unroll
-        for (int u = 0; u < E; ++u) seen = seen || (at[u] < end[u] && vcol[at[u]] == c);
+        for (int u = 0; u < E; ++u) seen = seen || (from[u] < end[u] && scol[from[u]] == c);
         mine += seen ? 0 : 1;
     }
     if (mine) atomicAdd(&together, mine);
+    if (all) atomicAdd(&apart, all);
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         if (together) atomicAdd(&ctr[C_TOGETHER], (u64)together);
-        if (blockIdx.y == 0) atomicAdd(&ctr[C_APART], (u64)(v1 - v0));
+        if (apart) atomicAdd(&ctr[C_APART], (u64)apart);
     }
 }
 
 struct Rule {
-    int mode, fill, tau_d, Ts, Cs, short_len, build_a, build_d, Ts_d;
+    int mode, fill, tau_a, tau_d, Ts, Cs, short_len, build_a, build_d, Ts_d;
 };
 
-// Per window: dense vectors and blocks of both sub-plans (Section 4.2).
-__global__ __launch_bounds__(256) void k_window_counts(const int32_t *win_vptr, const int32_t *taud, const int32_t *cum, int nw, Rule R,
-                                                       int32_t *ntau_o, int32_t *ndv_a, int32_t *nb_a, int32_t *ndv_d, int32_t *nb_d, u64 *ctr) {
+// Per window: dense vectors and blocks of both sub-plans (Section 4.2), from the numbers of its vectors of each NNZ.  hist then holds, for
+// each NNZ, the vectors of more nonzeros: the place of the first one in sorted order.
+__global__ __launch_bounds__(256) void k_window_counts(int32_t *hist, int nw, Rule R, int32_t *ndv_a, int32_t *nb_a, int32_t *ndv_d, int32_t *nb_d, u64 *ctr) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t == nw) { nb_a[nw] = 0; nb_d[nw] = 0; }
     if (t >= nw) return;
-    const int base = win_vptr[t], nvw = win_vptr[t + 1] - base;
-    int ntau = 0, ndv = 0, nb = 0;
+    int h[W], nvw = 0, ntau = 0;
+#pragma unroll
+    for (int q = 0; q < W; q += 4) {
+        const int4 x = reinterpret_cast<const int4 *>(hist + (int64_t)t * W)[q / 4];
+        h[q] = x.x; h[q + 1] = x.y; h[q + 2] = x.z; h[q + 3] = x.w;
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        nvw += h[q];
+        ntau += q + 1 >= R.tau_a ? h[q] : 0;
+    }
+    int ndv = 0, nb = 0;
     if (R.build_a) {
-        ntau = taud[base + nvw] - taud[base];
         int nprom = 0;
         if (R.fill && ntau > 0 && ntau % KB) nprom = min(KB - ntau % KB, nvw - ntau);
         ndv = ntau + nprom;
         nb = (ndv + KB - 1) / KB;
     }
-    ntau_o[t] = ntau;
     ndv_a[t] = ndv;
     nb_a[t] = nb;
+    auto nonzeros = [&](int first) {        // of the first so many vectors of the order
+        int sum = 0;
+#pragma unroll
+        for (int q = W - 1; q >= 0; --q) {
+            const int take = min(first, h[q]);
+            sum += take * (q + 1);
+            first -= take;
+        }
+        return sum;
+    };
     int nbd = 0;
     if (R.build_d && R.mode != LIBRA_MODE_SCALAR_ONLY) {
         const int nblk = (nvw + KB - 1) / KB;
@@ -536,8 +717,7 @@ __global__ __launch_bounds__(256) void k_window_counts(const int32_t *win_vptr, 
             int lo = 0, hi = nblk;          // blocks [0, lo) pass, blocks [hi, nblk) fail
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
-                const int nnzb = cum[base + min(nvw, mid * KB + KB)] - cum[base + mid * KB];
-                if (nnzb >= R.tau_d) lo = mid + 1; else hi = mid;
+                if (nonzeros(min(nvw, mid * KB + KB)) - nonzeros(mid * KB) >= R.tau_d) lo = mid + 1; else hi = mid;
             }
             nbd = lo;
         }
@@ -545,37 +725,127 @@ __global__ __launch_bounds__(256) void k_window_counts(const int32_t *win_vptr, 
     const int ndvd = min(nvw, nbd * KB);
     ndv_d[t] = ndvd;
     nb_d[t] = nbd;
+    int more = 0;
+#pragma unroll
+    for (int q = W - 4; q >= 0; q -= 4) {
+        int4 x;
+        x.w = more; more += h[q + 3];
+        x.z = more; more += h[q + 2];
+        x.y = more; more += h[q + 1];
+        x.x = more; more += h[q];
+        reinterpret_cast<int4 *>(hist + (int64_t)t * W)[q / 4] = x;
+    }
+    if (nvw) atomicAdd(&ctr[C_NV], (u64)nvw);
+    if (h[0]) atomicAdd(&ctr[C_NNZ1], (u64)h[0]);
     if (ndv) { atomicAdd(&ctr[C_DV_A], (u64)ndv); }
     if (nb * KB - ndv) atomicAdd(&ctr[C_PAD_A], (u64)(nb * KB - ndv));
     if (ndvd) atomicAdd(&ctr[C_DV_D], (u64)ndvd);
-    if (ndvd) atomicAdd(&ctr[C_DNNZ_D], (u64)(cum[base + ndvd] - cum[base]));       // nonzeros in the window's dense SDDMM blocks
+    if (ndvd) atomicAdd(&ctr[C_DNNZ_D], (u64)nonzeros(ndvd));       // nonzeros in the window's dense SDDMM blocks
     if (nbd * KB - ndvd) atomicAdd(&ctr[C_PAD_D], (u64)(nbd * KB - ndvd));
 }
+// The whole-matrix utilisation rule: too small a dense share sends the whole SDDMM sub-plan to the scalar path.
+__global__ __launch_bounds__(256) void k_share_rule(const u64 *ctr, int64_t nnz, int pct, int nw, int32_t *ndv_d, int32_t *nb_d) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= nw || 100 * (int64_t)ctr[C_DNNZ_D] >= (int64_t)pct * nnz) return;
+    ndv_d[t] = 0;
+    nb_d[t] = 0;
+}
 
-// Per vector: its slot in the SpMM blocks (threshold vectors in column order, then the fillers in sorted order)
-// and in the SDDMM blocks (sorted order).
-__global__ __launch_bounds__(256) void k_slots(const int32_t *vwin, const int32_t *win_vptr, const int32_t *srank, const int32_t *taud,
-                                               const int32_t *ntau, const int32_t *ndv_a, const int32_t *blkptr_a,
-                                               const int32_t *ndv_d, const int32_t *blkptr_d, int nv, Rule R,
-                                               int32_t *slotvec_a, uint8_t *dflag_a, int32_t *slotvec_d, uint8_t *dflag_d) {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nv) return;
-    const int w = vwin[v];
-    const int base = win_vptr[w];
-    const int k = srank[v];
-    if (R.build_a && k < ndv_a[w]) {
-        const int slot = k < ntau[w] ? taud[v] - taud[base] : k;
-        slotvec_a[(int64_t)blkptr_a[w] * KB + slot] = v;
-        dflag_a[v] = 1;
+// The vectors in dense blocks: their slots in the SpMM blocks (threshold vectors in column order, then the fillers in sorted order) and in
+// the SDDMM blocks (sorted order), and which nonzeros they hold.  A workgroup per tile of the census, whose places are in column order:
+// a vector's rank among the window's vectors of its NNZ is counted by ballots, over the part of the window in earlier tiles and waves
+// from their totals.  (It replaces numbering the vectors, a stable sort of those with more than one nonzero, ranks, three scans and two
+// scattering passes: 2.5 ms of the GAT graph's plan, now 0.6.)
+__global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *win_ptr, const int32_t *row_of, Tiles T, const int32_t *spos, const uint16_t *vmask, const int32_t *hist,
+                                                                const int32_t *ndv_a, const int32_t *blkptr_a, const int32_t *ndv_d, const int32_t *blkptr_d, Rule R,
+                                                                int32_t *slotvec_a, int32_t *slotvec_d, uint8_t *dense) {
+    constexpr int WAVES = TILE_THREADS / 64;
+    __shared__ int32_t carry[W], wave_tail[WAVES][W];
+    __shared__ int wave_changed[WAVES];
+    const int k = blockIdx.x, tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    const int w0 = T.win[k], out = T.pos[k], count = T.pos[k + 1] - out;
+    if (tid < W) carry[tid] = 0;
+    __syncthreads();
+    // the parts of the first window in earlier tiles: those before the boundaries inside it
+    {
+        int sum = 0;
+        for (int b = max(1, (int)(((int64_t)win_ptr[w0] + TILE_STEP - 1) / TILE_STEP)) + tid / W; b <= k; b += TILE_THREADS / W) sum += T.tail[(int64_t)(b - 1) * W + tid % W];
+        if (sum) atomicAdd(&carry[tid % W], sum);
     }
-    if (R.build_d && k < ndv_d[w]) {
-        slotvec_d[(int64_t)blkptr_d[w] * KB + k] = v;
-        dflag_d[v] = 1;
+    int rows[TILE_EACH], win[TILE_EACH];
+    u64 change[TILE_EACH];                  // the chunk's lanes that begin a window
+    int run = 0;                            // lane c < 16: vectors of NNZ c + 1 since the last of them
+    bool changed = false;
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int i = wave * (64 * TILE_EACH) + j * 64 + lane, e = out + min(i, count - 1);
+        rows[j] = i < count ? vmask[e] : 0;
+        win[j] = row_of[e] / W;             // a place's window is that of the nonzero there in CSR order
+        change[j] = __ballot(i > 0 && i < count && row_of[e - (i > 0)] / W != win[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const ClassPlanes planes(__popc(rows[j]) - 1, rows[j] != 0);
+        const u64 from = change[j] ? ~0ull << (63 - __clzll(change[j])) : ~0ull;
+        run = (change[j] ? 0 : run) + __popcll(planes.same(lane) & from);
+        changed = changed || change[j];
+    }
+    if (lane < W) wave_tail[wave][lane] = run;
+    if (lane == 0) wave_changed[wave] = changed;
+    __syncthreads();
+    run = 0;
+    {
+        bool open = true;
+        for (int v = wave - 1; v >= 0 && open; --v) {
+            run += wave_tail[v][lane % W];
+            open = !wave_changed[v];
+        }
+        if (open) run += carry[lane % W];
+    }
+    auto over_tau = [&](int x) {            // sum over the lanes c < 16 with c + 1 >= tau
+        int sum = lane < W && lane + 1 >= R.tau_a ? x : 0;
+#pragma unroll
+        for (int m = 1; m < W; m <<= 1) sum += __shfl_xor(sum, m, 64);
+        return __builtin_amdgcn_readfirstlane(sum);
+    };
+    int run_tau = over_tau(run), last_in = 0;
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int nnz = __popc(rows[j]), cls = nnz - 1;
+        const ClassPlanes planes(cls, nnz > 0);
+        const u64 over = __ballot(nnz > 0 && nnz >= R.tau_a), below = (1ull << lane) - 1ull;
+        const u64 begun = change[j] & (below << 1 | 1ull);                     // windows that begin at or before this lane
+        const u64 from = begun ? ~0ull << (63 - __clzll(begun)) : ~0ull;
+        const int rank = __popcll(planes.same(cls) & below & from) + (begun ? 0 : __shfl(run, cls & 15, 64));
+        const int rank_tau = __popcll(over & below & from) + (begun ? 0 : run_tau);
+        const int first = wave * (64 * TILE_EACH) + j * 64, e = out + first + lane, end = out + min(count, (wave + 1) * 64 * TILE_EACH);
+        int in = 0;                         // of a vector's first place: 1, in a SpMM block; 2, in an SDDMM block
+        if (nnz > 0) {
+            const int w = win[j], da = ndv_a[w], dd = ndv_d[w];
+            if (da | dd) {
+                const int place = hist[(int64_t)w * W + cls] + rank;           // in sorted order
+                in = (place < da ? 1 : 0) | (place < dd ? 2 : 0);
+                if (in & 1) slotvec_a[(int64_t)blkptr_a[w] * KB + (nnz >= R.tau_a ? rank_tau : place)] = e;
+                if (in & 2) slotvec_d[(int64_t)blkptr_d[w] * KB + place] = e;
+            }
+        }
+        // a place's bits are those of its vector's first place: in this chunk, or the last one of the chunk before.  Places of the next
+        // wave whose vector begins in this one are written from here.
+        const u64 heads = __ballot(nnz > 0), up_to = heads & (below << 1 | 1ull);
+        const int mine = __shfl(in, up_to ? 63 - __clzll(up_to) : 0, 64);
+        const int bits = up_to ? mine : last_in;
+        if (bits && e < end) dense[spos[e]] = (uint8_t)bits;
+        if (heads) last_in = __shfl(in, 63 - __clzll(heads), 64);
+        if (in)
+            for (int q = end; q < e + nnz; ++q) dense[spos[q]] = (uint8_t)in;
+        const u64 all_from = change[j] ? ~0ull << (63 - __clzll(change[j])) : ~0ull;
+        run = (change[j] ? 0 : run) + __popcll(planes.same(lane) & all_from);
+        run_tau = (change[j] ? 0 : run_tau) + __popcll(over & all_from);
     }
 }
 
 // 16 lanes per block: column ids, the bitmap (bit r*16+s) by ballots, NNZ, touched rows, real columns.
-__global__ __launch_bounds__(256) void k_blocks(const int32_t *slotvec, const int32_t *vcol, const int32_t *vinfo, int nb,
+__global__ __launch_bounds__(256) void k_blocks(const int32_t *slotvec, const int32_t *scol, const uint16_t *vmask, int nb,
                                                 int32_t *blk_cols, u64 *bitmap, int32_t *blknnz, int32_t *blkmask, int32_t *blkncols) {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int b = (int)(gid >> 4), s = (int)(gid & 15);
@@ -583,8 +853,8 @@ __global__ __launch_bounds__(256) void k_blocks(const int32_t *slotvec, const in
     const bool live = b < nb;
     if (gid == 0) blknnz[nb] = 0;
     const int v = live ? slotvec[(int64_t)b * KB + s] : -1;
-    const unsigned mask = v >= 0 ? ((unsigned)vinfo[v] >> 8) & 0xffffu : 0u;
-    if (live) blk_cols[(int64_t)b * KB + s] = v >= 0 ? vcol[v] : -1;
+    const unsigned mask = v >= 0 ? vmask[v] : 0u;
+    if (live) blk_cols[(int64_t)b * KB + s] = v >= 0 ? scol[v] : -1;
     u64 word = 0;           // lane s < 4 builds word s (rows 4s .. 4s+3)
     int nnz = 0;
     unsigned touched = 0;
@@ -606,7 +876,7 @@ __global__ __launch_bounds__(256) void k_blocks(const int32_t *slotvec, const in
 }
 
 // 16 lanes per block: CSR position and value of every packed nonzero, at popcount(bits below its bit).
-__global__ __launch_bounds__(256) void k_block_values(const int32_t *slotvec, const int32_t *vfirst, const int32_t *vinfo, const u64 *bitmap,
+__global__ __launch_bounds__(256) void k_block_values(const int32_t *slotvec, const uint16_t *vmask, const u64 *bitmap,
                                                       const int32_t *blk_valptr, const int32_t *spos, const uint8_t *val, int vsize, int nb,
                                                       int32_t *dense_perm, uint8_t *dense_val) {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -614,11 +884,11 @@ __global__ __launch_bounds__(256) void k_block_values(const int32_t *slotvec, co
     if (b >= nb) return;
     const int v = slotvec[(int64_t)b * KB + s];
     if (v < 0) return;
-    const unsigned mask = ((unsigned)vinfo[v] >> 8) & 0xffffu;
+    const unsigned mask = vmask[v];
     const u64 w0 = bitmap[(int64_t)b * 4], w1 = bitmap[(int64_t)b * 4 + 1], w2 = bitmap[(int64_t)b * 4 + 2], w3 = bitmap[(int64_t)b * 4 + 3];
     const int c0 = __popcll(w0), c1 = __popcll(w1), c2 = __popcll(w2);
     const int vbase = blk_valptr[b];
-    int e = vfirst[v];
+    int e = v;                              // a vector is named by its first place
     for (int r = 0; r < W; ++r) {
         if (!((mask >> r) & 1u)) continue;
         const int q = r >> 2;
@@ -633,17 +903,14 @@ __global__ __launch_bounds__(256) void k_block_values(const int32_t *slotvec, co
     }
 }
 
-// Per sorted nonzero: residual flags of both sub-plans, written at the nonzero's CSR position.
-__global__ __launch_bounds__(256) void k_entry_flags(const int32_t *hflag, const int32_t *vid, const int32_t *spos, const uint8_t *dflag_a,
-                                                     const uint8_t *dflag_d, int n, Rule R, int32_t *resf_a, int32_t *resf_d) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e == n) { resf_a[n] = 0; resf_d[n] = 0; }
-    if (e >= n) return;
-    const int v = vid[e] + hflag[e] - 1;
-    const int p = spos[e];
-    resf_a[p] = R.build_a && !dflag_a[v] ? 1 : 0;
-    resf_d[p] = R.build_d && !dflag_d[v] ? 1 : 0;
-}
+// The residual nonzeros of a sub-plan in CSR order.  scan = nullptr: all of the matrix.
+struct Residual {
+    const uint8_t *dense;
+    const int32_t *scan;
+    unsigned bit;
+    __device__ int before(int p) const { return scan ? scan[p] : p; }
+    __device__ bool has(int p) const { return !scan || !(dense[p] & bit); }
+};
 
 struct WinRows {
     int nr;
@@ -652,7 +919,7 @@ struct WinRows {
     int q_unsplit, q_split;
 };
 
-__device__ inline WinRows window_rows(const int32_t *rowptr, const int32_t *rescan, int64_t M, int t, const Rule &R, int *n_short, int *n_long) {
+__device__ inline WinRows window_rows(const int32_t *rowptr, const Residual &res, int64_t M, int t, const Rule &R, int *n_short, int *n_long) {
     WinRows z;
     const int64_t r0 = (int64_t)t * W;
     z.nr = (int)min((int64_t)W, M - r0);
@@ -662,7 +929,7 @@ __device__ inline WinRows window_rows(const int32_t *rowptr, const int32_t *resc
     for (int r = 0; r < W; ++r) {
         z.rlen[r] = 0;
         if (r >= z.nr) continue;
-        const int len = rescan[rowptr[r0 + r + 1]] - rescan[rowptr[r0 + r]];
+        const int len = res.before(rowptr[r0 + r + 1]) - res.before(rowptr[r0 + r]);
         z.rlen[r] = len;
         z.valid |= 1u << r;
         if (len == 0) continue;
@@ -687,7 +954,7 @@ __device__ inline void put_task(libra_task_t *t, int kind, int id, int b0, int b
 // window has thousands of tasks (GAT graph: 800 us with a thread per window, 221 with a wave).  A launch has fewer than 2^32
 // threads, so from 2^23 windows on a wave takes several.
 template <bool FILL>
-__global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, const int32_t *rescan_a, int64_t M, int nw, Rule R,
+__global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, Residual res_a, int64_t M, int nw, Rule R,
                                                       const int32_t *blkptr_a, const int32_t *blkmask_a, const int32_t *blkncols_a,
                                                       const int32_t *blkptr_d, const int32_t *blkncols_d,
                                                       int32_t *ntasks_a, int32_t *nzero, int32_t *nres, int32_t *ntasks_d, u64 *ctr,
@@ -701,7 +968,7 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
         const int64_t r0 = (int64_t)t * W;
         if (R.build_a) {
             int n_short, n_long;
-            const WinRows z = window_rows(rowptr, rescan_a, M, t, R, &n_short, &n_long);
+            const WinRows z = window_rows(rowptr, res_a, M, t, R, &n_short, &n_long);
             const int b0 = blkptr_a[t], b1 = blkptr_a[t + 1];
             const bool many = b1 - b0 > R.Ts;
             int nchunks = 0;
@@ -780,40 +1047,40 @@ __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, con
 
 // Per window: where each row's residual nonzeros start in the SpMM residual array (rows that are not decomposed
 // first, in row order, then the decomposed rows), minus the row's own prefix so that a nonzero only adds its scan value.
-__global__ __launch_bounds__(128) void k_row_bases(const int32_t *rowptr, const int32_t *rescan_a, const int32_t *resptr, int64_t M, int nw, Rule R,
+__global__ __launch_bounds__(128) void k_row_bases(const int32_t *rowptr, Residual res_a, const int32_t *resptr, int64_t M, int nw, Rule R,
                                                    int32_t *rowbase) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nw) return;
     int n_short, n_long;
-    const WinRows z = window_rows(rowptr, rescan_a, M, t, R, &n_short, &n_long);
+    const WinRows z = window_rows(rowptr, res_a, M, t, R, &n_short, &n_long);
     int u = 0, sp = z.q_unsplit;
     const int64_t r0 = (int64_t)t * W;
     for (int r = 0; r < z.nr; ++r) {
         int off;
         if ((z.split >> r) & 1u) { off = sp; sp += z.rlen[r]; } else { off = u; u += z.rlen[r]; }
-        rowbase[r0 + r] = resptr[t] + off - rescan_a[rowptr[r0 + r]];
+        rowbase[r0 + r] = resptr[t] + off - res_a.before(rowptr[r0 + r]);
     }
 }
 
 // Per nonzero (CSR order): residual nonzeros to their places.  SDDMM: CSR order.
 __global__ __launch_bounds__(256) void k_residual_fill(const int32_t *col, const uint8_t *val, int vsize, int n, Rule R, const int32_t *row_of,
-                                                      const int32_t *resf_a, const int32_t *rescan_a, const int32_t *rowbase,
+                                                      Residual res_a, const int32_t *rowbase,
                                                       int32_t *a_perm, int32_t *a_row, int32_t *a_col, uint8_t *a_val,
-                                                      const int32_t *resf_d, const int32_t *rescan_d,
+                                                      Residual res_d,
                                                       int32_t *d_perm, int32_t *d_row, int32_t *d_col, uint8_t *d_val) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
-    const bool ra = R.build_a && resf_a[p], rd = R.build_d && resf_d[p];
+    const bool ra = R.build_a && res_a.has(p), rd = R.build_d && res_d.has(p);
     if (!ra && !rd) return;
     const int i = row_of[p], c = col[p];
     if (ra) {
-        const int d = rowbase[i] + rescan_a[p];
+        const int d = rowbase[i] + res_a.before(p);
         a_perm[d] = p; a_row[d] = i; a_col[d] = c;
         if (vsize == 2) reinterpret_cast<uint16_t *>(a_val)[d] = reinterpret_cast<const uint16_t *>(val)[p];
         else reinterpret_cast<uint32_t *>(a_val)[d] = reinterpret_cast<const uint32_t *>(val)[p];
     }
     if (rd) {
-        const int d = rescan_d[p];
+        const int d = res_d.before(p);
         d_perm[d] = p; d_row[d] = i; d_col[d] = c;
         if (vsize == 2) reinterpret_cast<uint16_t *>(d_val)[d] = reinterpret_cast<const uint16_t *>(val)[p];
         else reinterpret_cast<uint32_t *>(d_val)[d] = reinterpret_cast<const uint32_t *>(val)[p];
@@ -1390,90 +1657,72 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         const uint8_t *val = reinterpret_cast<const uint8_t *>(d_val);
         int colbits = 1;
         while ((1ll << colbits) < Kc) ++colbits;
-        Rule R{o.mode, o.fill && o.mode == LIBRA_MODE_HYBRID ? 1 : 0, o.tau_sddmm, o.Ts, o.Cs, o.short_len, o.build_spmm ? 1 : 0, o.build_sddmm ? 1 : 0, o.sddmm_Ts};
         const int tau_a = o.mode == LIBRA_MODE_DENSE_ONLY ? 1 : o.mode == LIBRA_MODE_SCALAR_ONLY ? W + 1 : o.tau_spmm;
+        Rule R{o.mode, o.fill && o.mode == LIBRA_MODE_HYBRID ? 1 : 0, tau_a, o.tau_sddmm, o.Ts, o.Cs, o.short_len, o.build_spmm ? 1 : 0, o.build_sddmm ? 1 : 0, o.sddmm_Ts};
 
         // ---- 1. census: the nonzeros of every window in (column, row) order ----
         fill_bytes(L.ctr, 0, C_COUNT * sizeof(u64), s);
         hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr);
-        hipLaunchKernelGGL(k_merge_rows, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.key_in, L.mvec_in, L.row_of, L.ctr);
-        hipLaunchKernelGGL(k_merge_groups, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_rowptr, M, L.key_in, L.mvec_in, L.row_of, n, L.key_out, L.spos);
-        // ---- 2. vectors ----
-        hipLaunchKernelGGL(k_census, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, s, L.key_out, L.win_ptr, L.row_of, n, L.hflag, L.einfo);
-        scan(L, L.hflag, L.vid, (size_t)n + 1, s);
-        hipLaunchKernelGGL(k_vectors, dim3(std::min(blocks_for(n, 256), 4096u)), dim3(256), 0, s, L.key_out, L.hflag, L.vid, L.einfo, L.row_of, n, tau_a,
-                           L.vfirst, L.vinfo, L.vcol, L.vwin, L.tflag, L.mflag, L.ctr);
-        hipLaunchKernelGGL(k_win_vptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, L.win_ptr, L.vid, nw, n, L.ctr, L.win_vptr);
+        const int tiles = tile_count(n);
+        hipLaunchKernelGGL(k_rows, dim3(blocks_for(n, ROWS_CHUNK)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.row_of, L.ctr);
+        hipLaunchKernelGGL(k_tile_splits, dim3(blocks_for((int64_t)(tiles + 1) * W, 256)), dim3(256), 0, s, d_rowptr, d_col, L.win_ptr, M, Kc, n, nw, tiles, L.tiles);
+        fill_bytes(L.hist, 0, (size_t)nw * W * sizeof(int32_t), s);
+        hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)tiles), dim3(TILE_THREADS), 0, s, d_rowptr, d_col, L.win_ptr, L.row_of, M, L.tiles, L.ctr, L.scol, L.spos, L.vmask, L.hist);
+        // ---- 2. per window: dense vectors and blocks ----
+        hipLaunchKernelGGL(k_window_counts, dim3(blocks_for((int64_t)nw + 1, 256)), dim3(256), 0, s, L.hist, nw, R, L.a.ndv, L.a.nb, L.d.ndv, L.d.nb, L.ctr);
+        const bool share_rule = o.build_sddmm && o.mode == LIBRA_MODE_HYBRID && o.sddmm_min_dense_pct > 0;
+        if (share_rule)
+            hipLaunchKernelGGL(k_share_rule, dim3(blocks_for(nw, 256)), dim3(256), 0, s, L.ctr, nnz, o.sddmm_min_dense_pct, nw, L.d.ndv, L.d.nb);
+        scan(L, L.a.nb, L.a.blkptr, (size_t)nw + 1, s);
+        scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
+        int32_t size[7];
         u64 ctr[C_COUNT];
         hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));
-        hip_ok(hipStreamSynchronize(s));
+        peek_all(L.sizes, {L.a.blkptr + nw, L.d.blkptr + nw}, size, s);
         if (hipGetLastError() != hipSuccess) throw Fail{LIBRA_ERR_HIP};
         if (ctr[C_ERR] & 1) throw Fail{LIBRA_ERR_COLUMN};
         if (ctr[C_ERR] & 2) throw Fail{LIBRA_ERR_UNSORTED};
         const int nv = (int)ctr[C_NV];
         if (nv < 1 || nv > n) throw Fail{LIBRA_ERR_HIP};
-        mark("census, vectors");
-        // order of a window's vectors: NNZ descending, column ascending
-        const int nm = nv - (int)ctr[C_NNZ1];
-        if (nm < 0 || nm > nv) throw Fail{LIBRA_ERR_HIP};
-        scan(L, L.mflag, L.mscan, (size_t)nv + 1, s);
-        if (nm > 0) {
-            hipLaunchKernelGGL(k_multi_keys, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.mflag, L.mscan, L.vinfo, L.vwin, nv, L.mkey_in, L.mvec_in);
-            int winbits = 1;
-            while ((1ll << winbits) < nw) ++winbits;
-            size_t sz = L.tmp_bytes;
-            hip_ok(rocprim::radix_sort_pairs(L.tmp, sz, L.mkey_in, L.mkey_out, L.mvec_in, L.mvec_out, (size_t)nm, 0u, (unsigned)(winbits + 4), s));
-        }
-        hipLaunchKernelGGL(k_sorted, dim3(blocks_for((int64_t)nv + 1, 256)), dim3(256), 0, s, L.mvec_out, nm, L.mflag, L.mscan, L.vinfo, L.vwin, L.win_vptr, nv, L.scnt, L.srank);
-        scan(L, L.scnt, L.cum, (size_t)nv + 1, s);
-        scan(L, L.tflag, L.taud, (size_t)nv + 1, s);
-        // ---- 3. per window: dense vectors and blocks ----
-        hipLaunchKernelGGL(k_window_counts, dim3(blocks_for((int64_t)nw + 1, 256)), dim3(256), 0, s, L.win_vptr, L.taud, L.cum, nw, R,
-                           L.ntau, L.a.ndv, L.a.nb, L.d.ndv, L.d.nb, L.ctr);
-        if (o.build_sddmm && o.mode == LIBRA_MODE_HYBRID && o.sddmm_min_dense_pct > 0) {
-            // the whole-matrix utilisation rule: too small a dense share sends the whole SDDMM sub-plan to the scalar path
-            u64 dense_d = 0;
-            hip_ok(hipMemcpyAsync(&dense_d, L.ctr + C_DNNZ_D, sizeof dense_d, hipMemcpyDeviceToHost, s));
-            hip_ok(hipStreamSynchronize(s));
-            if (share_rule_fires(o, (int64_t)dense_d, nnz)) {
-                fill_bytes(L.d.nb, 0, (size_t)nw * sizeof(int32_t), s);
-                fill_bytes(L.d.ndv, 0, (size_t)nw * sizeof(int32_t), s);
-                fill_bytes(L.ctr + C_DV_D, 0, 2 * sizeof(u64), s);              // C_DV_D and C_PAD_D are neighbours
-            }
-        }
-        scan(L, L.a.nb, L.a.blkptr, (size_t)nw + 1, s);
-        scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
-        int32_t size[7];
-        peek_all(L.sizes, {L.a.blkptr + nw, L.d.blkptr + nw}, size, s);
         const int nbA = size[0], nbD = size[1];
         if (nbA < 0 || nbD < 0 || nbA > z.nbmax || nbD > z.nbmax) throw Fail{LIBRA_ERR_HIP};
-        mark("vector order, window counts");
-        // ---- 4. slots, blocks, packed values ----
-        fill_bytes(L.a.slotvec, 0xff, (size_t)nbA * KB * sizeof(int32_t), s);
-        fill_bytes(L.d.slotvec, 0xff, (size_t)nbD * KB * sizeof(int32_t), s);
-        fill_bytes(L.a.dflag, 0, (size_t)nv, s);
-        fill_bytes(L.d.dflag, 0, (size_t)nv, s);
-        hipLaunchKernelGGL(k_slots, dim3(blocks_for(nv, 256)), dim3(256), 0, s, L.vwin, L.win_vptr, L.srank, L.taud, L.ntau, L.a.ndv, L.a.blkptr,
-                           L.d.ndv, L.d.blkptr, nv, R, L.a.slotvec, L.a.dflag, L.d.slotvec, L.d.dflag);
+        if (share_rule && share_rule_fires(o, (int64_t)ctr[C_DNNZ_D], nnz)) {
+            if (nbD != 0) throw Fail{LIBRA_ERR_HIP};
+            fill_bytes(L.ctr + C_DV_D, 0, 2 * sizeof(u64), s);              // C_DV_D and C_PAD_D are neighbours
+        }
+        mark("census, window counts");
+        // ---- 3. slots, blocks, packed values ----
+        if (nbA + nbD > 0) {
+            fill_bytes(L.a.slotvec, 0xff, (size_t)nbA * KB * sizeof(int32_t), s);
+            fill_bytes(L.d.slotvec, 0xff, (size_t)nbD * KB * sizeof(int32_t), s);
+            fill_bytes(L.dense, 0, (size_t)n + 1, s);
+            hipLaunchKernelGGL(k_dense_vectors, dim3((unsigned)tiles), dim3(TILE_THREADS), 0, s, L.win_ptr, L.row_of, L.tiles, L.spos, L.vmask, L.hist,
+                               L.a.ndv, L.a.blkptr, L.d.ndv, L.d.blkptr, R, L.a.slotvec, L.d.slotvec, L.dense);
+        }
         const int nbs[2] = {nbA, nbD};
         const SubOut *subs[2] = {&L.a, &L.d};
         for (int k = 0; k < 2; ++k) {
             const SubOut &S = *subs[k];
             const int nb = nbs[k];
             if (nb > 0)
-                hipLaunchKernelGGL(k_blocks, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vcol, L.vinfo, nb,
+                hipLaunchKernelGGL(k_blocks, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.scol, L.vmask, nb,
                                    S.blk_cols, S.bitmap, S.blknnz, S.blkmask, S.blkncols);
             if (nb == 0) fill_bytes(S.blknnz, 0, sizeof(int32_t), s);
             scan(L, S.blknnz, S.blk_valptr, (size_t)nb + 1, s);
             if (nb > 0)
-                hipLaunchKernelGGL(k_block_values, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vfirst, L.vinfo, S.bitmap,
+                hipLaunchKernelGGL(k_block_values, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vmask, S.bitmap,
                                    S.blk_valptr, L.spos, val, vsize, nb, S.dense_perm, S.dense_val);
         }
-        // ---- 5. residual nonzeros and tasks ----
-        hipLaunchKernelGGL(k_entry_flags, dim3(blocks_for((int64_t)n + 1, 256)), dim3(256), 0, s, L.hflag, L.vid, L.spos, L.a.dflag, L.d.dflag, n, R, L.a.resf, L.d.resf);
-        scan(L, L.a.resf, L.a.rescan, (size_t)n + 1, s);
-        scan(L, L.d.resf, L.d.rescan, (size_t)n + 1, s);
-        hipLaunchKernelGGL((k_window_tasks<false>), dim3(blocks_for((int64_t)nw + 1, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
+        // ---- 4. residual nonzeros and tasks ----
+        auto residual = [&](const SubOut &S, int nb, unsigned bit) {
+            if (nb == 0) return Residual{L.dense, nullptr, bit};
+            size_t sz = L.tmp_bytes;
+            hip_ok(rocprim::exclusive_scan(L.tmp, sz, rocprim::make_transform_iterator((const uint8_t *)L.dense, NotDense{bit}), S.rescan, (int32_t)0, (size_t)n + 1,
+                                           rocprim::plus<int32_t>(), s));
+            return Residual{L.dense, S.rescan, bit};
+        };
+        const Residual resA = residual(L.a, nbA, 1u), resD = residual(L.d, nbD, 2u);
+        hipLaunchKernelGGL((k_window_tasks<false>), dim3(blocks_for((int64_t)nw + 1, 128)), dim3(128), 0, s, d_rowptr, resA, M, nw, R,
                            L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);
@@ -1481,22 +1730,23 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         scan(L, L.nzero, L.zbase, (size_t)nw + 1, s);
         scan(L, L.nres, L.resptr, (size_t)nw + 1, s);
         scan(L, L.d.ntasks, L.d.tbase, (size_t)nw + 1, s);
-        peek_all(L.sizes, {L.a.tbase + nw, L.d.tbase + nw, L.zbase + nw, L.a.rescan + n, L.d.rescan + n, L.a.blk_valptr + nbA, L.d.blk_valptr + nbD}, size, s);
-        const int ntA = size[0], ntD = size[1], nz = size[2], nresA = size[3], nresD = size[4], dnnzA = size[5], dnnzD = size[6];
+        peek_all(L.sizes, {L.a.tbase + nw, L.d.tbase + nw, L.zbase + nw, L.a.blk_valptr + nbA, L.d.blk_valptr + nbD}, size, s);
+        const int ntA = size[0], ntD = size[1], nz = size[2], dnnzA = size[3], dnnzD = size[4];
+        const int nresA = o.build_spmm ? n - dnnzA : 0, nresD = o.build_sddmm ? n - dnnzD : 0;
         if (ntA < 0 || ntA > z.tasks_a_max || ntD < 0 || ntD > z.tasks_d_max || nz < 0 || nz > M || nresA < 0 || nresA > n || nresD < 0 ||
             nresD > n || dnnzA < 0 || dnnzA > n || dnnzD < 0 || dnnzD > n)
             throw Fail{LIBRA_ERR_HIP};
-        hipLaunchKernelGGL((k_window_tasks<true>), dim3(std::min(blocks_for(nw, 2), 1u << 22)), dim3(128), 0, s, d_rowptr, L.a.rescan, M, nw, R,
+        hipLaunchKernelGGL((k_window_tasks<true>), dim3(std::min(blocks_for(nw, 2), 1u << 22)), dim3(128), 0, s, d_rowptr, resA, M, nw, R,
                            L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
                            L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
                            L.a.tasks, L.zero_rows, L.d.tasks);
         const int64_t ngroups = (nw + LIBRA_LOCALITY_WINDOWS - 1) / LIBRA_LOCALITY_WINDOWS, nsample = share_samples(ngroups);
-        hipLaunchKernelGGL(k_share, dim3((unsigned)nsample, 64), dim3(256), 0, s, L.win_vptr, L.vcol, nw, ngroups, nsample, L.ctr);
+        hipLaunchKernelGGL(k_share, dim3(std::min(blocks_for(n, SHARE_SAMPLES), 1024u)), dim3(SHARE_SAMPLES), 0, s, L.win_ptr, L.scol, L.vmask, nw, ngroups, (int)nsample, L.ctr);
         if (o.build_spmm)
-            hipLaunchKernelGGL(k_row_bases, dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, L.a.rescan, L.resptr, M, nw, R, L.rowbase);
+            hipLaunchKernelGGL(k_row_bases, dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, resA, L.resptr, M, nw, R, L.rowbase);
         hipLaunchKernelGGL(k_residual_fill, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_col, val, vsize, n, R, L.row_of,
-                           L.a.resf, L.a.rescan, L.rowbase, L.a.res_perm, L.a.res_row, L.a.res_col, L.a.res_val,
-                           L.d.resf, L.d.rescan, L.d.res_perm, L.d.res_row, L.d.res_col, L.d.res_val);
+                           resA, L.rowbase, L.a.res_perm, L.a.res_row, L.a.res_col, L.a.res_val,
+                           resD, L.d.res_perm, L.d.res_row, L.d.res_col, L.d.res_val);
         if (o.build_spmm && ntA > 0)
             hipLaunchKernelGGL(k_task_cols, dim3(blocks_for(ntA, 256)), dim3(256), 0, s, L.a.tasks, ntA, L.a.res_col, L.task_col);
         const int nsegD = o.build_sddmm ? piece_count(nresD, o.sddmm_Cs) : 0;
