@@ -1781,6 +1781,11 @@ __global__ __launch_bounds__(256) void pack_blocked_entries_kernel(const int32_t
         reinterpret_cast<V *>(blk + RES_BLOCK * 4)[slot] = val[i];
     }
 }
+void pack_entries(int value_bytes, const int32_t *col, const void *val, const int32_t *row, int64_t n, void *entries, int32_t *base, hipStream_t s) {
+    const dim3 grid((unsigned)std::min<int64_t>((n + 255) / 256, 1 << 16)), block(256);
+    if (value_bytes == 4) hipLaunchKernelGGL((pack_blocked_entries_kernel<uint32_t>), grid, block, 0, s, col, (const uint32_t *)val, row, n, (unsigned char *)entries, base);
+    else hipLaunchKernelGGL((pack_blocked_entries_kernel<uint16_t>), grid, block, 0, s, col, (const uint16_t *)val, row, n, (unsigned char *)entries, base);
+}
 template <class V>
 __global__ __launch_bounds__(256) void pack_sddmm_values_kernel(const int32_t *perm, const V *val, int64_t n, SdPv *out) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -1924,6 +1929,10 @@ size_t libra::plan_buffer_bytes(const libra_plan_t *plan) {
     return u.off + 256;
 }
 
+void libra::pack_sddmm_entries(int value_bytes, const int32_t *col, const void *val, const int32_t *row, int64_t n, void *entries, int32_t *base, void *stream) {
+    pack_entries(value_bytes, col, val, row, n, entries, base, (hipStream_t)stream);
+}
+
 int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const DeviceSource &dd, void *dev_buf, size_t bytes, void *stream) {
     if (!dev_buf) return LIBRA_ERR_NULL;
     if (bytes < plan_buffer_bytes(P) || ((uintptr_t)dev_buf & 255)) return LIBRA_ERR_BUFFER;
@@ -1939,21 +1948,11 @@ int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const De
         const SubPlan &sa = P->spmm, &sd = P->sddmm;
         if (da.write_tasks && sa.n.tasks) da.write_tasks(const_cast<DevTask *>(sa.dev.tasks), sa.n.tasks);
         if (dd.write_tasks && sd.n.tasks) dd.write_tasks(const_cast<DevTask *>(sd.dev.tasks), sd.n.tasks);
-        if (sa.n.res) {
-            if (P->vdt == LIBRA_F32)
-                hipLaunchKernelGGL((pack_blocked_entries_kernel<float>), grid(sa.n.res), dim3(256), 0, s, da.res_col,
-                                   (const float *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent, (int32_t *)nullptr);
-            else
-                hipLaunchKernelGGL((pack_blocked_entries_kernel<uint16_t>), grid(sa.n.res), dim3(256), 0, s, da.res_col,
-                                   (const uint16_t *)da.res_val, da.res_row, sa.n.res, (unsigned char *)sa.dev.res_ent, (int32_t *)nullptr);
-        }
-        if (sd.n.res) {
-            if (P->vdt == LIBRA_F32)
-                hipLaunchKernelGGL((pack_blocked_entries_kernel<float>), grid(sd.n.res), dim3(256), 0, s, dd.res_col,
-                                   (const float *)dd.res_val, dd.res_row, sd.n.res, (unsigned char *)sd.dev.res_ent, (int32_t *)sd.dev.res_base);
-            else
-                hipLaunchKernelGGL((pack_blocked_entries_kernel<uint16_t>), grid(sd.n.res), dim3(256), 0, s, dd.res_col,
-                                   (const uint16_t *)dd.res_val, dd.res_row, sd.n.res, (unsigned char *)sd.dev.res_ent, (int32_t *)sd.dev.res_base);
+        if (da.write_residuals) {
+            da.write_residuals(sa.dev, sd.dev);
+        } else {
+            if (sa.n.res) pack_entries(P->vsize, da.res_col, da.res_val, da.res_row, sa.n.res, sa.dev.res_ent, nullptr, s);
+            if (sd.n.res) pack_entries(P->vsize, dd.res_col, dd.res_val, dd.res_row, sd.n.res, sd.dev.res_ent, const_cast<int32_t *>(sd.dev.res_base), s);
         }
         if (sd.n.dense) {
             if (P->vdt == LIBRA_F32)

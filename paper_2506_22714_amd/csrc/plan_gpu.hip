@@ -1062,44 +1062,82 @@ __global__ __launch_bounds__(128) void k_row_bases(const int32_t *rowptr, Residu
     }
 }
 
-// Per nonzero (CSR order): residual nonzeros to their places.  SDDMM: CSR order.
-__global__ __launch_bounds__(256) void k_residual_fill(const int32_t *col, const uint8_t *val, int vsize, int n, Rule R, const int32_t *row_of,
-                                                      Residual res_a, const int32_t *rowbase,
-                                                      int32_t *a_perm, int32_t *a_row, int32_t *a_col, uint8_t *a_val,
-                                                      Residual res_d,
-                                                      int32_t *d_perm, int32_t *d_row, int32_t *d_col, uint8_t *d_val) {
+// Where the residual nonzeros of a sub-plan go: arrays of the host planner's format, or the blocked entries of the plan's device copy
+// (`entries`), with their CSR positions (perm; the SDDMM ones have none if they are the whole matrix) and the SDDMM ones' rows.
+struct ResidualOut {
+    int32_t *perm, *row, *col;
+    uint8_t *val;
+    unsigned char *entries;
+    int32_t *base;              // SDDMM entries: first row per block
+};
+template <class V>
+__device__ inline void put_entry(unsigned char *entries, int d, int col, unsigned upper, V v) {
+    unsigned char *blk = entries + (int64_t)(d / RES_BLOCK) * (RES_BLOCK * (4 + (int)sizeof(V)));
+    reinterpret_cast<uint32_t *>(blk)[d % RES_BLOCK] = (uint32_t)col | upper << RES_ROW_SHIFT;
+    reinterpret_cast<V *>(blk + RES_BLOCK * 4)[d % RES_BLOCK] = v;
+}
+// Per nonzero (CSR order): residual nonzeros to their places.  SDDMM: CSR order.  Entries of SDDMM sub-plans that are not the whole matrix
+// need the row of their block's first entry and are packed from the arrays by a pass of their own.  Bound by memory: GAT graph (59.7 M
+// nonzeros, 35 bytes each) 521 us; to arrays that two passes packed and two copies moved, 1,250.
+template <class V>
+__global__ __launch_bounds__(256) void k_residual_fill(const int32_t *col, const V *val, int n, Rule R, const int32_t *row_of, Residual res_a, const int32_t *rowbase, ResidualOut a,
+                                                      Residual res_d, ResidualOut d) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const bool ra = R.build_a && res_a.has(p), rd = R.build_d && res_d.has(p);
     if (!ra && !rd) return;
     const int i = row_of[p], c = col[p];
+    const V v = val[p];
     if (ra) {
-        const int d = rowbase[i] + res_a.before(p);
-        a_perm[d] = p; a_row[d] = i; a_col[d] = c;
-        if (vsize == 2) reinterpret_cast<uint16_t *>(a_val)[d] = reinterpret_cast<const uint16_t *>(val)[p];
-        else reinterpret_cast<uint32_t *>(a_val)[d] = reinterpret_cast<const uint32_t *>(val)[p];
+        const int q = rowbase[i] + res_a.before(p);
+        a.perm[q] = p;
+        if (a.entries) {
+            put_entry(a.entries, q, c, (unsigned)(i % W), v);
+        } else {
+            a.row[q] = i; a.col[q] = c;
+            reinterpret_cast<V *>(a.val)[q] = v;
+        }
     }
     if (rd) {
-        const int d = res_d.before(p);
-        d_perm[d] = p; d_row[d] = i; d_col[d] = c;
-        if (vsize == 2) reinterpret_cast<uint16_t *>(d_val)[d] = reinterpret_cast<const uint16_t *>(val)[p];
-        else reinterpret_cast<uint32_t *>(d_val)[d] = reinterpret_cast<const uint32_t *>(val)[p];
+        const int q = res_d.before(p);
+        if (d.perm) d.perm[q] = p;
+        d.row[q] = i;
+        if (d.entries) {                    // the whole matrix: the block begins at nonzero p - p % RES_BLOCK
+            const int first = row_of[p - p % RES_BLOCK];
+            put_entry(d.entries, q, c, min((unsigned)(i - first), RES_FAR), v);
+            if (p % RES_BLOCK == 0) d.base[p / RES_BLOCK] = first;
+        } else {
+            d.col[q] = c;
+            reinterpret_cast<V *>(d.val)[q] = v;
+        }
     }
 }
 
-// Per SpMM task: first column of a row segment's entries (the host orders the segments by it), -1 for other tasks.
+// The nonzero (CSR position) that is residual nonzero x of those counted by `res`; it lies in [lo, hi).
+__device__ inline int residual_at(const Residual &res, int x, int lo, int hi) {
+    if (!res.scan) return x;
+    while (lo < hi) {                       // the first with more than x of them before its successor
+        const int mid = lo + ((hi - lo) >> 1);
+        if (res.scan[mid + 1] <= x) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
 // Per flat SDDMM residual segment (cs entries of the residual list): its first column if the segment lies in one row, else -1.
-__global__ __launch_bounds__(256) void k_segment_cols(const int32_t *res_row, const int32_t *res_col, int nres, int cs, int nseg, int32_t *seg_col) {
+__global__ __launch_bounds__(256) void k_segment_cols(const int32_t *row_of, const int32_t *col, Residual res, int n, int nres, int cs, int nseg, int32_t *seg_col) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nseg) return;
     const int64_t q = (int64_t)i * cs, q1 = q + cs < nres ? q + cs : nres;
-    seg_col[i] = res_row[q] == res_row[q1 - 1] ? res_col[q] : -1;
+    const int p = residual_at(res, (int)q, 0, n), p1 = residual_at(res, (int)q1 - 1, p, n);
+    seg_col[i] = row_of[p] == row_of[p1] ? col[p] : -1;
 }
-
-__global__ __launch_bounds__(256) void k_task_cols(const libra_task_t *tasks, int nt, const int32_t *res_col, int32_t *task_col) {
+// Per SpMM task: first column of a row segment's entries (the tables order the segments by it), -1 for other tasks.
+__global__ __launch_bounds__(256) void k_task_cols(const libra_task_t *tasks, int nt, const int32_t *rowptr, const int32_t *rowbase, const int32_t *col, Residual res, int32_t *task_col) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nt) return;
-    task_col[i] = tasks[i].kind == LIBRA_TASK_CHUNK ? res_col[tasks[i].res_begin] : -1;
+    const libra_task_t &t = tasks[i];
+    int c = -1;
+    if (t.kind == LIBRA_TASK_CHUNK) c = col[residual_at(res, t.res_begin - rowbase[t.id], rowptr[t.id], rowptr[t.id + 1])];
+    task_col[i] = c;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1744,14 +1782,21 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         hipLaunchKernelGGL(k_share, dim3(std::min(blocks_for(n, SHARE_SAMPLES), 1024u)), dim3(SHARE_SAMPLES), 0, s, L.win_ptr, L.scol, L.vmask, nw, ngroups, (int)nsample, L.ctr);
         if (o.build_spmm)
             hipLaunchKernelGGL(k_row_bases, dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, resA, L.resptr, M, nw, R, L.rowbase);
-        hipLaunchKernelGGL(k_residual_fill, dim3(blocks_for(n, 256)), dim3(256), 0, s, d_col, val, vsize, n, R, L.row_of,
-                           resA, L.rowbase, L.a.res_perm, L.a.res_row, L.a.res_col, L.a.res_val,
-                           resD, L.d.res_perm, L.d.res_row, L.d.res_col, L.d.res_val);
+        auto fill_residuals = [&](const ResidualOut &a, const ResidualOut &d) {
+            auto run = [&](auto tag) {
+                typedef decltype(tag) V;
+                hipLaunchKernelGGL((k_residual_fill<V>), dim3(blocks_for(n, 256)), dim3(256), 0, s, d_col, (const V *)d_val, n, R, L.row_of, resA, L.rowbase, a, resD, d);
+            };
+            if (vsize == 2) run(uint16_t{});
+            else run(uint32_t{});
+        };
+        const ResidualOut arraysA{L.a.res_perm, L.a.res_row, L.a.res_col, L.a.res_val, nullptr, nullptr}, arraysD{L.d.res_perm, L.d.res_row, L.d.res_col, L.d.res_val, nullptr, nullptr};
+        if (keep_host_copy) fill_residuals(arraysA, arraysD);                  // otherwise when the plan's device copy has its places
         if (o.build_spmm && ntA > 0)
-            hipLaunchKernelGGL(k_task_cols, dim3(blocks_for(ntA, 256)), dim3(256), 0, s, L.a.tasks, ntA, L.a.res_col, L.task_col);
+            hipLaunchKernelGGL(k_task_cols, dim3(blocks_for(ntA, 256)), dim3(256), 0, s, L.a.tasks, ntA, d_rowptr, L.rowbase, d_col, resA, L.task_col);
         const int nsegD = o.build_sddmm ? piece_count(nresD, o.sddmm_Cs) : 0;
         if (nsegD > 0)
-            hipLaunchKernelGGL(k_segment_cols, dim3(blocks_for(nsegD, 256)), dim3(256), 0, s, L.d.res_row, L.d.res_col, nresD, o.sddmm_Cs, nsegD, L.seg_col);
+            hipLaunchKernelGGL(k_segment_cols, dim3(blocks_for(nsegD, 256)), dim3(256), 0, s, L.row_of, d_col, resD, n, nresD, o.sddmm_Cs, nsegD, L.seg_col);
         hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));
         hip_ok(hipStreamSynchronize(s));
         if (hipGetLastError() != hipSuccess) throw Fail{LIBRA_ERR_HIP};
@@ -1848,8 +1893,8 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         if (plan_buf) {
             // the plan's device copy straight from the workspace: no round trip through host memory
             auto src = [&](const SubOut &S, const TaskView &v, const int32_t *list, int empty_kind, const int32_t *zero_rows) {
-                DeviceSource d{S.blk_cols, S.blk_valptr, S.dense_perm, S.res_perm, S.res_row, S.res_col, zero_rows,
-                               reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val, d_rowptr, rows_here ? L.medium_rows : nullptr, nullptr};
+                DeviceSource d{S.blk_cols, S.blk_valptr, S.dense_perm, keep_host_copy ? S.res_perm : nullptr, keep_host_copy ? S.res_row : nullptr, S.res_col, zero_rows,
+                               reinterpret_cast<const uint64_t *>(S.bitmap), S.dense_val, S.res_val, d_rowptr, rows_here ? L.medium_rows : nullptr, nullptr, nullptr};
                 if (order_here)
                     d.write_tasks = [&S, v, list, empty_kind, s](DevTask *out, int64_t n) {
                         const int per_die = (int)((n + XC - 1) / XC);
@@ -1858,7 +1903,18 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
                     };
                 return d;
             };
-            if (int rc = adopt_device_arrays(P, src(L.a, va, L.o.order_a, LIBRA_TASK_WINDOW, L.zero_rows), src(L.d, vd, L.o.order_d, LIBRA_TASK_CHUNK, nullptr),
+            DeviceSource source_a = src(L.a, va, L.o.order_a, LIBRA_TASK_WINDOW, L.zero_rows);
+            if (!keep_host_copy)
+                source_a.write_residuals = [&](const SubPlanDev &a, const SubPlanDev &d) {
+                    ResidualOut to_a{const_cast<int32_t *>(a.res_perm), nullptr, nullptr, nullptr, (unsigned char *)a.res_ent, nullptr};
+                    ResidualOut to_d{const_cast<int32_t *>(d.res_perm), const_cast<int32_t *>(d.res_row), L.d.res_col, L.d.res_val, nullptr, const_cast<int32_t *>(d.res_base)};
+                    const bool whole = nresD == n;
+                    if (whole) to_d.entries = (unsigned char *)d.res_ent;
+                    fill_residuals(to_a, to_d);
+                    if (nresD > 0 && !whole)
+                        pack_sddmm_entries(vsize, L.d.res_col, L.d.res_val, d.res_row, nresD, d.res_ent, const_cast<int32_t *>(d.res_base), s);
+                };
+            if (int rc = adopt_device_arrays(P, source_a, src(L.d, vd, L.o.order_d, LIBRA_TASK_CHUNK, nullptr),
                                              plan_buf, plan_bytes, stream)) throw Fail{rc};
         }
         mark("plan buffer written");

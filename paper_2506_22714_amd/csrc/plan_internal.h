@@ -89,6 +89,9 @@ struct DeviceSource {
     const void *dense_val, *res_val;
     const int32_t *rowptr, *medium_rows;        // of the matrix (medium_rows: nullptr = the plan's host list)
     std::function<void(DevTask *out, int64_t n)> write_tasks;      // set if the task table was ordered on the device: queues its records
+    // set (with the SpMM sub-plan) if the residual entries of both sub-plans are not in arrays: queues the passes that write them, with
+    // their permutations and rows, to their places in the plan's device copy
+    std::function<void(const SubPlanDev &spmm, const SubPlanDev &sddmm)> write_residuals;
 };
 
 struct SubPlan {
@@ -170,6 +173,8 @@ LIBRA_HD inline int64_t sampled_group(int64_t k, int64_t ngroups, int64_t nsampl
 int adopt_device_arrays(libra_plan_s *plan, const DeviceSource &spmm, const DeviceSource &sddmm, void *dev_buf, size_t bytes, void *stream);
 // Are the SDDMM output records sorted by CSR position and do they carry a stage slot (16-bit values, the kernels' window and block)?
 inline bool sorted_records(const libra_plan_s *P) { return P->vdt != LIBRA_F32 && P->o.W == 16 && P->o.KB == 16; }
+// Queues the pass that packs SDDMM residual entries from arrays in device memory (`stream`: a hipStream_t).
+void pack_sddmm_entries(int value_bytes, const int32_t *col, const void *val, const int32_t *row, int64_t n, void *entries, int32_t *base, void *stream);
 // Bytes libra_plan_upload / adopt_device_arrays need for a plan with these array sizes.
 size_t plan_buffer_bytes(const libra_plan_s *plan);
 }  // namespace libra
