@@ -119,7 +119,8 @@ struct Layout {
     int32_t *hist, *nzero, *zbase, *nres, *resptr, *zero_rows, *task_col, *seg_col;
     SubOut a, d;
     OrderScratch o;
-    int32_t *sizes, *medium_rows, *long_rows, *long_lens;
+    int32_t *sizes, *medium_rows, *long_rows;
+    uint32_t *long_lens;
     void *tmp;
     size_t tmp_bytes;
     size_t total;
@@ -137,24 +138,45 @@ struct NotDense {                       // of a nonzero's bits in `dense` (1: in
 size_t order_items(const Sizes &z) { return (size_t)std::max(z.tasks_a_max, std::max(z.tasks_d_max, z.segs_d_max)); }
 int64_t order_slots(int64_t tasks) { return 2 * tasks + 64; }      // the die-aware orders add empty tasks
 
+// Stable sorts of task keys.  By default rocPRIM merge-sorts up to 2^20 items, two launches for each doubling from 1,024 on; from
+// SORT_BY_DIGITS items on the passes over 8-bit digits are fewer launches (GAT graph, three sorts of some 500,000 items: 0.75 ms, now 0.45).
+constexpr size_t SORT_BY_DIGITS = 1 << 17;
+template <bool DESC, class K, class In>
+hipError_t sort_pairs(void *tmp, size_t &bytes, K *key_in, K *key_out, In in, int32_t *out, size_t n, unsigned bits, hipStream_t s) {
+    typedef rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config, rocprim::default_config, 0> ByDigits;
+    auto run = [&](auto config) {
+        typedef decltype(config) Config;
+        if constexpr (DESC) return rocprim::radix_sort_pairs_desc<Config>(tmp, bytes, key_in, key_out, in, out, n, 0u, bits, s);
+        else return rocprim::radix_sort_pairs<Config>(tmp, bytes, key_in, key_out, in, out, n, 0u, bits, s);
+    };
+    if (tmp) return n >= SORT_BY_DIGITS ? run(ByDigits{}) : run(rocprim::default_config{});
+    size_t most = 0;                        // the size query: of either
+    if (hipError_t e = run(ByDigits{})) return e;
+    most = bytes;
+    bytes = 0;
+    if (hipError_t e = run(rocprim::default_config{})) return e;
+    bytes = std::max(bytes, most);
+    return hipSuccess;
+}
+
 size_t rocprim_temp_bytes(const Sizes &z) {
     size_t best = 0, sz = 0;
     (void)rocprim::exclusive_scan(nullptr, sz, (int32_t *)nullptr, (int32_t *)nullptr, (int32_t)0, (size_t)(z.n + z.nw + 2),
                             rocprim::plus<int32_t>());
     best = std::max(best, sz);
-    const size_t m = order_items(z) + 16;
+    const size_t m = std::max(order_items(z) + 16, (size_t)z.n / LIBRA_SOFTMAX_LONG_ROW + 1);
     sz = 0;
     (void)rocprim::exclusive_scan(nullptr, sz, rocprim::make_transform_iterator((const uint8_t *)nullptr, NotDense{1}), (int32_t *)nullptr, (int32_t)0, (size_t)(z.n + 1),
                             rocprim::plus<int32_t>());
     best = std::max(best, sz);
     sz = 0;
-    (void)rocprim::radix_sort_pairs(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, m, 0, 32);
+    (void)sort_pairs<false>(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, (const int32_t *)nullptr, (int32_t *)nullptr, m, 32, nullptr);
     best = std::max(best, sz);
     sz = 0;
-    (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 64);
+    (void)sort_pairs<true>(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 64, nullptr);
     best = std::max(best, sz);
     sz = 0;
-    (void)rocprim::radix_sort_pairs_desc(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 0, 32);
+    (void)sort_pairs<true>(nullptr, sz, (uint32_t *)nullptr, (uint32_t *)nullptr, rocprim::counting_iterator<int32_t>(0), (int32_t *)nullptr, m, 32, nullptr);
     best = std::max(best, sz);
     sz = 0;
     (void)rocprim::inclusive_scan(nullptr, sz, (u64 *)nullptr, (u64 *)nullptr, m, rocprim::maximum<u64>());
@@ -179,7 +201,7 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     L.sizes = A.take<int32_t>(64);
     L.medium_rows = A.take<int32_t>((size_t)z.M);
     L.long_rows = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
-    L.long_lens = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
+    L.long_lens = A.take<uint32_t>(3 * (n / LIBRA_SOFTMAX_LONG_ROW + 1));        // lengths, sorted lengths, sorted rows
     L.win_ptr = A.take<int32_t>(nw + 1);
     const size_t boundaries = (size_t)tile_count(z.n) + 1;
     L.tiles.pos = A.take<int32_t>(boundaries);
@@ -255,7 +277,7 @@ __global__ __launch_bounds__(256) void k_check_rowptr(const int32_t *rowptr, int
     const bool bad = i < M ? rowptr[i + 1] < rowptr[i] : i == M && (rowptr[0] != 0 || rowptr[M] != n);
     if (bad) atomicOr(&ctr[C_ERR], (u64)4);
 }
-__global__ __launch_bounds__(256) void k_row_lengths(const int32_t *rowptr, const int32_t *rows, int n, int32_t *len) {
+__global__ __launch_bounds__(256) void k_row_lengths(const int32_t *rowptr, const int32_t *rows, int n, uint32_t *len) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) len[i] = rowptr[rows[i] + 1] - rowptr[rows[i]];
 }
@@ -1298,10 +1320,9 @@ __global__ __launch_bounds__(256) void k_order_group_items(const int32_t *list, 
 __global__ void k_order_queue_starts(const int32_t *base, int rounds, int32_t *start) {
     if (threadIdx.x <= XC) start[threadIdx.x] = base[threadIdx.x * rounds];
 }
-// Slot 8 j + x of the region is the j-th item of queue x, or an empty task; last = slots up to the last task that does something.
-__global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *queue, const int32_t *pieces, int4 p0, int4 p1, int np, int4 n0, int4 n1, int slots,
-                                                    int32_t *out, int32_t *last) {
-    const int i = (gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;      // the end first: the others then leave `last` alone
+// Slot 8 j + x of the region is the j-th item of queue x, or an empty task.
+__global__ __launch_bounds__(256) void k_order_emit(const int32_t *queue, const int32_t *pieces, int4 p0, int4 p1, int np, int4 n0, int4 n1, int slots, int32_t *out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= slots) return;
     const int x = i % XC, j = i / XC;
     const int begin[XC + 1] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, np}, len[XC] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
@@ -1318,9 +1339,21 @@ __global__ __launch_bounds__(256) void k_order_emit(TaskView v, const int32_t *q
         item = queue[pieces[3 * b + 2] + j - pieces[3 * b + 1]];
     }
     out[i] = item;
-    // the last such slot of the wave
-    const u64 used = __ballot(item >= 0 && !v.empty(item));
-    if (used && (int)(threadIdx.x & 63) == 63 - __builtin_clzll(used) && __hip_atomic_load(last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= i) atomicMax(last, i + 1);
+}
+// The slots up to the last task that does something: one workgroup, from the end on (the queues are levelled, so it is near the end).  As
+// a maximum that all waves of k_order_emit look at, two tables of 500,000 slots took 200 us and not 22.
+__global__ __launch_bounds__(1024) void k_order_last(TaskView v, const int32_t *out, int slots, int32_t *last) {
+    __shared__ int found;
+    if (threadIdx.x == 0) found = 0;
+    __syncthreads();
+    for (int64_t end = slots; end > 0 && found == 0; end -= 1024) {
+        const int64_t i = end - 1 - (int64_t)threadIdx.x;
+        const int item = i >= 0 ? out[i] : -1;
+        __syncthreads();                    // every thread has seen that nothing was found before
+        if (item >= 0 && !v.empty(item)) atomicMax(&found, (int)i + 1);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *last = found;
 }
 // Device task records, die by die (as the host packs them); slots past the table's end and -1 hold empty tasks.
 __global__ __launch_bounds__(256) void k_order_records(TaskView v, const int32_t *order, int n, int per_die, const int32_t *blk_valptr, int empty_kind, DevTask *out) {
@@ -1402,14 +1435,14 @@ struct Orderer {
     }
     void sort_by_key(const int32_t *in, int32_t *out, size_t n, int bits) {          // key_in -> key_out, stable
         size_t sz = L.tmp_bytes;
-        hip_ok(rocprim::radix_sort_pairs(L.tmp, sz, L.o.key_in, L.o.key_out, in, out, n, 0u, (unsigned)bits, s));
+        hip_ok(sort_pairs<false>(L.tmp, sz, L.o.key_in, L.o.key_out, in, out, n, (unsigned)bits, s));
     }
     // items 0 .. n-1 by descending cost, stable
     void heaviest_first(int n, int32_t *out) {
         if (n == 0) return;
         run(k_order_costs, n, v, n, L.o.key_in);
         size_t sz = L.tmp_bytes;
-        hip_ok(rocprim::radix_sort_pairs_desc(L.tmp, sz, L.o.key_in, L.o.key_out, rocprim::counting_iterator<int32_t>(0), out, (size_t)n, 0u, 32u, s));
+        hip_ok(sort_pairs<true>(L.tmp, sz, L.o.key_in, L.o.key_out, rocprim::counting_iterator<int32_t>(0), out, (size_t)n, 32u, s));
     }
     void identity(int n, int first, int32_t *out) { if (n) run(k_order_identity, n, n, first, out); }
     int copy(const int32_t *list, int n, int32_t *out) {
@@ -1461,10 +1494,10 @@ struct Orderer {
         begin[XC] = (int)table.size() / 3;
         if (begin[XC] > MAX_PIECES) throw Fail{LIBRA_ERR_HIP};
         hip_ok(hipMemcpyAsync(L.o.pieces, table.data(), table.size() * 4, hipMemcpyHostToDevice, s));
-        launch(k_order_fill, 1, 64, L.o.meta + 32, 1, 0);
-        run(k_order_emit, slots, v, (const int32_t *)L.o.queue, (const int32_t *)L.o.pieces, make_int4(begin[0], begin[1], begin[2], begin[3]),
+        run(k_order_emit, slots, (const int32_t *)L.o.queue, (const int32_t *)L.o.pieces, make_int4(begin[0], begin[1], begin[2], begin[3]),
             make_int4(begin[4], begin[5], begin[6], begin[7]), begin[XC], make_int4(len[0], len[1], len[2], len[3]),
-            make_int4(len[4], len[5], len[6], len[7]), slots, out, L.o.meta + 32);
+            make_int4(len[4], len[5], len[6], len[7]), slots, out);
+        launch(k_order_last, 1, 1024, v, (const int32_t *)out, slots, L.o.meta + 32);
         const int end = peek(L.o.meta + 32, s);         // also keeps `table` alive until it has been copied
         check(end >= 0 && end <= slots);
         return end;
@@ -1485,7 +1518,7 @@ struct Orderer {
         run(k_order_group_costs, ng, (const u64 *)o.wide_out, (const int32_t *)o.first, ng, o.wide_in);
         int32_t *gord = reinterpret_cast<int32_t *>(o.key_in), *size = reinterpret_cast<int32_t *>(o.key_out);
         size_t sz = L.tmp_bytes;
-        hip_ok(rocprim::radix_sort_pairs_desc(L.tmp, sz, o.wide_in, o.wide_out, rocprim::counting_iterator<int32_t>(0), gord, (size_t)ng, 0u, 40u, s));
+        hip_ok(sort_pairs<true>(L.tmp, sz, o.wide_in, o.wide_out, rocprim::counting_iterator<int32_t>(0), gord, (size_t)ng, 40u, s));
         run(k_order_deal, rounds * XC + 1, (const int32_t *)gord, (const int32_t *)o.first, ng, rounds, size, o.rank);
         scan_sum<int32_t>(size, o.base, (size_t)rounds * XC + 1);
         run(k_order_group_items, n, (const int32_t *)o.ord2, (const int32_t *)o.flag, (const int32_t *)o.scan, (const int32_t *)o.first,
@@ -1658,15 +1691,13 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             hip_ok(hipStreamSynchronize(s));
             P->n_medium_rows = count[0];
             if (count[1] > 0) {
-                std::vector<int32_t> rows, len, by(count[1]);
-                hipLaunchKernelGGL(k_row_lengths, dim3(blocks_for(count[1], 256)), dim3(256), 0, s, d_rowptr, L.long_rows, count[1], L.long_lens);
-                fetch(rows, L.long_rows, (size_t)count[1], s);
-                fetch(len, L.long_lens, (size_t)count[1], s);
+                uint32_t *len = L.long_lens, *by_len = len + count[1];
+                int32_t *sorted = reinterpret_cast<int32_t *>(by_len + count[1]);
+                hipLaunchKernelGGL(k_row_lengths, dim3(blocks_for(count[1], 256)), dim3(256), 0, s, d_rowptr, L.long_rows, count[1], len);
+                size_t sz = L.tmp_bytes;
+                hip_ok(sort_pairs<true>(L.tmp, sz, len, by_len, (const int32_t *)L.long_rows, sorted, (size_t)count[1], 32u, s));
+                fetch(P->long_rows, sorted, (size_t)count[1], s);
                 hip_ok(hipStreamSynchronize(s));
-                for (int i = 0; i < count[1]; ++i) by[i] = i;
-                std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return len[a] > len[b]; });
-                P->long_rows.resize(by.size());
-                for (size_t i = 0; i < by.size(); ++i) P->long_rows[i] = rows[by[i]];
             }
         } else {
             fetch(P->rowptr, d_rowptr, (size_t)M + 1, s);
