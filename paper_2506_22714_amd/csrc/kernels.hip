@@ -1710,24 +1710,66 @@ int spmm_launch(const libra_plan_t *P, const SpmmArgs &a, int n, int64_t nt, hip
 namespace {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// One row of workgroups per copy.
+__global__ __launch_bounds__(256) void device_copies_kernel(DeviceCopies c) {
+    const auto &p = c.part[blockIdx.y];
+    const uint64_t tid = (uint64_t)blockIdx.x * 256 + threadIdx.x, nthreads = (uint64_t)gridDim.x * 256;
+    const uintptr_t at = (uintptr_t)p.to | (uintptr_t)p.from;
+    auto move = [&](auto tag, uint64_t begin) {
+        typedef decltype(tag) V;
+        const uint64_t n = p.bytes / sizeof(V);
+        for (uint64_t i = begin / sizeof(V) + tid; i < n; i += nthreads) reinterpret_cast<V *>(p.to)[i] = reinterpret_cast<const V *>(p.from)[i];
+        return n * sizeof(V);
+    };
+    uint64_t done = 0;
+    if (!(at & 15)) done = move(uint4{}, 0);
+    else if (!(at & 3)) done = move(uint32_t{}, 0);
+    move(uint8_t{}, done);
+}
+
 // Lays arrays out back to back (256-byte aligned, 16 spare bytes each) and copies them from host memory, from
-// device memory, or only reserves their place (arrays that a kernel packs afterwards).
+// device memory, or only reserves their place (arrays that a kernel packs afterwards).  `gathered`: copies inside device memory share
+// launches, neighbouring copies from host memory become one; they are queued by flush().
 struct Uploader {
     char *base = nullptr;     // nullptr: size pass only
     size_t off = 0;
     hipStream_t s = nullptr;
-    bool ok = true;
+    bool ok = true, gathered = false;
+    DeviceCopies copies;
+    struct FromHost { const void *from; size_t bytes, at; };
+    std::vector<FromHost> from_host;
+    std::vector<std::vector<char>> joined;        // alive until the copies have finished
     template <class P>
     void put(const void *host_src, const void *dev_src, size_t bytes, P *&dst) {
         if (base) {
             dst = reinterpret_cast<P *>(base + off);
-            if (bytes && host_src && hipMemcpyAsync(base + off, host_src, bytes, hipMemcpyHostToDevice, s) != hipSuccess) ok = false;
-            if (bytes && !host_src && dev_src && hipMemcpyAsync(base + off, dev_src, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) ok = false;
+            if (gathered) {
+                if (bytes && host_src) from_host.push_back({host_src, bytes, off});
+                if (bytes && !host_src && dev_src) {
+                    if (copies.full()) ok = copies.flush(s) && ok;
+                    copies.add(base + off, dev_src, bytes);
+                }
+            } else {
+                if (bytes && host_src && hipMemcpyAsync(base + off, host_src, bytes, hipMemcpyHostToDevice, s) != hipSuccess) ok = false;
+                if (bytes && !host_src && dev_src && hipMemcpyAsync(base + off, dev_src, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) ok = false;
+            }
         }
         off += align256(bytes + 16);
     }
     template <class V, class P>
     void putv(const V &v, P *&dst) { put(v.data(), nullptr, v.size() * sizeof(v[0]), dst); }
+    void flush() {
+        ok = copies.flush(s) && ok;
+        for (size_t i = 0; i < from_host.size();) {
+            size_t e = i + 1;                   // the next array begins at most a page behind the end of this one: one copy
+            while (e < from_host.size() && from_host[e].at - (from_host[e - 1].at + from_host[e - 1].bytes) < 4096) ++e;
+            const size_t begin = from_host[i].at, end = from_host[e - 1].at + from_host[e - 1].bytes;
+            joined.emplace_back(end - begin);
+            for (; i < e; ++i) std::memcpy(joined.back().data() + (from_host[i].at - begin), from_host[i].from, from_host[i].bytes);
+            if (hipMemcpyAsync(base + begin, joined.back().data(), end - begin, hipMemcpyHostToDevice, s) != hipSuccess) ok = false;
+        }
+        from_host.clear();
+    }
 };
 
 // Slots of the device task table: the table's length rounded up to whole rounds of the dies.
@@ -1844,6 +1886,9 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     const bool pack_a = st && !(da && da->write_tasks);
     if (pack_a) st->tasks_a = pack_tasks(P, sa, true);
     u.put(pack_a ? (const void *)st->tasks_a.data() : nullptr, nullptr, task_slots(sa.n.tasks) * sizeof(DevTask), sa.dev.tasks);
+    const bool pack_d = st && !(dd && dd->write_tasks);
+    if (pack_d) st->tasks_d = pack_tasks(P, sd, false);
+    u.put(pack_d ? (const void *)st->tasks_d.data() : nullptr, nullptr, task_slots(sd.n.tasks) * sizeof(DevTask), sd.dev.tasks);
     u.put(H(sa.blk_cols.data()), da ? da->blk_cols : nullptr, (size_t)sa.n.col_slots * 4, sa.dev.blk_cols);
     u.put(H(sa.blk_bitmap.data()), da ? da->blk_bitmap : nullptr, (size_t)sa.n.bitmap_words * 8, sa.dev.blk_bitmap);
     u.put(H(sa.blk_valptr.data()), da ? da->blk_valptr : nullptr, P->o.build_spmm ? (size_t)(sa.n.blocks + 1) * 4 : 0, sa.dev.blk_valptr);
@@ -1866,9 +1911,6 @@ void layout(libra_plan_t *P, Uploader &u, Staging *st, const DeviceSource *da, c
     u.put(H(sa.res_perm.data()), da ? da->res_perm : nullptr, nres * 4, sa.dev.res_perm);
     u.put(H(sa.zero_rows.data()), da ? da->zero_rows : nullptr, (size_t)sa.n.zero_rows * 4, sa.dev.zero_rows);
     // ---- SDDMM ----
-    const bool pack_d = st && !(dd && dd->write_tasks);
-    if (pack_d) st->tasks_d = pack_tasks(P, sd, false);
-    u.put(pack_d ? (const void *)st->tasks_d.data() : nullptr, nullptr, task_slots(sd.n.tasks) * sizeof(DevTask), sd.dev.tasks);
     u.put(H(sd.blk_cols.data()), dd ? dd->blk_cols : nullptr, (size_t)sd.n.col_slots * 4, sd.dev.blk_cols);
     u.put(H(sd.blk_bitmap.data()), dd ? dd->blk_bitmap : nullptr, (size_t)sd.n.bitmap_words * 8, sd.dev.blk_bitmap);
     u.put(H(sd.blk_valptr.data()), dd ? dd->blk_valptr : nullptr, P->o.build_sddmm ? (size_t)(sd.n.blocks + 1) * 4 : 0, sd.dev.blk_valptr);
@@ -1933,6 +1975,16 @@ void libra::pack_sddmm_entries(int value_bytes, const int32_t *col, const void *
     pack_entries(value_bytes, col, val, row, n, entries, base, (hipStream_t)stream);
 }
 
+bool libra::DeviceCopies::flush(void *stream) {
+    if (n == 0) return true;
+    uint64_t most = 0;
+    for (int i = 0; i < n; ++i) most = std::max(most, part[i].bytes);
+    const unsigned blocks = (unsigned)std::min<uint64_t>(most / (256 * 16) + 1, 2048);
+    hipLaunchKernelGGL(device_copies_kernel, dim3(blocks, (unsigned)n), dim3(256), 0, (hipStream_t)stream, *this);
+    n = 0;
+    return hipGetLastError() == hipSuccess;
+}
+
 int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const DeviceSource &dd, void *dev_buf, size_t bytes, void *stream) {
     if (!dev_buf) return LIBRA_ERR_NULL;
     if (bytes < plan_buffer_bytes(P) || ((uintptr_t)dev_buf & 255)) return LIBRA_ERR_BUFFER;
@@ -1943,7 +1995,9 @@ int libra::adopt_device_arrays(libra_plan_t *P, const DeviceSource &da, const De
         Uploader u;
         u.base = (char *)dev_buf;
         u.s = s;
+        u.gathered = true;
         layout(P, u, &st, &da, &dd);
+        u.flush();
         auto grid = [](int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1 << 16)); };
         const SubPlan &sa = P->spmm, &sd = P->sddmm;
         if (da.write_tasks && sa.n.tasks) da.write_tasks(const_cast<DevTask *>(sa.dev.tasks), sa.n.tasks);

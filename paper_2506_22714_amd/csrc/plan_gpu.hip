@@ -46,6 +46,11 @@ typedef unsigned long long u64;
 // level; 2^20 rows (plan and one step of the GAT graph) 13.15 / 12.05 ms.
 constexpr int64_t DEVICE_ROWS_MIN = 1 << 17;
 
+// Tables of fewer tasks are ordered on the host: there a task costs 40 - 70 ns (copies both ways, radix sorts of 40-byte records,
+// merging), here the launches and waits cost 0.2 ms and a task 1 ns.  GAT graph (1.05 M tasks in both tables): 71 -> 1.5 ms,
+// the whole plan 86.7 -> 24.1 ms; 8,000 tasks without segments: 0.32 ms on the host, 0.21 here.
+constexpr int64_t DEVICE_ORDER_MIN = 8192;
+
 enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_COUNT };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -122,6 +127,7 @@ struct Layout {
     int32_t *sizes, *medium_rows, *long_rows;
     uint32_t *long_lens;
     void *tmp;
+    char *stage;
     size_t tmp_bytes;
     size_t total;
 };
@@ -193,11 +199,17 @@ size_t rocprim_temp_bytes(const Sizes &z) {
     return best + 4096;
 }
 
+// What goes to the host together: the counters, and tables that are ordered there with the first values of their blocks.
+size_t stage_bytes(const Sizes &z) {
+    return align256(C_COUNT * sizeof(u64)) + (size_t)DEVICE_ORDER_MIN * (sizeof(libra_task_t) + 2 * sizeof(int32_t)) + 2 * ((size_t)z.nbmax + 1) * sizeof(int32_t) + 8 * 256;
+}
+
 Layout make_layout(const Sizes &z, int vsize, void *base) {
     Layout L{};
     Arena A{(char *)base};
     const size_t n = (size_t)z.n, nw = (size_t)z.nw, nb = (size_t)z.nbmax;
     L.ctr = A.take<u64>(C_COUNT);
+    L.hist = A.take<int32_t>(nw * W);       // right behind the counters: cleared together
     L.sizes = A.take<int32_t>(64);
     L.medium_rows = A.take<int32_t>((size_t)z.M);
     L.long_rows = A.take<int32_t>(n / LIBRA_SOFTMAX_LONG_ROW + 1);
@@ -208,7 +220,6 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     L.tiles.win = A.take<int32_t>(boundaries);
     L.tiles.split = A.take<int32_t>(boundaries * W);
     L.tiles.tail = A.take<int32_t>(boundaries * W);
-    L.hist = A.take<int32_t>(nw * W);
     L.scol = A.take<int32_t>(n);
     L.spos = A.take<int32_t>(n);
     L.vmask = A.take<uint16_t>(n);
@@ -258,6 +269,7 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
         o.order_a = A.take<int32_t>((size_t)order_slots(z.tasks_a_max));
         o.order_d = A.take<int32_t>((size_t)order_slots(z.tasks_d_max + z.segs_d_max));
     }
+    L.stage = A.take<char>(stage_bytes(z));
     L.tmp_bytes = rocprim_temp_bytes(z);
     L.tmp = A.take<uint8_t>(L.tmp_bytes);
     L.total = align256(A.off) + 256;
@@ -934,35 +946,25 @@ struct Residual {
     __device__ bool has(int p) const { return !scan || !(dense[p] & bit); }
 };
 
-struct WinRows {
-    int nr;
-    int rlen[W];
-    unsigned valid, split, scalar;
-    int q_unsplit, q_split;
+// The residual parts of a window's rows, a lane per row (16 neighbouring lanes per window).
+struct RowPart {
+    int before, len;            // residual nonzeros before the row, and in it
+    unsigned valid, split, scalar;      // of the window: rows of the matrix, decomposed rows, others with residual nonzeros
 };
-
-__device__ inline WinRows window_rows(const int32_t *rowptr, const Residual &res, int64_t M, int t, const Rule &R, int *n_short, int *n_long) {
-    WinRows z;
-    const int64_t r0 = (int64_t)t * W;
-    z.nr = (int)min((int64_t)W, M - r0);
-    z.valid = z.split = z.scalar = 0;
-    z.q_unsplit = z.q_split = 0;
-    *n_short = *n_long = 0;
-    for (int r = 0; r < W; ++r) {
-        z.rlen[r] = 0;
-        if (r >= z.nr) continue;
-        const int len = res.before(rowptr[r0 + r + 1]) - res.before(rowptr[r0 + r]);
-        z.rlen[r] = len;
-        z.valid |= 1u << r;
-        if (len == 0) continue;
-        if (len < R.short_len) {
-            ++*n_short;
-        } else {
-            ++*n_long;
-            if (len > R.Cs) z.split |= 1u << r;
-        }
-        if (!((z.split >> r) & 1u)) { z.scalar |= 1u << r; z.q_unsplit += len; } else z.q_split += len;
-    }
+__device__ inline int sum_over_rows(int x) {
+#pragma unroll
+    for (int m = 1; m < W; m <<= 1) x += __shfl_xor(x, m, W);
+    return x;
+}
+__device__ inline unsigned rows_where(bool x) { return (unsigned)(__ballot(x) >> (threadIdx.x % 64 / W * W)) & 0xffffu; }
+__device__ inline RowPart row_part(const int32_t *rowptr, const Residual &res, int64_t M, int t, const Rule &R) {
+    const int64_t row = (int64_t)t * W + threadIdx.x % W;
+    RowPart z;
+    z.before = res.before(rowptr[min(row, M)]);
+    z.len = res.before(rowptr[min(row + 1, M)]) - z.before;
+    z.valid = rows_where(row < M);
+    z.split = rows_where(z.len > 0 && z.len >= R.short_len && z.len > R.Cs);
+    z.scalar = rows_where(z.len > 0) & ~z.split;
     return z;
 }
 
@@ -971,116 +973,122 @@ __device__ inline void put_task(libra_task_t *t, int kind, int id, int b0, int b
     t->scalar_mask = sc; t->atomic_mask = at; t->store_mask = st; t->cost = cost;
 }
 
-// Per window: the hybrid load-balancing rule (Section 4.3).  FILL = false counts tasks, rows to clear and
-// residual nonzeros, a window per thread; FILL = true writes them at the offsets the prefix sums gave, a window per wave: a hub
-// window has thousands of tasks (GAT graph: 800 us with a thread per window, 221 with a wave).  A launch has fewer than 2^32
-// threads, so from 2^23 windows on a wave takes several.
-template <bool FILL>
+// Per window: the hybrid load-balancing rule (Section 4.3).  This pass counts tasks, rows to clear and residual nonzeros, 16 lanes per
+// window.  The matrix's numbers go to their counters once per workgroup, of which there are few.
+__global__ __launch_bounds__(256) void k_window_sizes(const int32_t *rowptr, Residual res_a, int64_t M, int nw, Rule R, const int32_t *blkptr_a, const int32_t *blkptr_d,
+                                                      int32_t *ntasks_a, int32_t *nzero, int32_t *nres, int32_t *ntasks_d, u64 *ctr) {
+    __shared__ unsigned counts[4];
+    if (threadIdx.x < 4) counts[threadIdx.x] = 0;
+    __syncthreads();
+    const int r = threadIdx.x % W;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { ntasks_a[nw] = 0; nzero[nw] = 0; nres[nw] = 0; ntasks_d[nw] = 0; }
+    unsigned n_short = 0, n_long = 0, n_split = 0, n_chunks = 0;
+    for (int64_t t = (int64_t)blockIdx.x * (256 / W) + threadIdx.x / W; t < nw; t += (int64_t)gridDim.x * (256 / W)) {
+        int ta = 0, zero = 0, residual = 0;
+        if (R.build_a) {
+            const RowPart z = row_part(rowptr, res_a, M, (int)t, R);
+            const unsigned shorts = rows_where(z.len > 0 && z.len < R.short_len);
+            const int chunks = sum_over_rows(z.split >> r & 1u ? piece_count(z.len, R.Cs) : 0), nb = blkptr_a[t + 1] - blkptr_a[t];
+            const bool many = nb > R.Ts;
+            ta = (many ? piece_count(nb, R.Ts) + (z.scalar ? 1 : 0) : 1) + chunks;
+            zero = __popc(many ? z.valid : z.split);
+            residual = sum_over_rows(z.len);
+            n_short += __popc(shorts);
+            n_long += __popc((z.scalar | z.split) & ~shorts);
+            n_split += __popc(z.split);
+            n_chunks += chunks;
+        }
+        if (r == 0) {
+            ntasks_a[t] = ta;
+            nzero[t] = zero;
+            nres[t] = residual;
+            ntasks_d[t] = R.build_d ? piece_count(blkptr_d[t + 1] - blkptr_d[t], R.Ts_d) : 0;
+        }
+    }
+    if (r == 0) {
+        const unsigned n[4] = {n_short, n_long, n_split, n_chunks};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (n[k]) atomicAdd(&counts[k], n[k]);
+    }
+    __syncthreads();
+    const int to[4] = {C_SHORT, C_LONG, C_SPLIT, C_SEGMENTS};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((int)threadIdx.x == k && counts[k]) atomicAdd(&ctr[to[k]], (u64)counts[k]);
+}
+
+// The same rule: tasks and rows to clear at the offsets the prefix sums gave, a window per wave (a hub window has thousands of tasks);
+// and where each row's residual nonzeros start in the SpMM residual array (rows that are not decomposed first, in row order, then
+// the decomposed rows), minus the row's own prefix so that a nonzero only adds its scan value.  With a lane per row and per block:
+// GAT graph 118 us in both passes; one thread or wave that walked the rows, and a third pass, 332.  A launch has fewer than 2^32 threads, so
+// from 2^23 windows on a wave takes several.
 __global__ __launch_bounds__(128) void k_window_tasks(const int32_t *rowptr, Residual res_a, int64_t M, int nw, Rule R,
                                                       const int32_t *blkptr_a, const int32_t *blkmask_a, const int32_t *blkncols_a,
                                                       const int32_t *blkptr_d, const int32_t *blkncols_d,
-                                                      int32_t *ntasks_a, int32_t *nzero, int32_t *nres, int32_t *ntasks_d, u64 *ctr,
                                                       const int32_t *tbase_a, const int32_t *zbase, const int32_t *resptr, const int32_t *tbase_d,
-                                                      libra_task_t *tasks_a, int32_t *zero_rows, libra_task_t *tasks_d) {
-    constexpr int LANES = FILL ? 64 : 1;
-    const int lane = threadIdx.x % LANES;
-    int t = blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES;
-    if (!FILL && t == nw) { ntasks_a[nw] = 0; nzero[nw] = 0; nres[nw] = 0; ntasks_d[nw] = 0; }
-    for (; t < nw; t += gridDim.x * (blockDim.x / LANES)) {
+                                                      libra_task_t *tasks_a, int32_t *zero_rows, int32_t *rowbase, libra_task_t *tasks_d) {
+    const int lane = threadIdx.x % 64, r = lane % W;
+    for (int t = (int)(blockIdx.x * 2 + threadIdx.x / 64); t < nw; t += (int)(gridDim.x * 2)) {
         const int64_t r0 = (int64_t)t * W;
         if (R.build_a) {
-            int n_short, n_long;
-            const WinRows z = window_rows(rowptr, res_a, M, t, R, &n_short, &n_long);
+            const RowPart z = row_part(rowptr, res_a, M, t, R);
+            const bool split = z.split >> r & 1u, mine = lane < W && (z.valid >> r & 1u);
+            // places in the residual array: an inclusive sum over the rows of either kind
+            int plain = split ? 0 : z.len, cut = split ? z.len : 0;
+            const int plain_all = sum_over_rows(plain), own = z.len;
+#pragma unroll
+            for (int m = 1; m < W; m <<= 1) {
+                const int x = __shfl_up(plain, m, W), y = __shfl_up(cut, m, W);
+                if (r >= m) { plain += x; cut += y; }
+            }
+            const int q0 = resptr[t], q1 = q0 + plain_all, start = split ? q1 + cut - own : q0 + plain - own;
+            if (mine) rowbase[r0 + r] = start - z.before;
             const int b0 = blkptr_a[t], b1 = blkptr_a[t + 1];
-            const bool many = b1 - b0 > R.Ts;
-            int nchunks = 0;
-            for (int r = 0; r < z.nr; ++r)
-                if ((z.split >> r) & 1u) nchunks += piece_count(z.rlen[r], R.Cs);
-            if (!FILL) {
-                const int nwt = many ? piece_count(b1 - b0, R.Ts) + (z.scalar ? 1 : 0) : 1;
-                ntasks_a[t] = nwt + nchunks;
-                nzero[t] = many ? z.nr : __popc(z.split);
-                nres[t] = z.q_unsplit + z.q_split;
-                if (n_short) atomicAdd(&ctr[C_SHORT], (u64)n_short);
-                if (n_long) atomicAdd(&ctr[C_LONG], (u64)n_long);
-                if (z.split) atomicAdd(&ctr[C_SPLIT], (u64)__popc(z.split));
-                if (nchunks) atomicAdd(&ctr[C_SEGMENTS], (u64)nchunks);
-            } else {
-                libra_task_t *out = tasks_a + tbase_a[t];
-                int32_t *zr = zero_rows + zbase[t];
-                const int q0 = resptr[t], q1 = q0 + z.q_unsplit;
-                auto touched = [&](int g0, int g1) { unsigned m = 0; for (int b = g0; b < g1; ++b) m |= (unsigned)blkmask_a[b]; return m; };
-                auto cols_in = [&](int g0, int g1) { unsigned c = 0; for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_a[b]; return c; };
-                if (many) {
-                    const int groups = piece_count(b1 - b0, R.Ts);
-                    for (int g = lane; g < groups; g += LANES) {
-                        const int g0 = b0 + g * R.Ts, g1 = piece_end(g0, b1, R.Ts);
-                        put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched(g0, g1), 0u, cols_in(g0, g1));
-                    }
-                    out += groups;
-                    if (z.scalar) {
-                        if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
-                        ++out;
-                    }
-                    if (lane == 0)
-                        for (int r = 0; r < z.nr; ++r) *zr++ = (int32_t)(r0 + r);
-                } else {
-                    if (lane == 0) {
-                        put_task(out, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched(b0, b1), z.valid & ~z.split,
-                                 cols_in(b0, b1) + (unsigned)(q1 - q0));
-                        for (int r = 0; r < z.nr; ++r)
-                            if ((z.split >> r) & 1u) *zr++ = (int32_t)(r0 + r);
-                    }
+            libra_task_t *out = tasks_a + tbase_a[t];
+            int32_t *zr = zero_rows + zbase[t];
+            if (b1 - b0 > R.Ts) {
+                const int groups = piece_count(b1 - b0, R.Ts);
+                for (int g = lane; g < groups; g += 64) {
+                    const int g0 = b0 + g * R.Ts, g1 = piece_end(g0, b1, R.Ts);
+                    unsigned touched = 0, cols = 0;
+                    for (int b = g0; b < g1; ++b) { touched |= (unsigned)blkmask_a[b]; cols += (unsigned)blkncols_a[b]; }
+                    put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, q0, q0, 0u, touched, 0u, cols);
+                }
+                out += groups;
+                if (z.scalar) {
+                    if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b1, b1, q0, q1, z.scalar, z.scalar, 0u, (unsigned)(q1 - q0));
                     ++out;
                 }
-                int q = q1;
-                for (int r = 0; r < z.nr; ++r) {
-                    if (!((z.split >> r) & 1u)) continue;
-                    const int n = piece_count(z.rlen[r], R.Cs), e = q + z.rlen[r];
-                    for (int k = lane; k < n; k += LANES) {
-                        const int qs = q + k * R.Cs, qe = piece_end(qs, e, R.Cs);
-                        put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + r), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
-                    }
-                    out += n;
-                    q = e;
-                }
+                if (mine) zr[r] = (int32_t)(r0 + r);
+            } else {
+                unsigned touched = 0, cols = 0;
+                for (int b = b0 + lane; b < b1; b += 64) { touched |= (unsigned)blkmask_a[b]; cols += (unsigned)blkncols_a[b]; }
+#pragma unroll
+                for (int m = 1; m < 64; m <<= 1) { touched |= __shfl_xor(touched, m, 64); cols += __shfl_xor(cols, m, 64); }
+                if (lane == 0) put_task(out, LIBRA_TASK_WINDOW, t, b0, b1, q0, q1, z.scalar, z.split & touched, z.valid & ~z.split, cols + (unsigned)(q1 - q0));
+                if (mine && split) zr[__popc(z.split & ((1u << r) - 1u))] = (int32_t)(r0 + r);
+                ++out;
             }
-        } else if (!FILL) {
-            ntasks_a[t] = 0; nzero[t] = 0; nres[t] = 0;
+            for (unsigned left = z.split; left; left &= left - 1u) {
+                const int row = __ffs(left) - 1, q = __shfl(start, row, 64), len = __shfl(own, row, 64), n = piece_count(len, R.Cs);
+                for (int k = lane; k < n; k += 64) {
+                    const int qs = q + k * R.Cs, qe = piece_end(qs, q + len, R.Cs);
+                    put_task(out + k, LIBRA_TASK_CHUNK, (int)(r0 + row), 0, 0, qs, qe, 0u, 0u, 0u, (unsigned)(qe - qs));
+                }
+                out += n;
+            }
         }
         if (R.build_d) {
             const int b0 = blkptr_d[t], b1 = blkptr_d[t + 1];
-            if (!FILL) {
-                ntasks_d[t] = piece_count(b1 - b0, R.Ts_d);
-            } else {
-                libra_task_t *out = tasks_d + tbase_d[t];
-                for (int g = lane; g < piece_count(b1 - b0, R.Ts_d); g += LANES) {
-                    const int g0 = b0 + g * R.Ts_d, g1 = piece_end(g0, b1, R.Ts_d);
-                    unsigned c = 0;
-                    for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
-                    put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
-                }
+            libra_task_t *out = tasks_d + tbase_d[t];
+            for (int g = lane; g < piece_count(b1 - b0, R.Ts_d); g += 64) {
+                const int g0 = b0 + g * R.Ts_d, g1 = piece_end(g0, b1, R.Ts_d);
+                unsigned c = 0;
+                for (int b = g0; b < g1; ++b) c += (unsigned)blkncols_d[b];
+                put_task(out + g, LIBRA_TASK_WINDOW, t, g0, g1, 0, 0, 0u, 0u, 0u, c + (unsigned)W);
             }
-        } else if (!FILL) {
-            ntasks_d[t] = 0;
         }
-    }
-}
-
-// Per window: where each row's residual nonzeros start in the SpMM residual array (rows that are not decomposed
-// first, in row order, then the decomposed rows), minus the row's own prefix so that a nonzero only adds its scan value.
-__global__ __launch_bounds__(128) void k_row_bases(const int32_t *rowptr, Residual res_a, const int32_t *resptr, int64_t M, int nw, Rule R,
-                                                   int32_t *rowbase) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nw) return;
-    int n_short, n_long;
-    const WinRows z = window_rows(rowptr, res_a, M, t, R, &n_short, &n_long);
-    int u = 0, sp = z.q_unsplit;
-    const int64_t r0 = (int64_t)t * W;
-    for (int r = 0; r < z.nr; ++r) {
-        int off;
-        if ((z.split >> r) & 1u) { off = sp; sp += z.rlen[r]; } else { off = u; u += z.rlen[r]; }
-        rowbase[r0 + r] = resptr[t] + off - res_a.before(rowptr[r0 + r]);
     }
 }
 
@@ -1392,6 +1400,61 @@ void scan(const Layout &L, const int32_t *in, int32_t *out, size_t n, hipStream_
     hip_ok(rocprim::exclusive_scan(L.tmp, sz, in, out, (int32_t)0, n, rocprim::plus<int32_t>(), s));
 }
 
+// Prefix sums of up to four short arrays in one launch, a workgroup each (two rounds of 8,192 items at most); longer ones are rocPRIM's.
+constexpr int SHORT_SCAN = 16384;
+struct ScanJobs { const int32_t *in[4]; int32_t *out[4]; int32_t n[4]; };
+__global__ __launch_bounds__(1024) void k_scan_short(ScanJobs jobs) {
+    __shared__ int32_t wave_sum[16];
+    const int32_t *in = nullptr;
+    int32_t *out = nullptr;
+    int n = 0, carry = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((int)blockIdx.x == k) { in = jobs.in[k]; out = jobs.out[k]; n = jobs.n[k]; }
+    const int tid = threadIdx.x;
+    for (int base = 0; base < n; base += 8192) {
+        int v[8], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = base + tid * 8 + j < n ? in[base + tid * 8 + j] : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { const int x = v[j]; v[j] = sum; sum += x; }
+        int scan = sum;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int x = __shfl_up(scan, m, 64);
+            if (tid % 64 >= m) scan += x;
+        }
+        if (tid % 64 == 63) wave_sum[tid / 64] = scan;
+        __syncthreads();
+        int before = carry + scan - sum, all = 0;
+        for (int w = 0; w < 16; ++w) {
+            const int x = wave_sum[w];
+            before += w < tid / 64 ? x : 0;
+            all += x;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (base + tid * 8 + j < n) out[base + tid * 8 + j] = before + v[j];
+        carry += all;
+        __syncthreads();
+    }
+}
+struct ScanJob { const int32_t *in; int32_t *out; int64_t n; };
+void scan_all(const Layout &L, std::initializer_list<ScanJob> jobs, hipStream_t s) {
+    ScanJobs small{};
+    int count = 0;
+    for (const ScanJob &j : jobs) {
+        if (j.n > SHORT_SCAN) {
+            scan(L, j.in, j.out, (size_t)j.n, s);
+        } else {
+            small.in[count] = j.in;
+            small.out[count] = j.out;
+            small.n[count++] = (int32_t)j.n;
+        }
+    }
+    if (count) hipLaunchKernelGGL(k_scan_short, dim3((unsigned)count), dim3(1024), 0, s, small);
+}
+
 template <class T>
 void fetch(std::vector<T> &dst, const void *src, size_t n, hipStream_t s) {
     dst.resize(n);
@@ -1571,11 +1634,6 @@ struct Orderer {
     }
 };
 
-// Tables of fewer tasks are ordered on the host: there a task costs 40 - 70 ns (copies both ways, radix sorts of 40-byte records,
-// merging), here the launches and waits cost 0.2 ms and a task 1 ns.  GAT graph (1.05 M tasks in both tables): 71 -> 1.5 ms,
-// the whole plan 86.7 -> 24.1 ms; 8,000 tasks without segments: 0.32 ms on the host, 0.21 here.
-constexpr int64_t DEVICE_ORDER_MIN = 8192;
-
 // Noops of a table as the host planner writes them.
 inline libra_task_t task_at(const std::vector<libra_task_t> &tasks, int item, int cs, int nres, int empty_kind) {
     if (item < 0) return libra_task_t{empty_kind, 0, 0, 0, 0, 0, 0u, 0u, 0u, 0u};
@@ -1730,20 +1788,18 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         Rule R{o.mode, o.fill && o.mode == LIBRA_MODE_HYBRID ? 1 : 0, tau_a, o.tau_sddmm, o.Ts, o.Cs, o.short_len, o.build_spmm ? 1 : 0, o.build_sddmm ? 1 : 0, o.sddmm_Ts};
 
         // ---- 1. census: the nonzeros of every window in (column, row) order ----
-        fill_bytes(L.ctr, 0, C_COUNT * sizeof(u64), s);
+        fill_bytes(L.ctr, 0, (size_t)((char *)(L.hist + (size_t)nw * W) - (char *)L.ctr), s);
         hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr);
         const int tiles = tile_count(n);
         hipLaunchKernelGGL(k_rows, dim3(blocks_for(n, ROWS_CHUNK)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.row_of, L.ctr);
         hipLaunchKernelGGL(k_tile_splits, dim3(blocks_for((int64_t)(tiles + 1) * W, 256)), dim3(256), 0, s, d_rowptr, d_col, L.win_ptr, M, Kc, n, nw, tiles, L.tiles);
-        fill_bytes(L.hist, 0, (size_t)nw * W * sizeof(int32_t), s);
         hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)tiles), dim3(TILE_THREADS), 0, s, d_rowptr, d_col, L.win_ptr, L.row_of, M, L.tiles, L.ctr, L.scol, L.spos, L.vmask, L.hist);
         // ---- 2. per window: dense vectors and blocks ----
         hipLaunchKernelGGL(k_window_counts, dim3(blocks_for((int64_t)nw + 1, 256)), dim3(256), 0, s, L.hist, nw, R, L.a.ndv, L.a.nb, L.d.ndv, L.d.nb, L.ctr);
         const bool share_rule = o.build_sddmm && o.mode == LIBRA_MODE_HYBRID && o.sddmm_min_dense_pct > 0;
         if (share_rule)
             hipLaunchKernelGGL(k_share_rule, dim3(blocks_for(nw, 256)), dim3(256), 0, s, L.ctr, nnz, o.sddmm_min_dense_pct, nw, L.d.ndv, L.d.nb);
-        scan(L, L.a.nb, L.a.blkptr, (size_t)nw + 1, s);
-        scan(L, L.d.nb, L.d.blkptr, (size_t)nw + 1, s);
+        scan_all(L, {{L.a.nb, L.a.blkptr, (int64_t)nw + 1}, {L.d.nb, L.d.blkptr, (int64_t)nw + 1}}, s);
         int32_t size[7];
         u64 ctr[C_COUNT];
         hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));
@@ -1773,14 +1829,15 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         for (int k = 0; k < 2; ++k) {
             const SubOut &S = *subs[k];
             const int nb = nbs[k];
-            if (nb > 0)
-                hipLaunchKernelGGL(k_blocks, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.scol, L.vmask, nb,
-                                   S.blk_cols, S.bitmap, S.blknnz, S.blkmask, S.blkncols);
-            if (nb == 0) fill_bytes(S.blknnz, 0, sizeof(int32_t), s);
-            scan(L, S.blknnz, S.blk_valptr, (size_t)nb + 1, s);
-            if (nb > 0)
-                hipLaunchKernelGGL(k_block_values, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vmask, S.bitmap,
-                                   S.blk_valptr, L.spos, val, vsize, nb, S.dense_perm, S.dense_val);
+            if (nb == 0) {
+                fill_bytes(S.blk_valptr, 0, sizeof(int32_t), s);
+                continue;
+            }
+            hipLaunchKernelGGL(k_blocks, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.scol, L.vmask, nb,
+                               S.blk_cols, S.bitmap, S.blknnz, S.blkmask, S.blkncols);
+            scan_all(L, {{S.blknnz, S.blk_valptr, (int64_t)nb + 1}}, s);
+            hipLaunchKernelGGL(k_block_values, dim3(blocks_for((int64_t)nb * 16, 256)), dim3(256), 0, s, S.slotvec, L.vmask, S.bitmap,
+                               S.blk_valptr, L.spos, val, vsize, nb, S.dense_perm, S.dense_val);
         }
         // ---- 4. residual nonzeros and tasks ----
         auto residual = [&](const SubOut &S, int nb, unsigned bit) {
@@ -1791,28 +1848,20 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             return Residual{L.dense, S.rescan, bit};
         };
         const Residual resA = residual(L.a, nbA, 1u), resD = residual(L.d, nbD, 2u);
-        hipLaunchKernelGGL((k_window_tasks<false>), dim3(blocks_for((int64_t)nw + 1, 128)), dim3(128), 0, s, d_rowptr, resA, M, nw, R,
-                           L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
-                           L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
-                           L.a.tasks, L.zero_rows, L.d.tasks);
-        scan(L, L.a.ntasks, L.a.tbase, (size_t)nw + 1, s);
-        scan(L, L.nzero, L.zbase, (size_t)nw + 1, s);
-        scan(L, L.nres, L.resptr, (size_t)nw + 1, s);
-        scan(L, L.d.ntasks, L.d.tbase, (size_t)nw + 1, s);
+        hipLaunchKernelGGL(k_window_sizes, dim3(std::min(blocks_for(nw, 256 / W), 1024u)), dim3(256), 0, s, d_rowptr, resA, M, nw, R, L.a.blkptr, L.d.blkptr,
+                           L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr);
+        scan_all(L, {{L.a.ntasks, L.a.tbase, (int64_t)nw + 1}, {L.nzero, L.zbase, (int64_t)nw + 1}, {L.nres, L.resptr, (int64_t)nw + 1}, {L.d.ntasks, L.d.tbase, (int64_t)nw + 1}}, s);
         peek_all(L.sizes, {L.a.tbase + nw, L.d.tbase + nw, L.zbase + nw, L.a.blk_valptr + nbA, L.d.blk_valptr + nbD}, size, s);
         const int ntA = size[0], ntD = size[1], nz = size[2], dnnzA = size[3], dnnzD = size[4];
         const int nresA = o.build_spmm ? n - dnnzA : 0, nresD = o.build_sddmm ? n - dnnzD : 0;
         if (ntA < 0 || ntA > z.tasks_a_max || ntD < 0 || ntD > z.tasks_d_max || nz < 0 || nz > M || nresA < 0 || nresA > n || nresD < 0 ||
             nresD > n || dnnzA < 0 || dnnzA > n || dnnzD < 0 || dnnzD > n)
             throw Fail{LIBRA_ERR_HIP};
-        hipLaunchKernelGGL((k_window_tasks<true>), dim3(std::min(blocks_for(nw, 2), 1u << 22)), dim3(128), 0, s, d_rowptr, resA, M, nw, R,
-                           L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols,
-                           L.a.ntasks, L.nzero, L.nres, L.d.ntasks, L.ctr, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
-                           L.a.tasks, L.zero_rows, L.d.tasks);
+        hipLaunchKernelGGL(k_window_tasks, dim3(std::min(blocks_for(nw, 2), 1u << 22)), dim3(128), 0, s, d_rowptr, resA, M, nw, R,
+                           L.a.blkptr, L.a.blkmask, L.a.blkncols, L.d.blkptr, L.d.blkncols, L.a.tbase, L.zbase, L.resptr, L.d.tbase,
+                           L.a.tasks, L.zero_rows, L.rowbase, L.d.tasks);
         const int64_t ngroups = (nw + LIBRA_LOCALITY_WINDOWS - 1) / LIBRA_LOCALITY_WINDOWS, nsample = share_samples(ngroups);
         hipLaunchKernelGGL(k_share, dim3(std::min(blocks_for(n, SHARE_SAMPLES), 1024u)), dim3(SHARE_SAMPLES), 0, s, L.win_ptr, L.scol, L.vmask, nw, ngroups, (int)nsample, L.ctr);
-        if (o.build_spmm)
-            hipLaunchKernelGGL(k_row_bases, dim3(blocks_for(nw, 128)), dim3(128), 0, s, d_rowptr, resA, L.resptr, M, nw, R, L.rowbase);
         auto fill_residuals = [&](const ResidualOut &a, const ResidualOut &d) {
             auto run = [&](auto tag) {
                 typedef decltype(tag) V;
@@ -1828,9 +1877,41 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         const int nsegD = o.build_sddmm ? piece_count(nresD, o.sddmm_Cs) : 0;
         if (nsegD > 0)
             hipLaunchKernelGGL(k_segment_cols, dim3(blocks_for(nsegD, 256)), dim3(256), 0, s, L.row_of, d_col, resD, n, nresD, o.sddmm_Cs, nsegD, L.seg_col);
-        hip_ok(hipMemcpyAsync(ctr, L.ctr, sizeof ctr, hipMemcpyDeviceToHost, s));
+        const bool order_here = (int64_t)ntA + ntD + nsegD >= DEVICE_ORDER_MIN;
+        // small tables, which the host orders, come there with the counters: packed on the device, one copy, one wait
+        struct Part { const void *from; size_t bytes, at; };
+        std::vector<Part> parts;
+        size_t packed = 0;
+        auto part = [&](const void *from, size_t bytes) {
+            parts.push_back({from, bytes, packed});
+            packed += align256(bytes);
+            return parts.size() - 1;
+        };
+        part(L.ctr, sizeof ctr);
+        const bool staged = !order_here && !keep_host_copy;
+        if (staged) {
+            if (o.build_spmm) {
+                part(L.a.tasks, (size_t)ntA * sizeof(libra_task_t));
+                part(L.task_col, (size_t)ntA * 4);
+                part(L.a.blk_valptr, ((size_t)nbA + 1) * 4);
+            }
+            if (o.build_sddmm) {
+                part(L.d.tasks, (size_t)ntD * sizeof(libra_task_t));
+                part(L.seg_col, (size_t)nsegD * 4);
+                part(L.d.blk_valptr, ((size_t)nbD + 1) * 4);
+            }
+        }
+        if (packed > stage_bytes(z)) throw Fail{LIBRA_ERR_HIP};
+        std::vector<char> host(packed);
+        {
+            DeviceCopies copies;
+            for (const Part &q : parts) copies.add(L.stage + q.at, q.from, q.bytes);
+            if (!copies.flush(s)) throw Fail{LIBRA_ERR_HIP};
+            hip_ok(hipMemcpyAsync(host.data(), L.stage, packed, hipMemcpyDeviceToHost, s));
+        }
         hip_ok(hipStreamSynchronize(s));
         if (hipGetLastError() != hipSuccess) throw Fail{LIBRA_ERR_HIP};
+        std::memcpy(ctr, host.data(), sizeof ctr);
         P->stats.device_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         mark("blocks, residual, tasks");
 
@@ -1839,13 +1920,25 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
         const int nts[2] = {ntA, ntD}, nres2[2] = {nresA, nresD}, dn[2] = {dnnzA, dnnzD};
         SubPlan *hs[2] = {&sa, &sd};
         P->host_arrays = keep_host_copy != 0;
-        const bool order_here = (int64_t)ntA + ntD + nsegD >= DEVICE_ORDER_MIN;
+        size_t next = 1;
+        auto unpack = [&](auto &to) {
+            const Part &q = parts[next++];
+            to.resize(q.bytes / sizeof(to[0]));
+            if (q.bytes) std::memcpy(to.data(), host.data() + q.at, q.bytes);
+        };
         for (int k = 0; k < 2; ++k) {
             if (!(k == 0 ? o.build_spmm : o.build_sddmm)) continue;
             const SubOut &S = *subs[k];
             SubPlan &H = *hs[k];
             H.n.blocks = nbs[k]; H.n.col_slots = (int64_t)nbs[k] * KB; H.n.bitmap_words = (int64_t)nbs[k] * 4;
             H.n.dense = dn[k]; H.n.res = nres2[k]; H.n.zero_rows = k == 0 ? nz : 0;
+            if (staged) {
+                unpack(H.tasks);
+                if (k == 0) unpack(H.task_col);
+                else unpack(H.seg_col);
+                unpack(H.blk_valptr);
+                continue;
+            }
             if (!order_here || keep_host_copy) fetch(H.tasks, S.tasks, (size_t)nts[k], s);
             if (!order_here && k == 0) fetch(H.task_col, L.task_col, (size_t)nts[k], s);
             if (!order_here && k == 1) fetch(H.seg_col, L.seg_col, (size_t)nsegD, s);

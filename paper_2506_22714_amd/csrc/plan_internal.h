@@ -173,6 +173,18 @@ LIBRA_HD inline int64_t sampled_group(int64_t k, int64_t ngroups, int64_t nsampl
 int adopt_device_arrays(libra_plan_s *plan, const DeviceSource &spmm, const DeviceSource &sddmm, void *dev_buf, size_t bytes, void *stream);
 // Are the SDDMM output records sorted by CSR position and do they carry a stage slot (16-bit values, the kernels' window and block)?
 inline bool sorted_records(const libra_plan_s *P) { return P->vdt != LIBRA_F32 && P->o.W == 16 && P->o.KB == 16; }
+// Copies inside device memory, up to 16 of them in one launch (of different lengths, none overlapping another's destination).
+struct DeviceCopies {
+    struct { void *to; const void *from; uint64_t bytes; } part[16];
+    int n = 0;
+    bool full() const { return n == 16; }
+    void add(void *to, const void *from, size_t bytes) {
+        if (!bytes) return;
+        part[n].to = to; part[n].from = from; part[n].bytes = bytes;
+        ++n;
+    }
+    bool flush(void *stream);   // false: the launch failed
+};
 // Queues the pass that packs SDDMM residual entries from arrays in device memory (`stream`: a hipStream_t).
 void pack_sddmm_entries(int value_bytes, const int32_t *col, const void *val, const int32_t *row, int64_t n, void *entries, int32_t *base, void *stream);
 // Bytes libra_plan_upload / adopt_device_arrays need for a plan with these array sizes.
