@@ -404,6 +404,35 @@ def _with_tuned(opts: dict, tuned, val_dtype: int, N, K) -> dict:
 
 
 # ---- convenience wrapper: a plan handle plus the torch buffer that backs its device copy ----
+# A call on a small matrix takes less time on the GPU than a handful of Python attribute chains: operands that are what they should be
+# are recognised by one short test, and everything else goes through the checks that say what is wrong.
+_torch = None
+
+
+def _gpu():
+    """torch, with the stream lookup that does not build a Stream object if this torch has it."""
+    global _torch, _stream
+    if _torch is None:
+        import torch
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None:
+            _stream = lambda: raw(device())                                         # noqa: E731
+        _torch = torch
+    return _torch
+
+
+def _stream():
+    return _gpu().cuda.current_stream().cuda_stream
+
+
+def _is_matrix(t, dtype, rows: int) -> bool:
+    return isinstance(t, _torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous() and t.dim() == 2 and t.shape[0] == rows
+
+
+def _is_vector(t, dtype, n: int) -> bool:
+    return isinstance(t, _torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous() and t.numel() == n
+
+
 class Plan:
     def __init__(self, M, Kc, rowptr, col, val, val_dtype: int | None = None, tuned=None, N: int | None = None,
                  K: int | None = None, **opts):
@@ -452,7 +481,10 @@ class Plan:
         self._facts(opts)
         return self
 
+    _dtype_cached = None
+
     def _facts(self, opts):
+        self._lib = lib()
         stats = libra_plan_stats(self.handle)
         self.nnz = stats["nnz"]
         # rows that a call with rounded results sums up in fp32 memory: those with several writers, all of them in two-kernel mode
@@ -487,9 +519,13 @@ class Plan:
         libra_plan_upload(self.handle, self._buf.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
         return self
 
-    def _torch_dtype(self):
-        import torch
-        return {F16: torch.float16, BF16: torch.bfloat16, F32: torch.float32}[self.val_dtype]
+    @property
+    def _dtype(self):
+        d = self._dtype_cached
+        if d is None:
+            torch = _gpu()
+            d = self._dtype_cached = {F16: torch.float16, BF16: torch.bfloat16, F32: torch.float32}[self.val_dtype]
+        return d
 
     # The C ABI sees pointers only: the sizes behind them are checked here, before any launch, and a mismatch raises
     # (an undersized operand would make a kernel read or write past its end).  Shape, type and layout first, the device last.
@@ -520,143 +556,171 @@ class Plan:
             raise ValueError(f"{name}: dtype {t.dtype} is not float16, bfloat16 or float32")
         return code
 
+    def _check_matrix(self, t, name, rows, cols=None, rows_contiguous=False):
+        if not (_is_matrix(t, self._dtype, rows) and (cols is None or t.shape[1] == cols)):
+            self._operand(t, name, self._dtype, shape=(rows, cols), rows_contiguous=rows_contiguous)
+
+    def _check_vector(self, t, name, dtype):
+        if not _is_vector(t, dtype, self.nnz):
+            self._operand(t, name, dtype, numel=self.nnz)
+
     def spmm(self, B, out=None):
-        import torch
-        self._operand(B, "B", self._torch_dtype(), shape=(self.Kc, None), rows_contiguous=True)
-        N = int(B.shape[1])
+        torch = _gpu()
+        self._check_matrix(B, "B", self.Kc, rows_contiguous=True)
+        N = B.shape[1]
         if out is None:
             out = torch.empty((self.M, N), dtype=torch.float32, device=B.device)
-        self._operand(out, "out", torch.float32, shape=(self.M, N), rows_contiguous=True)
-        if out.device != B.device:
-            raise ValueError("out: on another device than B")
-        libra_spmm(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), out.stride(0),
-                   torch.cuda.current_stream().cuda_stream)
+        else:
+            if not (_is_matrix(out, torch.float32, self.M) and out.shape[1] == N):
+                self._operand(out, "out", torch.float32, shape=(self.M, N), rows_contiguous=True)
+            if out.get_device() != B.get_device():
+                raise ValueError("out: on another device than B")
+        rc = self._lib.libra_spmm(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), out.stride(0), _stream())
+        if rc:
+            _check(rc, "libra_spmm")
         return out
 
     def spmm_rounded(self, B):
         """``spmm(B)`` in the plan's value type: the fp32 sums rounded once."""
-        import torch
         if self.val_dtype == F32:
             return self.spmm(B)
-        self._operand(B, "B", self._torch_dtype(), shape=(self.Kc, None), rows_contiguous=True)
-        N = int(B.shape[1])
+        torch = _gpu()
+        self._check_matrix(B, "B", self.Kc, rows_contiguous=True)
+        N = B.shape[1]
         out = torch.empty((self.M, N), dtype=B.dtype, device=B.device)
         scratch = torch.empty((self.M, N), dtype=torch.float32, device=B.device) if self._fp32_rows else None
-        libra_spmm_rounded(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), N, scratch.data_ptr() if scratch is not None else 0, N,
-                           torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_spmm_rounded(self.handle, B.data_ptr(), N, B.stride(0), out.data_ptr(), N, scratch.data_ptr() if scratch is not None else 0, N,
+                                          _stream())
+        if rc:
+            _check(rc, "libra_spmm_rounded")
         return out
 
     def sddmm(self, X, Y, out=None, pattern_only: bool = False):
-        import torch
-        self._operand(X, "X", self._torch_dtype(), shape=(self.M, None))
-        self._operand(Y, "Y", self._torch_dtype(), shape=(self.Kc, int(X.shape[1])))
+        torch = _gpu()
+        self._check_matrix(X, "X", self.M)
+        K = X.shape[1]
+        self._check_matrix(Y, "Y", self.Kc, K)
         if out is None:
             out = torch.empty(self.nnz, dtype=torch.float32, device=X.device)
-        self._operand(out, "out", torch.float32, numel=self.nnz)
-        if Y.device != X.device or out.device != X.device:
+        else:
+            self._check_vector(out, "out", torch.float32)
+        if not X.get_device() == Y.get_device() == out.get_device():
             raise ValueError("X, Y and out must be on one device")
-        (libra_sddmm_pattern if pattern_only else libra_sddmm)(self.handle, X.data_ptr(), Y.data_ptr(), X.shape[1], out.data_ptr(),
-                                                               torch.cuda.current_stream().cuda_stream)
+        call = self._lib.libra_sddmm_pattern if pattern_only else self._lib.libra_sddmm
+        rc = call(self.handle, X.data_ptr(), Y.data_ptr(), K, out.data_ptr(), _stream())
+        if rc:
+            _check(rc, "libra_sddmm_pattern" if pattern_only else "libra_sddmm")
         return out
 
     def sddmm_pattern_rounded(self, X, Y):
         """``sddmm(X, Y, pattern_only=True)`` in the plan's value type, rounded once."""
-        import torch
         if self.val_dtype == F32:
             return self.sddmm(X, Y, pattern_only=True)
-        self._operand(X, "X", self._torch_dtype(), shape=(self.M, None))
-        self._operand(Y, "Y", self._torch_dtype(), shape=(self.Kc, int(X.shape[1])))
-        if Y.device != X.device:
+        torch = _gpu()
+        self._check_matrix(X, "X", self.M)
+        K = X.shape[1]
+        self._check_matrix(Y, "Y", self.Kc, K)
+        if Y.get_device() != X.get_device():
             raise ValueError("X and Y must be on one device")
         out = torch.empty(self.nnz, dtype=X.dtype, device=X.device)
-        libra_sddmm_pattern_rounded(self.handle, X.data_ptr(), Y.data_ptr(), X.shape[1], out.data_ptr(),
-                                    torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_sddmm_pattern_rounded(self.handle, X.data_ptr(), Y.data_ptr(), K, out.data_ptr(), _stream())
+        if rc:
+            _check(rc, "libra_sddmm_pattern_rounded")
         return out
 
     def edge_softmax(self, scores, scale: float, out=None):
-        import torch
-        self._operand(scores, "scores", torch.float32, numel=self.nnz)
+        torch = _gpu()
+        self._check_vector(scores, "scores", torch.float32)
         if out is None:
-            out = torch.empty(self.nnz, dtype=self._torch_dtype(), device=scores.device)
-        code = self._value_code(out, "out")
-        self._operand(out, "out", None, numel=self.nnz)
-        if out.device != scores.device:
-            raise ValueError("out: on another device than scores")
-        libra_edge_softmax(self.handle, scores.data_ptr(), scale, out.data_ptr(), code,
-                           torch.cuda.current_stream().cuda_stream)
+            out, code = torch.empty(self.nnz, dtype=self._dtype, device=scores.device), self.val_dtype
+        else:
+            code = self._value_code(out, "out")
+            self._check_vector(out, "out", out.dtype)
+            if out.get_device() != scores.get_device():
+                raise ValueError("out: on another device than scores")
+        rc = self._lib.libra_edge_softmax(self.handle, scores.data_ptr(), scale, out.data_ptr(), code, _stream())
+        if rc:
+            _check(rc, "libra_edge_softmax")
         return out
 
     def edge_softmax_backward(self, alpha, dalpha, scale: float, out=None):
-        import torch
+        torch = _gpu()
         code = self._value_code(alpha, "alpha")
-        self._operand(alpha, "alpha", None, numel=self.nnz)
-        self._operand(dalpha, "dalpha", torch.float32, numel=self.nnz)
+        self._check_vector(alpha, "alpha", alpha.dtype)
+        self._check_vector(dalpha, "dalpha", torch.float32)
         if out is None:
             out = torch.empty(self.nnz, dtype=torch.float32, device=alpha.device)
-        self._operand(out, "out", torch.float32, numel=self.nnz)
-        if dalpha.device != alpha.device or out.device != alpha.device:
+        else:
+            self._check_vector(out, "out", torch.float32)
+        if not alpha.get_device() == dalpha.get_device() == out.get_device():
             raise ValueError("alpha, dalpha and out must be on one device")
-        libra_edge_softmax_backward(self.handle, alpha.data_ptr(), code, dalpha.data_ptr(), scale, out.data_ptr(),
-                                    torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_edge_softmax_backward(self.handle, alpha.data_ptr(), code, dalpha.data_ptr(), scale, out.data_ptr(), _stream())
+        if rc:
+            _check(rc, "libra_edge_softmax_backward")
         return out
 
     def edge_softmax_backward_rounded(self, alpha, dalpha, scale: float):
         """``edge_softmax_backward`` of a ``dalpha`` in alpha's type."""
-        import torch
+        torch = _gpu()
         code = self._value_code(alpha, "alpha")
-        self._operand(alpha, "alpha", None, numel=self.nnz)
-        self._operand(dalpha, "dalpha", alpha.dtype, numel=self.nnz)
-        if dalpha.device != alpha.device:
+        self._check_vector(alpha, "alpha", alpha.dtype)
+        self._check_vector(dalpha, "dalpha", alpha.dtype)
+        if dalpha.get_device() != alpha.get_device():
             raise ValueError("alpha and dalpha must be on one device")
         out = torch.empty(self.nnz, dtype=torch.float32, device=alpha.device)
-        libra_edge_softmax_backward_rounded(self.handle, alpha.data_ptr(), dalpha.data_ptr(), code, scale, out.data_ptr(),
-                                            torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_edge_softmax_backward_rounded(self.handle, alpha.data_ptr(), dalpha.data_ptr(), code, scale, out.data_ptr(), _stream())
+        if rc:
+            _check(rc, "libra_edge_softmax_backward_rounded")
         return out
 
     def value_products(self, vals, factors):
         """``(factors * vals.float())`` in the plan's value type, rounded once: values of A (CSR order) times fp32 factors."""
-        import torch
         if self.val_dtype == F32:
             return factors * vals
-        self._operand(vals, "vals", self._torch_dtype(), numel=self.nnz)
-        self._operand(factors, "factors", torch.float32, numel=self.nnz)
-        if factors.device != vals.device:
+        torch = _gpu()
+        self._check_vector(vals, "vals", self._dtype)
+        self._check_vector(factors, "factors", torch.float32)
+        if factors.get_device() != vals.get_device():
             raise ValueError("vals and factors must be on one device")
         out = torch.empty(self.nnz, dtype=vals.dtype, device=vals.device)
-        libra_value_products(vals.data_ptr(), factors.data_ptr(), self.nnz, self.val_dtype, out.data_ptr(),
-                             torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_value_products(vals.data_ptr(), factors.data_ptr(), self.nnz, self.val_dtype, out.data_ptr(), _stream())
+        if rc:
+            _check(rc, "libra_value_products")
         return out
 
     def set_values(self, vals, ops: int = OP_SPMM | OP_SDDMM, one_call: bool = False):
         """New values of A in CSR order.  ``one_call``: through libra_plan_set_values (both operators) instead of
         libra_plan_set_values_for."""
-        import torch
-        self._operand(vals, "vals", self._torch_dtype(), numel=self.nnz)
+        _gpu()
+        self._check_vector(vals, "vals", self._dtype)
         if one_call:
             if ops != OP_SPMM | OP_SDDMM:
                 raise ValueError("one_call refreshes both operators")
-            libra_plan_set_values(self.handle, vals.data_ptr(), self.val_dtype, torch.cuda.current_stream().cuda_stream)
-        else:
-            libra_plan_set_values_for(self.handle, vals.data_ptr(), self.val_dtype, ops, torch.cuda.current_stream().cuda_stream)
+            libra_plan_set_values(self.handle, vals.data_ptr(), self.val_dtype, _stream())
+            return
+        rc = self._lib.libra_plan_set_values_for(self.handle, vals.data_ptr(), self.val_dtype, ops, _stream())
+        if rc:
+            _check(rc, "libra_plan_set_values_for")
 
     def value_order(self, perm):
         """The form of a permutation of the nonzeros (int32) that :meth:`set_values_ordered` reads; belongs to this plan."""
-        import torch
-        self._operand(perm, "perm", torch.int32, numel=self.nnz)
+        torch = _gpu()
+        self._check_vector(perm, "perm", torch.int32)
         order_bytes, ws_bytes, scratch_bytes = libra_value_order_bytes(self.handle)
         order = torch.empty(order_bytes, dtype=torch.uint8, device=perm.device)
         ws = torch.empty(ws_bytes, dtype=torch.uint8, device=perm.device)
-        libra_value_order(self.handle, perm.data_ptr(), order.data_ptr(), order_bytes, ws.data_ptr(), ws_bytes,
-                          torch.cuda.current_stream().cuda_stream)
+        libra_value_order(self.handle, perm.data_ptr(), order.data_ptr(), order_bytes, ws.data_ptr(), ws_bytes, _stream())
         return order, scratch_bytes
 
     def set_values_ordered(self, vals, order):
         """SpMM values from ``vals`` in the order that ``order`` (of :meth:`value_order`) stands for: nonzero p takes vals[perm[p]]."""
-        import torch
-        self._operand(vals, "vals", self._torch_dtype(), numel=self.nnz)
+        torch = _gpu()
+        self._check_vector(vals, "vals", self._dtype)
         order, scratch_bytes = order
-        if order.device != vals.device:
+        if order.get_device() != vals.get_device():
             raise ValueError("vals: on another device than order")
         scratch = torch.empty(scratch_bytes, dtype=torch.uint8, device=vals.device) if scratch_bytes else None
-        libra_plan_set_values_ordered(self.handle, vals.data_ptr(), self.val_dtype, order.data_ptr(),
-                                      scratch.data_ptr() if scratch is not None else 0, torch.cuda.current_stream().cuda_stream)
+        rc = self._lib.libra_plan_set_values_ordered(self.handle, vals.data_ptr(), self.val_dtype, order.data_ptr(),
+                                                     scratch.data_ptr() if scratch is not None else 0, _stream())
+        if rc:
+            _check(rc, "libra_plan_set_values_ordered")
