@@ -1126,6 +1126,30 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, l
     }
 }
 
+// fp32 storage: 16 rows of X in LDS, fetched by direct loads, consecutive lanes on one row.  Piece c (16 bytes) of row r is kept at place
+// c ^ swizzle(r): 16 lanes that read one piece of 16 rows touch all banks.
+template <int K>
+struct XStage {
+    static constexpr int ROW = 4 * K, PIECES = K / 4, RPL = WAVE / PIECES, BYTES = W * ROW;
+    // Do segment tasks use it?  At K = 32 not beside window tasks: the registers of both tasks together would take a wave per SIMD (community
+    // matrix of 300,017 rows, default options 67.5 -> 69 - 76 us with any budget; without window tasks 55 -> 46).
+    template <bool DENSE> static constexpr bool SEGMENTS = !(DENSE && K == 32);
+    __device__ static int swizzle(int row) { return K == 32 ? row >> 1 & 7 : row & 15; }
+    // rows first .. first + count - 1; whole loads, whose further rows repeat the last one
+    __device__ static void fetch(const void *X, int64_t first, int count, lds_byte *stage) {
+        const int lane = threadIdx.x % WAVE;
+#pragma unroll
+        for (int i = 0; i < W / RPL; ++i) {
+            const int r = i * RPL + lane / PIECES;
+            if (i * RPL < count)
+                load_to_lds(reinterpret_cast<const char *>(X) + ((uint64_t)(first + min(r, count - 1)) * ROW + (uint32_t)((lane % PIECES) ^ swizzle(r)) * 16u), stage + i * RPL * ROW);
+        }
+    }
+    __device__ static float4_t piece(const lds_byte *stage, int row, int c) {
+        return *reinterpret_cast<const __attribute__((address_space(3))) float4_t *>(stage + row * ROW + (c ^ swizzle(row)) * 16);
+    }
+};
+
 // The same for fp32 storage: v_mfma_f32_16x16x4_f32.  A lane (g, j) fetches X[row j][16t + 4g .. +3] and Y[col j][16t + 4g .. +3] as
 // 16-byte loads; k-step 4t + e of the product takes element e of both, i.e. lane group g contributes k = 16t + 4g + e to
 // that step - any assignment of the k's to steps and lane groups gives the same sum as long as both operands use it.
@@ -1134,7 +1158,7 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, l
 template <int K>
 __device__ inline void sddmm_window_task_f32(const SddmmArgs &a, const DevTask &t) {
     constexpr int KT = K / 16;               // 16-byte pieces per lane and operand row
-    constexpr int BB = K <= 32 ? 4 : K <= 64 ? 2 : 1;      // blocks per batch (register budget)
+    constexpr int BB = K <= 32 ? 4 : 2;      // blocks per batch (register budget)
     const int lane = threadIdx.x % WAVE;
     const int g = lane >> 4, j = lane & 15;
     const float *X = reinterpret_cast<const float *>(a.X);
@@ -1189,6 +1213,61 @@ __device__ inline void sddmm_window_task_f32(const SddmmArgs &a, const DevTask &
             for (int e = 0; e < 4; ++e)
                 if (b0 + x < t.blk_end && (word[x] >> (e * 16 + j) & 1ull))
                     a.out[(int32_t)pv[x][e].x] = (a.pattern_only ? 1.f : __uint_as_float(pv[x][e].y)) * d[x][e];
+    }
+}
+
+// The same for the widest rows, where one block of Y rows at a time left the task waiting: the metadata of four blocks comes in one round
+// trip, X stays in LDS, and the registers that it leaves hold the rows of the next block, fetched before the products of this one.  Community
+// matrix of 300,017 rows, K = 128, blocks of 32 nonzeros or more: 183.6 -> 173.9 us.  (At K = 64 97 -> 109 us, at K = 32 level.)
+__device__ inline void sddmm_wide_window_task_f32(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
+    constexpr int K = 128, GB = 4;           // blocks per group of metadata
+    using S = XStage<K>;
+    constexpr int KT = K / 16;               // 16-byte pieces per lane and operand row
+    const int lane = threadIdx.x % WAVE;
+    const int g = lane >> 4, j = lane & 15;
+    const float *Y = reinterpret_cast<const float *>(a.Y);
+    S::fetch(a.X, (int64_t)t.id * W, (int)min((int64_t)W, a.M - (int64_t)t.id * W), stage);
+    for (int b0 = t.blk_begin; b0 < t.blk_end; b0 += GB) {
+        const int nb = min(GB, t.blk_end - b0);
+        int col[GB], vptr[GB];
+        uint64_t word[GB];
+#pragma unroll
+        for (int x = 0; x < GB; ++x) {
+            const int b = b0 + min(x, nb - 1);
+            col[x] = a.blk_cols[(int64_t)b * KB + j];
+            word[x] = a.blk_bitmap[(int64_t)b * 4 + g];          // rows 4g..4g+3 of the block, bit e*16 + j
+            vptr[x] = a.blk_valptr[b];
+        }
+        float4_t yb[2][KT];
+        uint2 pv[2][4];
+        auto request = [&](int x) {                              // rows and records of block x
+            const int c = max(col[x], 0);                        // padding slot: no bit is set in its column
+#pragma unroll
+            for (int s = 0; s < KT; ++s) yb[x & 1][s] = *reinterpret_cast<const float4_t *>(Y + (int64_t)c * K + 16 * s + 4 * g);
+            const int cnt = __popcll(word[x]);
+            const int c0 = __builtin_amdgcn_readlane(cnt, 0), c1 = __builtin_amdgcn_readlane(cnt, 16), c2 = __builtin_amdgcn_readlane(cnt, 32);
+            const int prefix = vptr[x] + (g > 0 ? c0 : 0) + (g > 1 ? c1 : 0) + (g > 2 ? c2 : 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pv[x & 1][e] = a.dense_pv[min(prefix + (int)__popcll(word[x] & ((1ull << (e * 16 + j)) - 1ull)), a.n_dense - 1)];
+        };
+        request(0);
+        if (b0 == t.blk_begin) wait_for_loads();                 // the rows of X
+#pragma unroll
+        for (int x = 0; x < GB; ++x) {
+            if (x < nb) {
+                if (x + 1 < GB && x + 1 < nb) request(x + 1);
+                float4_t d = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KT; ++s) {
+                    const float4_t xa = S::piece(stage, j, 4 * s + g);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[e], yb[x & 1][s][e], d, 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (word[x] >> (e * 16 + j) & 1ull) a.out[(int32_t)pv[x & 1][e].x] = (a.pattern_only ? 1.f : __uint_as_float(pv[x & 1][e].y)) * d[e];
+            }
+        }
     }
 }
 
@@ -1301,38 +1380,60 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, 
 }
 
 // The same for fp32 storage, where the vector ALUs are the faster unit (v_mfma_f32_16x16x4 forms 16 products per column of
-// the tile to use one): K/4 lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.
-template <int K>
-__device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, lds_float *stage) {
+// the tile to use one): K/4 lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.  If the rows of 64 nonzeros in
+// CSR order lie within 16 consecutive rows (nearly always) those rows of X come through LDS, once and not once per nonzero: the data
+// return units of the L1s then carry the rows of Y alone.  Residual nonzeros only, before -> with it: community matrix of 300,017 rows
+// K = 32 / 64 / 128 55.5 / 100.6 / 254.5 -> 46.2 / 85.8 / 214.2 us, power-law graph of 2^17 rows 35.3 / 63.5 / 141.8 -> 30.0 / 53.7 / 134.2.
+template <int K, bool STAGED>
+__device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
+    using S = XStage<K>;
     constexpr int LPN = K / 4;              // lanes per nonzero
     constexpr int NPW = WAVE / LPN;          // nonzeros per wave pass
-    constexpr int U = LPN <= 8 ? 8 : 4;      // passes in flight
-    static_assert(LPN >= 4 && LPN % 4 == 0 && LPN <= WAVE, "unsupported K (whole quads per nonzero)");
+    constexpr int U = 8;                     // passes in flight
+    static_assert(LPN >= 4 && LPN % 4 == 0 && LPN <= WAVE && WAVE % (NPW * U) == 0, "unsupported K (whole quads per nonzero)");
     const int lane = threadIdx.x % WAVE;
     const int sub = lane % LPN, grp = lane / LPN;
+    lds_float *sums = reinterpret_cast<lds_float *>(stage + (STAGED ? S::BYTES : 0));
     for (int q0 = t.res_begin; q0 < t.res_end; q0 += WAVE) {
         const int n = min(WAVE, t.res_end - q0);
         SegmentEntry<float> ent;
         ent.load(a, q0 + min(lane, n - 1));
         const int col = ent.col(), row = ent.row(a);
-        for (int e0 = 0; e0 < n; e0 += NPW * U) {
-            float4_t x[U], y[U];
+        const int r0 = __builtin_amdgcn_readfirstlane(row), rows = __builtin_amdgcn_readlane(row, WAVE - 1) - r0 + 1;
+        const bool near = STAGED && rows <= W;
+        if (near) S::fetch(a.X, r0, rows, stage);
+        auto sum_up = [&](int e0, int u, const float4_t &x, const float4_t &y) {
+            const float s = group_sum<LPN>(dot4(x, y));
+            if (sub == 0) sums[e0 + u * NPW + grp] = s;
+        };
+        auto y_row = [&](int from) { return load_row4(a.Y, __builtin_amdgcn_ds_bpermute(from, col), K * 4, sub); };
+        if (near) {
+            for (int e0 = 0; e0 < n; e0 += NPW * U) {
+                float4_t y[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int from = (e0 + u * NPW + grp) * 4;
-                const int r = __builtin_amdgcn_ds_bpermute(from, row), c = __builtin_amdgcn_ds_bpermute(from, col);
-                x[u] = load_row4(a.X, r, K * 4, sub);
-                y[u] = load_row4(a.Y, c, K * 4, sub);
+                for (int u = 0; u < U; ++u) y[u] = y_row((e0 + u * NPW + grp) * 4);
+                if (e0 == 0) wait_for_loads();
+#pragma unroll
+                for (int u = 0; u < U; ++u) sum_up(e0, u, S::piece(stage, __builtin_amdgcn_ds_bpermute((e0 + u * NPW + grp) * 4, row - r0), sub), y[u]);
             }
+        } else {
+            constexpr int V = STAGED ? U / 2 : U;  // both rows of a nonzero in registers
+            for (int e0 = 0; e0 < n; e0 += NPW * V) {
+                float4_t x[V], y[V];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float s = group_sum<LPN>(dot4(x[u], y[u]));
-                if (sub == 0) stage[e0 + u * NPW + grp] = s;
+                for (int u = 0; u < V; ++u) {
+                    const int from = (e0 + u * NPW + grp) * 4;
+                    x[u] = load_row4(a.X, __builtin_amdgcn_ds_bpermute(from, row), K * 4, sub);
+                    y[u] = y_row(from);
+                }
+#pragma unroll
+                for (int u = 0; u < V; ++u) sum_up(e0, u, x[u], y[u]);
             }
         }
         wave_sync();
-        if (lane < n) a.out[ent.pos] = (a.pattern_only ? 1.f : ent.value()) * stage[lane];
-        wave_sync();
+        if (lane < n) a.out[ent.pos] = (a.pattern_only ? 1.f : ent.value()) * sums[lane];
+        if constexpr (STAGED) wait_for_lds();                // the next batch overwrites the stage
+        else wave_sync();
     }
 }
 
@@ -1345,11 +1446,13 @@ __device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask 
 // graph 31.0 vs 32.3 us: a workgroup's slots are only free again when its slowest wave has finished).
 // DENSE = false: the table has no window task (a plan without dense blocks).  At K = 64 the LDS allows five waves per SIMD
 // and the registers are held to that (GAT 688 -> 674 us, power-law 41.9 -> 40.4); at K = 128 it would spill (327 -> 373).
+// fp32: at K = 128 the window task would take registers for three waves per SIMD.
+template <class T, int K> constexpr int SDDMM_WAVES = std::is_same<T, float>::value ? (K == 128 ? 4 : 1) : K == 64 ? 5 : 1;
 template <class T, int K, int WPB, bool DENSE, bool ROUNDED>
-__global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K == 64 && !std::is_same<T, float>::value ? 5 : 1))) void sddmm_task_kernel(SddmmArgs a) {
+__global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(SDDMM_WAVES<T, K>))) void sddmm_task_kernel(SddmmArgs a) {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int PRODUCTS = DENSE ? SD_GROUP * 256 * 4 : WAVE * 4, ROWS = RowStage<K>::BYTES;
-    constexpr int STAGE = F32 ? WAVE * 4 : PRODUCTS > ROWS ? PRODUCTS : ROWS;           // bytes per wave
+    constexpr int STAGE = F32 ? (XStage<K>::template SEGMENTS<DENSE> ? XStage<K>::BYTES : 0) + WAVE * 4 : PRODUCTS > ROWS ? PRODUCTS : ROWS;           // bytes per wave
     __shared__ __attribute__((aligned(16))) unsigned char stage_all[WPB * STAGE];
     const unsigned wave = WPB == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const unsigned seq = (blockIdx.x >> DIE_SHIFT) * WPB + wave;                // position in the die's part of the table
@@ -1357,11 +1460,12 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(K ==
     const DevTask t = a.tasks[(int64_t)(blockIdx.x & (LIBRA_XCDS - 1)) * a.tasks_per_die + seq];
     lds_byte *stage = (lds_byte *)stage_all + wave * STAGE;
     if (DENSE && t.kind == LIBRA_TASK_WINDOW) {
-        if constexpr (F32) sddmm_window_task_f32<K>(a, t);
+        if constexpr (F32 && K == 128) sddmm_wide_window_task_f32(a, t, stage);
+        else if constexpr (F32) sddmm_window_task_f32<K>(a, t);
         else sddmm_window_task<T, K, ROUNDED>(a, t, stage);
         return;
     }
-    if constexpr (F32) sddmm_segment_task_f32<K>(a, t, reinterpret_cast<lds_float *>(stage));
+    if constexpr (F32) sddmm_segment_task_f32<K, XStage<K>::template SEGMENTS<DENSE>>(a, t, stage);
     else sddmm_segment_task<T, K, ROUNDED>(a, t, stage);
 }
 
