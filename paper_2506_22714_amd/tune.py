@@ -66,8 +66,9 @@ ABLATION = [
 # found by coordinate descent from the library's defaults, written as a table that Plan.from_* can apply (tuned=...).
 # ---------------------------------------------------------------------------------------------------------------
 SPMM_AXES = [("spmm_min_vec_nnz", (2, 3, 4, 6)), ("ts", (8, 16, 32, 64)), ("cs", (64, 96, 128, 192, 256))]
-SDDMM_AXES = [("sddmm_min_blk_nnz", (16, 32, 64, 128, 257)), ("sddmm_cs", (64, 128, 256)), ("sddmm_ts", (2, 4, 8, 16)),
-              ("sddmm_min_dense_pct", (0, 50))]       # 0: the share rule is off
+# The share rule (0: off) first: without it a threshold pays where the blocks hold most of a matrix and costs as much where they hold
+# little, and the search goes to "no blocks".
+SDDMM_AXES = [("sddmm_min_dense_pct", (0, 50)), ("sddmm_min_blk_nnz", (16, 32, 64, 128, 257)), ("sddmm_cs", (64, 128, 256)), ("sddmm_ts", (2, 4, 8, 16))]
 SPMM_START = dict(spmm_min_vec_nnz=3, ts=16, cs=128)
 SDDMM_START = dict(sddmm_min_blk_nnz=64, sddmm_cs=128, sddmm_ts=4, sddmm_min_dense_pct=0)
 N_CLASSES = {"n32": 32, "n64": 64, "n128": 128}      # class name -> the width the class is tuned at
