@@ -789,7 +789,7 @@ __global__ __launch_bounds__(256) void k_share_rule(const u64 *ctr, int64_t nnz,
 // the SDDMM blocks (sorted order), and which nonzeros they hold.  A workgroup per tile of the census, whose places are in column order:
 // a vector's rank among the window's vectors of its NNZ is counted by ballots, over the part of the window in earlier tiles and waves
 // from their totals.  (It replaces numbering the vectors, a stable sort of those with more than one nonzero, ranks, three scans and two
-// scattering passes: 2.5 ms of the GAT graph's plan, now 0.6.)
+// scattering passes: 2.5 ms of the GAT graph's plan.  What the windows say is loaded for all seven chunks of a wave together: 610 -> 498 us.)
 __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *win_ptr, const int32_t *row_of, Tiles T, const int32_t *spos, const uint16_t *vmask, const int32_t *hist,
                                                                 const int32_t *ndv_a, const int32_t *blkptr_a, const int32_t *ndv_d, const int32_t *blkptr_d, Rule R,
                                                                 int32_t *slotvec_a, int32_t *slotvec_d, uint8_t *dense) {
@@ -817,6 +817,14 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
         win[j] = row_of[e] / W;             // a place's window is that of the nonzero there in CSR order
         change[j] = __ballot(i > 0 && i < count && row_of[e - (i > 0)] / W != win[j]);
     }
+    // what the windows say, for all chunks together: nothing below waits for more than one load
+    int da[TILE_EACH], dd[TILE_EACH], higher[TILE_EACH];     // vectors in dense blocks; vectors of more nonzeros than this one
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        da[j] = ndv_a[win[j]];
+        dd[j] = ndv_d[win[j]];
+        higher[j] = hist[(int64_t)win[j] * W + max((int)__popc(rows[j]) - 1, 0)];
+    }
 #pragma unroll
     for (int j = 0; j < TILE_EACH; ++j) {
         const ClassPlanes planes(__popc(rows[j]) - 1, rows[j] != 0);
@@ -842,7 +850,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
         for (int m = 1; m < W; m <<= 1) sum += __shfl_xor(sum, m, 64);
         return __builtin_amdgcn_readfirstlane(sum);
     };
-    int run_tau = over_tau(run), last_in = 0;
+    int run_tau = over_tau(run), last_in = 0, slot_a[TILE_EACH], slot_d[TILE_EACH], bits[TILE_EACH];
 #pragma unroll
     for (int j = 0; j < TILE_EACH; ++j) {
         const int nnz = __popc(rows[j]), cls = nnz - 1;
@@ -852,29 +860,39 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
         const u64 from = begun ? ~0ull << (63 - __clzll(begun)) : ~0ull;
         const int rank = __popcll(planes.same(cls) & below & from) + (begun ? 0 : __shfl(run, cls & 15, 64));
         const int rank_tau = __popcll(over & below & from) + (begun ? 0 : run_tau);
-        const int first = wave * (64 * TILE_EACH) + j * 64, e = out + first + lane, end = out + min(count, (wave + 1) * 64 * TILE_EACH);
-        int in = 0;                         // of a vector's first place: 1, in a SpMM block; 2, in an SDDMM block
-        if (nnz > 0) {
-            const int w = win[j], da = ndv_a[w], dd = ndv_d[w];
-            if (da | dd) {
-                const int place = hist[(int64_t)w * W + cls] + rank;           // in sorted order
-                in = (place < da ? 1 : 0) | (place < dd ? 2 : 0);
-                if (in & 1) slotvec_a[(int64_t)blkptr_a[w] * KB + (nnz >= R.tau_a ? rank_tau : place)] = e;
-                if (in & 2) slotvec_d[(int64_t)blkptr_d[w] * KB + place] = e;
-            }
-        }
-        // a place's bits are those of its vector's first place: in this chunk, or the last one of the chunk before.  Places of the next
-        // wave whose vector begins in this one are written from here.
+        const int place = higher[j] + rank;                          // in sorted order
+        // of a vector's first place: 1, in a SpMM block; 2, in an SDDMM block
+        const int in = nnz > 0 ? (place < da[j] ? 1 : 0) | (place < dd[j] ? 2 : 0) : 0;
+        slot_a[j] = in & 1 ? (nnz >= R.tau_a ? rank_tau : place) : -1;
+        slot_d[j] = in & 2 ? place : -1;
+        // a place's bits are those of its vector's first place: in this chunk, or the last one of the chunk before
         const u64 heads = __ballot(nnz > 0), up_to = heads & (below << 1 | 1ull);
         const int mine = __shfl(in, up_to ? 63 - __clzll(up_to) : 0, 64);
-        const int bits = up_to ? mine : last_in;
-        if (bits && e < end) dense[spos[e]] = (uint8_t)bits;
+        bits[j] = up_to ? mine : last_in;
         if (heads) last_in = __shfl(in, 63 - __clzll(heads), 64);
-        if (in)
-            for (int q = end; q < e + nnz; ++q) dense[spos[q]] = (uint8_t)in;
         const u64 all_from = change[j] ? ~0ull << (63 - __clzll(change[j])) : ~0ull;
         run = (change[j] ? 0 : run) + __popcll(planes.same(lane) & all_from);
         run_tau = (change[j] ? 0 : run_tau) + __popcll(over & all_from);
+    }
+    const int first = out + wave * (64 * TILE_EACH) + lane, end = out + min(count, (wave + 1) * 64 * TILE_EACH);
+    int to_a[TILE_EACH], to_d[TILE_EACH], p[TILE_EACH];
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int e = min(first + j * 64, out + count - 1);
+        to_a[j] = to_d[j] = p[j] = 0;
+        if (slot_a[j] >= 0) to_a[j] = blkptr_a[win[j]];
+        if (slot_d[j] >= 0) to_d[j] = blkptr_d[win[j]];
+        if (bits[j]) p[j] = spos[e];
+    }
+#pragma unroll
+    for (int j = 0; j < TILE_EACH; ++j) {
+        const int e = first + j * 64, in = (slot_a[j] >= 0 ? 1 : 0) | (slot_d[j] >= 0 ? 2 : 0);
+        if (slot_a[j] >= 0) slotvec_a[(int64_t)to_a[j] * KB + slot_a[j]] = e;
+        if (slot_d[j] >= 0) slotvec_d[(int64_t)to_d[j] * KB + slot_d[j]] = e;
+        if (bits[j] && e < end) dense[p[j]] = (uint8_t)bits[j];
+        // places of the next wave whose vector begins in this one
+        if (in)
+            for (int q = end; q < e + (int)__popc(rows[j]); ++q) dense[spos[q]] = (uint8_t)in;
     }
 }
 
