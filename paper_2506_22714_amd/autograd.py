@@ -28,7 +28,8 @@ class SparseMatrix:
         rowptr_t, col_t, perm_t = lb.transpose_csr(M, Kc, rowptr, col)
         self._perm_t = perm_t
         self.plan_t = lb.Plan.from_device_csr(Kc, M, rowptr_t, col_t, ones, resident=True, keep_host_copy=False, **opts)
-        self._order_t = self.plan_t.value_order(perm_t)
+        # a matrix for SDDMM alone has no SpMM arrays to put values into
+        self._order_t = None if opts.get("flags", 0) & lb.FLAG_NO_SPMM else self.plan_t.value_order(perm_t)
 
     @property
     def perm_t(self) -> torch.Tensor:
@@ -37,7 +38,8 @@ class SparseMatrix:
 
     def set_transposed(self, vals: torch.Tensor):
         """Values of A (CSR order) into the SpMM arrays of the plan of A^T."""
-        self.plan_t.set_values_ordered(vals, self._order_t)
+        if self._order_t is not None:
+            self.plan_t.set_values_ordered(vals, self._order_t)
 
     def close(self):
         self.plan.close()

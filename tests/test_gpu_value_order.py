@@ -106,3 +106,25 @@ def test_orders_that_are_no_permutations_are_refused(nnz):
         with pytest.raises(ValueError):
             p.set_values_ordered(vals, order)
     p.close()
+
+
+def test_matrices_without_nonzeros_and_without_spmm():
+    from paper_2506_22714_amd import autograd as ag
+    empty = ag.SparseMatrix(40, 30, torch.zeros(41, dtype=torch.int32, device="cuda"), torch.zeros(0, dtype=torch.int32, device="cuda"))
+    vals, B = torch.zeros(0, dtype=torch.float16, device="cuda"), torch.ones(30, 32, dtype=torch.float16, device="cuda", requires_grad=True)
+    C = ag.spmm(empty, vals, B)
+    C.sum().backward()
+    assert torch.equal(C, torch.zeros_like(C)) and torch.equal(B.grad, torch.zeros_like(B))
+    empty.close()
+    rowptr, col = random_csr(301, 203, 1000, 1, False)
+    sm = ag.SparseMatrix(301, 203, rowptr, col, flags=lb.FLAG_NO_SPMM)         # SDDMM alone: its values have a gradient
+    vals = values(1000, torch.float16, 1).requires_grad_()
+    X, Y = values(301 * 32, torch.float16, 2).view(301, 32), values(203 * 32, torch.float16, 3).view(203, 32)
+    out = ag.sddmm(sm, vals, X, Y)
+    out.sum().backward()
+    want = (X.float()[torch.repeat_interleave(torch.arange(301, device="cuda"), rowptr.diff().long())] * Y.float()[col.long()]).sum(1)
+    assert torch.equal(out.detach(), want * vals.detach().float()) and torch.equal(vals.grad, want.half())
+    with pytest.raises(lb.LibraError):
+        X2 = X.clone().requires_grad_()
+        ag.sddmm(sm, vals, X2, Y).sum().backward()
+    sm.close()
