@@ -1833,26 +1833,29 @@ __global__ __launch_bounds__(256) void device_copies_kernel(DeviceCopies c) {
 
 // Lays arrays out back to back (256-byte aligned, 16 spare bytes each) and copies them from host memory, from
 // device memory, or only reserves their place (arrays that a kernel packs afterwards).  `gathered`: copies inside device memory share
-// launches, neighbouring copies from host memory become one; they are queued by flush().
+// launches, and arrays from host memory with nothing between them become one copy, which writes the spare bytes between them; they are
+// queued by flush().
 struct Uploader {
     char *base = nullptr;     // nullptr: size pass only
     size_t off = 0;
     hipStream_t s = nullptr;
     bool ok = true, gathered = false;
     DeviceCopies copies;
-    struct FromHost { const void *from; size_t bytes, at; };
+    struct FromHost { const void *from; size_t bytes, at; bool next; };      // next: only spare bytes and empty arrays lie between it and the one before
     std::vector<FromHost> from_host;
+    bool host_before = false;                     // the last array that is not empty came from host memory
     std::vector<std::vector<char>> joined;        // alive until the copies have finished
     template <class P>
     void put(const void *host_src, const void *dev_src, size_t bytes, P *&dst) {
         if (base) {
             dst = reinterpret_cast<P *>(base + off);
             if (gathered) {
-                if (bytes && host_src) from_host.push_back({host_src, bytes, off});
+                if (bytes && host_src) from_host.push_back({host_src, bytes, off, host_before});
                 if (bytes && !host_src && dev_src) {
                     if (copies.full()) ok = copies.flush(s) && ok;
                     copies.add(base + off, dev_src, bytes);
                 }
+                if (bytes) host_before = host_src != nullptr;
             } else {
                 if (bytes && host_src && hipMemcpyAsync(base + off, host_src, bytes, hipMemcpyHostToDevice, s) != hipSuccess) ok = false;
                 if (bytes && !host_src && dev_src && hipMemcpyAsync(base + off, dev_src, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) ok = false;
@@ -1865,8 +1868,8 @@ struct Uploader {
     void flush() {
         ok = copies.flush(s) && ok;
         for (size_t i = 0; i < from_host.size();) {
-            size_t e = i + 1;                   // the next array begins at most a page behind the end of this one: one copy
-            while (e < from_host.size() && from_host[e].at - (from_host[e - 1].at + from_host[e - 1].bytes) < 4096) ++e;
+            size_t e = i + 1;
+            while (e < from_host.size() && from_host[e].next) ++e;
             const size_t begin = from_host[i].at, end = from_host[e - 1].at + from_host[e - 1].bytes;
             joined.emplace_back(end - begin);
             for (; i < e; ++i) std::memcpy(joined.back().data() + (from_host[i].at - begin), from_host[i].from, from_host[i].bytes);

@@ -371,6 +371,34 @@ def test_rows_of_large_matrices_are_checked_and_listed_on_the_device():
         assert e.value.code == lb.ERR["ROWPTR"]
 
 
+@pytest.mark.parametrize("flags", [lb.FLAG_NO_SPMM, lb.FLAG_NO_SDDMM, 0])
+def test_rows_listed_on_the_device_beside_tables_ordered_on_the_host(flags):
+    """Without the SpMM tables a matrix of 2^17 rows may have few tasks: the list of rows of 65 .. 2048 nonzeros, which is in device
+    memory, then lies in the plan between arrays that come from the host.  Every list from none to some thousand rows arrives whole."""
+    M, Kc = (1 << 17) + 3, 4096
+    for medium in (0, 1, 3, 200, 1500):
+        for longest in (64, 2500):
+            counts = np.zeros(M, dtype=np.int64)
+            counts[::64] = 1 + np.arange(counts[::64].size) % 40
+            counts[5:5 + 80 * medium:80] = 65 + np.arange(medium) % 60
+            counts[[17, M - 2]] = longest
+            rowptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+            col = (np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], counts)).astype(np.int32)
+            A = wl.Csr(M, Kc, rowptr, col, np.ones(col.size, dtype=np.float16))
+            pd = device_plan(A, resident=True, keep_host_copy=False, flags=flags)
+            if flags == lb.FLAG_NO_SPMM:
+                assert 0 < pd.stats()["sddmm_tasks"] < 8192
+            g = torch.Generator("cuda").manual_seed(1)
+            scores, dalpha = torch.randn(A.nnz, device="cuda", generator=g), torch.randn(A.nnz, device="cuda", generator=g)
+            ph = lb.Plan.from_csr(A, flags=flags).upload()
+            nan = lambda: torch.full_like(scores, float("nan"))
+            ah, ad = ph.edge_softmax(scores, 0.5, out=nan()), pd.edge_softmax(scores, 0.5, out=nan())
+            assert not ah.isnan().any() and torch.equal(ah, ad), (medium, longest)
+            assert torch.equal(ph.edge_softmax_backward(ah, dalpha, 0.5, out=nan()), pd.edge_softmax_backward(ah, dalpha, 0.5, out=nan()))
+            ph.close()
+            pd.close()
+
+
 @pytest.mark.parametrize("M,flags", [((1 << 27) + 1605, 0), ((1 << 30) + 37, lb.FLAG_NO_SPMM)])
 def test_more_windows_than_one_launch_has_waves(M, flags):
     """A wave writes the tasks of a window; with more than 2^23 windows a wave takes several, and 2^30 rows at a wave per window
