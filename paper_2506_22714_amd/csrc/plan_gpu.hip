@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void k_tile_splits(const int32_t *rowptr, cons
         const int64_t mid = (lo + hi) >> 1;
         int x = a, y = b;
         while (x < y) {
-            const int z = (x + y) >> 1;
+            const int z = x + ((y - x) >> 1);            // x + y may pass 2^31
             if ((int64_t)col[z] < mid) x = z + 1; else y = z;
         }
         const int before = sum(x - first);

@@ -429,6 +429,33 @@ def test_more_windows_than_one_launch_has_waves(M, flags):
     p.close()
 
 
+@pytest.mark.parametrize("M", [(1 << 13) + 8])
+def test_plans_of_very_many_nonzeros(M):
+    """Places of nonzeros are 32-bit numbers: more than 2^30 of them, of which two no longer add up in 32 bits.  A full matrix, the last row
+    100 nonzeros short: every nonzero lies in a dense block and no row has a residual one."""
+    Kc = 1 << 17
+    nnz = M * Kc - 100
+    o = lb.PlanOpts(flags=lb.FLAG_NO_SDDMM)
+    ws_bytes, plan_bytes = lb.libra_plan_device_workspace(M, nnz, o), 8 * nnz
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < ws_bytes + plan_bytes + 6 * nnz + (3 << 30):
+        pytest.skip("needs some 110 bytes of GPU memory per nonzero")
+    rowptr = (torch.arange(M + 1, device="cuda") * Kc).clamp_(max=nnz).int()
+    col = torch.arange(Kc, dtype=torch.int32, device="cuda").repeat(M)[:nnz]
+    val = torch.zeros(nnz, dtype=torch.float16, device="cuda")
+    ws, buf = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (ws_bytes, plan_bytes))
+    handle = lb.libra_plan_device(M, Kc, nnz, rowptr.data_ptr(), col.data_ptr(), val.data_ptr(), lb.F16, o, ws.data_ptr(), ws_bytes,
+                                  buf.data_ptr(), plan_bytes, False, torch.cuda.current_stream().cuda_stream)
+    st = lb.libra_plan_stats(handle)
+    lb.libra_plan_destroy(handle)
+    del rowptr, col, val, ws, buf
+    torch.cuda.empty_cache()
+    windows = (M + 15) // 16
+    assert st["n_vectors"] == st["spmm_dense_vectors"] == windows * Kc and st["n_vectors_nnz1"] == 0
+    assert st["spmm_dense_nnz"] == nnz and st["spmm_blocks"] == windows * Kc // 16
+    assert st["spmm_res_nnz"] == st["spmm_short_rows"] == st["spmm_long_rows"] == st["spmm_split_rows"] == 0
+
+
 @pytest.mark.parametrize("flags", [lb.FLAG_XCD_ORDER, lb.FLAG_NATURAL_ORDER])
 def test_more_tasks_than_one_launch_has_waves(flags):
     """A launch has fewer than 2^32 threads, i.e. 2^26 waves with a task each: tables of more tasks (segments of one nonzero) take
