@@ -429,10 +429,11 @@ def test_more_windows_than_one_launch_has_waves(M, flags):
     p.close()
 
 
-@pytest.mark.parametrize("M", [(1 << 13) + 8])
+@pytest.mark.parametrize("M", [(1 << 13) + 8, 1 << 14])
 def test_plans_of_very_many_nonzeros(M):
-    """Places of nonzeros are 32-bit numbers: more than 2^30 of them, of which two no longer add up in 32 bits.  A full matrix, the last row
-    100 nonzeros short: every nonzero lies in a dense block and no row has a residual one."""
+    """Places of nonzeros are 32-bit numbers: more than 2^30 of them, of which two no longer add up in 32 bits, and 100
+    fewer than 2^31, where the last tile of the census has places past the last one.  A full matrix, the last row short: every nonzero lies
+    in a dense block and no row has a residual one."""
     Kc = 1 << 17
     nnz = M * Kc - 100
     o = lb.PlanOpts(flags=lb.FLAG_NO_SDDMM)
