@@ -2108,7 +2108,7 @@ __global__ __launch_bounds__(256) void k_transpose_rowptr(const u64 *skey, int n
     if (c > Kc) return;
     int lo = 0, hi = n;
     while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
+        const int mid = lo + ((hi - lo) >> 1);       // lo + hi may pass 2^31
         if ((int64_t)(skey[mid] >> 32) < c) lo = mid + 1; else hi = mid;
     }
     rowptr_t[c] = lo;

@@ -75,6 +75,26 @@ def test_transposed_pattern_of_more_rows_than_one_launch_has_waves(M):
     assert np.array_equal(rp_t.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col, minlength=16))]))
 
 
+def test_transposed_pattern_of_very_many_nonzeros():
+    """More than 2^30 nonzeros, whose places no longer add up in 32 bits: a full matrix, the last row short."""
+    M, Kc, short = (1 << 13) + 8, 1 << 17, 100
+    nnz = M * Kc - short
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 60 * nnz:
+        pytest.skip("needs some 50 GiB")
+    rowptr = (torch.arange(M + 1, device="cuda") * Kc).clamp_(max=nnz).int()
+    col = torch.arange(Kc, dtype=torch.int32, device="cuda").repeat(M)[:nnz]
+    rowptr_t, col_t, perm_t = lb.transpose_csr(M, Kc, rowptr, col)
+    c, r = torch.arange(Kc + 1, device="cuda"), torch.arange(M, dtype=torch.int32, device="cuda")
+    assert torch.equal(rowptr_t, (c * M - (c - (Kc - short)).clamp(min=0)).int())
+    for first, columns, rows in ((0, Kc - short, M), (Kc - short, short, M - 1)):
+        part = slice(int(rowptr_t[first]), int(rowptr_t[first]) + columns * rows)
+        assert bool((col_t[part].view(columns, rows) == r[:rows]).all())
+        assert bool((perm_t[part].view(columns, rows) == r[:rows] * Kc + torch.arange(first, first + columns, dtype=torch.int32, device="cuda")[:, None]).all())
+    del rowptr, col, rowptr_t, col_t, perm_t
+    torch.cuda.empty_cache()
+
+
 
 @pytest.mark.parametrize("K", [32, 128])
 def test_sddmm_without_values(K):
