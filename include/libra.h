@@ -423,7 +423,8 @@ int libra_plan_set_values_for(libra_plan_t *plan, const void *vals_csr_dev, int 
  * the call reads, once per plan and permutation; libra_value_order_bytes gives the sizes of that form, of the workspace for making
  * it (free afterwards) and of the call's scratch memory (may be 0: NULL then).
  *   perm     device, int32[nnz], a permutation of 0 .. nnz - 1 (SHAPE if a place is out of range or a chunk of them not covered)
- *   order    device, 256-byte aligned;  workspace  device, 256-byte aligned;  libra_value_order synchronises the stream
+ *   order    device, 256-byte aligned;  workspace  device, 256-byte aligned;  libra_value_order synchronises the stream.  An order
+ *            is for the plan it was made with: its places and sizes are taken as they are, and no call can check them
  *   vals     device, nnz values of the plan's type;  scratch  device, aligned to a value
  * Errors: NULL, SHAPE, DTYPE, BUFFER, NOT_BUILT, NOT_UPLOADED, HIP.
  */

@@ -433,6 +433,11 @@ def _is_vector(t, dtype, n: int) -> bool:
     return isinstance(t, _torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous() and t.numel() == n
 
 
+class ValueOrder(tuple):
+    """(array, scratch bytes) of :meth:`Plan.value_order`, with the plan that it was made for."""
+    plan = None
+
+
 class Plan:
     def __init__(self, M, Kc, rowptr, col, val, val_dtype: int | None = None, tuned=None, N: int | None = None,
                  K: int | None = None, **opts):
@@ -485,6 +490,7 @@ class Plan:
 
     def _facts(self, opts):
         self._lib = lib()
+        self._token = object()              # what the orders of this plan's values carry
         stats = libra_plan_stats(self.handle)
         self.nnz = stats["nnz"]
         # rows that a call with rounded results sums up in fp32 memory: those with several writers, all of them in two-kernel mode
@@ -703,19 +709,23 @@ class Plan:
             _check(rc, "libra_plan_set_values_for")
 
     def value_order(self, perm):
-        """The form of a permutation of the nonzeros (int32) that :meth:`set_values_ordered` reads; belongs to this plan."""
+        """The form of a permutation of the nonzeros (int32) that :meth:`set_values_ordered` of this plan reads."""
         torch = _gpu()
         self._check_vector(perm, "perm", torch.int32)
         order_bytes, ws_bytes, scratch_bytes = libra_value_order_bytes(self.handle)
         order = torch.empty(order_bytes, dtype=torch.uint8, device=perm.device)
         ws = torch.empty(ws_bytes, dtype=torch.uint8, device=perm.device)
         libra_value_order(self.handle, perm.data_ptr(), order.data_ptr(), order_bytes, ws.data_ptr(), ws_bytes, _stream())
-        return order, scratch_bytes
+        made = ValueOrder((order, scratch_bytes))
+        made.plan = self._token
+        return made
 
     def set_values_ordered(self, vals, order):
         """SpMM values from ``vals`` in the order that ``order`` (of :meth:`value_order`) stands for: nonzero p takes vals[perm[p]]."""
         torch = _gpu()
         self._check_vector(vals, "vals", self._dtype)
+        if getattr(order, "plan", None) is not self._token:      # the kernels take its places and sizes as they are
+            raise ValueError("order: not made by value_order of this plan")
         order, scratch_bytes = order
         if order.get_device() != vals.get_device():
             raise ValueError("vals: on another device than order")

@@ -108,6 +108,24 @@ def test_orders_that_are_no_permutations_are_refused(nnz):
     p.close()
 
 
+def test_orders_of_other_plans_are_refused():
+    """Also where they are as long as an own one: the kernels take their places as they are."""
+    plans, orders = [], []
+    for i, opts in enumerate((dict(), dict(), dict(mode=lb.MODE_SCALAR_ONLY), dict(mode=lb.MODE_DENSE_ONLY))):
+        rowptr, col = random_csr(301, 203, 1000 + 7 * (i == 1), 1, False)
+        plans.append(lb.Plan.from_device_csr(301, 203, rowptr, col, torch.ones(col.numel(), dtype=torch.float16, device="cuda"), resident=True,
+                                             keep_host_copy=False, **opts))
+        orders.append(plans[i].value_order(torch.arange(col.numel(), dtype=torch.int32, device="cuda")))
+    for i, p in enumerate(plans):
+        vals = torch.ones(p.nnz, dtype=torch.float16, device="cuda")
+        p.set_values_ordered(vals, orders[i])
+        for bad in [o for k, o in enumerate(orders) if k != i] + [tuple(orders[i])]:
+            with pytest.raises(ValueError):
+                p.set_values_ordered(vals, bad)
+    for p in plans:
+        p.close()
+
+
 def test_matrices_without_nonzeros_and_without_spmm():
     from paper_2506_22714_amd import autograd as ag
     empty = ag.SparseMatrix(40, 30, torch.zeros(41, dtype=torch.int32, device="cuda"), torch.zeros(0, dtype=torch.int32, device="cuda"))
