@@ -422,7 +422,7 @@ int libra_plan_set_values_for(libra_plan_t *plan, const void *vals_csr_dev, int 
  * A's order, through the permutation that libra_csr_transpose_device gives.  libra_value_order turns the permutation into the form
  * the call reads, once per plan and permutation; libra_value_order_bytes gives the sizes of that form, of the workspace for making
  * it (free afterwards) and of the call's scratch memory (may be 0: NULL then).
- *   perm     device, int32[nnz], a permutation of 0 .. nnz - 1 (SHAPE if a place is out of range or a chunk of them not covered)
+ *   perm     device, int32[nnz], a permutation of 0 .. nnz - 1 (SHAPE if it is none)
  *   order    device, 256-byte aligned;  workspace  device, 256-byte aligned;  libra_value_order synchronises the stream.  An order
  *            is for the plan it was made with: its places and sizes are taken as they are, and no call can check them
  *   vals     device, nnz values of the plan's type;  scratch  device, aligned to a value

@@ -156,6 +156,7 @@ OrderArrays order_arrays(const OrderShape &h, void *base) {
 struct OrderWork {
     uint32_t *key_in, *key_out;
     int32_t *slot_in, *slot_out, *first, *bad;
+    uint8_t *seen;              // gather: per value, does a slot take it?
     void *tmp;
     size_t tmp_bytes, total;
 };
@@ -173,12 +174,18 @@ OrderWork order_work(const OrderShape &h, void *base) {
         (void)rocprim::radix_sort_pairs(nullptr, w.tmp_bytes, (uint32_t *)nullptr, (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, n, 0, 32);
         w.tmp_bytes += 4096;
         w.tmp = t.take<char>(w.tmp_bytes);
+    } else {
+        w.seen = t.take<uint8_t>((size_t)h.nnz);
     }
     w.total = t.off;
     return w;
 }
 
-__global__ void k_order_clear(int32_t *bad) { *bad = 0; }
+__global__ __launch_bounds__(256) void k_order_clear(int32_t *bad, uint8_t *seen, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *bad = 0;
+    if (i < n) seen[i] = 0;
+}
 // the CSR position that slot j holds, and its value's place in the new order (a place out of range is reported and taken as 0)
 __device__ inline int source_of(const int32_t *dense_perm, const int32_t *res_perm, int64_t nd, int64_t nd_pad, int64_t slot, const int32_t *order, int64_t nnz, int32_t *bad) {
     const int p = slot < nd_pad ? dense_perm[slot] : res_perm[slot - nd_pad];
@@ -191,11 +198,18 @@ __device__ inline int source_of(const int32_t *dense_perm, const int32_t *res_pe
 __device__ inline int64_t slot_of(int64_t i, int64_t nd, int64_t nd_pad) { return i < nd ? i : i - nd + nd_pad; }
 
 __global__ __launch_bounds__(256) void k_order_sources(const int32_t *dense_perm, const int32_t *res_perm, int64_t nd, int64_t nd_pad, int64_t nnz, const int32_t *order,
-                                                       int32_t *source, int32_t *bad) {
+                                                       int32_t *source, uint8_t *seen, int32_t *bad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nnz) return;
     const int64_t slot = slot_of(i, nd, nd_pad);
-    source[slot] = source_of(dense_perm, res_perm, nd, nd_pad, slot, order, nnz, bad);
+    const int q = source_of(dense_perm, res_perm, nd, nd_pad, slot, order, nnz, bad);
+    source[slot] = q;
+    seen[q] = 1;
+}
+// as many slots as values: an order that leaves no value out is a permutation
+__global__ __launch_bounds__(256) void k_order_all_seen(const uint8_t *seen, int64_t nnz, int32_t *bad) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nnz && !seen[i]) *bad = 1;
 }
 __global__ __launch_bounds__(256) void k_order_keys(const int32_t *dense_perm, const int32_t *res_perm, int64_t nd, int64_t nd_pad, int64_t nnz, const int32_t *order,
                                                     int T, int chunks, uint32_t *key, int32_t *slots, int32_t *bad) {
@@ -217,7 +231,7 @@ __global__ __launch_bounds__(256) void k_order_first(const uint32_t *key, int n,
     }
     first[k] = lo;
 }
-// a thread per chunk: its runs.  Every chunk has to be whole: an order that is no permutation is reported here
+// a thread per chunk: its runs.  Every chunk has to be whole: the places that follow from the runs would not be in the arrays otherwise
 __global__ __launch_bounds__(64) void k_order_runs(const int32_t *first, int chunks, int tiles, int T, int64_t nnz, int32_t *run, int32_t *to, int32_t *tile_first, int32_t *bad) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= chunks) return;
@@ -244,6 +258,21 @@ __global__ __launch_bounds__(256) void k_order_places(const uint32_t *key, const
 }
 
 constexpr int PASS_THREADS = 1024;
+// ... and no two of a chunk's values the same one: then the order is a permutation.  A workgroup per chunk, a bit per value.
+__global__ __launch_bounds__(PASS_THREADS) void k_order_chunks_whole(const uint16_t *in_chunk, int64_t nnz, int T, int32_t *bad) {
+    __shared__ uint32_t seen[VALUES<uint16_t> / 32];
+    const int64_t c0 = (int64_t)blockIdx.x * T;
+    const int n = (int)min((int64_t)T, nnz - c0);
+    for (int i = threadIdx.x; i < T / 32; i += PASS_THREADS) seen[i] = 0;
+    __syncthreads();
+    bool twice = false;
+    for (int i = threadIdx.x; i < n; i += PASS_THREADS) {
+        const unsigned q = in_chunk[c0 + i], bit = 1u << (q % 32);
+        twice = twice || (atomicOr(&seen[q / 32], bit) & bit);
+    }
+    if (twice) *bad = 1;
+}
+
 // First pass, a workgroup per chunk.  LDS: the chunk, then the runs' starts and destinations.
 template <class V>
 __global__ __launch_bounds__(PASS_THREADS) void order_chunks_kernel(const V *src, int64_t nnz, const uint16_t *in_chunk, const int32_t *run, const int32_t *to, int tiles, V *mid) {
@@ -391,9 +420,10 @@ extern "C" int libra_value_order(const libra_plan_t *P, const int32_t *order, vo
     hipStream_t s = (hipStream_t)stream;
     const SubPlanDev &d = P->spmm.dev;
     const dim3 each((unsigned)((h.nnz + 255) / 256)), block(256);
-    hipLaunchKernelGGL(k_order_clear, dim3(1), dim3(1), 0, s, w.bad);
+    hipLaunchKernelGGL(k_order_clear, h.passes ? dim3(1) : each, block, 0, s, w.bad, w.seen, h.passes ? 0 : h.nnz);
     if (!h.passes) {
-        hipLaunchKernelGGL(k_order_sources, each, block, 0, s, d.dense_perm, d.res_perm, h.nd, h.nd_pad, h.nnz, order, a.source, w.bad);
+        hipLaunchKernelGGL(k_order_sources, each, block, 0, s, d.dense_perm, d.res_perm, h.nd, h.nd_pad, h.nnz, order, a.source, w.seen, w.bad);
+        hipLaunchKernelGGL(k_order_all_seen, each, block, 0, s, w.seen, h.nnz, w.bad);
     } else {
         hipLaunchKernelGGL(k_order_keys, each, block, 0, s, d.dense_perm, d.res_perm, h.nd, h.nd_pad, h.nnz, order, h.T, h.chunks, w.key_in, w.slot_in, w.bad);
         const int64_t pairs = (int64_t)h.chunks * h.tiles;
@@ -404,12 +434,18 @@ extern "C" int libra_value_order(const libra_plan_t *P, const int32_t *order, vo
         hipLaunchKernelGGL(k_order_first, dim3((unsigned)((pairs + 256) / 256)), block, 0, s, w.key_out, (int)h.nnz, pairs, w.first);
         hipLaunchKernelGGL(k_order_runs, dim3((unsigned)((h.chunks + 63) / 64)), dim3(64), 0, s, w.first, h.chunks, h.tiles, h.T, h.nnz, a.run, a.to, a.tile_first, w.bad);
     }
-    int32_t bad = 0;
-    if (hipMemcpyAsync(&bad, w.bad, sizeof bad, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return LIBRA_ERR_HIP;
-    if (bad) return LIBRA_ERR_SHAPE;
+    // (both waits also keep the workspace until its last pass has ended)
+    auto refused = [&](int &rc) {
+        int32_t bad = 0;
+        rc = hipMemcpyAsync(&bad, w.bad, sizeof bad, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess ? LIBRA_ERR_HIP : bad ? LIBRA_ERR_SHAPE : LIBRA_OK;
+        return rc != LIBRA_OK;
+    };
+    int rc = LIBRA_OK;
+    if (refused(rc)) return rc;
     if (h.passes) {
         hipLaunchKernelGGL(k_order_places, each, block, 0, s, w.key_out, w.slot_out, d.dense_perm, d.res_perm, h.nd, h.nd_pad, h.nnz, order, h.T, h.chunks, h.tiles, a.to, a.in_chunk, a.in_tile);
-        if (hipStreamSynchronize(s) != hipSuccess) return LIBRA_ERR_HIP;          // the workspace may go now
+        hipLaunchKernelGGL(k_order_chunks_whole, dim3((unsigned)h.chunks), dim3(PASS_THREADS), 0, s, a.in_chunk, h.nnz, h.T, w.bad);
+        if (refused(rc)) return rc;
     }
     return hipGetLastError() == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP;
 }

@@ -95,7 +95,7 @@ def test_orders_that_are_no_permutations_are_refused(nnz):
     p = lb.Plan.from_device_csr(M, Kc, rowptr, col, values(nnz, torch.float16, 1), resident=True, keep_host_copy=False)
     good = torch.arange(nnz, dtype=torch.int32, device="cuda")
     p.value_order(good)
-    for at, to in ((0, nnz), (nnz - 1, -1)) + (((5, 40_000),) if nnz == PASSES_MIN else ()):
+    for at, to in ((0, nnz), (nnz - 1, -1), (5, 6), (nnz - 1, nnz - 2)) + (((5, 40_000),) if nnz == PASSES_MIN else ()):
         bad = good.clone()
         bad[at] = to
         with pytest.raises(lb.LibraError) as e:
