@@ -298,6 +298,10 @@ __global__ __launch_bounds__(256) void k_row_lengths(const int32_t *rowptr, cons
 // begin among them mark their first nonzero in LDS (of rows that begin at one place the last one counts, the others are empty), and a
 // nonzero's row is the largest mark up to it.  GAT graph: 217 us; a search through rowptr per wave of 64 nonzeros 601.
 constexpr int ROWS_EACH = 8, ROWS_CHUNK = 256 * ROWS_EACH;
+// Rows that a chunk's nonzeros may span for it: the workgroup walks them all, 0.2 us for each 256.  From here on, where nearly all are empty, a
+// search per nonzero.  Whole plans of 2^26 rows, marks / searches: a row of one nonzero in every 16 (32,768 rows per chunk) 4.86 / 4.90 ms,
+// in every 64 4.66 / 4.58, in every 1,024 7.8 / 4.3; 6,000 rows of 33 at both ends of 2^27 rows 232 / 5 ms.
+constexpr int64_t ROWS_MARKED = 1 << 15;
 __global__ __launch_bounds__(256) void k_rows(const int32_t *rowptr, const int32_t *col, int64_t M, int64_t Kc, int n, int32_t *row_of, u64 *ctr) {
     __shared__ __attribute__((aligned(16))) int32_t mark[ROWS_CHUNK];
     __shared__ int32_t wave_max[4];
@@ -317,30 +321,47 @@ __global__ __launch_bounds__(256) void k_rows(const int32_t *rowptr, const int32
         const int64_t mid = (last + hi) >> 1;
         if (rowptr[mid] <= end - 1) last = mid; else hi = mid;
     }
-    __syncthreads();
-    if (tid == 0) mark[0] = (int32_t)lo;
-    for (int64_t r = lo + 1 + tid; r <= last; r += 256) atomicMax(&mark[rowptr[r] - base], (int32_t)r);      // 0 < place < end - base
-    __syncthreads();
-    int row[ROWS_EACH], top = -1;
+    if (last - lo < ROWS_MARKED) {
+        __syncthreads();
+        if (tid == 0) mark[0] = (int32_t)lo;
+        for (int64_t r = lo + 1 + tid; r <= last; r += 256) atomicMax(&mark[rowptr[r] - base], (int32_t)r);      // 0 < place < end - base
+        __syncthreads();
+        int row[ROWS_EACH], top = -1;
 #pragma unroll
-    for (int j = 0; j < ROWS_EACH; ++j) {
-        top = max(top, mark[tid * ROWS_EACH + j]);
-        row[j] = top;
+        for (int j = 0; j < ROWS_EACH; ++j) {
+            top = max(top, mark[tid * ROWS_EACH + j]);
+            row[j] = top;
+        }
+        int scan = top;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int x = __shfl_up(scan, m, 64);
+            if (tid % 64 >= m) scan = max(scan, x);
+        }
+        if (tid % 64 == 63) wave_max[tid / 64] = scan;
+        int before = __shfl_up(scan, 1, 64);
+        if (tid % 64 == 0) before = -1;
+        __syncthreads();
+        for (int v = 0; v < tid / 64; ++v) before = max(before, wave_max[v]);
+#pragma unroll
+        for (int j = 0; j < ROWS_EACH; ++j) mark[tid * ROWS_EACH + j] = max(row[j], before);
+        __syncthreads();
+    } else {
+        // between these nonzeros lie many empty rows: a search per nonzero, a thread's eight side by side
+        int64_t from[ROWS_EACH];
+#pragma unroll
+        for (int j = 0; j < ROWS_EACH; ++j) from[j] = lo;
+        for (int64_t half = (int64_t)1 << (63 - __clzll(last - lo)); half > 0; half >>= 1) {
+#pragma unroll
+            for (int j = 0; j < ROWS_EACH; ++j) {
+                const int64_t r = from[j] + half;
+                if (rowptr[min(r, last)] <= min(base + tid + j * 256, end - 1) && r <= last) from[j] = r;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < ROWS_EACH; ++j) mark[tid + j * 256] = (int32_t)from[j];
+        __syncthreads();
     }
-    int scan = top;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const int x = __shfl_up(scan, m, 64);
-        if (tid % 64 >= m) scan = max(scan, x);
-    }
-    if (tid % 64 == 63) wave_max[tid / 64] = scan;
-    int before = __shfl_up(scan, 1, 64);
-    if (tid % 64 == 0) before = -1;
-    __syncthreads();
-    for (int v = 0; v < tid / 64; ++v) before = max(before, wave_max[v]);
-#pragma unroll
-    for (int j = 0; j < ROWS_EACH; ++j) mark[tid * ROWS_EACH + j] = max(row[j], before);
-    __syncthreads();
     unsigned bad = 0;
 #pragma unroll
     for (int j = 0; j < ROWS_EACH; ++j) {

@@ -86,3 +86,50 @@ def test_bad_columns_are_refused_wherever_they_lie(at):
         with pytest.raises(lb.LibraError) as e:
             device_plan(wl.Csr(A.M, A.Kc, A.rowptr, col, A.val))
         assert e.value.code in (lb.ERR[code], lb.ERR["COLUMN"])
+
+
+MARKED = 1 << 15            # rows that the 2048 nonzeros of a chunk span before each of them is searched for
+
+
+@pytest.mark.parametrize("span", [MARKED - 1, MARKED, MARKED + 1, 5 * MARKED + 77])
+@pytest.mark.parametrize("at", [1, 1024, 2047])
+def test_rows_of_nonzeros_far_apart(span, at):
+    """A chunk with `at` nonzeros (one and three a row in turn) before a run of empty rows and the rest behind it, whole chunks before and
+    after, empty rows at both ends of the matrix."""
+    M = 1000 + span + 9000
+    counts = np.zeros(M, dtype=np.int64)
+    left, row = 2048 + at, 1000
+    while left > 0:
+        counts[row] = min(left, 1 + row % 2 * 2)
+        left, row = left - counts[row], row + 1
+    first = int(np.searchsorted(np.cumsum(counts), 2048, side="right"))         # the row of nonzero 2048
+    counts[first + span:first + span + 3000] = 2
+    rows = np.repeat(np.arange(M), counts)
+    assert rows[2048] == first and rows[2048 + at] == first + span
+    A = csr(M, 500, rows, np.concatenate([np.arange(c) * 7 + i % 400 for i, c in enumerate(counts) if c]))
+    assert A.nnz == rows.size
+    for opts in (dict(), dict(flags=lb.FLAG_NO_SPMM, sddmm_min_blk_nnz=17)):
+        ph, pd = lb.Plan.from_csr(A, **opts), device_plan(A, **opts)
+        assert_same_plan(ph, pd, opts.get("flags", 0))
+        ph.close()
+        pd.close()
+
+
+def test_runs_of_empty_rows_take_no_more_time_than_empty_rows_everywhere():
+    """6,000 rows of 33 nonzeros among 2^26, at both ends or evenly: a workgroup that walked the run alone took 100 ms."""
+    M, n, per = 1 << 26, 6000, 33
+    times = []
+    for rows in (np.r_[0:n // 2, M - n // 2:M], np.arange(n) * (M // n)):
+        counts = torch.zeros(M, dtype=torch.int32, device="cuda")
+        counts[torch.from_numpy(rows).cuda()] = per
+        rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+        rowptr[1:] = torch.cumsum(counts, 0)
+        col = (torch.arange(per, device="cuda") * 100).int().repeat(n)
+        val = torch.ones(col.numel(), dtype=torch.float16, device="cuda")
+        best = 1e9
+        for _ in range(4):
+            p = lb.Plan.from_device_csr(M, 4096, rowptr, col, val, resident=True, keep_host_copy=False, flags=lb.FLAG_NO_SPMM)
+            best = min(best, p.stats()["plan_seconds"])
+            p.close()
+        times.append(best)
+    assert times[0] < 4 * times[1], times
