@@ -113,7 +113,11 @@ struct Tiles {
     int32_t *win;       // its window,
     int32_t *split;     // and per row of the window the first nonzero (CSR position) that lies behind it
     int32_t *tail;      // per tile: the vectors of each NNZ in the part of the next boundary's window that it holds
+    int32_t *group;     // sums of `tail` over TAIL_GROUP tiles; nullptr: not formed
 };
+// A tile of a window that begins in an earlier one adds up the tails between.  From 4 groups of tiles in a window on, which takes
+// 2 M nonzeros, it adds whole groups.
+constexpr int TAIL_GROUP = 256;
 
 struct Layout {
     int32_t *win_ptr, *row_of, *rowbase, *scol, *spos;
@@ -220,6 +224,7 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
     L.tiles.win = A.take<int32_t>(boundaries);
     L.tiles.split = A.take<int32_t>(boundaries * W);
     L.tiles.tail = A.take<int32_t>(boundaries * W);
+    L.tiles.group = A.take<int32_t>((boundaries / TAIL_GROUP + 1) * W);
     L.scol = A.take<int32_t>(n);
     L.spos = A.take<int32_t>(n);
     L.vmask = A.take<uint16_t>(n);
@@ -644,6 +649,19 @@ __global__ __launch_bounds__(TILE_THREADS) void k_tile_sort(const int32_t *rowpt
     if (tid < W) T.tail[(int64_t)k * W + tid] = tail[tid];
 }
 
+// Sums of the tiles' tails over groups of tiles; a group per workgroup.
+__global__ __launch_bounds__(256) void k_tail_groups(Tiles T, int tiles) {
+    __shared__ int32_t sum[W];
+    const int c = threadIdx.x % W, k0 = blockIdx.x * TAIL_GROUP, k1 = min(k0 + TAIL_GROUP, tiles);
+    if (threadIdx.x < W) sum[c] = 0;
+    __syncthreads();
+    int x = 0;
+    for (int k = k0 + threadIdx.x / W; k < k1; k += 256 / W) x += T.tail[(int64_t)k * W + c];
+    if (x) atomicAdd(&sum[c], x);
+    __syncthreads();
+    if (threadIdx.x < W) T.group[(int64_t)blockIdx.x * W + c] = sum[c];
+}
+
 // The sampled column-sharing statistic: how many distinct columns the windows of each sampled group of LIBRA_LOCALITY_WINDOWS windows
 // have together (a vector counts unless an earlier window of the group has its column) and one by one.  The places of all sampled
 // groups are one list, dealt to the threads: a hub's group has more of them than all others together.  GAT graph: 223 us, with 64
@@ -823,9 +841,18 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
     __syncthreads();
     // the parts of the first window in earlier tiles: those before the boundaries inside it
     {
-        int sum = 0;
-        for (int b = max(1, (int)(((int64_t)win_ptr[w0] + TILE_STEP - 1) / TILE_STEP)) + tid / W; b <= k; b += TILE_THREADS / W) sum += T.tail[(int64_t)(b - 1) * W + tid % W];
-        if (sum) atomicAdd(&carry[tid % W], sum);
+        const int c = tid % W, from = max(1, (int)(((int64_t)win_ptr[w0] + TILE_STEP - 1) / TILE_STEP)) - 1;           // tiles from .. k - 1
+        int sum = 0, end = k;
+        if (T.group) {
+            const int g0 = (from + TAIL_GROUP - 1) / TAIL_GROUP, g1 = k / TAIL_GROUP;
+            for (int g = g0 + tid / W; g < g1; g += TILE_THREADS / W) sum += T.group[(int64_t)g * W + c];
+            if (g0 < g1) {
+                for (int b = g1 * TAIL_GROUP + tid / W; b < k; b += TILE_THREADS / W) sum += T.tail[(int64_t)b * W + c];
+                end = g0 * TAIL_GROUP;
+            }
+        }
+        for (int b = from + tid / W; b < end; b += TILE_THREADS / W) sum += T.tail[(int64_t)b * W + c];
+        if (sum) atomicAdd(&carry[c], sum);
     }
     int rows[TILE_EACH], win[TILE_EACH];
     u64 change[TILE_EACH];                  // the chunk's lanes that begin a window
@@ -1862,7 +1889,12 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             fill_bytes(L.a.slotvec, 0xff, (size_t)nbA * KB * sizeof(int32_t), s);
             fill_bytes(L.d.slotvec, 0xff, (size_t)nbD * KB * sizeof(int32_t), s);
             fill_bytes(L.dense, 0, (size_t)n + 1, s);
-            hipLaunchKernelGGL(k_dense_vectors, dim3((unsigned)tiles), dim3(TILE_THREADS), 0, s, L.win_ptr, L.row_of, L.tiles, L.spos, L.vmask, L.hist,
+            Tiles parts = L.tiles;
+            if (std::min<int64_t>(n, W * Kc) >= 4ll * TAIL_GROUP * TILE_STEP)           // a window may have so many
+                hipLaunchKernelGGL(k_tail_groups, dim3(blocks_for(tiles, TAIL_GROUP)), dim3(256), 0, s, parts, tiles);
+            else
+                parts.group = nullptr;
+            hipLaunchKernelGGL(k_dense_vectors, dim3((unsigned)tiles), dim3(TILE_THREADS), 0, s, L.win_ptr, L.row_of, parts, L.spos, L.vmask, L.hist,
                                L.a.ndv, L.a.blkptr, L.d.ndv, L.d.blkptr, R, L.a.slotvec, L.d.slotvec, L.dense);
         }
         const int nbs[2] = {nbA, nbD};

@@ -133,3 +133,35 @@ def test_runs_of_empty_rows_take_no_more_time_than_empty_rows_everywhere():
             p.close()
         times.append(best)
     assert times[0] < 4 * times[1], times
+
+
+@pytest.mark.parametrize("M,Kc,share", [(16, 200_000, 0.6), (40, 130_003, 0.9), (33, 2_000_000, 0.07)])
+def test_windows_of_more_than_a_thousand_tiles(M, Kc, share):
+    """Whole groups of tiles, and parts of them, between a tile and the first one of its window."""
+    rng = np.random.default_rng(M)
+    n = [min(Kc, int(Kc * share * s)) for s in rng.uniform(0.8, 1.2, M)]
+    rows, cols = np.repeat(np.arange(M), n), np.concatenate([rng.choice(Kc, k, replace=False) for k in n])
+    with np.errstate(over="ignore"):            # the later values are infinities
+        A = csr(M, Kc, rows, cols)
+    assert np.diff(A.rowptr[::16]).max(initial=A.rowptr[16]) >= 4 * 256 * STEP
+    ph, pd = lb.Plan.from_csr(A, spmm_min_vec_nnz=3, sddmm_min_blk_nnz=40), device_plan(A, spmm_min_vec_nnz=3, sddmm_min_blk_nnz=40)
+    assert_same_plan(ph, pd)
+    ph.close()
+    pd.close()
+
+
+def test_a_window_of_all_nonzeros_takes_no_more_time_than_many_windows():
+    """2^28 nonzeros in one window or in 1,024: with a sum over all earlier tiles in every tile the first took three times as long."""
+    times = []
+    for M in (1 << 4, 1 << 14):
+        Kc = (1 << 28) // M
+        rowptr = torch.arange(M + 1, dtype=torch.int32, device="cuda") * Kc
+        col = torch.arange(Kc, dtype=torch.int32, device="cuda").repeat(M)
+        val = torch.zeros(M * Kc, dtype=torch.float16, device="cuda")
+        best = 1e9
+        for _ in range(4):
+            p = lb.Plan.from_device_csr(M, Kc, rowptr, col, val, resident=True, keep_host_copy=False, flags=lb.FLAG_NO_SDDMM)
+            best = min(best, p.stats()["plan_seconds"])
+            p.close()
+        times.append(best)
+    assert times[0] < 2 * times[1], times
