@@ -906,7 +906,8 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
         const u64 over = __ballot(nnz > 0 && nnz >= R.tau_a), below = (1ull << lane) - 1ull;
         const u64 begun = change[j] & (below << 1 | 1ull);                     // windows that begin at or before this lane
         const u64 from = begun ? ~0ull << (63 - __clzll(begun)) : ~0ull;
-        const int rank = __popcll(planes.same(cls) & below & from) + (begun ? 0 : __shfl(run, cls & 15, 64));
+        const int carried = __shfl(run, cls & 15, 64);       // (by all lanes: a lane that has left the branch hands out nothing)
+        const int rank = __popcll(planes.same(cls) & below & from) + (begun ? 0 : carried);
         const int rank_tau = __popcll(over & below & from) + (begun ? 0 : run_tau);
         const int place = higher[j] + rank;                          // in sorted order
         // of a vector's first place: 1, in a SpMM block; 2, in an SDDMM block
