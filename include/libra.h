@@ -263,7 +263,8 @@ int libra_spmm(const libra_plan_t *plan, const void *B, int32_t N, int64_t ldb,
  * neither written nor read again, but for the rows with several writers.
  *   R        device, M x N row-major in the plan's value type with row stride ldr (ldr >= N, ldr % 8 == 0); fully overwritten
  *   scratch  device, M x N fp32 with row stride lds (as C of libra_spmm; none of B, R); its contents afterwards mean nothing.
- *            May be NULL if no row has several writers (spmm_zero_rows = 0 in the statistics) and the plan is not in two-kernel mode
+ *            May be NULL if no row has several writers (spmm_zero_rows = 0 in the statistics) and the plan is not in two-kernel mode;
+ *            lds is not looked at then
  * Errors: as libra_spmm; DTYPE for an fp32 plan.
  */
 int libra_spmm_rounded(const libra_plan_t *plan, const void *B, int32_t N, int64_t ldb,

@@ -2198,7 +2198,7 @@ int spmm_call(const libra_plan_t *P, const void *B, int32_t N, int64_t ldb, floa
         // tail; community N=256: 535 -> 508 us).  Elsewhere they run one after the other: together they would compete for
         // the L2 with twice the rows of B (power-law N=512: 267 us apart, 354 us together).
         const int pieces = (n == 128 && P->o.xcd_order == 1) ? (N - n0) / 128 : 1;
-        int rc = spmm_piece(P, (const char *)B + (size_t)n0 * esz, n, pieces, ldb, C + n0, ldc, R && !all_rows ? (char *)R + (size_t)n0 * esz : nullptr, ldr, s);
+        int rc = spmm_piece(P, (const char *)B + (size_t)n0 * esz, n, pieces, ldb, C ? C + n0 : nullptr, ldc, R && !all_rows ? (char *)R + (size_t)n0 * esz : nullptr, ldr, s);
         if (rc != LIBRA_OK) return rc;
         n0 += n * pieces;
     }
@@ -2229,7 +2229,7 @@ extern "C" int libra_spmm_rounded(const libra_plan_t *P, const void *B, int32_t 
     if (ldr < N) return LIBRA_ERR_SHAPE;
     if (ldr % 8) return LIBRA_ERR_UNSUPPORTED;
     if ((uintptr_t)R & 15) return LIBRA_ERR_BUFFER;
-    return spmm_call(P, B, N, ldb, scratch, lds, R, ldr, stream);
+    return spmm_call(P, B, N, ldb, scratch, scratch ? lds : N, R, ldr, stream);
 }
 
 namespace {

@@ -53,6 +53,24 @@ def test_spmm_rounded(dtype, opts):
     p.close()
 
 
+@pytest.mark.parametrize("lds", [0, -1, 7, 64])
+def test_spmm_rounded_without_scratch_memory(lds):
+    """Rows with one writer need none, whatever its stride is given as; rows with several do."""
+    A = wl.random_pattern(333, 260, 0.05, seed=4, empty_rows=0.2)
+    p, q = plan(A, torch.float16), plan(matrix(), torch.float16, cs=50)
+    assert p.stats()["spmm_zero_rows"] == 0 < q.stats()["spmm_zero_rows"]
+    B = whole((A.Kc, 64), torch.float16, 3)
+    out = torch.full((A.M, 64), float("nan"), dtype=torch.float16, device="cuda")
+    call = lambda plan: lb.libra_spmm_rounded(plan.handle, B.data_ptr(), 64, 64, out.data_ptr(), 64, 0, lds, torch.cuda.current_stream().cuda_stream)
+    call(p)
+    assert torch.equal(out, p.spmm(B).half())
+    with pytest.raises(lb.LibraError) as e:
+        call(q)
+    assert e.value.code == lb.ERR["NULL"]
+    p.close()
+    q.close()
+
+
 def test_spmm_rounded_of_infinities_and_overflow():
     A = matrix()
     p = plan(A, torch.float16, cs=50)
