@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 
 #include <rocprim/rocprim.hpp>
@@ -93,13 +94,16 @@ int place_values(int vdt, const void *src, const int32_t *dense_perm, int64_t nd
 // Destination slots: the packed dense values, padded to whole blocks of entries, then the entries.  Slot j takes value source(j).
 // Small matrices gather: an array of sources and place_values_kernel.  Larger ones, whose values do not stay in an L2 (every gathered
 // value then costs a line from behind it), are permuted in two passes that read and write runs: the values are cut into chunks and
-// the slots into tiles of VALUES values (64 KiB, in LDS: two workgroups per compute unit); the first pass sorts a chunk by tile and appends each tile's values to the
+// the slots into tiles of VALUES values (64 KiB, in LDS); the first pass sorts a chunk by tile and appends each tile's values to the
 // tile's part of an intermediate array, the second puts a tile's values into slot order.  Bound by memory: 12 bytes per value of 16
-// bits, 16.8 M values at 4.1 TB/s.
+// bits, 16.8 M values at 4.1 TB/s.  The first pass has the runs of its chunk, 8 bytes per tile, in LDS too: two workgroups per compute
+// unit up to 2,047 tiles (67 M values of 16 bits, 33.5 M of 32), one from there on.
 template <class V> constexpr int VALUES = 65536 / (int)sizeof(V);
 // Random permutations, gather / two passes: fp16, 2^20 nonzeros 13 / 23 us, 2^21 20 / 26, 2^22 50 / 28, 2^24 291 / 49, 2^26 1,246 / 322;
 // fp32, 2^20 15 / 22, 2^21 30 / 24, 2^22 67 / 31, 2^24 317 / 101: the lines cross where the values are some 5 MB.  (As an index pass of
-// torch and set_values, fp16: 15, 25, 59, 309, 1,375.)  Upper bound: the runs of a chunk are listed in LDS beside it.
+// torch and set_values, fp16: 15, 25, 59, 309, 1,375.)  Upper bound: the runs of a chunk are listed in LDS beside it; at 2^27 nonzeros, the
+// most, fp16 2,624 / 786, fp32 2,696 / 1,860.  The runs are chunks x tiles: the order takes 4.1 bytes per nonzero at 2^24, 5 (fp16) and
+// 8 (fp32) at 2^27, where the gathered form takes 4.
 constexpr int64_t ORDER_PASSES_MIN_BYTES = 5 << 20, ORDER_PASSES_MAX = 1 << 27;
 
 struct OrderShape {
@@ -349,12 +353,28 @@ __global__ __launch_bounds__(PASS_THREADS) void order_tiles_kernel(const V *mid,
         *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(val + i);
     }
 }
+template <class V> constexpr size_t chunks_lds(int tiles) { return VALUES<V> * sizeof(V) + ((size_t)2 * tiles + 1) * 4; }
+
+// Lets order_chunks_kernel have the LDS of the most tiles, once per device.  (A size that follows the plan, set before each launch, would
+// be another thread's limit.)
+template <class V>
+bool allow_chunks_lds() {
+    static std::atomic<uint64_t> done{0};
+    constexpr size_t most = chunks_lds<V>((int)((ORDER_PASSES_MAX + RES_BLOCK + VALUES<V> - 1) / VALUES<V>));
+    static_assert(most <= 160 << 10, "the LDS of a compute unit");
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return true;
+    if (hipFuncSetAttribute((const void *)order_chunks_kernel<V>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess) return false;
+    done.fetch_or(bit, std::memory_order_relaxed);
+    return true;
+}
 template <class V>
 int run_passes(const libra_plan_t *P, const OrderShape &h, const OrderArrays &a, const void *src, void *scratch, hipStream_t s) {
     const SubPlan &sa = P->spmm;
-    const size_t lds = 65536 + ((size_t)2 * h.tiles + 1) * 4;
-    if (hipFuncSetAttribute((const void *)order_chunks_kernel<V>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return LIBRA_ERR_HIP;
-    hipLaunchKernelGGL((order_chunks_kernel<V>), dim3((unsigned)h.chunks), dim3(PASS_THREADS), lds, s, (const V *)src, h.nnz, a.in_chunk, a.run, a.to, h.tiles, (V *)scratch);
+    if (!allow_chunks_lds<V>()) return LIBRA_ERR_HIP;
+    hipLaunchKernelGGL((order_chunks_kernel<V>), dim3((unsigned)h.chunks), dim3(PASS_THREADS), chunks_lds<V>(h.tiles), s, (const V *)src, h.nnz, a.in_chunk, a.run, a.to, h.tiles, (V *)scratch);
     hipLaunchKernelGGL((order_tiles_kernel<V>), dim3((unsigned)h.tiles), dim3(PASS_THREADS), 0, s, (const V *)scratch, a.in_tile, a.tile_first, h.nd, h.nd_pad, h.slots,
                        (V *)sa.dev.dense_val, (unsigned char *)sa.dev.res_ent);
     return hipGetLastError() == hipSuccess ? LIBRA_OK : LIBRA_ERR_HIP;

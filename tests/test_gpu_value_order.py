@@ -88,6 +88,35 @@ def test_transposed_order_of_a_skewed_matrix():
     p.close()
 
 
+@pytest.mark.parametrize("dtype,nnz", [("f16", 1 << 27), ("f32", (1 << 26) + 16_385), ("f32", 1 << 27), ("f32", (1 << 27) + 64)])
+def test_ordered_values_of_very_large_matrices(dtype, nnz):
+    """Where the runs of a chunk take more LDS than leaves room for two workgroups, up to the most nonzeros, and past it."""
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs some 30 GiB")
+    dt, per = DTYPES[dtype], 64
+    M, Kc = (nnz + per - 1) // per, 1 << 16
+    g = torch.Generator(device="cuda").manual_seed(2)
+    rowptr = (torch.arange(M + 1, device="cuda") * per).clamp_(max=nnz).int()
+    # a window's rows share few columns of some strata and hardly any of the others
+    col = torch.randint(0, Kc // per, (M, per), device="cuda", generator=g, dtype=torch.int32)
+    col[:, ::2] %= 6
+    col = (col + torch.arange(per, device="cuda", dtype=torch.int32) * (Kc // per)).reshape(-1)[:nnz].contiguous()
+    p = lb.Plan.from_device_csr(M, Kc, rowptr, col, torch.ones(nnz, dtype=dt, device="cuda"), resident=True, keep_host_copy=False, flags=lb.FLAG_NO_SDDMM)
+    s = p.stats()
+    assert s["spmm_dense_nnz"] > nnz // 20 and s["spmm_res_nnz"] > nnz // 20
+    perm = torch.randperm(nnz, device="cuda", generator=g, dtype=torch.int32)
+    order = p.value_order(perm)
+    assert (order[1] > 0) == (nnz <= 1 << 27)               # scratch memory: the two passes
+    vals, B = values(nnz, dt, 3), values(Kc * 32, dt, 5).view(Kc, 32)
+    p.set_values(vals[perm], lb.OP_SPMM)
+    want = p.spmm(B)
+    p.set_values(torch.zeros_like(vals), lb.OP_SPMM)
+    p.set_values_ordered(vals, order)
+    assert torch.equal(p.spmm(B), want)
+    p.close()
+
+
 @pytest.mark.parametrize("nnz", [1000, PASSES_MIN])
 def test_orders_that_are_no_permutations_are_refused(nnz):
     M, Kc = (301, 203) if nnz == 1000 else (40_003, 30_011)
