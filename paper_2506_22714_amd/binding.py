@@ -235,16 +235,6 @@ def libra_edge_softmax_backward(plan, alpha_ptr: int, alpha_dtype: int, dalpha_p
                                              C.c_void_p(dscores_ptr), C.c_void_p(stream)), "libra_edge_softmax_backward")
 
 
-def libra_sddmm_pattern_rounded(plan, X_ptr: int, Y_ptr: int, K: int, out_ptr: int, stream: int = 0):
-    _check(lib().libra_sddmm_pattern_rounded(plan, C.c_void_p(X_ptr), C.c_void_p(Y_ptr), K, C.c_void_p(out_ptr), C.c_void_p(stream)),
-           "libra_sddmm_pattern_rounded")
-
-
-def libra_edge_softmax_backward_rounded(plan, alpha_ptr: int, dalpha_ptr: int, dtype: int, scale: float, dscores_ptr: int, stream: int = 0):
-    _check(lib().libra_edge_softmax_backward_rounded(plan, C.c_void_p(alpha_ptr), C.c_void_p(dalpha_ptr), dtype, C.c_float(scale),
-                                                     C.c_void_p(dscores_ptr), C.c_void_p(stream)), "libra_edge_softmax_backward_rounded")
-
-
 def libra_value_products(vals_ptr: int, factors_ptr: int, n: int, dtype: int, out_ptr: int, stream: int = 0):
     _check(lib().libra_value_products(C.c_void_p(vals_ptr), C.c_void_p(factors_ptr), n, dtype, C.c_void_p(out_ptr), C.c_void_p(stream)),
            "libra_value_products")
@@ -344,11 +334,6 @@ def libra_value_order_bytes(plan) -> tuple:
 def libra_value_order(plan, perm_ptr: int, order_ptr: int, order_bytes: int, ws_ptr: int, ws_bytes: int, stream: int = 0):
     _check(lib().libra_value_order(plan, C.c_void_p(perm_ptr), C.c_void_p(order_ptr), order_bytes, C.c_void_p(ws_ptr), ws_bytes,
                                    C.c_void_p(stream)), "libra_value_order")
-
-
-def libra_plan_set_values_ordered(plan, vals_ptr: int, dtype: int, order_ptr: int, scratch_ptr: int, stream: int = 0):
-    _check(lib().libra_plan_set_values_ordered(plan, C.c_void_p(vals_ptr), dtype, C.c_void_p(order_ptr), C.c_void_p(scratch_ptr),
-                                               C.c_void_p(stream)), "libra_plan_set_values_ordered")
 
 
 def libra_plan_destroy(plan):

@@ -1157,6 +1157,7 @@ struct XStage {
 // the per-lane popcount offsets and 4-byte stores.)
 template <int K>
 __device__ inline void sddmm_window_task_f32(const SddmmArgs &a, const DevTask &t) {
+    static_assert(K <= 64, "wider rows: sddmm_wide_window_task_f32");
     constexpr int KT = K / 16;               // 16-byte pieces per lane and operand row
     constexpr int BB = K <= 32 ? 4 : 2;      // blocks per batch (register budget)
     const int lane = threadIdx.x % WAVE;
