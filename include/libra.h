@@ -320,8 +320,9 @@ int libra_edge_softmax_backward_rounded(const libra_plan_t *plan, const void *al
                                         float scale, float *dscores, void *stream);
 
 /*
- * libra_value_products - out[p] = factors[p] * vals[p], formed in fp32 and rounded once to `dtype` (LIBRA_F16 or LIBRA_BF16):
- * the coefficients of the SDDMM's backward products (A o dout).
+ * libra_value_products - out[p] = factors[p] * vals[p], formed in fp32 and rounded to `dtype` (LIBRA_F16 or LIBRA_BF16): the
+ * coefficients of the SDDMM's backward products (A o dout).  Fp16 products are rounded from the exact ones, in one step: 6 in
+ * 100,000 are nearer to them by a unit in the last place than after fp32.
  *   vals, out  device, n values of `dtype`;  factors  device, fp32[n];  out may be vals
  * Errors: NULL, SHAPE, DTYPE, BUFFER (an array not aligned to its elements), HIP.
  */

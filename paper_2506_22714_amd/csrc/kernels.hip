@@ -1132,7 +1132,7 @@ template <int K>
 struct XStage {
     static constexpr int ROW = 4 * K, PIECES = K / 4, RPL = WAVE / PIECES, BYTES = W * ROW;
     // Do segment tasks use it?  At K = 32 not beside window tasks: the registers of both tasks together would take a wave per SIMD (community
-    // matrix of 300,017 rows, default options 67.5 -> 69 - 76 us with any budget; without window tasks 55 -> 46).
+    // matrix of 300,017 rows, default options 67.5 -> 69 - 76 us with any budget; without window tasks 57 -> 49).
     template <bool DENSE> static constexpr bool SEGMENTS = !(DENSE && K == 32);
     __device__ static int swizzle(int row) { return K == 32 ? row >> 1 & 7 : row & 15; }
     // rows first .. first + count - 1; whole loads, whose further rows repeat the last one
@@ -1384,7 +1384,7 @@ __device__ inline void sddmm_segment_task(const SddmmArgs &a, const DevTask &t, 
 // the tile to use one): K/4 lanes per nonzero, NPW nonzeros per wave pass, U passes in one batch of loads.  If the rows of 64 nonzeros in
 // CSR order lie within 16 consecutive rows (nearly always) those rows of X come through LDS, once and not once per nonzero: the data
 // return units of the L1s then carry the rows of Y alone.  Residual nonzeros only, before -> with it: community matrix of 300,017 rows
-// K = 32 / 64 / 128 55.5 / 100.6 / 254.5 -> 46.2 / 85.8 / 214.2 us, power-law graph of 2^17 rows 35.3 / 63.5 / 141.8 -> 30.0 / 53.7 / 134.2.
+// K = 32 / 64 / 128 57.4 / 96.3 / 254.9 -> 49.1 / 84.7 / 215.0 us, power-law graph of 2^17 rows 35.7 / 60.9 / 141.6 -> 30.5 / 55.1 / 121.7.
 template <int K, bool STAGED>
 __device__ inline void sddmm_segment_task_f32(const SddmmArgs &a, const DevTask &t, lds_byte *stage) {
     using S = XStage<K>;

@@ -114,9 +114,10 @@ def test_edge_softmax_backward_of_a_rounded_gradient(dtype):
 
 
 @pytest.mark.parametrize("dtype", list(DTYPES))
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 4099])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 4099, 1 << 20])
 def test_value_products(dtype, n):
-    """Groups of eight, remainders, and arrays that are only aligned to their elements."""
+    """Groups of eight, remainders, and arrays that are only aligned to their elements.  The product is rounded from fp32, or (fp16, where one
+    instruction does both) without that step between: where the two differ, which is rare, the result is nearer to the exact product."""
     dt = DTYPES[dtype]
     g = torch.Generator(device="cuda").manual_seed(n)
     for shift in ((0, 0), (1, 0), (0, 1), (3, 2)):
@@ -125,4 +126,54 @@ def test_value_products(dtype, n):
         out = torch.empty_like(vals)
         lb.libra_value_products(vals.data_ptr(), factors.data_ptr(), n, lb.F16 if dtype == "f16" else lb.BF16, out.data_ptr(),
                                 torch.cuda.current_stream().cuda_stream)
-        assert torch.equal(out, (factors * vals.float()).to(dt)), shift
+        by_fp32, exact = (factors * vals.float()).to(dt), factors.double() * vals.double()
+        other = out != by_fp32
+        assert int(other.sum()) <= n * 2.0 ** -11, shift         # an fp32 product lies next to the middle of two fp16 numbers
+        assert bool(((out.double() - exact).abs() < (by_fp32.double() - exact).abs())[other].all()), shift
+
+
+# ---- numbers that are not whole: rows with one writer are summed in one order, so that the results are the same bits ----
+@pytest.mark.parametrize("dtype", list(DTYPES))
+@pytest.mark.parametrize("opts", [dict(), dict(mode=lb.MODE_DENSE_ONLY, ts=100), dict(mode=lb.MODE_SCALAR_ONLY)], ids=str)
+def test_rounded_sums_of_any_numbers(dtype, opts):
+    dt = DTYPES[dtype]
+    A = wl.random_pattern(1333, 260, 0.1, seed=4, empty_rows=0.2)
+    p = plan(A, dt, **opts)
+    assert p.stats()["spmm_zero_rows"] == 0
+    g = torch.Generator(device="cuda").manual_seed(2)
+    p.set_values(torch.randn(A.nnz, device="cuda", generator=g).to(dt))
+    for N in (32, 64, 128, 224):
+        B = torch.randn(A.Kc, N, device="cuda", generator=g).to(dt)
+        want = p.spmm(B)
+        assert torch.equal(p.spmm(B), want) and torch.equal(p.spmm_rounded(B), want.to(dt))
+    perm = torch.randperm(A.nnz, device="cuda", generator=g, dtype=torch.int32)
+    vals = torch.randn(A.nnz, device="cuda", generator=g).to(dt)
+    p.set_values(vals[perm].contiguous(), lb.OP_SPMM)
+    want = p.spmm(B)
+    p.set_values_ordered(vals, p.value_order(perm))
+    assert torch.equal(p.spmm(B), want)
+    for K in (32, 64, 128):
+        X, Y = torch.randn(A.M, K, device="cuda", generator=g).to(dt), torch.randn(A.Kc, K, device="cuda", generator=g).to(dt)
+        assert torch.equal(p.sddmm_pattern_rounded(X, Y), p.sddmm(X, Y, pattern_only=True).to(dt))
+    p.close()
+
+
+@pytest.mark.parametrize("dtype", list(DTYPES))
+def test_rounded_sums_of_rows_with_several_writers(dtype):
+    """Added up in any order: two calls are as far apart as the order of fp32 sums allows, and at most one rounding further."""
+    dt = DTYPES[dtype]
+    A = matrix()
+    p = plan(A, dt, cs=16, ts=1)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    vals, B = torch.randn(A.nnz, device="cuda", generator=g).to(dt), torch.randn(A.Kc, 64, device="cuda", generator=g).to(dt)
+    p.set_values(vals)
+    rows = torch.repeat_interleave(torch.arange(A.M), torch.from_numpy(np.diff(A.rowptr)).long()).cuda()
+    terms = vals.double()[:, None] * B.double()[torch.from_numpy(A.col).long().cuda()]
+    exact = torch.zeros(A.M, 64, dtype=torch.float64, device="cuda").index_add_(0, rows, terms)
+    size = torch.zeros_like(exact).index_add_(0, rows, terms.abs())
+    longest = int(np.diff(A.rowptr).max())
+    fp32 = size * longest * 2.0 ** -24                            # of any order of additions
+    ulp = 2.0 ** -(11 if dtype == "f16" else 8)
+    assert bool(((p.spmm(B).double() - exact).abs() <= fp32).all())
+    assert bool(((p.spmm_rounded(B).double() - exact).abs() <= fp32 * (1 + ulp) + exact.abs() * ulp + 2.0 ** -25).all())
+    p.close()
