@@ -39,6 +39,24 @@ def test_width_classes():
     assert tune.geomean([2.0, 8.0]) == pytest.approx(4.0)
 
 
+def test_the_table_of_this_gpu_says_what_was_measured_and_what_was_set_by_hand():
+    """Every entry has the figures that the tuner writes; an entry that is not the search's says why, and what the search took."""
+    import os
+    t = tune.load_table(os.path.join(os.path.dirname(lb.__file__), "tuned_gfx950.json"))
+    assert not t["small_workloads"] and t["workloads"] == list(tune.TUNER_WORKLOADS)
+    for op, classes, start in (("spmm", tune.N_CLASSES, tune.SPMM_START), ("sddmm", tune.K_CLASSES, tune.SDDMM_START)):
+        for dtype in ("f16", "f32"):
+            assert t[op][dtype].keys() == classes.keys()
+            for e in t[op][dtype].values():
+                assert e["options"].keys() == start.keys() and e["settings_tried"] >= 5
+                assert 0 < e["geomean_us"] <= 1.005 * e["defaults_geomean_us"]         # a change has to be worth half a percent
+                if "by_hand" in e:
+                    why, searched = e["by_hand"].split("; the search took ")
+                    setting, us = searched.rsplit(": ", 1)
+                    assert why and json.loads(setting).keys() == start.keys() and json.loads(setting) != e["options"]
+                    assert e["geomean_us"] <= 1.005 * float(us.removesuffix(" us"))
+
+
 def test_table_is_parsed_checked_and_applied_to_a_plan(tmp_path):
     t = _table({"n32": dict(spmm_min_vec_nnz=2, ts=8, cs=64), "n64": dict(spmm_min_vec_nnz=4, ts=16, cs=128),
                 "n128": dict(spmm_min_vec_nnz=6, ts=32, cs=256)},
