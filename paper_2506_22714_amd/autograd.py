@@ -28,7 +28,8 @@ class SparseMatrix:
         rowptr_t, col_t, perm_t = lb.transpose_csr(M, Kc, rowptr, col)
         self._perm_t = perm_t
         self.plan_t = lb.Plan.from_device_csr(Kc, M, rowptr_t, col_t, ones, resident=True, keep_host_copy=False, **opts)
-        # a matrix for SDDMM alone has no SpMM arrays to put values into
+        # made here and not in the first backward pass, because it waits for the stream and sorts (2^24 nonzeros: 1.2 ms, 4.1 bytes each kept);
+        # a program that only runs forward needs no SparseMatrix but a Plan.  A matrix for SDDMM alone has no SpMM arrays to put values into
         self._order_t = None if opts.get("flags", 0) & lb.FLAG_NO_SPMM else self.plan_t.value_order(perm_t)
 
     @property
