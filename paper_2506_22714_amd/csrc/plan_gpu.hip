@@ -923,27 +923,26 @@ __global__ __launch_bounds__(TILE_THREADS) void k_dense_vectors(const int32_t *w
         run = (change[j] ? 0 : run) + __popcll(planes.same(lane) & all_from);
         run_tau = (change[j] ? 0 : run_tau) + __popcll(over & all_from);
     }
-    // (places are clamped inside the tile before they are added to its first one: near 2^31 nonzeros a sum past the last place would wrap)
-    const int from0 = wave * (64 * TILE_EACH) + lane, end = out + min(count, (wave + 1) * 64 * TILE_EACH);
+    // (unsigned: near 2^31 nonzeros the places past the last tile's end are no int)
+    const unsigned first = (unsigned)out + (unsigned)(wave * (64 * TILE_EACH) + lane), last = (unsigned)(out + count - 1), end = (unsigned)(out + min(count, (wave + 1) * 64 * TILE_EACH));
     int to_a[TILE_EACH], to_d[TILE_EACH], p[TILE_EACH];
 #pragma unroll
     for (int j = 0; j < TILE_EACH; ++j) {
+        const unsigned e = min(first + j * 64, last);
         to_a[j] = to_d[j] = p[j] = 0;
         if (slot_a[j] >= 0) to_a[j] = blkptr_a[win[j]];
         if (slot_d[j] >= 0) to_d[j] = blkptr_d[win[j]];
-        if (bits[j]) p[j] = spos[out + min(from0 + j * 64, count - 1)];
+        if (bits[j]) p[j] = spos[e];
     }
 #pragma unroll
     for (int j = 0; j < TILE_EACH; ++j) {
-        const int i = from0 + j * 64, in = (slot_a[j] >= 0 ? 1 : 0) | (slot_d[j] >= 0 ? 2 : 0);
-        if (i >= count) continue;
-        const int e = out + i;
-        if (slot_a[j] >= 0) slotvec_a[(int64_t)to_a[j] * KB + slot_a[j]] = e;
-        if (slot_d[j] >= 0) slotvec_d[(int64_t)to_d[j] * KB + slot_d[j]] = e;
-        if (bits[j]) dense[p[j]] = (uint8_t)bits[j];
+        const unsigned e = first + j * 64, in = (slot_a[j] >= 0 ? 1 : 0) | (slot_d[j] >= 0 ? 2 : 0);
+        if (slot_a[j] >= 0) slotvec_a[(int64_t)to_a[j] * KB + slot_a[j]] = (int32_t)e;
+        if (slot_d[j] >= 0) slotvec_d[(int64_t)to_d[j] * KB + slot_d[j]] = (int32_t)e;
+        if (bits[j] && e < end) dense[p[j]] = (uint8_t)bits[j];
         // places of the next wave whose vector begins in this one
         if (in)
-            for (int q = end; q < e + (int)__popc(rows[j]); ++q) dense[spos[q]] = (uint8_t)in;
+            for (unsigned q = end; q < e + __popc(rows[j]); ++q) dense[spos[q]] = (uint8_t)in;
     }
 }
 
