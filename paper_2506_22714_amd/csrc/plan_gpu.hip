@@ -115,8 +115,9 @@ struct Tiles {
     int32_t *tail;      // per tile: the vectors of each NNZ in the part of the next boundary's window that it holds
     int32_t *group;     // sums of `tail` over TAIL_GROUP tiles; nullptr: not formed
 };
-// A tile of a window that begins in an earlier one adds up the tails between.  From 4 groups of tiles in a window on, which takes
-// 2 M nonzeros, it adds whole groups.
+// A tile of a window that begins in an earlier one adds up the tails between.  Where a window may have 4 groups of tiles (2 M nonzeros)
+// it adds whole groups, or the time would be quadratic: plans of one window, tails / groups, 2^26 nonzeros 18.3 / 13.7 ms, 2^28 204 / 51, 2^29
+// 822 / 102.  The pass that forms the groups takes 5 - 9 us.
 constexpr int TAIL_GROUP = 256;
 
 struct Layout {
