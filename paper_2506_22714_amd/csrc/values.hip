@@ -463,6 +463,8 @@ extern "C" int libra_value_order(const libra_plan_t *P, const int32_t *order, vo
     int rc = LIBRA_OK;
     if (refused(rc)) return rc;
     if (h.passes) {
+        // (here too, so that a first call with the order, which may be captured, sets nothing)
+        if (!(P->vsize == 4 ? allow_chunks_lds<uint32_t>() : allow_chunks_lds<uint16_t>())) return LIBRA_ERR_HIP;
         hipLaunchKernelGGL(k_order_places, each, block, 0, s, w.key_out, w.slot_out, d.dense_perm, d.res_perm, h.nd, h.nd_pad, h.nnz, order, h.T, h.chunks, h.tiles, a.to, a.in_chunk, a.in_tile);
         hipLaunchKernelGGL(k_order_chunks_whole, dim3((unsigned)h.chunks), dim3(PASS_THREADS), 0, s, a.in_chunk, h.nnz, h.T, w.bad);
         if (refused(rc)) return rc;

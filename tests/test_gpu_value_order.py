@@ -175,3 +175,41 @@ def test_matrices_without_nonzeros_and_without_spmm():
         X2 = X.clone().requires_grad_()
         ag.sddmm(sm, vals, X2, Y).sum().backward()
     sm.close()
+
+
+@pytest.mark.parametrize("nnz", [1000, PASSES_MIN + 77])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_training_calls_can_be_captured_in_a_graph(dtype, nnz):
+    """They launch kernels on the caller's stream and nothing else: replays, with eager work between them and other values in place, give the
+    eager result.  Both forms of an order; the order itself is made before."""
+    dt = DTYPES[dtype]
+    M, Kc, K = (301, 203, 64) if nnz == 1000 else (40_003, 30_011, 32)
+    rowptr, col = random_csr(M, Kc, nnz, 3, True)
+    p = lb.Plan.from_device_csr(M, Kc, rowptr, col, values(nnz, dt, 1), resident=True, keep_host_copy=False, cs=16)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    order = p.value_order(torch.randperm(nnz, device="cuda", generator=g, dtype=torch.int32))
+    vals, B, X = values(nnz, dt, 3), values(Kc * K, dt, 4).view(Kc, K), values(M * K, dt, 5).view(M, K)
+    factors, alpha = values(nnz, torch.float32, 6), torch.rand(nnz, device="cuda", generator=g).to(dt)
+
+    def step():
+        p.set_values_ordered(p.value_products(vals, factors), order)
+        dalpha = p.sddmm_pattern_rounded(X, B)
+        return p.spmm_rounded(B), dalpha, p.edge_softmax_backward_rounded(alpha, dalpha, 0.5)
+
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        outs = step()
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(4):
+        vals.copy_(values(nnz, dt, 30 + rep))
+        for o in outs:
+            o.fill_(float("nan"))
+        p.set_values(torch.zeros_like(vals))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [o.clone() for o in outs]
+        want = step()
+        assert all(torch.equal(x, y) for x, y in zip(got, want)), rep
+    p.close()
