@@ -1084,11 +1084,11 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, l
         const int nb = min(SD_GROUP, t.blk_end - b0);
         // padding slots and blocks past the group fetch a row that no record points at
         const int col = max(a.blk_cols[(int64_t)(b0 + min(g, nb - 1)) * KB + j], 0);
-        const int v0 = a.blk_valptr[b0], v1 = a.blk_valptr[b0 + nb];
+        const unsigned v0 = (unsigned)a.blk_valptr[b0], v1 = (unsigned)a.blk_valptr[b0 + nb];         // unsigned: v1 + RU * WAVE may pass 2^31
         // the first records of the group travel with the Y rows
         uint2 rec[RU];
 #pragma unroll
-        for (int u = 0; u < RU; ++u) rec[u] = a.dense_pv[min(v0 + u * WAVE + lane, a.n_dense - 1)];
+        for (int u = 0; u < RU; ++u) rec[u] = a.dense_pv[min(v0 + u * WAVE + lane, (unsigned)a.n_dense - 1u)];
         float4_t d[SD_GROUP];
 #pragma unroll
         for (int h = 0; h < SD_GROUP; h += S::ROWS / KB) {
@@ -1112,10 +1112,10 @@ __device__ inline void sddmm_window_task(const SddmmArgs &a, const DevTask &t, l
                 for (int e = 0; e < 4; ++e) products[x * 256 + e * WAVE + lane] = d[x][e];
             }
         wave_sync();
-        for (int q = v0; q < v1; q += RU * WAVE) {
+        for (unsigned q = v0; q < v1; q += RU * WAVE) {
             if (q > v0) {
 #pragma unroll
-                for (int u = 0; u < RU; ++u) rec[u] = a.dense_pv[min(q + u * WAVE + lane, a.n_dense - 1)];
+                for (int u = 0; u < RU; ++u) rec[u] = a.dense_pv[min(q + u * WAVE + lane, (unsigned)a.n_dense - 1u)];
             }
 #pragma unroll
             for (int u = 0; u < RU; ++u)

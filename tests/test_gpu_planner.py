@@ -457,6 +457,43 @@ def test_plans_of_very_many_nonzeros(M):
     assert st["spmm_res_nnz"] == st["spmm_short_rows"] == st["spmm_long_rows"] == st["spmm_split_rows"] == 0
 
 
+def test_sddmm_of_nearly_the_most_nonzeros():
+    """The last window's output records lie next to 2^31, where a wave's next 256 of them do not count in 32 bits with a sign."""
+    M, Kc, K = 1 << 14, 1 << 17, 32
+    nnz = M * Kc - 66
+    o = lb.PlanOpts(flags=lb.FLAG_NO_SPMM)
+    ws_bytes, plan_bytes = lb.libra_plan_device_workspace(M, nnz, o), 13 * nnz
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < ws_bytes + plan_bytes + 6 * nnz + (3 << 30):
+        pytest.skip("needs some 230 GiB")
+    rowptr = (torch.arange(M + 1, device="cuda") * Kc).clamp_(max=nnz).int()
+    col = torch.arange(Kc, dtype=torch.int32, device="cuda").repeat(M)[:nnz]
+    val = torch.zeros(nnz, dtype=torch.float16, device="cuda")
+    ws, buf = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (ws_bytes, plan_bytes))
+    stream = torch.cuda.current_stream().cuda_stream
+    handle = lb.libra_plan_device(M, Kc, nnz, rowptr.data_ptr(), col.data_ptr(), val.data_ptr(), lb.F16, o, ws.data_ptr(), ws_bytes,
+                                  buf.data_ptr(), plan_bytes, False, stream)
+    del rowptr, col, val, ws
+    torch.cuda.empty_cache()
+    assert lb.libra_plan_stats(handle)["sddmm_dense_nnz"] == nnz
+    g = torch.Generator("cuda").manual_seed(1)
+    X, Y = (torch.randint(-3, 4, (n, K), device="cuda", generator=g).half() for n in (M, Kc))
+    out = torch.full((M * Kc,), float("nan"), device="cuda")
+    lb.libra_sddmm_pattern(handle, X.data_ptr(), Y.data_ptr(), K, out.data_ptr(), stream)
+    assert bool(out[nnz:].isnan().all())
+    out = out.view(M, Kc)
+    Yt = Y.float().T.contiguous()
+    for r in range(0, M, 1024):
+        want = X[r:r + 1024].float() @ Yt
+        same = out[r:r + 1024] == want
+        if r + 1024 == M:
+            same[-1, Kc - 66:] = True
+        assert bool(same.all()), r
+    lb.libra_plan_destroy(handle)
+    del out, buf, want, same
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("flags", [lb.FLAG_XCD_ORDER, lb.FLAG_NATURAL_ORDER])
 def test_more_tasks_than_one_launch_has_waves(flags):
     """A launch has fewer than 2^32 threads, i.e. 2^26 waves with a task each: tables of more tasks (segments of one nonzero) take
