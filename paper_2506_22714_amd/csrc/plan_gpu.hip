@@ -51,7 +51,7 @@ constexpr int64_t DEVICE_ROWS_MIN = 1 << 17;
 // the whole plan 86.7 -> 24.1 ms; 8,000 tasks without segments: 0.32 ms on the host, 0.21 here.
 constexpr int64_t DEVICE_ORDER_MIN = 8192;
 
-enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_COUNT };
+enum Counter { C_NV = 0, C_NNZ1, C_SHORT, C_LONG, C_SPLIT, C_DV_A, C_PAD_A, C_DV_D, C_PAD_D, C_ERR, C_TOGETHER, C_APART, C_DNNZ_D, C_SEGMENTS, C_WIDE, C_COUNT };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -115,10 +115,10 @@ struct Tiles {
     int32_t *tail;      // per tile: the vectors of each NNZ in the part of the next boundary's window that it holds
     int32_t *group;     // sums of `tail` over TAIL_GROUP tiles; nullptr: not formed
 };
-// A tile of a window that begins in an earlier one adds up the tails between.  Where a window may have 4 groups of tiles (2 M nonzeros)
+// A tile of a window that begins in an earlier one adds up the tails between.  Where a window has 4 groups of tiles (1.8 M nonzeros)
 // it adds whole groups, or the time would be quadratic: plans of one window, tails / groups, 2^26 nonzeros 18.3 / 13.7 ms, 2^28 204 / 51, 2^29
-// 822 / 102.  The pass that forms the groups takes 5 - 9 us.
-constexpr int TAIL_GROUP = 256;
+// 822 / 102.  Below that the pass that forms the groups (9 us on the GAT graph) would be for nothing.
+constexpr int TAIL_GROUP = 256, WIDE_WINDOW = 4 * TAIL_GROUP * TILE_STEP;
 
 struct Layout {
     int32_t *win_ptr, *row_of, *rowbase, *scol, *spos;
@@ -285,9 +285,12 @@ Layout make_layout(const Sizes &z, int vsize, void *base) {
 // ------------------------------------------------------------------------------------------
 // kernels
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_win_ptr(const int32_t *rowptr, int64_t M, int nw, int32_t *win_ptr) {
+__global__ __launch_bounds__(256) void k_win_ptr(const int32_t *rowptr, int64_t M, int nw, int32_t *win_ptr, u64 *ctr) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t <= nw) win_ptr[t] = rowptr[min((int64_t)M, t * W)];
+    if (t > nw) return;
+    const int first = rowptr[min(M, t * W)];
+    win_ptr[t] = first;
+    if (rowptr[min(M, (t + 1) * W)] - first >= WIDE_WINDOW) ctr[C_WIDE] = 1;
 }
 
 __global__ __launch_bounds__(256) void k_check_rowptr(const int32_t *rowptr, int64_t M, int n, u64 *ctr) {
@@ -1858,7 +1861,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
 
         // ---- 1. census: the nonzeros of every window in (column, row) order ----
         fill_bytes(L.ctr, 0, (size_t)((char *)(L.hist + (size_t)nw * W) - (char *)L.ctr), s);
-        hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr);
+        hipLaunchKernelGGL(k_win_ptr, dim3(blocks_for(nw + 1, 256)), dim3(256), 0, s, d_rowptr, M, nw, L.win_ptr, L.ctr);
         const int tiles = tile_count(n);
         hipLaunchKernelGGL(k_rows, dim3(blocks_for(n, ROWS_CHUNK)), dim3(256), 0, s, d_rowptr, d_col, M, Kc, n, L.row_of, L.ctr);
         hipLaunchKernelGGL(k_tile_splits, dim3(blocks_for((int64_t)(tiles + 1) * W, 256)), dim3(256), 0, s, d_rowptr, d_col, L.win_ptr, M, Kc, n, nw, tiles, L.tiles);
@@ -1891,7 +1894,7 @@ extern "C" int libra_plan_device(int64_t M, int64_t Kc, int64_t nnz, const int32
             fill_bytes(L.d.slotvec, 0xff, (size_t)nbD * KB * sizeof(int32_t), s);
             fill_bytes(L.dense, 0, (size_t)n + 1, s);
             Tiles parts = L.tiles;
-            if (std::min<int64_t>(n, W * Kc) >= 4ll * TAIL_GROUP * TILE_STEP)           // a window may have so many
+            if (ctr[C_WIDE])
                 hipLaunchKernelGGL(k_tail_groups, dim3(blocks_for(tiles, TAIL_GROUP)), dim3(256), 0, s, parts, tiles);
             else
                 parts.group = nullptr;
